@@ -169,10 +169,11 @@ PairConfig choose_config(int64_t n, int precision, int device) {
   // for smaller FP64 systems so that they still spread over many workgroups
   c.ipl = precision != NBODY_FP64 ? 1 : (n >= (int64_t(1) << 18) ? 4 : (n >= (int64_t(1) << 14) ? 2 : 1));
   const nbody_config& t = t_cfg;
+  bool tuned = false;
   {
     std::lock_guard<std::mutex> lk(g_tune_mu);
     auto it = g_tuned.find(std::make_tuple(device, precision, n));
-    if (it != g_tuned.end()) c = it->second;
+    if ((tuned = it != g_tuned.end())) c = it->second;
     else {
       c.split = 0;
       c.sym = n >= (precision == NBODY_FP64 ? kSymMinN64 : kSymMinN) ? 1 : 0;
@@ -189,6 +190,10 @@ PairConfig choose_config(int64_t n, int precision, int device) {
   if (t.pairs) c.sym = c.sym_vjp = c.sym_vjp64 = c.sym_jerk = c.sym_jerk64 = c.sym_snap = c.sym_snap64 = t.pairs == 2 ? 1 : 0;
   c.rescue = t.rescue == 2 ? 0 : 1;
   c.sweep = t.sweep;
+  // the row kernels (unless the tuner found a tile configuration faster at n)
+  // have no tile configuration: a set one keeps the tile kernels
+  if (!tuned) c.rows = precision == NBODY_FP64 && n <= kRowsMaxN ? 1 : 0;
+  if (t.ipl || t.split || t.pairs == 2) c.rows = 0;
   // the symmetric kernels read a set split as a least number of launches (0 =
   // automatic); the ordered kernels that serve the same sizes (acceleration +
   // jerk (+ snap) below their thresholds, the FP64 VJP) keep their own j-split
@@ -813,6 +818,22 @@ int nbody_tune(int64_t n, int32_t precision, const char* cache_path, nbody_confi
     ms /= reps;
     log.push_back({c, ms});
     if (ms < best_ms) { best_ms = ms; bc = c; }
+  }
+  if (precision == NBODY_FP64 && n <= kRowsMaxN) {
+    // the row kernels: kept for automatic selection if they beat every tile
+    // configuration; the configuration reported stays the fastest of those
+    PairConfig c = bc;
+    c.rows = 1;
+    int st = launch_accel(n, dx, dm, da, 1.0, 0.01, precision, false, c, nullptr);
+    if (st) { cleanup(); return st; }
+    const int reps = 3;
+    (void)hipEventRecord(e0, nullptr);
+    for (int r = 0; r < reps; ++r) launch_accel(n, dx, dm, da, 1.0, 0.01, precision, false, c, nullptr);
+    (void)hipEventRecord(e1, nullptr);
+    if (hipEventSynchronize(e1) != hipSuccess) { cleanup(); return set_error(NBODY_EHIP, "tune: sync failed"); }
+    float ms = 0;
+    (void)hipEventElapsedTime(&ms, e0, e1);
+    if (ms / reps < best_ms) bc.rows = 1;
   }
   cleanup();
   record_tuned(dev, n, precision, bc);

@@ -60,6 +60,9 @@ constexpr int64_t kSymMinNJerk64 = 8192;
 constexpr int64_t kSymMinNSnap64 = 8192;
 constexpr int64_t kSymMinNJerk = 12288;
 constexpr int64_t kSymMinNSnap = 8192;
+// The row kernels serve the FP64 evaluations below the symmetric kernels' sizes
+// (their lanes' plain sums are also only as long as a fold block up to there).
+constexpr int64_t kRowsMaxN = 8191;
 
 // Per-call configuration of the all-pairs kernels.
 struct PairConfig {
@@ -72,6 +75,7 @@ struct PairConfig {
   int sym_jerk64 = 0;  // 1: the symmetric FP64 acceleration + jerk
   int sym_snap64 = 0;  // 1: the symmetric FP64 acceleration + jerk + snap
   int sym_snap = 0;  // 1: the symmetric acceleration + jerk + snap (FP32C/FP32 only)
+  int rows = 0;  // 1: the row kernels (small systems; below the symmetric kernels' sizes)
   int launches = 0;  // symmetric kernels: least number of launches of the half ring (0 = automatic)
   int rescue = 1;  // FP32C force: recompute rows flagged by the error estimate in FP64
   int sweep = 0;   // adjoint sweep: 0 = recompute overlapped on a second stream where allowed, 1 = one stream
@@ -182,8 +186,37 @@ int launch_ens_rescue(int32_t ncl, const int64_t* d_off, const double* d_eps, in
 
 // Elementwise KDK pieces over 3n entries.
 int launch_kick(int64_t n3, double* v, const double* a, double h, hipStream_t s);
-int launch_kick_drift(int64_t n3, double* x, double* v, const double* a, double h, double dt,
+int launch_kick_drift(int64_t n3, const double* x, double* xo, double* v, const double* a, double h, double dt,
                       int nkicks, hipStream_t s);
+
+// The FP64 row kernels (rows64.hip), for n <= kRowsMaxN: one launch per
+// evaluation, or per step with the elementwise update that follows it.  None
+// needs scratch; the outputs an update writes for other rows to read next (xo,
+// xp, vp, ap, lvo) are other buffers than the inputs.
+int launch_rows64_accel(int64_t n, const double* x, const double* m, double* a, double G, double eps, bool excl,
+                        hipStream_t s);
+int launch_rows64_jerk(int64_t n, const double* x, const double* v, const double* m, double* a, double* jk, double G,
+                       double eps, bool excl, hipStream_t s);
+int launch_rows64_snap(int64_t n, const double* x, const double* v, const double* acc, const double* m, double* a,
+                       double* jk, double* sn, double G, double eps, bool excl, hipStream_t s);
+int launch_rows64_vjp(int64_t n, const double* x, const double* m, const double* w, double* gx, double* gm, double G,
+                      double eps, bool excl, hipStream_t s);
+// a(x), then nkicks half-kicks of v and, with xo, the drift of x into xo.
+int launch_rows64_kdk(int64_t n, const double* x, double* xo, double* v, double* a, const double* m, double h, double dt,
+                      int nkicks, double G, double eps, bool excl, hipStream_t s);
+// The evaluation at the predicted (xp, vp), the corrector on the state, and with
+// xo the next prediction into (xo, vo).
+int launch_rows64_hermite4(int64_t n, const double* xp, const double* vp, const double* m, double* x, double* v,
+                           double* a, double* jk, double* xo, double* vo, double dt, double G, double eps, bool excl,
+                           hipStream_t s);
+// The same in sixth order; p and o hold (xp, vp, ap), o may be null.
+int launch_rows64_hermite6(int64_t n, double* const* p, const double* m, double* x, double* v, double* a, double* jk,
+                           double* sn, double* cr, double* const* o, double dt, double G, double eps, bool excl,
+                           hipStream_t s);
+// The VJP at (x, m) with cotangent lv, lx += gx, gm += its mass term, and with
+// lvo lv + dt lx into lvo.
+int launch_rows64_adjoint(int64_t n, const double* x, const double* m, const double* lv, double* lx, double* gm,
+                          double* lvo, double dt, double G, double eps, bool excl, hipStream_t s);
 
 // scale * phi_i, phi_i = sum_{j != i} m_j (|d|^2 + eps^2)^-1/2 in FP64, into phi[n].
 int launch_potential(int64_t n, const double* x, const double* m, double eps, double scale, double* phi,

@@ -3,8 +3,10 @@
 // energy/momentum diagnostics and the checkpointed adjoint sweep.  All of this
 // is FP64 and bound by HBM bandwidth; the all-pairs work lives in pairs.hip.
 #include <mutex>
+#include <utility>
 
 #include "common.h"
+#include "elementwise.h"
 
 namespace nb {
 
@@ -17,7 +19,8 @@ inline unsigned ew_blocks(int64_t cnt) { return (unsigned)((cnt + kEw - 1) / kEw
 // v += h a (nkicks times, each rounded separately) then x += dt v.
 // nkicks = 2 is the closing half-kick of one step followed by the opening
 // half-kick of the next, so one call of S steps equals two calls of S1 + S2.
-__global__ void kick_drift_kernel(int64_t n3, double* __restrict__ x, double* __restrict__ v,
+// The drifted positions go to xo, which may be x.
+__global__ void kick_drift_kernel(int64_t n3, const double* x, double* xo, double* __restrict__ v,
                                   const double* __restrict__ a, double h, double dt, int nkicks) {
   int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (e >= n3) return;
@@ -25,7 +28,7 @@ __global__ void kick_drift_kernel(int64_t n3, double* __restrict__ x, double* __
   double ve = v[e];
   for (int k = 0; k < nkicks; ++k) ve = fma(h, ae, ve);
   v[e] = ve;
-  x[e] = fma(dt, ve, x[e]);
+  xo[e] = fma(dt, ve, x[e]);
 }
 
 __global__ void kick_kernel(int64_t n3, double* __restrict__ v, const double* __restrict__ a, double h) {
@@ -57,76 +60,34 @@ __global__ void adjoint_update_kernel(int64_t n, double* __restrict__ lx, double
   if (e < n) gm[e] += gmp[e];
 }
 
-// Hermite predictor: xp = x + v dt + a dt^2/2 + j dt^3/6, vp = v + a dt + j dt^2/2.
 __global__ void hermite_predict_kernel(int64_t n3, const double* __restrict__ x, const double* __restrict__ v,
                                        const double* __restrict__ a, const double* __restrict__ jk, double dt,
                                        double* __restrict__ xp, double* __restrict__ vp) {
   int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (e >= n3) return;
-  const double h2 = 0.5 * dt * dt, h3 = dt * dt * dt / 6.0;
-  xp[e] = fma(jk[e], h3, fma(a[e], h2, fma(v[e], dt, x[e])));
-  vp[e] = fma(jk[e], h2, fma(a[e], dt, v[e]));
+  if (e < n3) hermite4_predict(x[e], v[e], a[e], jk[e], dt, xp[e], vp[e]);
 }
 
-// Hermite corrector, in place on (x, v, a, jk) from the evaluation (a1, j1):
-//   v1 = v + (a0 + a1) dt/2 + (j0 - j1) dt^2/12
-//   x1 = x + (v + v1) dt/2 + (a0 - a1) dt^2/12
 __global__ void hermite_correct_kernel(int64_t n3, double* __restrict__ x, double* __restrict__ v,
                                        double* __restrict__ a, double* __restrict__ jk,
                                        const double* __restrict__ a1, const double* __restrict__ j1, double dt) {
   int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (e >= n3) return;
-  const double h = 0.5 * dt, h12 = dt * dt / 12.0;
-  const double a0 = a[e], j0 = jk[e], an = a1[e], jn = j1[e], v0 = v[e];
-  const double v1 = fma(j0 - jn, h12, fma(a0 + an, h, v0));
-  x[e] = fma(a0 - an, h12, fma(v0 + v1, h, x[e]));
-  v[e] = v1;
-  a[e] = an;
-  jk[e] = jn;
+  if (e < n3) hermite4_correct(x[e], v[e], a[e], jk[e], a1[e], j1[e], dt);
 }
 
-// Sixth-order Hermite predictor (shared step h, crackle c from the previous step):
-//   xp = x + v h + a h^2/2 + j h^3/6 + s h^4/24 + c h^5/120
-//   vp = v + a h + j h^2/2 + s h^3/6 + c h^4/24
-//   ap = a + j h + s h^2/2 + c h^3/6
 __global__ void hermite6_predict_kernel(int64_t n3, const double* __restrict__ x, const double* __restrict__ v,
                                         const double* __restrict__ a, const double* __restrict__ jk,
                                         const double* __restrict__ sn, const double* __restrict__ cr, double h,
                                         double* __restrict__ xp, double* __restrict__ vp, double* __restrict__ ap) {
   int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (e >= n3) return;
-  const double c2 = h * h / 2.0, c3 = h * h * h / 6.0, c4 = h * h * h * h / 24.0, c5 = h * h * h * h * h / 120.0;
-  const double ae = a[e], je = jk[e], se = sn[e], ce = cr[e];
-  xp[e] = fma(ce, c5, fma(se, c4, fma(je, c3, fma(ae, c2, fma(v[e], h, x[e])))));
-  vp[e] = fma(ce, c4, fma(se, c3, fma(je, c2, fma(ae, h, v[e]))));
-  ap[e] = fma(ce, c3, fma(se, c2, fma(je, h, ae)));
+  if (e < n3) hermite6_predict(x[e], v[e], a[e], jk[e], sn[e], cr[e], h, xp[e], vp[e], ap[e]);
 }
 
-// Sixth-order Hermite corrector, in place on (x, v, a, jk, sn, cr) from the
-// evaluation (a1, j1, s1) at the predicted state:
-//   v1 = v + (a + a1) h/2 - (j1 - j) h^2/10 + (s + s1) h^3/120
-//   x1 = x + (v + v1) h/2 - (a1 - a) h^2/10 + (j + j1) h^3/120
-// and the crackle for the next predictor, the third derivative at t = h of the
-// quintic through (a, j, s) at both ends: 60 A - 36 B + 9 C with
-//   A = (a1 - a - j h - s h^2/2) / h^3,  B = (j1 - j - s h) / h^2,  C = (s1 - s) / h.
 __global__ void hermite6_correct_kernel(int64_t n3, double* __restrict__ x, double* __restrict__ v,
                                         double* __restrict__ a, double* __restrict__ jk, double* __restrict__ sn,
                                         double* __restrict__ cr, const double* __restrict__ a1,
                                         const double* __restrict__ j1, const double* __restrict__ s1, double h) {
   int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (e >= n3) return;
-  const double hh = h / 2.0, h10 = h * h / 10.0, h120 = h * h * h / 120.0;
-  const double a0 = a[e], j0 = jk[e], s0 = sn[e], an = a1[e], jn = j1[e], snn = s1[e], v0 = v[e];
-  const double v1 = fma(s0 + snn, h120, fma(-(jn - j0), h10, fma(a0 + an, hh, v0)));
-  x[e] = fma(j0 + jn, h120, fma(-(an - a0), h10, fma(v0 + v1, hh, x[e])));
-  v[e] = v1;
-  const double A = (an - a0 - j0 * h - s0 * (h * h / 2.0)) / (h * h * h);
-  const double B = (jn - j0 - s0 * h) / (h * h);
-  const double C = (snn - s0) / h;
-  cr[e] = 60.0 * A - 36.0 * B + 9.0 * C;
-  a[e] = an;
-  jk[e] = jn;
-  sn[e] = snn;
+  if (e < n3) hermite6_correct(x[e], v[e], a[e], jk[e], sn[e], cr[e], a1[e], j1[e], s1[e], h);
 }
 
 // ---- deterministic reduction of the diagnostics -----------------------
@@ -222,10 +183,10 @@ int launch_kick(int64_t n3, double* v, const double* a, double h, hipStream_t s)
   return NBODY_OK;
 }
 
-int launch_kick_drift(int64_t n3, double* x, double* v, const double* a, double h, double dt, int nkicks,
-                      hipStream_t s) {
+int launch_kick_drift(int64_t n3, const double* x, double* xo, double* v, const double* a, double h, double dt,
+                      int nkicks, hipStream_t s) {
   if (n3 == 0) return NBODY_OK;
-  kick_drift_kernel<<<ew_blocks(n3), kEw, 0, s>>>(n3, x, v, a, h, dt, nkicks);
+  kick_drift_kernel<<<ew_blocks(n3), kEw, 0, s>>>(n3, x, xo, v, a, h, dt, nkicks);
   NB_LAUNCH_CHECK("kick_drift_kernel");
   return NBODY_OK;
 }
@@ -283,9 +244,36 @@ int check_finite(const double* p, int64_t cnt, hipStream_t s, bool* all_finite) 
   return NBODY_OK;
 }
 
+// The KDK loop on the row kernels: one launch a step, which evaluates the
+// positions x_k, kicks, and drifts into x_{k+1} in another buffer (other
+// workgroups still read x_k): traj's next slot, or x and a temporary in turn so
+// that x_nsteps lands in x.
+static int run_kdk_rows(int64_t n, double* x, double* v, double* a, const double* m, double dt, int64_t nsteps, double G,
+                        double eps, bool excl, bool acc_valid, const PairConfig& cfg, hipStream_t s, double* traj) {
+  const int64_t n3 = 3 * n;
+  const double h = 0.5 * dt;
+  int st = NBODY_OK;
+  double* tmp = nullptr;
+  if (!traj && nsteps > 1 && !(tmp = static_cast<double*>(pair_scratch(cfg, sizeof(double) * (size_t)n3, &st)))) return st;
+  auto at = [&](int64_t k) -> double* { return traj ? traj + (size_t)k * n3 : (nsteps - k) % 2 == 0 || k == 0 ? x : tmp; };
+  if (!acc_valid) {
+    // a(x_0), with the first kick and drift where x_1 has a buffer of its own
+    const bool fuse = nsteps > 0 && at(1) != at(0);
+    if ((st = launch_rows64_kdk(n, at(0), fuse ? at(1) : nullptr, v, a, m, h, dt, fuse ? 1 : 0, G, eps, excl, s))) return st;
+    acc_valid = !fuse;
+  }
+  if (nsteps > 0 && acc_valid && (st = launch_kick_drift(n3, at(0), at(1), v, a, h, dt, 1, s))) return st;
+  for (int64_t k = 1; k <= nsteps; ++k) {
+    const bool last = k == nsteps;
+    if ((st = launch_rows64_kdk(n, at(k), last ? nullptr : at(k + 1), v, a, m, h, dt, last ? 1 : 2, G, eps, excl, s))) return st;
+  }
+  return NBODY_OK;
+}
+
 int run_kdk(int64_t n, double* x, double* v, double* a, const double* m, double dt, int64_t nsteps,
             double G, double eps, int precision, bool excl, bool acc_valid, const PairConfig& cfg,
             hipStream_t s, double* traj) {
+  if (cfg.rows && precision == NBODY_FP64) return run_kdk_rows(n, x, v, a, m, dt, nsteps, G, eps, excl, acc_valid, cfg, s, traj);
   const int64_t n3 = 3 * n;
   const double h = 0.5 * dt;
   int st;
@@ -294,7 +282,7 @@ int run_kdk(int64_t n, double* x, double* v, double* a, const double* m, double 
     if (st) return st;
   }
   for (int64_t k = 0; k < nsteps; ++k) {
-    st = launch_kick_drift(n3, x, v, a, h, dt, k == 0 ? 1 : 2, s);
+    st = launch_kick_drift(n3, x, x, v, a, h, dt, k == 0 ? 1 : 2, s);
     if (st) return st;
     st = launch_accel(n, x, m, a, G, eps, precision, excl, cfg, s);
     if (st) return st;
@@ -316,6 +304,22 @@ int run_hermite(int64_t n, double* x, double* v, double* a, double* jk, const do
   if (nsteps == 0) return NBODY_OK;
   double* ws = static_cast<double*>(workspace(current_device(), 1, sizeof(double) * 4 * (size_t)n3, &st));
   if (!ws) return st;
+  if (cfg.rows && precision == NBODY_FP64) {
+    // one launch a step: evaluate one pair of predicted buffers, correct the
+    // state and predict the next step into the other pair
+    double* p[2][2] = {{ws, ws + n3}, {ws + 2 * n3, ws + 3 * n3}};
+    hermite_predict_kernel<<<ew_blocks(n3), kEw, 0, s>>>(n3, x, v, a, jk, dt, p[0][0], p[0][1]);
+    NB_LAUNCH_CHECK("hermite_predict_kernel");
+    for (int64_t k = 0; k < nsteps; ++k) {
+      double* const* q = p[k % 2];
+      double* const* o = p[(k + 1) % 2];
+      const bool more = k + 1 < nsteps;
+      if ((st = launch_rows64_hermite4(n, q[0], q[1], m, x, v, a, jk, more ? o[0] : nullptr, more ? o[1] : nullptr, dt, G,
+                                       eps, excl, s)))
+        return st;
+    }
+    return NBODY_OK;
+  }
   double* xp = ws;
   double* vp = xp + n3;
   double* a1 = vp + n3;
@@ -348,6 +352,19 @@ int run_hermite6(int64_t n, double* x, double* v, double* a, double* jk, double*
     if ((st = launch_accel_jerk(n, x, v, m, a1, j1, G, eps, precision, excl, cfg, s))) return st;
     if ((st = launch_accel_jerk_snap(n, x, v, a1, m, a, jk, sn, G, eps, precision, excl, cfg, s))) return st;
     if ((st = launch_fill(n3, cr, 0.0, s))) return st;
+  }
+  if (cfg.rows && precision == NBODY_FP64) {
+    // one launch a step, as in run_hermite (xp, vp, ap and a1, j1, s1 hold the two predictions)
+    double* p[2][3] = {{xp, vp, ap}, {a1, j1, s1}};
+    if (nsteps > 0) {
+      hermite6_predict_kernel<<<ew_blocks(n3), kEw, 0, s>>>(n3, x, v, a, jk, sn, cr, dt, xp, vp, ap);
+      NB_LAUNCH_CHECK("hermite6_predict_kernel");
+    }
+    for (int64_t k = 0; k < nsteps; ++k)
+      if ((st = launch_rows64_hermite6(n, p[k % 2], m, x, v, a, jk, sn, cr, k + 1 < nsteps ? p[(k + 1) % 2] : nullptr, dt,
+                                       G, eps, excl, s)))
+        return st;
+    return NBODY_OK;
   }
   for (int64_t k = 0; k < nsteps; ++k) {
     hermite6_predict_kernel<<<ew_blocks(n3), kEw, 0, s>>>(n3, x, v, a, jk, sn, cr, dt, xp, vp, ap);
@@ -462,6 +479,12 @@ int run_traj_grad(int64_t n, const double* ckx, const double* ckv, int64_t every
   // lambda_x and lambda_v live in the caller's outputs gx0 / gv0.
   double* lx = gx0;
   double* lv = gv0;
+  // on the row kernels the VJP's launch also does its update; lambda_v, which
+  // every workgroup reads, then drifts between gv0 and gxp's space in turn (one
+  // drift a step: it starts where the last one leaves it in gv0)
+  const bool rows = cfg.rows && precision == NBODY_FP64;
+  double* lvo = gxp;
+  if (rows && nsteps % 2 == 1) std::swap(lv, lvo);
   if ((st = launch_copy(n3, gxT, lx, s))) return st;
   if ((st = launch_copy(n3, gvT, lv, s))) return st;
   if ((st = launch_fill(n, gm, 0.0, s))) return st;
@@ -494,6 +517,11 @@ int run_traj_grad(int64_t n, const double* ckx, const double* ckv, int64_t every
       const double c = (p == nsteps) ? h : dt;
       const double* xp = traj + (size_t)(p - k0) * n3;
       int e;
+      if (rows) {
+        if ((e = launch_rows64_adjoint(n, xp, m, lv, lx, gm, lvo, dt, G * c, eps, excl, s))) return e;
+        std::swap(lv, lvo);
+        continue;
+      }
       if ((e = launch_vjp(n, xp, m, lv, gxp, gmp, G * c, eps, precision, excl, cfg, s))) return e;
       adjoint_update_kernel<<<ew_blocks(n3), kEw, 0, s>>>(n, lx, lv, gm, gxp, gmp, dt, 1);
       NB_LAUNCH_CHECK("adjoint_update_kernel");
@@ -534,6 +562,7 @@ int run_traj_grad(int64_t n, const double* ckx, const double* ckv, int64_t every
     if (sw) return sw;
   }
   // opening half-kick of step 0 at x_0
+  if (nsteps > 0 && rows) return launch_rows64_adjoint(n, ckx, m, lv, lx, gm, nullptr, dt, G * h, eps, excl, s);
   if (nsteps > 0) {
     if ((st = launch_vjp(n, ckx, m, lv, gxp, gmp, G * h, eps, precision, excl, cfg, s))) return st;
     adjoint_update_kernel<<<ew_blocks(n3), kEw, 0, s>>>(n, lx, lv, gm, gxp, gmp, dt, 0);

@@ -1,5 +1,5 @@
-// Device-side pair arithmetic shared by the all-pairs kernels (pairs.hip) and
-// the persistent ensemble kernel (ensemble.hip).
+// Device-side pair arithmetic shared by the all-pairs kernels (pairs.hip, the
+// row kernels) and the persistent ensemble kernel (ensemble.hip).
 #pragma once
 
 #include <type_traits>
@@ -145,6 +145,96 @@ __device__ __forceinline__ float near_rc2(double xa, double ya, double za, doubl
   const float fx = fmaxf(kNearX, kNearN / cbrtf((float)(n > 0 ? n : 1)));
   const float dc = fmaxf(fx * (float)fmax(fabs(xa), fmax(fabs(ya), fabs(za))), kNearEps * (float)eps);
   return dc * dc + (float)(eps * eps);
+}
+
+// Pair terms shared by the ordered evaluations of every size.
+// u = m_k w_j - m_j w_k without contraction, so that u is exactly zero for j == k.
+template <typename R>
+__device__ __forceinline__ R cross_weight(R mk, R wj, R mj, R wk) {
+#pragma clang fp contract(off)
+  R a = mk * wj;
+  R b = mj * wk;
+  return a - b;
+}
+
+// One VJP pair term for lane particle k and record j, displacement d = x_j - x_k:
+//   g += r^-3 u - 3 r^-5 (d.u) d,  gm -= r^-3 (d . w_j),  u = m_k w_j - m_j w_k.
+template <typename R>
+__device__ __forceinline__ R vjp_pair(R dx, R dy, R dz, R e2, R mj, R wjx, R wjy, R wjz, R mk, R wkx, R wky,
+                                      R wkz, bool self, R& px, R& py, R& pz, R& pm) {
+  R r2 = fma(dz, dz, fma(dy, dy, fma(dx, dx, e2)));
+  R ri = rsq(r2);
+  R ri2 = ri * ri;
+  R r3 = ri2 * ri;
+  R r5 = r3 * ri2;
+  r3 = self ? R(0) : r3;
+  r5 = self ? R(0) : r5;
+  R ux = cross_weight(mk, wjx, mj, wkx);
+  R uy = cross_weight(mk, wjy, mj, wky);
+  R uz = cross_weight(mk, wjz, mj, wkz);
+  R du = fma(dz, uz, fma(dy, uy, dx * ux));
+  R c = R(3) * r5 * du;
+  px = fma(-c, dx, fma(r3, ux, px));
+  py = fma(-c, dy, fma(r3, uy, py));
+  pz = fma(-c, dz, fma(r3, uz, pz));
+  R dw = fma(dz, wjz, fma(dy, wjy, dx * wjx));
+  pm = fma(-r3, dw, pm);
+  return r2;
+}
+
+// One acceleration + jerk pair term (App. A, Algorithm 3) for displacement d =
+// x_j - x_i and velocity difference w = v_j - v_i, added to pa and pj; self
+// leaves the own pair out.  Returns the softened squared distance.
+template <typename R>
+__device__ __forceinline__ R jerk_pair(R dx, R dy, R dz, R wx, R wy, R wz, R mj, R e2, bool self, R* pa, R* pj) {
+  const R r2 = fma(dz, dz, fma(dy, dy, fma(dx, dx, e2)));
+  const R ri = rsq(r2);
+  R ri2 = ri * ri;
+  R tj = (mj * ri) * ri2;                            // t_j = p_w,j r^-3
+  if (self) {
+    tj = R(0);
+    ri2 = R(0);
+  }
+  const R vr = fma(dz, wz, fma(dy, wy, dx * wx));    // v_r = r . v
+  const R qq = R(-3) * ri2 * vr;                     // q = A v_r, A = -3 r^-2
+  pa[0] = fma(tj, dx, pa[0]);
+  pa[1] = fma(tj, dy, pa[1]);
+  pa[2] = fma(tj, dz, pa[2]);
+  pj[0] = fma(tj, fma(qq, dx, wx), pj[0]);
+  pj[1] = fma(tj, fma(qq, dy, wy), pj[1]);
+  pj[2] = fma(tj, fma(qq, dz, wz), pj[2]);
+  return r2;
+}
+
+// One acceleration + jerk + snap pair term (displacement d, velocity and
+// acceleration differences w and u) added to pa, pj and ps; self leaves the own
+// pair out.  Returns the softened squared distance.
+template <typename R>
+__device__ __forceinline__ R snap_pair(const R* d, const R* w, const R* u, R mj, R e2, bool self, R* pa, R* pj,
+                                       R* ps) {
+  const R r2 = fma(d[2], d[2], fma(d[1], d[1], fma(d[0], d[0], e2)));
+  const R ri = rsq(r2);
+  R sinv = ri * ri;
+  R tj = (mj * ri) * sinv;
+  if (self) {
+    tj = R(0);
+    sinv = R(0);
+  }
+  const R alpha = fma(d[2], w[2], fma(d[1], w[1], d[0] * w[0])) * sinv;
+  const R wwdu = fma(d[2], u[2], fma(d[1], u[1], fma(d[0], u[0], fma(w[2], w[2], fma(w[1], w[1], w[0] * w[0])))));
+  const R beta = fma(wwdu, sinv, alpha * alpha);
+  const R a3 = R(-3) * alpha;
+  const R b3 = R(-3) * beta;
+#pragma unroll
+  for (int c = 0; c < 3; ++c) {
+    const R P0 = tj * d[c];
+    const R P1 = fma(a3, P0, tj * w[c]);
+    const R P2 = fma(R(2) * a3, P1, fma(b3, P0, tj * u[c]));
+    pa[c] += P0;
+    pj[c] += P1;
+    ps[c] += P2;
+  }
+  return r2;
 }
 
 }  // namespace nb

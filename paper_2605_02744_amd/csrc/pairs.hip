@@ -237,40 +237,6 @@ __device__ __forceinline__ WRec<MODE> load_wrec(const double* __restrict__ x, co
   return o;
 }
 
-// u = m_k w_j - m_j w_k without contraction, so that u is exactly zero for j == k.
-template <typename R>
-__device__ __forceinline__ R cross_weight(R mk, R wj, R mj, R wk) {
-#pragma clang fp contract(off)
-  R a = mk * wj;
-  R b = mj * wk;
-  return a - b;
-}
-
-// One VJP pair term for lane particle k and record j, displacement d = x_j - x_k:
-//   g += r^-3 u - 3 r^-5 (d.u) d,  gm -= r^-3 (d . w_j),  u = m_k w_j - m_j w_k.
-template <typename R>
-__device__ __forceinline__ R vjp_pair(R dx, R dy, R dz, R e2, R mj, R wjx, R wjy, R wjz, R mk, R wkx, R wky,
-                                      R wkz, bool self, R& px, R& py, R& pz, R& pm) {
-  R r2 = fma(dz, dz, fma(dy, dy, fma(dx, dx, e2)));
-  R ri = rsq(r2);
-  R ri2 = ri * ri;
-  R r3 = ri2 * ri;
-  R r5 = r3 * ri2;
-  r3 = self ? R(0) : r3;
-  r5 = self ? R(0) : r5;
-  R ux = cross_weight(mk, wjx, mj, wkx);
-  R uy = cross_weight(mk, wjy, mj, wky);
-  R uz = cross_weight(mk, wjz, mj, wkz);
-  R du = fma(dz, uz, fma(dy, uy, dx * ux));
-  R c = R(3) * r5 * du;
-  px = fma(-c, dx, fma(r3, ux, px));
-  py = fma(-c, dy, fma(r3, uy, py));
-  pz = fma(-c, dz, fma(r3, uz, pz));
-  R dw = fma(dz, wjz, fma(dy, wjy, dx * wjx));
-  pm = fma(-r3, dw, pm);
-  return r2;
-}
-
 // gx_k = G sum_j [ r^-3 u - 3 r^-5 (d.u) d ],  gm_k = -G sum_j r^-3 (d . w_j),
 // d = x_j - x_k, u = m_k w_j - m_j w_k, r^2 = |d|^2 + eps^2.
 // split == 1: writes G * sums to gx (3n) and gm (n).
@@ -413,27 +379,6 @@ __global__ __launch_bounds__(kBlock) void vjp_kernel(int n, const double* __rest
 // the lane's repair radius is redone with float-float displacements for those
 // pairs.  split == 1 writes G*sums to a and jk; split > 1 writes slice y's
 // unscaled 6n partials (a then jerk) at part + y*6n.
-template <typename R>
-__device__ __forceinline__ R jerk_pair(R dx, R dy, R dz, R wx, R wy, R wz, R mj, R e2, bool self, R* pa, R* pj) {
-  const R r2 = fma(dz, dz, fma(dy, dy, fma(dx, dx, e2)));
-  const R ri = rsq(r2);
-  R ri2 = ri * ri;
-  R tj = (mj * ri) * ri2;                            // t_j = p_w,j r^-3
-  if (self) {
-    tj = R(0);
-    ri2 = R(0);
-  }
-  const R vr = fma(dz, wz, fma(dy, wy, dx * wx));    // v_r = r . v
-  const R qq = R(-3) * ri2 * vr;                     // q = A v_r, A = -3 r^-2
-  pa[0] = fma(tj, dx, pa[0]);
-  pa[1] = fma(tj, dy, pa[1]);
-  pa[2] = fma(tj, dz, pa[2]);
-  pj[0] = fma(tj, fma(qq, dx, wx), pj[0]);
-  pj[1] = fma(tj, fma(qq, dy, wy), pj[1]);
-  pj[2] = fma(tj, fma(qq, dz, wz), pj[2]);
-  return r2;
-}
-
 template <int MODE, int IPL, bool EXCL>
 __global__ __launch_bounds__(kBlock) void jerk_kernel(int n, const double* __restrict__ x,
                                                       const double* __restrict__ v,
@@ -650,34 +595,6 @@ __device__ __forceinline__ SRec<MODE> load_srec(const double* __restrict__ x, co
     o.u.x = o.u.y = o.u.z = o.u.w = R(0);
   }
   return o;
-}
-
-template <typename R>
-__device__ __forceinline__ R snap_pair(const R* d, const R* w, const R* u, R mj, R e2, bool self, R* pa, R* pj,
-                                       R* ps) {
-  const R r2 = fma(d[2], d[2], fma(d[1], d[1], fma(d[0], d[0], e2)));
-  const R ri = rsq(r2);
-  R sinv = ri * ri;
-  R tj = (mj * ri) * sinv;
-  if (self) {
-    tj = R(0);
-    sinv = R(0);
-  }
-  const R alpha = fma(d[2], w[2], fma(d[1], w[1], d[0] * w[0])) * sinv;
-  const R wwdu = fma(d[2], u[2], fma(d[1], u[1], fma(d[0], u[0], fma(w[2], w[2], fma(w[1], w[1], w[0] * w[0])))));
-  const R beta = fma(wwdu, sinv, alpha * alpha);
-  const R a3 = R(-3) * alpha;
-  const R b3 = R(-3) * beta;
-#pragma unroll
-  for (int c = 0; c < 3; ++c) {
-    const R P0 = tj * d[c];
-    const R P1 = fma(a3, P0, tj * w[c]);
-    const R P2 = fma(R(2) * a3, P1, fma(b3, P0, tj * u[c]));
-    pa[c] += P0;
-    pj[c] += P1;
-    ps[c] += P2;
-  }
-  return r2;
 }
 
 template <int MODE, int IPL, bool EXCL>
@@ -955,6 +872,7 @@ int launch_accel_jerk_snap(int64_t n, const double* x, const double* v, const do
   if (n == 0) return NBODY_OK;
   if (cfg.sym_snap && precision != kFP64)
     return launch_sym_snap(n, x, v, acc, m, a, jk, sn, G, eps, precision, excl, cfg, s);
+  if (cfg.rows && precision == kFP64) return launch_rows64_snap(n, x, v, acc, m, a, jk, sn, G, eps, excl, s);
   if (cfg.sym_snap64 && precision == kFP64) return launch_sym_snap64(n, x, v, acc, m, a, jk, sn, G, eps, excl, cfg, s);
   const int split = cfg.split < 1 ? 1 : cfg.split;
   switch (precision) {
@@ -969,6 +887,7 @@ int launch_accel_jerk(int64_t n, const double* x, const double* v, const double*
                       double eps, int precision, bool excl, const PairConfig& cfg, hipStream_t s) {
   if (n == 0) return NBODY_OK;
   if (cfg.sym_jerk && precision != kFP64) return launch_sym_jerk(n, x, v, m, a, jk, G, eps, precision, excl, cfg, s);
+  if (cfg.rows && precision == kFP64) return launch_rows64_jerk(n, x, v, m, a, jk, G, eps, excl, s);
   if (cfg.sym_jerk64 && precision == kFP64) return launch_sym_jerk64(n, x, v, m, a, jk, G, eps, excl, cfg, s);
   const int split = cfg.split < 1 ? 1 : cfg.split;
   const bool one = cfg.ipl <= 1;
@@ -986,6 +905,7 @@ int launch_accel_jerk(int64_t n, const double* x, const double* v, const double*
 int launch_accel(int64_t n, const double* x, const double* m, double* a, double G, double eps,
                  int precision, bool excl, const PairConfig& cfg, hipStream_t s) {
   if (n == 0) return NBODY_OK;
+  if (cfg.rows && precision == kFP64) return launch_rows64_accel(n, x, m, a, G, eps, excl, s);
   if (cfg.sym) {
     if (precision == kFP64) return launch_sym_accel64(n, x, m, a, G, eps, excl, cfg, s);
     return launch_sym_accel(n, x, m, a, G, eps, precision, excl, cfg, s);
@@ -1014,6 +934,7 @@ int launch_vjp(int64_t n, const double* x, const double* m, const double* w, dou
                double G, double eps, int precision, bool excl, const PairConfig& cfg, hipStream_t s) {
   if (n == 0) return NBODY_OK;
   if (cfg.sym_vjp && precision != kFP64) return launch_sym_vjp(n, x, m, w, gx, gm, G, eps, precision, excl, cfg, s);
+  if (cfg.rows && precision == kFP64) return launch_rows64_vjp(n, x, m, w, gx, gm, G, eps, excl, s);
   if (cfg.sym_vjp64 && precision == kFP64) return launch_sym_vjp64(n, x, m, w, gx, gm, G, eps, cfg, s);
   const int split = cfg.split < 1 ? 1 : cfg.split;
   // The VJP keeps twice the accumulators of the force, so it runs at most 2 i per lane.

@@ -1,0 +1,314 @@
+// Row evaluations of small FP64 systems: the device side (rows64.hip launches it).
+//
+// One workgroup owns kRows consecutive particles (rows) and evaluates them against
+// every j, so an evaluation is one launch that leaves finished sums and needs no
+// scratch; what follows an evaluation elementwise (kicks and drift, the Hermite
+// corrector and predictor, the adjoint's update) is done on those sums by the
+// same launch.  The tile kernels of pairs.hip split the j-range of a small
+// system over workgroups instead, which costs a second kernel for the slice sums
+// and a third for the update.
+//
+// The lanes split j (lane t takes j = t, t + 256, ...), the rows sit in scalar
+// registers: a j-record loaded once serves kRows independent pairs, which hide
+// the FP64 latencies of one another at the low occupancy a small system leaves,
+// and neighbouring lanes load neighbouring records, straight from L2 (no LDS
+// staging, no barrier in the loop).  The kRows * NC sums of a lane are added over
+// the wave by exchanging halves (each exchange sums two values at once, so a
+// wave's sums cost about three instructions per value and not six full
+// butterflies), then over the four waves in order: fixed order, no atomics.  A
+// lane's plain FP64 sum has at most kRowsMaxN / 256 = 32 terms and is then added
+// over 8 levels, fewer roundings in a row than the 64 plain terms of a fold block
+// in the tile kernels.
+//
+// Bound: up to ~2000 particles the latency of one launch and one lane's chain
+// (3.4 us per evaluation at 1000), above that FP64 issue.  Measured per step,
+// tile kernels with their slice sums and updates -> rows: KDK 15.1 -> 4.5 us at
+// 1024; fourth-order Hermite 58 -> 36 us at 5000.  Rows per workgroup, accel /
+// jerk / snap / vjp in us: at 1024 4 rows 3.4 / 4.6 / 6.0 / 4.5, 2 rows 3.4 / 4.9 /
+// 5.5 / 4.7, 8 rows 4.3 / 7.0 / - / 7.5 (half the CUs idle); at 5000 4 rows 20.6 /
+// 35 / 61 / 39, 2 rows 28 / 47 / 68 / 51 (record loads), 6 rows 23 / 39 / - / 46
+// (fewer workgroups than the CUs divide evenly).  Up to 2048 particles a lane
+// loads its records four ahead (snap: two): right after the launch that wrote
+// them they come from beyond L2, and with one or two waves per SIMD nothing else
+// hides that (KDK step at 1024 5.2 us one at a time, 4.5 us four ahead); above,
+// other waves do, and fewer registers are worth more.
+#pragma once
+
+#include "elementwise.h"
+#include "pair_math.h"
+
+namespace nb {
+namespace {
+
+constexpr int kRowT = 256;  // lanes per workgroup
+constexpr int kRows = 4;    // rows per workgroup
+
+struct RowArgs {
+  int n;
+  const double* x;  // [3][n]
+  const double* m;  // [n]
+  const double* w;  // [3][n] velocities or cotangent
+  const double* u;  // [3][n] accelerations (snap)
+  double e2;
+};
+
+// The double at a byte offset from a base that is the same for every lane: the
+// base stays scalar and one offset serves all of a record's arrays.
+__device__ __forceinline__ double at_off(const double* base, unsigned off) {
+  return *reinterpret_cast<const double*>(reinterpret_cast<const char*>(base) + off);
+}
+
+// The evaluations: NC sums per row, NW doubles per record.  w[0 .. 2] is the
+// position, w[3] the mass, then velocity or cotangent and acceleration; row() and
+// rec() load them, past() is a record past the end: far away and massless, so
+// its terms are exact zeros.
+template <int NW>
+struct RowRec {
+  double w[NW];
+  static __device__ __forceinline__ RowRec at(const RowArgs& A, unsigned off) {
+    RowRec r;
+#pragma unroll
+    for (int c = 0; c < 3; ++c) r.w[c] = at_off(A.x + (size_t)c * A.n, off);
+    r.w[3] = at_off(A.m, off);
+#pragma unroll
+    for (int c = 4; c < NW; ++c) r.w[c] = at_off(c < 7 ? A.w + (size_t)(c - 4) * A.n : A.u + (size_t)(c - 7) * A.n, off);
+    return r;
+  }
+  static __device__ __forceinline__ RowRec past() {
+    RowRec r;
+#pragma unroll
+    for (int c = 0; c < NW; ++c) r.w[c] = c < 3 ? 1.0e30 : 0.0;
+    return r;
+  }
+};
+
+struct RowAccel {
+  static constexpr int NC = 3, NW = 4;
+  // m_j s^-3/2 from y = rsq(s) and the residual h = 1 - s y^2 in one step:
+  // (1 - h)^(-3/2) = 1 + 3h/2 + 15h^2/8 + O(h^3), |h| ~ 1e-7, one operation less
+  // than refining y first and cubing it, and two roundings fewer
+  static __device__ __forceinline__ void pair(const RowRec<NW>& r, const RowRec<NW>& s, double e2, bool self, double* p) {
+    const double dx = r.w[0] - s.w[0], dy = r.w[1] - s.w[1], dz = r.w[2] - s.w[2];
+    const double q = fma(dz, dz, fma(dy, dy, fma(dx, dx, e2)));
+    const double y = __builtin_amdgcn_rsq(q);
+    const double y2 = y * y, h = fma(-q, y2, 1.0), ym = y2 * (y * r.w[3]);
+    double f = fma(ym, h * fma(1.875, h, 1.5), ym);
+    f = self ? 0.0 : f;
+    p[0] = fma(f, dx, p[0]);
+    p[1] = fma(f, dy, p[1]);
+    p[2] = fma(f, dz, p[2]);
+  }
+};
+
+struct RowJerk {
+  static constexpr int NC = 6, NW = 7;
+  static __device__ __forceinline__ void pair(const RowRec<NW>& r, const RowRec<NW>& s, double e2, bool self, double* p) {
+    jerk_pair<double>(r.w[0] - s.w[0], r.w[1] - s.w[1], r.w[2] - s.w[2], r.w[4] - s.w[4], r.w[5] - s.w[5],
+                      r.w[6] - s.w[6], r.w[3], e2, self, p, p + 3);
+  }
+};
+
+struct RowSnap {
+  static constexpr int NC = 9, NW = 10;
+  static __device__ __forceinline__ void pair(const RowRec<NW>& r, const RowRec<NW>& s, double e2, bool self, double* p) {
+    const double d[3] = {r.w[0] - s.w[0], r.w[1] - s.w[1], r.w[2] - s.w[2]};
+    const double w[3] = {r.w[4] - s.w[4], r.w[5] - s.w[5], r.w[6] - s.w[6]};
+    const double u[3] = {r.w[7] - s.w[7], r.w[8] - s.w[8], r.w[9] - s.w[9]};
+    snap_pair<double>(d, w, u, r.w[3], e2, self, p, p + 3, p + 6);
+  }
+};
+
+struct RowVjp {
+  static constexpr int NC = 4, NW = 7;
+  static __device__ __forceinline__ void pair(const RowRec<NW>& r, const RowRec<NW>& s, double e2, bool self, double* p) {
+    vjp_pair<double>(r.w[0] - s.w[0], r.w[1] - s.w[1], r.w[2] - s.w[2], e2, r.w[3], r.w[4], r.w[5], r.w[6], s.w[3],
+                     s.w[4], s.w[5], s.w[6], self, p[0], p[1], p[2], p[3]);
+  }
+};
+
+// Two doubles through one exchange of halves (X = 32: the wave's halves; 16: the
+// odd rows of 16 lanes of a with the even rows of b), summed: lanes of the first
+// kind hold a's sum over both kinds, lanes of the second kind b's.
+template <int X>
+__device__ __forceinline__ double swap_add(double a, double b) {
+  const unsigned al = (unsigned)__double2loint(a), ah = (unsigned)__double2hiint(a);
+  const unsigned bl = (unsigned)__double2loint(b), bh = (unsigned)__double2hiint(b);
+  if constexpr (X == 32) {
+    const auto l = __builtin_amdgcn_permlane32_swap(al, bl, false, false);
+    const auto h = __builtin_amdgcn_permlane32_swap(ah, bh, false, false);
+    return __hiloint2double((int)h[0], (int)l[0]) + __hiloint2double((int)h[1], (int)l[1]);
+  } else {
+    const auto l = __builtin_amdgcn_permlane16_swap(al, bl, false, false);
+    const auto h = __builtin_amdgcn_permlane16_swap(ah, bh, false, false);
+    return __hiloint2double((int)h[0], (int)l[0]) + __hiloint2double((int)h[1], (int)l[1]);
+  }
+}
+
+// A double rotated within each row of 16 lanes by K, added to itself.
+template <int K>
+__device__ __forceinline__ double ror_add(double v) {
+  const int l = __builtin_amdgcn_mov_dpp(__double2loint(v), 0x120 + K, 0xF, 0xF, true);
+  const int h = __builtin_amdgcn_mov_dpp(__double2hiint(v), 0x120 + K, 0xF, 0xF, true);
+  return v + __hiloint2double(h, l);
+}
+
+// Sums the M values of every lane over the wave and stores them at dst[0 .. M).
+// After the two exchanges slot q of a lane in row r (of 4) holds value
+// 4q + 2 (r & 1) + (r >> 1), summed over the four rows.
+template <int M>
+__device__ __forceinline__ void wave_sums(const double (&p)[M], double* dst) {
+  const int lane = threadIdx.x & 63, row = lane >> 4;
+#pragma unroll
+  for (int q = 0; q < M; q += 4) {
+    auto at = [&](int k) { return q + k < M ? p[q + k < M ? q + k : 0] : 0.0; };
+    double v = swap_add<16>(swap_add<32>(at(0), at(1)), swap_add<32>(at(2), at(3)));
+    v = ror_add<8>(v);
+    v = ror_add<4>(v);
+    v = ror_add<2>(v);
+    v = ror_add<1>(v);
+    const int k = q + 2 * (row & 1) + (row >> 1);
+    if ((lane & 15) == 0 && k < M) dst[k] = v;
+  }
+}
+
+// ------------------------------------------------ what follows an evaluation
+// Each is called by one thread per (row i, component c < NO) with tot[q] the
+// row's sum of component q; n is the components' stride.
+
+// The sums times scale: components 0-2 at o0, 3-5 at o1, 6-8 at o2 (the VJP's
+// component 3, a particle array, at o1).
+struct EpiStore {
+  double scale;
+  double *o0, *o1, *o2;
+  template <int NC>
+  __device__ __forceinline__ void apply(int n, int i, int c, const double* tot) const {
+    double* o = c < 3 ? o0 + (size_t)c * n : c < 6 ? o1 + (size_t)(c - 3) * n : o2 + (size_t)(c - 6) * n;
+    o[i] = scale * tot[c];
+  }
+  template <int NC> static constexpr int outs() { return NC; }
+};
+
+// KDK: a, the closing half-kick (and, with two kicks, the next step's opening
+// one, each rounded separately) and with xo the drift into xo, another buffer
+// than the positions x this launch still reads.
+struct EpiKdk {
+  double scale, h, dt;
+  int nkicks;
+  const double* x;
+  double *xo, *v, *a;
+  template <int NC>
+  __device__ __forceinline__ void apply(int n, int i, int c, const double* tot) const {
+    const size_t e = (size_t)c * n + i;
+    const double ae = scale * tot[c];
+    double ve = v[e];
+    for (int k = 0; k < nkicks; ++k) ve = fma(h, ae, ve);
+    a[e] = ae;
+    v[e] = ve;
+    if (xo) xo[e] = fma(dt, ve, x[e]);
+  }
+  template <int NC> static constexpr int outs() { return 3; }
+};
+
+// Fourth-order Hermite: the corrector on the row's state and with xp the next
+// step's prediction, into other buffers than this launch reads.
+struct EpiHermite4 {
+  double scale, dt;
+  double *x, *v, *a, *jk, *xp, *vp;
+  template <int NC>
+  __device__ __forceinline__ void apply(int n, int i, int c, const double* tot) const {
+    const size_t e = (size_t)c * n + i;
+    const double an = scale * tot[c], jn = scale * tot[3 + c];
+    double xe = x[e], ve = v[e], ae = a[e], je = jk[e];
+    hermite4_correct(xe, ve, ae, je, an, jn, dt);
+    x[e] = xe; v[e] = ve; a[e] = ae; jk[e] = je;
+    if (xp) hermite4_predict(xe, ve, ae, je, dt, xp[e], vp[e]);
+  }
+  template <int NC> static constexpr int outs() { return 3; }
+};
+
+// Sixth-order Hermite, the same way.
+struct EpiHermite6 {
+  double scale, dt;
+  double *x, *v, *a, *jk, *sn, *cr, *xp, *vp, *ap;
+  template <int NC>
+  __device__ __forceinline__ void apply(int n, int i, int c, const double* tot) const {
+    const size_t e = (size_t)c * n + i;
+    const double an = scale * tot[c], jn = scale * tot[3 + c], s1 = scale * tot[6 + c];
+    double xe = x[e], ve = v[e], ae = a[e], je = jk[e], se = sn[e], ce;
+    hermite6_correct(xe, ve, ae, je, se, ce, an, jn, s1, dt);
+    x[e] = xe; v[e] = ve; a[e] = ae; jk[e] = je; sn[e] = se; cr[e] = ce;
+    if (xp) hermite6_predict(xe, ve, ae, je, se, ce, dt, xp[e], vp[e], ap[e]);
+  }
+  template <int NC> static constexpr int outs() { return 3; }
+};
+
+// The adjoint's update after a VJP: lx += gx, gm += the mass term, and with lvo
+// lv's drift into lvo, another buffer than the cotangents lv this launch reads.
+struct EpiAdjoint {
+  double scale, dt;
+  double *lx, *gm;
+  const double* lv;
+  double* lvo;
+  template <int NC>
+  __device__ __forceinline__ void apply(int n, int i, int c, const double* tot) const {
+    if (c == 3) {
+      gm[i] += scale * tot[3];
+      return;
+    }
+    const size_t e = (size_t)c * n + i;
+    const double l = lx[e] + scale * tot[c];
+    lx[e] = l;
+    if (lvo) lvo[e] = fma(dt, l, lv[e]);
+  }
+  template <int NC> static constexpr int outs() { return NC; }
+};
+
+// Grid: ceil(n / kRows) workgroups of kRowT lanes; U records per lane are loaded
+// before any is used.
+template <class E, int U, bool EXCL, class Epi>
+__global__ __launch_bounds__(kRowT) void rows64_kernel(RowArgs A, Epi epi) {
+  constexpr int NC = E::NC, M = kRows * NC, W = kRowT / 64;
+  using Rec = RowRec<E::NW>;
+  __shared__ double s_red[W][M];
+  __shared__ double s_tot[M];
+  const int t = threadIdx.x;
+  const int i0 = blockIdx.x * kRows;
+  Rec s[kRows];
+#pragma unroll
+  for (int k = 0; k < kRows; ++k) s[k] = Rec::at(A, 8u * (unsigned)min(i0 + k, A.n - 1));
+  double p[M];
+#pragma unroll
+  for (int q = 0; q < M; ++q) p[q] = 0.0;
+  for (int jb = 0; jb < A.n; jb += U * kRowT) {
+    Rec r[U];
+    if (jb + U * kRowT <= A.n) {  // the same for every lane: no tests in whole blocks
+#pragma unroll
+      for (int u = 0; u < U; ++u) r[u] = Rec::at(A, 8u * (unsigned)(jb + u * kRowT + t));
+    } else {
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        r[u] = Rec::past();
+        if (jb + u * kRowT + t < A.n) r[u] = Rec::at(A, 8u * (unsigned)(jb + u * kRowT + t));
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int j = jb + u * kRowT + t;
+      if (jb + u * kRowT >= A.n) break;  // the same for every lane
+#pragma unroll
+      for (int k = 0; k < kRows; ++k) E::pair(r[u], s[k], A.e2, EXCL && j == i0 + k, p + k * NC);
+    }
+  }
+  wave_sums<M>(p, s_red[t / 64]);
+  __syncthreads();
+  if (t < M) s_tot[t] = ((s_red[0][t] + s_red[1][t]) + s_red[2][t]) + s_red[3][t];
+  __syncthreads();
+  constexpr int kOuts = Epi::template outs<NC>();
+  if (t < kRows * kOuts) {
+    const int k = t % kRows, c = t / kRows;
+    if (i0 + k < A.n) epi.template apply<NC>(A.n, i0 + k, c, s_tot + k * NC);
+  }
+}
+
+}  // namespace
+}  // namespace nb
