@@ -148,6 +148,10 @@ int nbody_energy(int64_t n, const double* x, const double* v, const double* m,
  * specific energy of particle i is |v_i|^2/2 + phi_i: the per-particle energy
  * distribution that Sec. 4.1 (Fig. 4) compares between the accelerated run
  * and the double-precision reference; sum_i m_i phi_i = 2 W of nbody_energy.
+ * From 8192 particles on (or as nbody_config.pairs says; the same holds for
+ * nbody_energy) each unordered pair is evaluated once and applied to both
+ * particles, summed in a fixed order, with a workspace of per-distance sums as
+ * nbody_accel's.
  * x: [3][n], m: [n], phi: [n] FP64 device memory, caller-owned; phi must not
  * alias x or m.  Errors: as nbody_accel (NBODY_ENONFINITE with
  * NBODY_CHECK_FINITE). */
@@ -341,13 +345,13 @@ typedef struct nbody_config {
   int32_t pairs;   /* form of the force kernel of nbody_accel and of the KDK
                       steps, of nbody_accel_vjp and the adjoint sweep, of
                       nbody_accel_jerk, nbody_accel_jerk_snap and the Hermite
-                      steps:
+                      steps, of nbody_potential and nbody_energy:
                       0 = automatic (the tuned choice for (n, precision),
                       else symmetric from 49152 particles on in FP32C/FP32
                       and from 8192 in FP64 for the force, from 12288 in
                       FP32C/FP32 and 8192 in FP64 for the VJP and for
                       acceleration + jerk, from 8192 in every precision for
-                      acceleration + jerk + snap),
+                      acceleration + jerk + snap, from 8192 for the potential),
                       1 = ordered: every ordered pair evaluated for its i (in
                       FP64 below 8192 particles by one launch per evaluation or
                       step, unless ipl or split is set);

@@ -51,7 +51,7 @@ constexpr double kFarAway = 1.0e15;  // position of padding j-records (mass 0)
 // against the ordered kernels): the FP32C/FP32 force from 49152 particles, the
 // FP64 force from 8192, the FP32C/FP32 VJP from 12288, the FP64 VJP from 8192,
 // the FP32C/FP32 acceleration + jerk from 12288 and the FP64 one from 8192, the
-// acceleration + jerk + snap from 8192 in every precision.
+// acceleration + jerk + snap from 8192 in every precision, the potential from 8192.
 constexpr int64_t kSymMinN = 49152;
 constexpr int64_t kSymMinN64 = 8192;
 constexpr int64_t kSymMinNVjp = 12288;
@@ -60,6 +60,7 @@ constexpr int64_t kSymMinNJerk64 = 8192;
 constexpr int64_t kSymMinNSnap64 = 8192;
 constexpr int64_t kSymMinNJerk = 12288;
 constexpr int64_t kSymMinNSnap = 8192;
+constexpr int64_t kSymMinNPot = 8192;
 // The row kernels serve the FP64 evaluations below the symmetric kernels' sizes
 // (their lanes' plain sums are also only as long as a fold block up to there).
 constexpr int64_t kRowsMaxN = 8191;
@@ -201,6 +202,8 @@ int launch_rows64_snap(int64_t n, const double* x, const double* v, const double
                        double* jk, double* sn, double G, double eps, bool excl, hipStream_t s);
 int launch_rows64_vjp(int64_t n, const double* x, const double* m, const double* w, double* gx, double* gm, double G,
                       double eps, bool excl, hipStream_t s);
+int launch_rows64_potential(int64_t n, const double* x, const double* m, double eps, double scale, double* phi,
+                            hipStream_t s);
 // a(x), then nkicks half-kicks of v and, with xo, the drift of x into xo.
 int launch_rows64_kdk(int64_t n, const double* x, double* xo, double* v, double* a, const double* m, double h, double dt,
                       int nkicks, double G, double eps, bool excl, hipStream_t s);
@@ -218,9 +221,18 @@ int launch_rows64_hermite6(int64_t n, double* const* p, const double* m, double*
 int launch_rows64_adjoint(int64_t n, const double* x, const double* m, const double* lv, double* lx, double* gm,
                           double* lvo, double dt, double G, double eps, bool excl, hipStream_t s);
 
-// scale * phi_i, phi_i = sum_{j != i} m_j (|d|^2 + eps^2)^-1/2 in FP64, into phi[n].
+// scale * phi_i, phi_i = sum_{j != i} m_j (|d|^2 + eps^2)^-1/2 in FP64, into
+// phi[n]: by rows with cfg.rows, else symmetric with cfg.sym, else ordered with
+// cfg.split slices of the j-range.
 int launch_potential(int64_t n, const double* x, const double* m, double eps, double scale, double* phi,
-                     int split, hipStream_t s);
+                     const PairConfig& cfg, hipStream_t s);
+
+// The same from the symmetric FP64 kernel (launches as above).
+int launch_sym_pot64(int64_t n, const double* x, const double* m, double* phi, double scale, double eps,
+                     const PairConfig& cfg, hipStream_t s);
+
+// The form of the potential of n particles on this thread (cfg of launch_potential).
+PairConfig potential_config(int64_t n, int device);
 
 // Configuration of the batched (ensemble) kernels: mode 0 resident systems,
 // 1 resident with split systems, 2 streamed items, 3 per-step wave items, 4

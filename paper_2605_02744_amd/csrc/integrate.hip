@@ -214,11 +214,7 @@ int launch_energy(int64_t n, const double* x, const double* v, const double* m, 
   DD* part = reinterpret_cast<DD*>(ws);
   double* phi = reinterpret_cast<double*>(ws + part_bytes);
   if (n > 0) {
-    const int64_t iblocks = (n + kBlock - 1) / kBlock;
-    const int64_t want = 4LL * cu_count(current_device());
-    int split = (int)std::min<int64_t>(64, std::max<int64_t>(1, (want + iblocks - 1) / iblocks));
-    st = launch_potential(n, x, m, eps, 1.0, phi, split, s);
-    if (st) return st;
+    if ((st = launch_potential(n, x, m, eps, 1.0, phi, potential_config(n, current_device()), s))) return st;
   }
   energy_partial_kernel<<<kRedBlocks, kRedBlock, 0, s>>>(n, x, v, m, phi, G, part);
   NB_LAUNCH_CHECK("energy_partial_kernel");

@@ -953,8 +953,15 @@ int launch_vjp(int64_t n, const double* x, const double* m, const double* w, dou
 // scale * phi_i (FP64) into phi[n]; the energy diagnostics use scale = 1,
 // nbody_potential scale = -G.
 int launch_potential(int64_t n, const double* x, const double* m, double eps, double scale, double* phi,
-                     int split, hipStream_t s) {
+                     const PairConfig& cfg, hipStream_t s) {
   if (n == 0) return NBODY_OK;
+  if (cfg.rows) return launch_rows64_potential(n, x, m, eps, scale, phi, s);
+  int split = cfg.split;
+  if (cfg.sym) {
+    const int st = launch_sym_pot64(n, x, m, phi, scale, eps, cfg, s);
+    if (st != NBODY_ENOMEM) return st;
+    split = 1;  // no room for the pairs' slots: the ordered kernel, which then needs none
+  }
   const int chunk = split_chunk(n, split);
   const int sp = effective_split(n, split);
   dim3 grid((unsigned)((n + kBlock - 1) / kBlock), (unsigned)sp);

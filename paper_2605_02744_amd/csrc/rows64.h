@@ -126,6 +126,16 @@ struct RowVjp {
   }
 };
 
+// The potential sum m_j s^-1/2; its callers always leave the own pair out.
+struct RowPot {
+  static constexpr int NC = 1, NW = 4;
+  static __device__ __forceinline__ void pair(const RowRec<NW>& r, const RowRec<NW>& s, double e2, bool self, double* p) {
+    const double dx = r.w[0] - s.w[0], dy = r.w[1] - s.w[1], dz = r.w[2] - s.w[2];
+    const double v = r.w[3] * rsqrt64(fma(dz, dz, fma(dy, dy, fma(dx, dx, e2))));
+    p[0] += self ? 0.0 : v;
+  }
+};
+
 // Two doubles through one exchange of halves (X = 32: the wave's halves; 16: the
 // odd rows of 16 lanes of a with the even rows of b), summed: lanes of the first
 // kind hold a's sum over both kinds, lanes of the second kind b's.
@@ -176,7 +186,7 @@ __device__ __forceinline__ void wave_sums(const double (&p)[M], double* dst) {
 // row's sum of component q; n is the components' stride.
 
 // The sums times scale: components 0-2 at o0, 3-5 at o1, 6-8 at o2 (the VJP's
-// component 3, a particle array, at o1).
+// component 3 is a particle array, as is the potential's only one: o1 and o0).
 struct EpiStore {
   double scale;
   double *o0, *o1, *o2;

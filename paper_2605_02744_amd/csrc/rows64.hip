@@ -49,6 +49,11 @@ int launch_rows64_vjp(int64_t n, const double* x, const double* m, const double*
   return launch<RowVjp>(n, x, m, w, nullptr, eps, excl, EpiStore{G, gx, gm, nullptr}, s);
 }
 
+int launch_rows64_potential(int64_t n, const double* x, const double* m, double eps, double scale, double* phi,
+                            hipStream_t s) {
+  return launch<RowPot>(n, x, m, nullptr, nullptr, eps, true, EpiStore{scale, phi, nullptr, nullptr}, s);
+}
+
 int launch_rows64_kdk(int64_t n, const double* x, double* xo, double* v, double* a, const double* m, double h, double dt,
                       int nkicks, double G, double eps, bool excl, hipStream_t s) {
   return launch<RowAccel>(n, x, m, nullptr, nullptr, eps, excl, EpiKdk{G, h, dt, nkicks, x, xo, v, a}, s);

@@ -127,9 +127,15 @@ __global__ void sym_reduce_kernel(int n, int npad, int nb, int dmax, int half, i
   if (p >= n) return;
   double* o = c < 3 ? out + (size_t)c * n + p : c < 6 ? outm + (size_t)(c - 3) * n + p : outs + (size_t)(c - 6) * n + p;
   const int J = p / kSI;
-  double acc = first ? 0.0 : *o;
+  // the potential's terms all have one sign, so plain adds would not average
+  // their roundings out as they do for the others' random signs
+  double acc = first ? 0.0 : *o, lo = 0.0;
+  auto add = [&](double v) {
+    if constexpr (C == 1) fold(acc, lo, v);
+    else acc += v;
+  };
   if (first)
-    for (int k = 0; k < pds; ++k) acc += pd[((size_t)k * C + c) * npad + p];
+    for (int k = 0; k < pds; ++k) add(pd[((size_t)k * C + c) * npad + p]);
   const bool est = eo && c == 0;
   float ea = 0.f;
   if (est) {
@@ -147,29 +153,30 @@ __global__ void sym_reduce_kernel(int n, int npad, int nb, int dmax, int half, i
   int s = 0;
   for (; s + 4 <= sn; s += 4) {
     const S v0 = q[s * stride], v1 = q[(s + 1) * stride], v2 = q[(s + 2) * stride], v3 = q[(s + 3) * stride];
-    acc += (double)v0;
-    acc += (double)v1;
-    acc += (double)v2;
-    acc += (double)v3;
+    add((double)v0);
+    add((double)v1);
+    add((double)v2);
+    add((double)v3);
   }
-  for (; s < sn; ++s) acc += (double)q[s * stride];
+  for (; s < sn; ++s) add((double)q[s * stride]);
   const double* qi = pi + (size_t)c * npad + p;
   const size_t pstride = (size_t)C * npad;
   int k = 0;
   for (; k + 4 <= nparts; k += 4) {
     const double v0 = qi[k * pstride], v1 = qi[(k + 1) * pstride], v2 = qi[(k + 2) * pstride],
                  v3 = qi[(k + 3) * pstride];
-    acc += v0;
-    acc += v1;
-    acc += v2;
-    acc += v3;
+    add(v0);
+    add(v1);
+    add(v2);
+    add(v3);
   }
-  for (; k < nparts; ++k) acc += qi[k * pstride];
+  for (; k < nparts; ++k) add(qi[k * pstride]);
   if (est) {
     for (int d = 0; d < sn; ++d) ea += pw[(size_t)d * npad + p];
     for (int k = 0; k < nparts; ++k) ea += pe[(size_t)k * npad + p];
     eo[p] = ea;
   }
+  if constexpr (C == 1) acc += lo;
   *o = last ? G * acc : acc;
 }
 

@@ -283,6 +283,166 @@ __global__ __launch_bounds__(kSL* kDiagG) void sym64_diag_kernel(S64Args A, doub
 }
 
 
+// ------------------------------------------------ symmetric FP64 potential
+// phi_i = sum_{j != i} m_j s^-1/2 on the same layout with one component per
+// particle: the pair's s^-1/2 serves both, phi_i gets it times m_j and phi_j times
+// m_i, so a pair evaluation of 13 FP64 operations and one v_rsq_f64 replaces two
+// of 14 and 1, and one double (not three) moves per step of two i.  Bound by FP64
+// issue like the ordered kernel: 2.42 -> 1.18 ms at 65536 (1.77e12 -> 3.64e12
+// interactions/s), 97 against 165 us at 16384; the default from 8192 particles
+// (41 us against 60 ordered and 50 by rows; 41 against 31 by rows at 6000).
+struct PSet {
+  double x[2], y[2], z[2], m[2];
+};
+
+template <int K>
+__device__ __forceinline__ void pstep64(const PSet& s, const double4* __restrict__ rowp, double e2, double (&p)[2],
+                                        double& aj) {
+  const double4 r = rowp[K];
+  double t = 0.0;
+#pragma unroll
+  for (int u = 0; u < 2; ++u) {
+    const double dx = r.x - s.x[u], dy = r.y - s.y[u], dz = r.z - s.z[u];
+    const double ri = rsqrt64(fma(dz, dz, fma(dy, dy, fma(dx, dx, e2))));
+    p[u] = fma(r.w, ri, p[u]);
+    t = u == 0 ? s.m[u] * ri : fma(s.m[u], ri, t);
+  }
+  if constexpr (K == 0) aj += t;
+  else aj += row_ror64<K>(t);
+}
+
+template <int... K>
+__device__ __forceinline__ void psub64(const PSet& s, const double4* __restrict__ rowp, double e2, double (&p)[2],
+                                       double& aj, std::integer_sequence<int, K...>) {
+  (pstep64<K>(s, rowp, e2, p, aj), ...);
+}
+
+__device__ __forceinline__ void load_pset(const S64Args& A, int g, int t, PSet& s) {
+  DSet d;
+  load_dset(A, g, t, d);
+#pragma unroll
+  for (int u = 0; u < 2; ++u) {
+    s.x[u] = d.x[u]; s.y[u] = d.y[u]; s.z[u] = d.z[u];
+    s.m[u] = -d.mneg[u];
+  }
+}
+
+// Grid and tiles as sym64_kernel.
+__global__ __launch_bounds__(kSL, 8) void psym64_kernel(S64Args A) {
+  __shared__ double4 s_rec[2][4][2 * kSR];  // each sub-block twice in a row
+  __shared__ double s_part[kSW][kST];
+
+  const int t = threadIdx.x;
+  const int rl = t & (kSR - 1);
+  const int wave = t / 64;
+  const int lid = xcd_local_index(blockIdx.x, gridDim.x);
+  const int g = lid % A.nb;
+  const int part = lid / A.nb;
+  const int kbeg = part * A.T;
+  const int rend = (A.half && g >= A.nb / 2) ? A.dmax : A.dmax + 1;  // g's ring ends before this distance
+  const int ntiles = max(0, min(kbeg + A.T, (rend - A.d_lo) * kSTiles) - kbeg);
+  const double e2 = A.eps * A.eps;
+
+  PSet s;
+  load_pset(A, g, t, s);
+  double hp[2] = {0.0, 0.0}, lp[2] = {0.0, 0.0};
+  const int xor32 = ((t & 63) ^ 32) * 4;
+
+  const unsigned lane_off = (unsigned)((((t & 63) >> 1) & (kSR - 1)) * sizeof(double4) + (t & 1) * 16);
+  auto stage = [&](int k, int b) {  // as sym64_kernel
+    const int rec0 = __builtin_amdgcn_readfirstlane(((g + A.d_lo + (kbeg + k) / kSTiles) % A.nb) * kSI + ((kbeg + k) % kSTiles) * kST);
+    const char* base = reinterpret_cast<const char*>(A.rec) + (size_t)rec0 * sizeof(double4);
+    unsigned o = lane_off;
+    asm volatile("" : "+v"(o));
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+      __builtin_amdgcn_global_load_lds(base + q * kSR * sizeof(double4) + o, (lds_ptr)&s_rec[b][q][0], 16, 0, 0);
+  };
+
+  if (ntiles > 0 && t >= 3 * 64) {
+    stage(0, 0);
+    __builtin_amdgcn_s_waitcnt(0);
+  }
+  __syncthreads();
+
+  for (int k = 0; k < ntiles; ++k) {
+    const int b = k & 1;
+    const int d = A.d_lo + (kbeg + k) / kSTiles;
+    const int tt = (kbeg + k) % kSTiles;
+    if (t >= 3 * 64 && k + 1 < ntiles) stage(k + 1, b ^ 1);
+    double p[2] = {0.0, 0.0};
+#pragma unroll 1
+    for (int q = 0; q < 4; ++q) {
+      double aj = 0.0;
+      psub64(s, &s_rec[b][q][rl], e2, p, aj, std::make_integer_sequence<int, kSR>{});
+      aj += swizzle64_xor16(aj);
+      aj += bpermute64(xor32, aj);
+      s_part[wave][q * kSR + rl] = aj;
+    }
+#pragma unroll
+    for (int u = 0; u < 2; ++u) fold(hp[u], lp[u], p[u]);
+    __syncthreads();
+    if (t < kST) {
+      double v = 0.0;
+#pragma unroll
+      for (int w = 0; w < kSW; ++w) v += s_part[w][t];
+      A.pj[(size_t)(d - A.d_lo) * A.npad + (size_t)((g + d) % A.nb) * kSI + tt * kST + t] = v;
+    } else if (t >= 3 * 64) {
+      __builtin_amdgcn_s_waitcnt(0);  // the next tile's copies have landed in LDS
+    }
+    __syncthreads();
+  }
+
+#pragma unroll
+  for (int u = 0; u < 2; ++u) A.pi[(size_t)part * A.npad + (size_t)g * kSI + u * kSL + t] = hp[u] + lp[u];
+}
+
+// The block with itself, as sym64_diag_kernel, the own pair left out by index.
+__global__ __launch_bounds__(kSL* kDiagG) void psym64_diag_kernel(S64Args A, double* __restrict__ pd) {
+  __shared__ double4 s_rec[kSI];
+  __shared__ double s_part[kDiagG - 1][kSI];
+  const int t = threadIdx.x % kSL, grp = threadIdx.x / kSL;
+  const int g = blockIdx.x;
+  const double e2 = A.eps * A.eps;
+  const int span = kSI / ((int)gridDim.y * kDiagG), fl = span < kFold ? span : kFold;
+  const int f0 = ((int)blockIdx.y * kDiagG + grp) * span;
+  PSet s;
+  load_pset(A, g, t, s);
+  for (int k = threadIdx.x; k < kSI; k += kSL * kDiagG) s_rec[k] = A.rec[(size_t)g * kSI + k];
+  __syncthreads();
+  double hp[2] = {0.0, 0.0}, lp[2] = {0.0, 0.0};
+#pragma unroll 1
+  for (int f = f0; f < f0 + span; f += fl) {
+    double p[2] = {0.0, 0.0};
+#pragma unroll 8
+    for (int j = f; j < f + fl; ++j) {
+      const double4 r = s_rec[j];
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        const double dx = r.x - s.x[u], dy = r.y - s.y[u], dz = r.z - s.z[u];
+        const double v = r.w * rsqrt64(fma(dz, dz, fma(dy, dy, fma(dx, dx, e2))));
+        p[u] += j == u * kSL + t ? 0.0 : v;
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < 2; ++u) fold(hp[u], lp[u], p[u]);
+  }
+  if (grp > 0) {
+#pragma unroll
+    for (int u = 0; u < 2; ++u) s_part[grp - 1][u * kSL + t] = hp[u] + lp[u];
+  }
+  __syncthreads();
+  if (grp > 0) return;
+#pragma unroll
+  for (int u = 0; u < 2; ++u) {
+    const int k = u * kSL + t;
+    double v = hp[u] + lp[u];
+#pragma unroll
+    for (int q = 0; q < kDiagG - 1; ++q) v += s_part[q][k];
+    pd[(size_t)blockIdx.y * A.npad + (size_t)g * kSI + k] = v;
+  }
+}
+
 // ------------------------------------------------ symmetric FP64 VJP
 // The vector-Jacobian product of the acceleration on the same layout, in FP64:
 // with d = x_j - x_k, r^2 = |d|^2 + eps^2 and u = m_k w_j - m_j w_k, the
@@ -1137,6 +1297,80 @@ __global__ __launch_bounds__(kSL* kSDiagG) void ssym64_diag_kernel(S64SArgs A, d
 }
 
 }  // namespace
+
+int launch_sym_pot64(int64_t n, const double* x, const double* m, double* phi, double scale, double eps,
+                     const PairConfig& cfg, hipStream_t s) {
+  if (n == 0) return NBODY_OK;
+  int nb, T, D;
+  // per particle: FP64 j-side slot sums per distance, FP64 i-side sums per workgroup,
+  // FP64 block-diagonal sums (in pds slices) and one staged double4 record
+  const int pds = diag_slices((int)((n + kSI - 1) / kSI));
+  sym_plan(n, cfg.launches, sizeof(double), sizeof(double), sizeof(double), pds * (int)sizeof(double) + (int)sizeof(double4),
+           cfg.scratch ? cfg.scratch_bytes : SIZE_MAX, &nb, &T,
+           &D);
+  const int dmax = nb / 2;
+  const int half = (nb % 2 == 0) ? 1 : 0;
+  const int64_t npad = (int64_t)nb * kSI;
+  const int nparts = D * kSTiles / T;
+  const int nchunks = dmax > 0 ? (dmax + D - 1) / D : 0;
+  // the side stream as in launch_sym_accel64
+  std::unique_lock<std::mutex> side_lk;
+  SideStream* side = nchunks >= 2 && !cfg.scratch ? acquire_side_stream(s, side_lk) : nullptr;
+  const int nbuf = side ? 2 : 1;
+  int st = NBODY_OK;
+  const size_t pj_bytes = sizeof(double) * (size_t)npad * D;
+  const size_t pi_bytes = sizeof(double) * (size_t)npad * nparts;
+  const size_t pd_bytes = sizeof(double) * (size_t)npad * pds;
+  const size_t rec_bytes = sizeof(double4) * (size_t)npad;
+  const size_t buf_bytes = pj_bytes + pi_bytes;  // one slot set
+  char* ws = static_cast<char*>(pair_scratch(cfg, nbuf * buf_bytes + pd_bytes + rec_bytes, &st));
+  if (!ws) return st;
+  S64Args A;
+  A.x = x; A.m = m; A.n = (int)n; A.nb = nb; A.npad = (int)npad; A.dmax = dmax; A.half = half;
+  A.T = T; A.nparts = nparts; A.eps = eps; A.d_lo = 1;
+  auto slots = [&](int b, S64Args& Q) {
+    Q.pj = reinterpret_cast<double*>(ws + (size_t)b * buf_bytes);
+    Q.pi = reinterpret_cast<double*>(ws + (size_t)b * buf_bytes + pj_bytes);
+  };
+  slots(0, A);
+  double* pd = reinterpret_cast<double*>(ws + nbuf * buf_bytes);
+  double4* rec = reinterpret_cast<double4*>(ws + nbuf * buf_bytes + pd_bytes);
+  A.rec = rec;
+  sym64_stage_kernel<<<(unsigned)((npad + 255) / 256), 256, 0, s>>>(A, rec);
+  NB_LAUNCH_CHECK("sym64_stage_kernel");
+  const dim3 dg((unsigned)nb, (unsigned)pds);
+  auto diag = [&](hipStream_t ds) -> int {
+    psym64_diag_kernel<<<dg, kSL * kDiagG, 0, ds>>>(A, pd);
+    NB_LAUNCH_CHECK("psym64_diag_kernel");
+    return NBODY_OK;
+  };
+  const dim3 rg((unsigned)((n + 255) / 256), 1);
+  if (dmax == 0) {
+    if ((st = diag(s))) return st;
+    sym_reduce_kernel<1, double><<<rg, 256, 0, s>>>((int)n, (int)npad, nb, dmax, half, 1, 0, 0, A.pj, A.pi, pd, phi,
+                                                    nullptr, scale, 1, 1, nullptr, nullptr, nullptr, nullptr, pds);
+    NB_LAUNCH_CHECK("sym_reduce_kernel");
+    return NBODY_OK;
+  }
+  auto pair = [&](int c, int b) -> int {
+    S64Args B = A;
+    slots(b, B);
+    B.d_lo = 1 + c * D;
+    psym64_kernel<<<(unsigned)nb * (unsigned)nparts, kSL, 0, s>>>(B);
+    NB_LAUNCH_CHECK("psym64_kernel");
+    return NBODY_OK;
+  };
+  auto sum = [&](int c, int b, hipStream_t rs) -> int {
+    S64Args B = A;
+    slots(b, B);
+    sym_reduce_kernel<1, double><<<rg, 256, 0, rs>>>((int)n, (int)npad, nb, dmax, half, 1 + c * D, D, nparts, B.pj, B.pi,
+                                                     pd, phi, nullptr, scale, c == 0, c == nchunks - 1, nullptr, nullptr,
+                                                     nullptr, nullptr, pds);
+    NB_LAUNCH_CHECK("sym_reduce_kernel");
+    return NBODY_OK;
+  };
+  return run_sym_chunks(side, s, nchunks, nbuf, diag, pair, sum);
+}
 
 int launch_sym_accel64(int64_t n, const double* x, const double* m, double* a, double G, double eps, bool excl,
                        const PairConfig& cfg, hipStream_t s) {

@@ -63,6 +63,7 @@ def test_row_evaluations_match_tiles(nb, n, eps):
     both(nb, lambda: nb.nbody_accel_vjp(tx, tm, tw, **kw))
     both(nb, lambda: nb.nbody_accel_jerk(tx, tv, tm, **kw))
     both(nb, lambda: nb.nbody_accel_jerk_snap(tx, tv, ta, tm, **kw))
+    both(nb, lambda: [nb.nbody_potential(tx, tm, G=1.3, eps=eps)])
 
 
 @pytest.mark.parametrize("n", [3, 257, 1022])
@@ -116,3 +117,26 @@ def test_row_gradient_matches_tiles(nb, steps, every):
 
     print("row gradient steps=%d every=%d" % (steps, every), flush=True)
     both(nb, grad)
+
+
+@pytest.mark.parametrize("n", [1, 511, 513, 1024, 2500, 8192, 9001])
+@pytest.mark.parametrize("launches", [0, 2])
+def test_symmetric_potential_matches_tiles(nb, n, launches):
+    """One block, odd and even numbers of blocks of 512, ragged ends, a half ring
+    in one and two launches, with and without softening; the energy's potential
+    is the same one."""
+    x, v, m = ics.two_component(n, seed=60 + n) if n > 20 else ics.random_cloud(n, seed=60 + n)
+    tx, tv, tm = dev(x), dev(v), dev(m)
+    for eps in (0.01, 0.0):
+        print("potential n=%d launches=%d eps=%g" % (n, launches, eps), flush=True)
+        got = {}
+        for form in (dict(pairs=2, split=launches), dict(split=3)):
+            nb.nbody_set_config(**form)
+            try:
+                got[form["split"] == 3] = [nb.nbody_potential(tx, tm, G=0.7, eps=eps).clone(),
+                                           nb.nbody_energy(tx, tv, tm, G=0.7, eps=eps)[1:2].clone()]
+            finally:
+                nb.nbody_set_config()
+        for p, q in zip(got[False], got[True]):
+            assert torch.isfinite(p).all()
+            assert (p - q).abs().max().item() <= TOL * max(q.abs().max().item(), 1e-300), (p - q).abs().max().item()
