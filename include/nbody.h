@@ -210,7 +210,7 @@ int nbody_traj_grad(int64_t n, const double* ckpt_x, const double* ckpt_v, int64
  * nbody_step would advance it alone (same pair arithmetic, FP64 state).  By
  * default (nbody_config.bsplit and friends all zero, no tuned choice) every
  * step is a few launches over items of 64 particles of all systems: two per
- * step (mode 3: kicks and records, then forces), or three for FP32C/FP32
+ * step (mode 3: kicks and records, then forces), or three (two in FP64) for
  * layouts whose systems span several blocks of 64 (mode 4: each unordered
  * pair of a system once, then a fixed-order sum of the far-side terms), and
  * one more with the FP32C rescue (the FP64 rows); the steps of a call may be
@@ -313,7 +313,7 @@ typedef struct nbody_config {
                       launches its half ring of block pairs is cut into */
   int32_t bsplit;  /* batched kernel, used when any of bsplit, bpass, bitem is
                       non-zero (all zero: the tuned choice for the layout, else
-                      mode 4 for FP32C and FP32 when the layout's block pairs
+                      mode 4, or its FP64 form, when the layout's block pairs
                       outnumber its blocks of 64, else mode 3): 0 = one workgroup per system, its records
                       resident in LDS (force it with bpass); 1 = as 0, but systems costlier than
                       the per-CU average split across up to 4 workgroups that
@@ -329,8 +329,9 @@ typedef struct nbody_config {
                       of the far side are added per particle in FP64 in a fixed
                       order by a third launch per step, and with the FP32C rescue
                       a fourth recomputes the flagged rows); FP32C and FP32 only
-                      (FP64 runs mode 3), and layouts whose per-distance sums would
-                      exceed 1 GiB (about 3 x sum of N_c^2 / 128 floats) run mode 3.
+                      (a set 4 in FP64 runs mode 3; the FP64 form is an automatic
+                      choice only), and layouts whose per-distance sums would exceed
+                      1 GiB (about 3 x sum of N_c^2 / 128 values) run mode 3.
                       Modes 1 and 2 need every workgroup of the launch resident at
                       once: with another kernel occupying the GPU a bounded wait can
                       expire, and the affected systems then end NaN.  Modes 0 and 3
@@ -416,7 +417,9 @@ int nbody_tune(int64_t n, int32_t precision, const char* cache_path, nbody_confi
  * library's own copies (the caller's arrays are only read), and keeps the
  * fastest whose state stays finite.  Candidates: the resident kernel with 1, 2
  * or 4 i-particles per lane per pass, the per-step items of 64 (mode 3) and,
- * for FP32C and FP32, their symmetric form (mode 4); with allow_cooperative != 0 also the
+ * their symmetric form (mode 4, or its FP64 form, which cannot be set: where it
+ * is the fastest, later calls use it and best names the fastest of the others);
+ * with allow_cooperative != 0 also the
  * split mode and the streamed kernel with items of 64, 256, 512 or 1024 particles
  * (the modes that need every workgroup of a launch resident at once). allow_cooperative = 2 keeps
  * to the single-launch modes 0, 1 and 2 (all steps in one persistent launch).

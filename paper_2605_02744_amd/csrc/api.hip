@@ -24,7 +24,7 @@ void release_stream_plans();
 void release_sym_ensemble_plans();
 void release_side_streams();
 void release_sweep_streams();
-bool sym_ensemble_default(int32_t ncl, const int64_t* off);
+bool sym_ensemble_default(int32_t ncl, const int64_t* off, int precision);
 
 // ------------------------------------------------------------------ errors
 static thread_local std::string g_err;
@@ -323,8 +323,8 @@ std::vector<TunedBatch> g_tuned_batch;
 
 // The thread's forced configuration if it sets any batched field, else the
 // tuned one for this layout, else the per-step wave items: their symmetric form
-// (mode 4) for FP32C/FP32 layouts whose systems mostly span several blocks of
-// 64, else the ordered form (mode 3).
+// (mode 4, mode 5 in FP64) for layouts whose systems mostly span several blocks
+// of 64, else the ordered form (mode 3).
 BatchConfig batch_config_for(int32_t ncl, const int64_t* off, const double* eps, int precision, int device) {
   const nbody_config& t = t_cfg;
   BatchConfig bc;
@@ -341,11 +341,10 @@ BatchConfig batch_config_for(int32_t ncl, const int64_t* off, const double* eps,
         std::equal(e.off.begin(), e.off.end(), off) && std::equal(e.eps.begin(), e.eps.end(), eps) &&
         e.bc.rescue == bc.rescue)
       return e.bc;
-  // the symmetric per-step items where they pay (FP32C and FP32 layouts whose
-  // systems mostly span several blocks of 64), else the ordered ones; both
-  // carry the FP32C rescue
-  const bool sym = precision == NBODY_FP32 || precision == NBODY_FP32C;
-  bc.mode = (sym && sym_ensemble_default(ncl, off)) ? 4 : 3;
+  // the symmetric per-step items where they pay (layouts whose systems mostly
+  // span several blocks of 64), else the ordered ones; both carry the FP32C rescue
+  const int sym = precision == NBODY_FP64 ? 5 : 4;
+  bc.mode = sym_ensemble_default(ncl, off, precision) ? sym : 3;
   return bc;
 }
 
@@ -556,7 +555,7 @@ int nbody_tune_batched(int32_t ncl, const int64_t* off, const double* eps, const
     for (int pass : {1, 2, 4}) cand.push_back(BatchConfig{0, pass, 0, rescue});
     if (allow_cooperative != 2) {
       cand.push_back(BatchConfig{3, 0, 64, rescue});
-      if (p->precision != NBODY_FP64) cand.push_back(BatchConfig{4, 0, 0, rescue});
+      cand.push_back(BatchConfig{p->precision == NBODY_FP64 ? 5 : 4, 0, 0, rescue});
     }
     if (allow_cooperative) {
       cand.push_back(BatchConfig{1, 0, 0, rescue});
@@ -578,8 +577,8 @@ int nbody_tune_batched(int32_t ncl, const int64_t* off, const double* eps, const
     return set_error(NBODY_ENOMEM, "tune_batched: allocation failed");
   }
   const bool excl = (p->flags & NBODY_EXCLUDE_SELF) != 0;
-  float best_ms = 0.0f;
-  int best_k = -1;
+  float best_ms = 0.0f, set_ms = 0.0f;
+  int best_k = -1, set_k = -1;  // the fastest, and the fastest that nbody_set_config can set (mode 5 cannot be)
   for (size_t k = 0; k < cand.size(); ++k) {
     if (hipMemcpy(sx, x, b3, hipMemcpyDeviceToDevice) != hipSuccess ||
         hipMemcpy(sv, v, b3, hipMemcpyDeviceToDevice) != hipSuccess) {
@@ -606,6 +605,10 @@ int nbody_tune_batched(int32_t ncl, const int64_t* off, const double* eps, const
       best_ms = ms;
       best_k = (int)k;
     }
+    if (finite_ok && cand[k].mode != 5 && (set_k < 0 || ms < set_ms)) {
+      set_ms = ms;
+      set_k = (int)k;
+    }
   }
   cleanup();
   if (best_k < 0) return set_error(NBODY_ENONFINITE, "tune_batched: every configuration produced non-finite state");
@@ -624,7 +627,8 @@ int nbody_tune_batched(int32_t ncl, const int64_t* off, const double* eps, const
       g_tuned_batch.push_back(TunedBatch{dev, p->precision, std::vector<int64_t>(off, off + ncl + 1),
                                          std::vector<double>(eps, eps + ncl), bc});
   }
-  if (best) *best = nbody_config{0, 0, bc.mode, bc.pass, bc.item, 0, 0};
+  const BatchConfig rc = set_k < 0 ? BatchConfig{} : cand[set_k];
+  if (best) *best = nbody_config{0, 0, rc.mode, rc.pass, rc.item, 0, 0};
   return NBODY_OK;
 }
 

@@ -236,7 +236,7 @@ PairConfig potential_config(int64_t n, int device);
 
 // Configuration of the batched (ensemble) kernels: mode 0 resident systems,
 // 1 resident with split systems, 2 streamed items, 3 per-step wave items, 4
-// symmetric per-step items; pass = i-particles per lane per pass of mode 0/1
+// symmetric per-step items (FP32C and FP32), 5 the same in FP64; pass = i-particles per lane per pass of mode 0/1
 // (0 = automatic); item = most particles per item of mode 2 (0 = automatic).
 struct BatchConfig {
   int mode = 0;

@@ -1,4 +1,5 @@
-// Symmetric per-step ensemble (nbody_config.bsplit = 4; FP32C and FP32).
+// Symmetric per-step ensemble (nbody_config.bsplit = 4: FP32C and FP32; its FP64
+// form below is an automatic choice only).
 //
 // Every unordered pair of a system is evaluated once and its term applied to
 // both particles (the antisymmetry of Eq. 1), as in the single-system symmetric
@@ -46,6 +47,7 @@
 #include <vector>
 
 #include "sym_common.h"
+#include "wave64.h"
 
 namespace nb {
 namespace {
@@ -526,6 +528,211 @@ __global__ void esym_reduce_est_kernel(int nblocks, const EItem* __restrict__ bl
   }
 }
 
+// ------------------------------------------------------------------ FP64
+// The FP64 form: the same blocks, parts, slots and order of sums, all in FP64.
+// A wave's records lie in LDS as two arrays of double2, (x, y) and (z, m), so
+// that the 16 records a row reads at a step cover the banks once (as double4
+// records they would cover every other 16 bytes twice, and with one i per lane
+// the pair loop would wait for LDS).  A sub-block's far-side sums are added over
+// the four rows by exchanging halves in registers, which leaves x, y and z in
+// rows of their own: they go straight to the slots, with no LDS between.  The
+// reduction also kicks, drifts and writes the next step's records, so a step is
+// two launches.  Bound by FP64 issue (23 FP64 operations, one v_rsq_f64 and 6
+// DPP moves per pair evaluation, which serves two interactions).  Measured per
+// step against the ordered items of mode 3, whose waves each walk a whole system:
+// 100 systems of 64 to 2000 particles 300 -> 109 us (too few waves there to hide
+// an FP64 chain), 512 of 64 to 4096 2.11 -> 1.73 ms, 8 of 1000 to 4096 604 -> 58 us.
+constexpr int kE64Block = 512;
+constexpr int kE64Waves = kE64Block / 64;
+constexpr int kE64MaxPerCu = 2;  // 4 waves per SIMD (112 VGPRs; 6 waves spill 4 of 80 and are no faster)
+
+template <int K>
+__device__ __forceinline__ void esym64_step(const double4& ip, double mneg, const double2* __restrict__ xy,
+                                            const double2* __restrict__ zm, double e2, double (&p)[3],
+                                            double (&aj)[3]) {
+  const double2 a = xy[K], b = zm[K];
+  const double dx = a.x - ip.x, dy = a.y - ip.y, dz = b.x - ip.z;
+  const double f = rsqrt64_cubed(fma(dz, dz, fma(dy, dy, fma(dx, dx, e2))));
+  const double si = b.y * f, sj = mneg * f;
+  p[0] = fma(si, dx, p[0]);
+  p[1] = fma(si, dy, p[1]);
+  p[2] = fma(si, dz, p[2]);
+  const double tx = sj * dx, ty = sj * dy, tz = sj * dz;
+  if constexpr (K == 0) { aj[0] += tx; aj[1] += ty; aj[2] += tz; }
+  else {
+    aj[0] += row_ror64<K>(tx);
+    aj[1] += row_ror64<K>(ty);
+    aj[2] += row_ror64<K>(tz);
+  }
+}
+
+template <int... K>
+__device__ __forceinline__ void esym64_sub(const double4& ip, double mneg, const double2* __restrict__ xy,
+                                           const double2* __restrict__ zm, double e2, double (&p)[3], double (&aj)[3],
+                                           std::integer_sequence<int, K...>) {
+  (esym64_step<K>(ip, mneg, xy, zm, e2, p, aj), ...);
+}
+
+template <bool EXCL>
+__global__ __launch_bounds__(kE64Block, kE64MaxPerCu * kE64Waves / 4) void esym64_force_kernel(
+    const ESys* __restrict__ sys, const EItem* __restrict__ items, const int* __restrict__ wg_off,
+    const int* __restrict__ wg_list, const double4* __restrict__ rec, double* __restrict__ a,
+    double* __restrict__ islot, double* __restrict__ slots, int64_t total) {
+  __shared__ double2 s_xy[kE64Waves][4][2 * kSR];  // each sub-block twice
+  __shared__ double2 s_zm[kE64Waves][4][2 * kSR];
+  __shared__ int next_item;
+  const int t = threadIdx.x;
+  const int wv = t >> 6, lane = t & 63, rl = lane & (kSR - 1), row = lane >> 4;
+  const int q0 = wg_off[blockIdx.x], q1 = wg_off[blockIdx.x + 1];
+  if (t == 0) next_item = 0;
+  __syncthreads();
+  for (;;) {
+    int k = 0;
+    if (lane == 0) k = atomicAdd(&next_item, 1);
+    k = __builtin_amdgcn_readfirstlane(k);
+    if (k >= q1 - q0) break;
+    const EItem it = items[wg_list[q0 + k]];
+    const ESys& S = sys[it.sys];
+    const int nc = S.nc, nb = S.nb;
+    const double4* rs = rec + S.o;
+    const double e2 = S.eps * S.eps;
+    const int il = it.b * 64 + lane;
+    const bool valid = lane < it.ni;
+    // padding (past the system's end): far away and massless
+    auto load = [&](int j) { return j < nc ? rs[j] : make_double4(kFarAway, kFarAway, kFarAway, 0.0); };
+    const double4 ip = load(valid ? il : nc);
+    const double mneg = -ip.w;
+    auto put = [&](const double4& r) {
+      wave_sync();
+      s_xy[wv][row][rl] = s_xy[wv][row][rl + kSR] = make_double2(r.x, r.y);
+      s_zm[wv][row][rl] = s_zm[wv][row][rl + kSR] = make_double2(r.z, r.w);
+      wave_sync();
+    };
+    double h[3] = {0.0, 0.0, 0.0}, l[3] = {0.0, 0.0, 0.0};
+    double4 nr = make_double4(0.0, 0.0, 0.0, 0.0);
+    const int r0 = it.d0 > 0 ? it.d0 : 1;  // first distance of the ring in this part
+    if (it.d0 == 0) put(load(it.b * 64 + lane));
+    if (r0 < it.d1) nr = load((it.b + r0 < nb ? it.b + r0 : it.b + r0 - nb) * 64 + lane);
+    if (it.d0 == 0) {
+      // the block with itself: ordered pairs, i-side only
+      double p[3] = {0.0, 0.0, 0.0};
+#pragma unroll 8
+      for (int jj = 0; jj < 64; ++jj) {
+        const double2 u = s_xy[wv][jj >> 4][jj & (kSR - 1)], w = s_zm[wv][jj >> 4][jj & (kSR - 1)];
+        const double dx = u.x - ip.x, dy = u.y - ip.y, dz = w.x - ip.z;
+        double f = w.y * rsqrt64_cubed(fma(dz, dz, fma(dy, dy, fma(dx, dx, e2))));
+        if constexpr (EXCL) f = jj == lane ? 0.0 : f;
+        p[0] = fma(f, dx, p[0]);
+        p[1] = fma(f, dy, p[1]);
+        p[2] = fma(f, dz, p[2]);
+      }
+#pragma unroll
+      for (int c = 0; c < 3; ++c) fold(h[c], l[c], p[c]);
+    }
+    const size_t npad = (size_t)nb * 64;
+#pragma unroll 1
+    for (int d = r0; d < it.d1; ++d) {
+      const int J = it.b + d < nb ? it.b + d : it.b + d - nb;
+      put(nr);
+      if (d + 1 < it.d1) nr = load((J + 1 < nb ? J + 1 : J + 1 - nb) * 64 + lane);
+      double p[3] = {0.0, 0.0, 0.0};
+      // rows 0, 1, 2, 3 end up with x, z, y and z again
+      double* dst = slots + S.sbase + (size_t)(d - 1) * 3 * npad + (size_t)(row == 0 ? 0 : row == 2 ? 1 : 2) * npad +
+                    (size_t)J * 64 + rl;
+#pragma unroll 1
+      for (int q = 0; q < 4; ++q) {
+        double aj[3] = {0.0, 0.0, 0.0};
+        esym64_sub(ip, mneg, &s_xy[wv][q][rl], &s_zm[wv][q][rl], e2, p, aj, std::make_integer_sequence<int, kSR>{});
+        const double v = swap_add<16>(swap_add<32>(aj[0], aj[1]), swap_add<32>(aj[2], aj[2]));
+        dst[q * kSR] = v;  // no branch: the compiler would sink the i-side sums past it, and spill
+      }
+#pragma unroll
+      for (int c = 0; c < 3; ++c) fold(h[c], l[c], p[c]);
+    }
+    if (valid) {
+      // part 0 (the one with the block itself) writes a, unscaled; the others their slots
+      double* o = it.part == 0 ? a + S.o + il : islot + S.ibase + (size_t)(it.part - 1) * 3 * npad + il;
+      const size_t st = it.part == 0 ? (size_t)total : npad;
+#pragma unroll
+      for (int c = 0; c < 3; ++c) o[c * st] = h[c] + l[c];
+    }
+  }
+}
+
+// The start of a call's first step: kicks (0 or 1) and, with a kick, the drift,
+// then the records.
+__global__ void esym64_publish_kernel(int64_t total, double* __restrict__ x, double* __restrict__ v,
+                                      const double* __restrict__ a, const double* __restrict__ m,
+                                      double4* __restrict__ rec, double h, double dt, int kicks) {
+  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < total; i += (int64_t)gridDim.x * blockDim.x) {
+    double xn[3];
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+      const int64_t e = c * total + i;
+      xn[c] = x[e];
+      if (kicks > 0) {
+        const double ve = fma(h, a[e], v[e]);
+        v[e] = ve;
+        xn[c] = fma(dt, ve, xn[c]);
+        x[e] = xn[c];
+      }
+    }
+    rec[i] = make_double4(xn[0], xn[1], xn[2], m[i]);
+  }
+}
+
+// a as in esym_reduce_kernel (with compensated sums, which cost nothing beside the
+// slots' traffic), then nkicks half-kicks (rounded separately) and,
+// with drift, the drift and the record's component (the masses stay).
+__global__ void esym64_reduce_kernel(int nblocks, const EItem* __restrict__ blocks, const ESys* __restrict__ sys,
+                                     int64_t total, const double* __restrict__ islot, const double* __restrict__ slots,
+                                     double* __restrict__ a, double G, double* __restrict__ x, double* __restrict__ v,
+                                     double4* __restrict__ rec, double h, double dt, int nkicks, int drift) {
+  const int c = blockIdx.y;
+  for (int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; g < (int64_t)nblocks * 64;
+       g += (int64_t)gridDim.x * blockDim.x) {
+    const EItem it = blocks[g >> 6];
+    const int lane = (int)(g & 63);
+    if (lane >= it.ni) continue;
+    const ESys& S = sys[it.sys];
+    const int p = it.b * 64 + lane;
+    const int64_t i = S.o + p, e = c * total + i;
+    const size_t npad = (size_t)S.nb * 64, stride = 3 * npad;
+    int dn = S.dmax;
+    if (S.half && dn > 0) {
+      int src = it.b - S.dmax;
+      if (src < 0) src += S.nb;
+      if (src >= S.nb / 2) --dn;
+    }
+    const int np = (esym_dend(S, it.b) + S.lp - 1) / S.lp;
+    const double* iq = islot + S.ibase + c * npad + p;
+    double acc = a[e], lo = 0.0;
+    for (int k = 1; k < np; ++k) fold(acc, lo, iq[(size_t)(k - 1) * stride]);
+    const double* q = slots + S.sbase + c * npad + p;
+    int d = 0;
+    for (; d + 8 <= dn; d += 8) {
+      double f[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) f[u] = q[(size_t)(d + u) * stride];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) fold(acc, lo, f[u]);
+    }
+    for (; d < dn; ++d) fold(acc, lo, q[(size_t)d * stride]);
+    const double ae = G * (acc + lo);
+    a[e] = ae;
+    if (nkicks > 0) {
+      double ve = v[e];
+      for (int k = 0; k < nkicks; ++k) ve = fma(h, ae, ve);
+      v[e] = ve;
+      if (drift) {
+        const double xn = fma(dt, ve, x[e]);
+        x[e] = xn;
+        reinterpret_cast<double*>(rec + i)[c] = xn;
+      }
+    }
+  }
+}
+
 // ------------------------------------------------------------------ plans
 struct EPlan {
   std::vector<int64_t> off;
@@ -541,6 +748,9 @@ struct EPlan {
   float4* d_rhi = nullptr;
   float4* d_rlo = nullptr;
   float* d_slots = nullptr;
+  // FP64
+  double4* d_rec = nullptr;
+  double* d_slots64 = nullptr;
   // FP32C: the rescue's estimate slots, the systems' offsets and softenings
   // on the device, and the per-system lists of flagged rows
   float* d_iest = nullptr;
@@ -556,7 +766,7 @@ std::vector<EPlan*> g_eplans;
 
 void free_eplan(EPlan* p) {
   for (void* q : {(void*)p->d_sys, (void*)p->d_blocks, (void*)p->d_items, (void*)p->d_islot, (void*)p->d_wg_off,
-                  (void*)p->d_wg_list, (void*)p->d_rhi, (void*)p->d_rlo, (void*)p->d_slots, (void*)p->d_iest,
+                  (void*)p->d_wg_list, (void*)p->d_rec, (void*)p->d_slots64, (void*)p->d_rhi, (void*)p->d_rlo, (void*)p->d_slots, (void*)p->d_iest,
                   (void*)p->d_wslots, (void*)p->d_off, (void*)p->d_eps, (void*)p->d_rcnt, (void*)p->d_rlist})
     if (q) (void)hipFree(q);
   delete p;
@@ -570,14 +780,14 @@ bool eupload(T** dst, const std::vector<T>& src) {
 }
 
 // Bytes of j-side slots the layout needs: per system, dmax distances x 3
-// components x its padded particle count, in FP32.
-size_t esym_slot_bytes(int32_t ncl, const int64_t* off) {
+// components x its padded particle count, in FP32 or FP64.
+size_t esym_slot_bytes(int32_t ncl, const int64_t* off, int precision) {
   size_t f = 0;
   for (int c = 0; c < ncl; ++c) {
     const int64_t nb = (off[c + 1] - off[c] + 63) / 64;
     f += (size_t)(nb / 2) * 3 * (size_t)nb * 64;
   }
-  return f * sizeof(float);
+  return f * (precision == NBODY_FP64 ? sizeof(double) : sizeof(float));
 }
 
 // Blocks: every system cut into blocks of 64.  Items: each block's distances
@@ -596,13 +806,19 @@ int build_eplan(int32_t ncl, const int64_t* off, const double* eps, int precisio
   p->device = device;
   p->ncl = ncl;
   p->total = off[ncl];
-  int per_cu = kEMaxPerCu;
-  for (const void* f : {reinterpret_cast<const void*>(&esym_force_kernel<true, false, false>),
-                        reinterpret_cast<const void*>(&esym_force_kernel<true, true, false>),
-                        reinterpret_cast<const void*>(&esym_force_kernel<true, false, true>),
-                        reinterpret_cast<const void*>(&esym_force_kernel<true, true, true>)}) {
+  const bool f64 = precision == NBODY_FP64;
+  const int waves = f64 ? kE64Waves : kEWaves;
+  int per_cu = f64 ? kE64MaxPerCu : kEMaxPerCu;
+  const std::vector<const void*> kernels =
+      f64 ? std::vector<const void*>{reinterpret_cast<const void*>(&esym64_force_kernel<false>),
+                                     reinterpret_cast<const void*>(&esym64_force_kernel<true>)}
+          : std::vector<const void*>{reinterpret_cast<const void*>(&esym_force_kernel<true, false, false>),
+                                     reinterpret_cast<const void*>(&esym_force_kernel<true, true, false>),
+                                     reinterpret_cast<const void*>(&esym_force_kernel<true, false, true>),
+                                     reinterpret_cast<const void*>(&esym_force_kernel<true, true, true>)};
+  for (const void* f : kernels) {
     int k = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&k, f, kEBlock, 0) != hipSuccess) {
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&k, f, waves * 64, 0) != hipSuccess) {
       (void)hipGetLastError();
       k = 1;
     }
@@ -616,7 +832,9 @@ int build_eplan(int32_t ncl, const int64_t* off, const double* eps, int precisio
     const int64_t nb = (off[c + 1] - off[c] + 63) / 64;
     work += nb * (nb / 2) + nb - ((nb % 2 == 0) ? nb / 2 : 0);
   }
-  const int lp = (int)std::max<int64_t>(4, std::min<int64_t>(64, work / (4 * (int64_t)cap_wg * kEWaves)));
+  // at least four distances a part in FP32, one in FP64, whose pair takes three
+  // times as long (30 systems of 100 to 400 particles: 18 us a step against 35)
+  const int lp = (int)std::max<int64_t>(f64 ? 1 : 4, std::min<int64_t>(64, work / (4 * (int64_t)cap_wg * waves)));
   std::vector<EItem> blocks, items;
   std::vector<double> cost;
   int64_t sbase = 0, ibase = 0, iebase = 0, wbase = 0;
@@ -650,7 +868,7 @@ int build_eplan(int32_t ncl, const int64_t* off, const double* eps, int precisio
       }
     }
   }
-  const int nwg = std::max(1, std::min<int>((int)((items.size() + kEWaves - 1) / kEWaves), cap_wg));
+  const int nwg = std::max(1, std::min<int>((int)((items.size() + waves - 1) / waves), cap_wg));
   std::vector<int> order(items.size());
   for (size_t k = 0; k < items.size(); ++k) order[k] = (int)k;
   std::stable_sort(order.begin(), order.end(), [&](int u, int w) { return cost[u] > cost[w]; });
@@ -674,9 +892,15 @@ int build_eplan(int32_t ncl, const int64_t* off, const double* eps, int precisio
   const size_t nrec = (size_t)std::max<int64_t>(1, p->total);
   bool ok = eupload(&p->d_sys, sys) && eupload(&p->d_blocks, blocks) && eupload(&p->d_items, items) &&
             hipMalloc(&p->d_islot, sizeof(double) * (size_t)std::max<int64_t>(1, ibase)) == hipSuccess && eupload(&p->d_wg_off, wg_off) &&
-            eupload(&p->d_wg_list, wg_list) && hipMalloc(&p->d_rhi, nrec * sizeof(float4)) == hipSuccess &&
-            hipMalloc(&p->d_rlo, nrec * sizeof(float4)) == hipSuccess &&
-            hipMalloc(&p->d_slots, sizeof(float) * (size_t)std::max<int64_t>(1, sbase)) == hipSuccess;
+            eupload(&p->d_wg_list, wg_list);
+  const size_t nslot = (size_t)std::max<int64_t>(1, sbase);
+  if (ok && f64)
+    ok = hipMalloc(&p->d_rec, nrec * sizeof(double4)) == hipSuccess &&
+         hipMalloc(&p->d_slots64, sizeof(double) * nslot) == hipSuccess;
+  if (ok && !f64)
+    ok = hipMalloc(&p->d_rhi, nrec * sizeof(float4)) == hipSuccess &&
+         hipMalloc(&p->d_rlo, nrec * sizeof(float4)) == hipSuccess &&
+         hipMalloc(&p->d_slots, sizeof(float) * nslot) == hipSuccess;
   if (ok && precision == NBODY_FP32C)
     ok = hipMalloc(&p->d_iest, sizeof(float) * (size_t)std::max<int64_t>(1, iebase)) == hipSuccess &&
          hipMalloc(&p->d_wslots, sizeof(float) * (size_t)std::max<int64_t>(1, wbase)) == hipSuccess &&
@@ -747,19 +971,46 @@ int launch_esteps(const EPlan* p, double* x, double* v, double* a, const double*
   return NBODY_OK;
 }
 
+int launch_esteps64(const EPlan* p, double* x, double* v, double* a, const double* m, double dt, int64_t nsteps,
+                    double G, bool acc_valid, bool excl, hipStream_t s) {
+  if (p->total == 0 || (nsteps == 0 && acc_valid)) return NBODY_OK;
+  const double h = 0.5 * dt;
+  const unsigned ew = (unsigned)std::min<int64_t>(((int64_t)p->nblocks * 64 + 255) / 256, 4096);
+  const unsigned pw = (unsigned)std::min<int64_t>((p->total + 255) / 256, 4096);
+  esym64_publish_kernel<<<pw, 256, 0, s>>>(p->total, x, v, a, m, p->d_rec, h, dt, acc_valid ? 1 : 0);
+  NB_LAUNCH_CHECK("esym64_publish_kernel");
+  // evaluations at x_k, k = 0 (without a valid a) or 1 .. nsteps
+  for (int64_t k = acc_valid ? 1 : 0; k <= nsteps; ++k) {
+    if (excl)
+      esym64_force_kernel<true><<<p->nwg, kE64Block, 0, s>>>(p->d_sys, p->d_items, p->d_wg_off, p->d_wg_list, p->d_rec, a,
+                                                             p->d_islot, p->d_slots64, p->total);
+    else
+      esym64_force_kernel<false><<<p->nwg, kE64Block, 0, s>>>(p->d_sys, p->d_items, p->d_wg_off, p->d_wg_list, p->d_rec, a,
+                                                              p->d_islot, p->d_slots64, p->total);
+    NB_LAUNCH_CHECK("esym64_force_kernel");
+    // the closing half-kick of step k (none at k = 0) and the opening one of step k + 1
+    const int nkicks = (k > 0 ? 1 : 0) + (k < nsteps ? 1 : 0);
+    esym64_reduce_kernel<<<dim3(ew, 3), 256, 0, s>>>(p->nblocks, p->d_blocks, p->d_sys, p->total, p->d_islot,
+                                                     p->d_slots64, a, G, x, v, p->d_rec, h, dt, nkicks, k < nsteps ? 1 : 0);
+    NB_LAUNCH_CHECK("esym64_reduce_kernel");
+  }
+  return NBODY_OK;
+}
+
 }  // namespace
 
 int run_batched_stream(int32_t ncl, const int64_t* off, const double* eps, double* x, double* v, double* a,
                        const double* m, double dt, int64_t nsteps, double G, int precision, bool excl,
                        bool acc_valid, int bitem, bool per_step, bool rescue, hipStream_t s);
 
-// Mode 4.  FP64, and layouts whose slots would exceed kESlotCap, run the
-// ordered per-step wave items (mode 3) instead; FP32C takes the rescue as
-// asked in either form.
+// Modes 4 (FP32C and FP32; FP64 runs mode 3) and 5 (FP64).  Layouts whose slots
+// would exceed kESlotCap run the ordered per-step wave items (mode 3) instead;
+// FP32C takes the rescue as asked in either form.
 int run_batched_sym(int32_t ncl, const int64_t* off, const double* eps, double* x, double* v, double* a,
                     const double* m, double dt, int64_t nsteps, double G, int precision, bool excl, bool acc_valid,
-                    bool rescue, hipStream_t s) {
-  if (precision == NBODY_FP64 || esym_slot_bytes(ncl, off) > kESlotCap)
+                    const BatchConfig& bc, hipStream_t s) {
+  const bool rescue = bc.rescue != 0;
+  if ((precision == NBODY_FP64 && bc.mode != 5) || esym_slot_bytes(ncl, off, precision) > kESlotCap)
     return run_batched_stream(ncl, off, eps, x, v, a, m, dt, nsteps, G, precision, excl, acc_valid, 64, true, rescue,
                               s);
   for (int c = 0; c < ncl; ++c)
@@ -773,9 +1024,13 @@ int run_batched_sym(int32_t ncl, const int64_t* off, const double* eps, double* 
     if (hipStreamIsCapturing(s, &cs) == hipSuccess && cs != hipStreamCaptureStatusNone)
       return set_error(NBODY_EINVAL, "batched: the plan for this layout must be built by one call outside stream capture");
     int st = build_eplan(ncl, off, eps, precision, device, &p);
+    if (st == NBODY_ENOMEM && bc.mode == 5)  // an automatic choice: without room for its slots, the ordered items
+      return run_batched_stream(ncl, off, eps, x, v, a, m, dt, nsteps, G, precision, excl, acc_valid, 64, true, rescue,
+                                s);
     if (st) return st;
     g_eplans.push_back(p);
   }
+  if (precision == NBODY_FP64) return launch_esteps64(p, x, v, a, m, dt, nsteps, G, acc_valid, excl, s);
   if (precision == NBODY_FP32C && rescue)
     return launch_esteps<true, true>(p, x, v, a, m, dt, nsteps, G, acc_valid, excl, s);
   if (precision == NBODY_FP32C) return launch_esteps<true, false>(p, x, v, a, m, dt, nsteps, G, acc_valid, excl, s);
@@ -786,14 +1041,14 @@ int run_batched_sym(int32_t ncl, const int64_t* off, const double* eps, double* 
 // outnumber its blocks (its systems mostly span several blocks of 64): a
 // layout of single-block systems has no pair to save and would only pay the
 // third launch.
-bool sym_ensemble_default(int32_t ncl, const int64_t* off) {
+bool sym_ensemble_default(int32_t ncl, const int64_t* off, int precision) {
   int64_t blocks = 0, ring = 0;
   for (int c = 0; c < ncl; ++c) {
     const int64_t nb = (off[c + 1] - off[c] + 63) / 64;
     blocks += nb;
     ring += nb * (nb / 2) - ((nb % 2 == 0) ? nb / 2 : 0);
   }
-  return ring >= blocks && esym_slot_bytes(ncl, off) <= kESlotCap;
+  return ring >= blocks && esym_slot_bytes(ncl, off, precision) <= kESlotCap;
 }
 
 void release_sym_ensemble_plans() {

@@ -36,6 +36,7 @@
 
 #include "elementwise.h"
 #include "pair_math.h"
+#include "wave64.h"
 
 namespace nb {
 namespace {
@@ -84,15 +85,9 @@ struct RowRec {
 
 struct RowAccel {
   static constexpr int NC = 3, NW = 4;
-  // m_j s^-3/2 from y = rsq(s) and the residual h = 1 - s y^2 in one step:
-  // (1 - h)^(-3/2) = 1 + 3h/2 + 15h^2/8 + O(h^3), |h| ~ 1e-7, one operation less
-  // than refining y first and cubing it, and two roundings fewer
   static __device__ __forceinline__ void pair(const RowRec<NW>& r, const RowRec<NW>& s, double e2, bool self, double* p) {
     const double dx = r.w[0] - s.w[0], dy = r.w[1] - s.w[1], dz = r.w[2] - s.w[2];
-    const double q = fma(dz, dz, fma(dy, dy, fma(dx, dx, e2)));
-    const double y = __builtin_amdgcn_rsq(q);
-    const double y2 = y * y, h = fma(-q, y2, 1.0), ym = y2 * (y * r.w[3]);
-    double f = fma(ym, h * fma(1.875, h, 1.5), ym);
+    double f = r.w[3] * rsqrt64_cubed(fma(dz, dz, fma(dy, dy, fma(dx, dx, e2))));
     f = self ? 0.0 : f;
     p[0] = fma(f, dx, p[0]);
     p[1] = fma(f, dy, p[1]);
@@ -136,32 +131,6 @@ struct RowPot {
   }
 };
 
-// Two doubles through one exchange of halves (X = 32: the wave's halves; 16: the
-// odd rows of 16 lanes of a with the even rows of b), summed: lanes of the first
-// kind hold a's sum over both kinds, lanes of the second kind b's.
-template <int X>
-__device__ __forceinline__ double swap_add(double a, double b) {
-  const unsigned al = (unsigned)__double2loint(a), ah = (unsigned)__double2hiint(a);
-  const unsigned bl = (unsigned)__double2loint(b), bh = (unsigned)__double2hiint(b);
-  if constexpr (X == 32) {
-    const auto l = __builtin_amdgcn_permlane32_swap(al, bl, false, false);
-    const auto h = __builtin_amdgcn_permlane32_swap(ah, bh, false, false);
-    return __hiloint2double((int)h[0], (int)l[0]) + __hiloint2double((int)h[1], (int)l[1]);
-  } else {
-    const auto l = __builtin_amdgcn_permlane16_swap(al, bl, false, false);
-    const auto h = __builtin_amdgcn_permlane16_swap(ah, bh, false, false);
-    return __hiloint2double((int)h[0], (int)l[0]) + __hiloint2double((int)h[1], (int)l[1]);
-  }
-}
-
-// A double rotated within each row of 16 lanes by K, added to itself.
-template <int K>
-__device__ __forceinline__ double ror_add(double v) {
-  const int l = __builtin_amdgcn_mov_dpp(__double2loint(v), 0x120 + K, 0xF, 0xF, true);
-  const int h = __builtin_amdgcn_mov_dpp(__double2hiint(v), 0x120 + K, 0xF, 0xF, true);
-  return v + __hiloint2double(h, l);
-}
-
 // Sums the M values of every lane over the wave and stores them at dst[0 .. M).
 // After the two exchanges slot q of a lane in row r (of 4) holds value
 // 4q + 2 (r & 1) + (r >> 1), summed over the four rows.
@@ -172,10 +141,10 @@ __device__ __forceinline__ void wave_sums(const double (&p)[M], double* dst) {
   for (int q = 0; q < M; q += 4) {
     auto at = [&](int k) { return q + k < M ? p[q + k < M ? q + k : 0] : 0.0; };
     double v = swap_add<16>(swap_add<32>(at(0), at(1)), swap_add<32>(at(2), at(3)));
-    v = ror_add<8>(v);
-    v = ror_add<4>(v);
-    v = ror_add<2>(v);
-    v = ror_add<1>(v);
+    v += row_ror64<8>(v);
+    v += row_ror64<4>(v);
+    v += row_ror64<2>(v);
+    v += row_ror64<1>(v);
     const int k = q + 2 * (row & 1) + (row >> 1);
     if ((lane & 15) == 0 && k < M) dst[k] = v;
   }

@@ -14,18 +14,10 @@
 // six and the sixth-order Hermite evaluation (acceleration, jerk, snap) with
 // nine.
 #include "sym_common.h"
+#include "wave64.h"
 
 namespace nb {
 namespace {
-
-// A double rotated within each row of 16 lanes: lane r gets lane (r - K) mod 16's value.
-template <int K>
-__device__ __forceinline__ double row_ror64(double v) {
-  const unsigned long long b = (unsigned long long)__double_as_longlong(v);
-  const unsigned lo = (unsigned)__builtin_amdgcn_mov_dpp((int)(unsigned)(b & 0xffffffffull), 0x120 + K, 0xF, 0xF, true);
-  const unsigned hi = (unsigned)__builtin_amdgcn_mov_dpp((int)(unsigned)(b >> 32), 0x120 + K, 0xF, 0xF, true);
-  return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
-}
 
 // The two 32-bit halves of a double through ds_swizzle / ds_bpermute.
 __device__ __forceinline__ double swizzle64_xor16(double v) {
