@@ -353,9 +353,10 @@ typedef struct nbody_config {
                       FP32C/FP32 and 8192 in FP64 for the VJP and for
                       acceleration + jerk, from 8192 in every precision for
                       acceleration + jerk + snap, from 8192 for the potential),
-                      1 = ordered: every ordered pair evaluated for its i (in
-                      FP64 below 8192 particles by one launch per evaluation or
-                      step, unless ipl or split is set);
+                      1 = ordered: every ordered pair evaluated for its i
+                      (below 8192 particles, and up to 24576 for the force in
+                      FP32C and FP32, by one launch per evaluation or step,
+                      unless ipl or split is set);
                       2 = symmetric: every unordered pair evaluated once and
                       applied to both particles (a_j gets the opposite of i's
                       term scaled by m_i / m_j), results summed in a fixed order
@@ -400,11 +401,11 @@ int nbody_set_config(const nbody_config* cfg);
  * (synchronous; allocates and frees its own buffers) and record the fastest
  * in the library's per-device table, which automatic selection then uses for
  * that (n, precision).  The choice is per (n, precision) because the fastest
- * tiling depends on both, hence those arguments.  (Below 8192 particles in FP64
- * the automatic choice needs no tile configuration: one launch per evaluation,
- * each workgroup summing four particles over every j; it stays the automatic
- * choice if it beats every tile configuration, and best then still names the
- * fastest of those.)  If cache_path is non-NULL
+ * tiling depends on both, hence those arguments.  (For small systems,
+ * below 8192 particles in FP64 and up to 24576 in FP32C and FP32, the automatic
+ * choice needs no tile configuration: one launch per evaluation, each workgroup
+ * summing a few particles over every j; it stays the automatic choice if it beats
+ * every tile configuration, and best then still names the fastest of those.)  If cache_path is non-NULL
  * the table is also appended there as one JSON object per line.  best (host,
  * may be NULL) receives the chosen configuration. */
 int nbody_tune(int64_t n, int32_t precision, const char* cache_path, nbody_config* best);

@@ -162,6 +162,9 @@ static int auto_split(int64_t n, int ipl, int device) {
   return (int)std::max<int64_t>(1, std::min<int64_t>(s, std::min<int64_t>(smax, 1024)));
 }
 
+// Largest system whose force the row kernels serve.
+static int64_t rows_max_n(int precision) { return precision == NBODY_FP64 ? kRowsMaxN : kRowsMaxNForce32; }
+
 PairConfig choose_config(int64_t n, int precision, int device) {
   PairConfig c;
   // measured at N = 2^20: one i per lane is fastest for the FP32 pair loops,
@@ -192,8 +195,9 @@ PairConfig choose_config(int64_t n, int precision, int device) {
   c.sweep = t.sweep;
   // the row kernels (unless the tuner found a tile configuration faster at n)
   // have no tile configuration: a set one keeps the tile kernels
-  if (!tuned) c.rows = precision == NBODY_FP64 && n <= kRowsMaxN ? 1 : 0;
-  if (t.ipl || t.split || t.pairs == 2) c.rows = 0;
+  if (!tuned) c.rows = n <= rows_max_n(precision) ? 1 : 0;
+  c.rows_eval = n <= kRowsMaxN ? 1 : 0;
+  if (t.ipl || t.split || t.pairs == 2) c.rows = c.rows_eval = 0;
   // the symmetric kernels read a set split as a least number of launches (0 =
   // automatic); the ordered kernels that serve the same sizes (acceleration +
   // jerk (+ snap) below their thresholds, the FP64 VJP) keep their own j-split
@@ -834,7 +838,7 @@ int nbody_tune(int64_t n, int32_t precision, const char* cache_path, nbody_confi
     log.push_back({c, ms});
     if (ms < best_ms) { best_ms = ms; bc = c; }
   }
-  if (precision == NBODY_FP64 && n <= kRowsMaxN) {
+  if (n <= rows_max_n(precision)) {
     // the row kernels: kept for automatic selection if they beat every tile
     // configuration; the configuration reported stays the fastest of those
     PairConfig c = bc;

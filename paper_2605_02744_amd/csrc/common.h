@@ -61,9 +61,16 @@ constexpr int64_t kSymMinNSnap64 = 8192;
 constexpr int64_t kSymMinNJerk = 12288;
 constexpr int64_t kSymMinNSnap = 8192;
 constexpr int64_t kSymMinNPot = 8192;
-// The row kernels serve the FP64 evaluations below the symmetric kernels' sizes
-// (their lanes' plain sums are also only as long as a fold block up to there).
+// Largest systems of the row kernels.  In FP64 they serve every evaluation below
+// the symmetric kernels' sizes (their lanes' plain sums are also only as long as a
+// fold block up to there).  In FP32C and FP32 (us, rows against tile kernels with
+// their slice sums, flags and rescue): force 64 / 99 at 10000, 103 / 116 at 16384 (512
+// workgroups of 32 rows, all resident), 169 / 171 at 20000, 204 / 224 at 24000 and
+// 304 / 285 at 28000, which starts the second round of workgroups; jerk 66 / 77 and
+// VJP 75 / 84 at 8191, 155 / 102 and 175 / 113 at 10000; snap 108 / 130 at 8191,
+// where the symmetric kernel takes over.
 constexpr int64_t kRowsMaxN = 8191;
+constexpr int64_t kRowsMaxNForce32 = 24576;
 
 // Per-call configuration of the all-pairs kernels.
 struct PairConfig {
@@ -76,7 +83,8 @@ struct PairConfig {
   int sym_jerk64 = 0;  // 1: the symmetric FP64 acceleration + jerk
   int sym_snap64 = 0;  // 1: the symmetric FP64 acceleration + jerk + snap
   int sym_snap = 0;  // 1: the symmetric acceleration + jerk + snap (FP32C/FP32 only)
-  int rows = 0;  // 1: the row kernels (small systems; below the symmetric kernels' sizes)
+  int rows = 0;       // 1: the row kernels (small systems) for the force
+  int rows_eval = 0;  // 1: the row kernels for the VJP, the jerk and the snap
   int launches = 0;  // symmetric kernels: least number of launches of the half ring (0 = automatic)
   int rescue = 1;  // FP32C force: recompute rows flagged by the error estimate in FP64
   int sweep = 0;   // adjoint sweep: 0 = recompute overlapped on a second stream where allowed, 1 = one stream
@@ -190,36 +198,38 @@ int launch_kick(int64_t n3, double* v, const double* a, double h, hipStream_t s)
 int launch_kick_drift(int64_t n3, const double* x, double* xo, double* v, const double* a, double h, double dt,
                       int nkicks, hipStream_t s);
 
-// The FP64 row kernels (rows64.hip), for n <= kRowsMaxN: one launch per
+// The row kernels (rows64.hip, rows32.hip), for small systems: one launch per
 // evaluation, or per step with the elementwise update that follows it.  None
 // needs scratch; the outputs an update writes for other rows to read next (xo,
-// xp, vp, ap, lvo) are other buffers than the inputs.
-int launch_rows64_accel(int64_t n, const double* x, const double* m, double* a, double G, double eps, bool excl,
-                        hipStream_t s);
-int launch_rows64_jerk(int64_t n, const double* x, const double* v, const double* m, double* a, double* jk, double G,
-                       double eps, bool excl, hipStream_t s);
-int launch_rows64_snap(int64_t n, const double* x, const double* v, const double* acc, const double* m, double* a,
-                       double* jk, double* sn, double G, double eps, bool excl, hipStream_t s);
-int launch_rows64_vjp(int64_t n, const double* x, const double* m, const double* w, double* gx, double* gm, double G,
-                      double eps, bool excl, hipStream_t s);
-int launch_rows64_potential(int64_t n, const double* x, const double* m, double eps, double scale, double* phi,
-                            hipStream_t s);
+// xp, vp, ap, lvo) are other buffers than the inputs.  rescue: FP32C rows flagged
+// by their error estimate in FP64 (the force only).
+struct RowCall {
+  int64_t n;
+  const double* m;
+  double G, eps;
+  int precision;
+  bool excl, rescue;
+  hipStream_t s;
+};
+int launch_rows_accel(const RowCall& c, const double* x, double* a);
+int launch_rows_jerk(const RowCall& c, const double* x, const double* v, double* a, double* jk);
+int launch_rows_snap(const RowCall& c, const double* x, const double* v, const double* acc, double* a, double* jk,
+                     double* sn);
+int launch_rows_vjp(const RowCall& c, const double* x, const double* w, double* gx, double* gm);
+int launch_rows_potential(const RowCall& c, const double* x, double scale, double* phi);
 // a(x), then nkicks half-kicks of v and, with xo, the drift of x into xo.
-int launch_rows64_kdk(int64_t n, const double* x, double* xo, double* v, double* a, const double* m, double h, double dt,
-                      int nkicks, double G, double eps, bool excl, hipStream_t s);
+int launch_rows_kdk(const RowCall& c, const double* x, double* xo, double* v, double* a, double h, double dt, int nkicks);
 // The evaluation at the predicted (xp, vp), the corrector on the state, and with
 // xo the next prediction into (xo, vo).
-int launch_rows64_hermite4(int64_t n, const double* xp, const double* vp, const double* m, double* x, double* v,
-                           double* a, double* jk, double* xo, double* vo, double dt, double G, double eps, bool excl,
-                           hipStream_t s);
+int launch_rows_hermite4(const RowCall& c, const double* xp, const double* vp, double* x, double* v, double* a,
+                         double* jk, double* xo, double* vo, double dt);
 // The same in sixth order; p and o hold (xp, vp, ap), o may be null.
-int launch_rows64_hermite6(int64_t n, double* const* p, const double* m, double* x, double* v, double* a, double* jk,
-                           double* sn, double* cr, double* const* o, double dt, double G, double eps, bool excl,
-                           hipStream_t s);
+int launch_rows_hermite6(const RowCall& c, double* const* p, double* x, double* v, double* a, double* jk, double* sn,
+                         double* cr, double* const* o, double dt);
 // The VJP at (x, m) with cotangent lv, lx += gx, gm += its mass term, and with
 // lvo lv + dt lx into lvo.
-int launch_rows64_adjoint(int64_t n, const double* x, const double* m, const double* lv, double* lx, double* gm,
-                          double* lvo, double dt, double G, double eps, bool excl, hipStream_t s);
+int launch_rows_adjoint(const RowCall& c, const double* x, const double* lv, double* lx, double* gm, double* lvo,
+                        double dt);
 
 // scale * phi_i, phi_i = sum_{j != i} m_j (|d|^2 + eps^2)^-1/2 in FP64, into
 // phi[n]: by rows with cfg.rows, else symmetric with cfg.sym, else ordered with

@@ -245,9 +245,11 @@ int check_finite(const double* p, int64_t cnt, hipStream_t s, bool* all_finite) 
 // workgroups still read x_k): traj's next slot, or x and a temporary in turn so
 // that x_nsteps lands in x.
 static int run_kdk_rows(int64_t n, double* x, double* v, double* a, const double* m, double dt, int64_t nsteps, double G,
-                        double eps, bool excl, bool acc_valid, const PairConfig& cfg, hipStream_t s, double* traj) {
+                        double eps, int precision, bool excl, bool acc_valid, const PairConfig& cfg, hipStream_t s,
+                        double* traj) {
   const int64_t n3 = 3 * n;
   const double h = 0.5 * dt;
+  const RowCall c{n, m, G, eps, precision, excl, cfg.rescue != 0, s};
   int st = NBODY_OK;
   double* tmp = nullptr;
   if (!traj && nsteps > 1 && !(tmp = static_cast<double*>(pair_scratch(cfg, sizeof(double) * (size_t)n3, &st)))) return st;
@@ -255,13 +257,13 @@ static int run_kdk_rows(int64_t n, double* x, double* v, double* a, const double
   if (!acc_valid) {
     // a(x_0), with the first kick and drift where x_1 has a buffer of its own
     const bool fuse = nsteps > 0 && at(1) != at(0);
-    if ((st = launch_rows64_kdk(n, at(0), fuse ? at(1) : nullptr, v, a, m, h, dt, fuse ? 1 : 0, G, eps, excl, s))) return st;
+    if ((st = launch_rows_kdk(c, at(0), fuse ? at(1) : nullptr, v, a, h, dt, fuse ? 1 : 0))) return st;
     acc_valid = !fuse;
   }
   if (nsteps > 0 && acc_valid && (st = launch_kick_drift(n3, at(0), at(1), v, a, h, dt, 1, s))) return st;
   for (int64_t k = 1; k <= nsteps; ++k) {
     const bool last = k == nsteps;
-    if ((st = launch_rows64_kdk(n, at(k), last ? nullptr : at(k + 1), v, a, m, h, dt, last ? 1 : 2, G, eps, excl, s))) return st;
+    if ((st = launch_rows_kdk(c, at(k), last ? nullptr : at(k + 1), v, a, h, dt, last ? 1 : 2))) return st;
   }
   return NBODY_OK;
 }
@@ -269,7 +271,7 @@ static int run_kdk_rows(int64_t n, double* x, double* v, double* a, const double
 int run_kdk(int64_t n, double* x, double* v, double* a, const double* m, double dt, int64_t nsteps,
             double G, double eps, int precision, bool excl, bool acc_valid, const PairConfig& cfg,
             hipStream_t s, double* traj) {
-  if (cfg.rows && precision == NBODY_FP64) return run_kdk_rows(n, x, v, a, m, dt, nsteps, G, eps, excl, acc_valid, cfg, s, traj);
+  if (cfg.rows) return run_kdk_rows(n, x, v, a, m, dt, nsteps, G, eps, precision, excl, acc_valid, cfg, s, traj);
   const int64_t n3 = 3 * n;
   const double h = 0.5 * dt;
   int st;
@@ -300,7 +302,7 @@ int run_hermite(int64_t n, double* x, double* v, double* a, double* jk, const do
   if (nsteps == 0) return NBODY_OK;
   double* ws = static_cast<double*>(workspace(current_device(), 1, sizeof(double) * 4 * (size_t)n3, &st));
   if (!ws) return st;
-  if (cfg.rows && precision == NBODY_FP64) {
+  if (cfg.rows_eval) {
     // one launch a step: evaluate one pair of predicted buffers, correct the
     // state and predict the next step into the other pair
     double* p[2][2] = {{ws, ws + n3}, {ws + 2 * n3, ws + 3 * n3}};
@@ -310,8 +312,8 @@ int run_hermite(int64_t n, double* x, double* v, double* a, double* jk, const do
       double* const* q = p[k % 2];
       double* const* o = p[(k + 1) % 2];
       const bool more = k + 1 < nsteps;
-      if ((st = launch_rows64_hermite4(n, q[0], q[1], m, x, v, a, jk, more ? o[0] : nullptr, more ? o[1] : nullptr, dt, G,
-                                       eps, excl, s)))
+      if ((st = launch_rows_hermite4(RowCall{n, m, G, eps, precision, excl, false, s}, q[0], q[1], x, v, a, jk,
+                                     more ? o[0] : nullptr, more ? o[1] : nullptr, dt)))
         return st;
     }
     return NBODY_OK;
@@ -349,7 +351,7 @@ int run_hermite6(int64_t n, double* x, double* v, double* a, double* jk, double*
     if ((st = launch_accel_jerk_snap(n, x, v, a1, m, a, jk, sn, G, eps, precision, excl, cfg, s))) return st;
     if ((st = launch_fill(n3, cr, 0.0, s))) return st;
   }
-  if (cfg.rows && precision == NBODY_FP64) {
+  if (cfg.rows_eval) {
     // one launch a step, as in run_hermite (xp, vp, ap and a1, j1, s1 hold the two predictions)
     double* p[2][3] = {{xp, vp, ap}, {a1, j1, s1}};
     if (nsteps > 0) {
@@ -357,8 +359,8 @@ int run_hermite6(int64_t n, double* x, double* v, double* a, double* jk, double*
       NB_LAUNCH_CHECK("hermite6_predict_kernel");
     }
     for (int64_t k = 0; k < nsteps; ++k)
-      if ((st = launch_rows64_hermite6(n, p[k % 2], m, x, v, a, jk, sn, cr, k + 1 < nsteps ? p[(k + 1) % 2] : nullptr, dt,
-                                       G, eps, excl, s)))
+      if ((st = launch_rows_hermite6(RowCall{n, m, G, eps, precision, excl, false, s}, p[k % 2], x, v, a, jk, sn, cr,
+                                     k + 1 < nsteps ? p[(k + 1) % 2] : nullptr, dt)))
         return st;
     return NBODY_OK;
   }
@@ -478,7 +480,7 @@ int run_traj_grad(int64_t n, const double* ckx, const double* ckv, int64_t every
   // on the row kernels the VJP's launch also does its update; lambda_v, which
   // every workgroup reads, then drifts between gv0 and gxp's space in turn (one
   // drift a step: it starts where the last one leaves it in gv0)
-  const bool rows = cfg.rows && precision == NBODY_FP64;
+  const bool rows = cfg.rows_eval != 0;
   double* lvo = gxp;
   if (rows && nsteps % 2 == 1) std::swap(lv, lvo);
   if ((st = launch_copy(n3, gxT, lx, s))) return st;
@@ -514,7 +516,7 @@ int run_traj_grad(int64_t n, const double* ckx, const double* ckv, int64_t every
       const double* xp = traj + (size_t)(p - k0) * n3;
       int e;
       if (rows) {
-        if ((e = launch_rows64_adjoint(n, xp, m, lv, lx, gm, lvo, dt, G * c, eps, excl, s))) return e;
+        if ((e = launch_rows_adjoint(RowCall{n, m, G * c, eps, precision, excl, false, s}, xp, lv, lx, gm, lvo, dt))) return e;
         std::swap(lv, lvo);
         continue;
       }
@@ -558,7 +560,8 @@ int run_traj_grad(int64_t n, const double* ckx, const double* ckv, int64_t every
     if (sw) return sw;
   }
   // opening half-kick of step 0 at x_0
-  if (nsteps > 0 && rows) return launch_rows64_adjoint(n, ckx, m, lv, lx, gm, nullptr, dt, G * h, eps, excl, s);
+  if (nsteps > 0 && rows) 
+    return launch_rows_adjoint(RowCall{n, m, G * h, eps, precision, excl, false, s}, ckx, lv, lx, gm, nullptr, dt);
   if (nsteps > 0) {
     if ((st = launch_vjp(n, ckx, m, lv, gxp, gmp, G * h, eps, precision, excl, cfg, s))) return st;
     adjoint_update_kernel<<<ew_blocks(n3), kEw, 0, s>>>(n, lx, lv, gm, gxp, gmp, dt, 0);

@@ -870,9 +870,9 @@ int launch_accel_jerk_snap(int64_t n, const double* x, const double* v, const do
                            double* a, double* jk, double* sn, double G, double eps, int precision, bool excl,
                            const PairConfig& cfg, hipStream_t s) {
   if (n == 0) return NBODY_OK;
+  if (cfg.rows_eval) return launch_rows_snap(RowCall{n, m, G, eps, precision, excl, false, s}, x, v, acc, a, jk, sn);
   if (cfg.sym_snap && precision != kFP64)
     return launch_sym_snap(n, x, v, acc, m, a, jk, sn, G, eps, precision, excl, cfg, s);
-  if (cfg.rows && precision == kFP64) return launch_rows64_snap(n, x, v, acc, m, a, jk, sn, G, eps, excl, s);
   if (cfg.sym_snap64 && precision == kFP64) return launch_sym_snap64(n, x, v, acc, m, a, jk, sn, G, eps, excl, cfg, s);
   const int split = cfg.split < 1 ? 1 : cfg.split;
   switch (precision) {
@@ -886,8 +886,8 @@ int launch_accel_jerk_snap(int64_t n, const double* x, const double* v, const do
 int launch_accel_jerk(int64_t n, const double* x, const double* v, const double* m, double* a, double* jk, double G,
                       double eps, int precision, bool excl, const PairConfig& cfg, hipStream_t s) {
   if (n == 0) return NBODY_OK;
+  if (cfg.rows_eval) return launch_rows_jerk(RowCall{n, m, G, eps, precision, excl, false, s}, x, v, a, jk);
   if (cfg.sym_jerk && precision != kFP64) return launch_sym_jerk(n, x, v, m, a, jk, G, eps, precision, excl, cfg, s);
-  if (cfg.rows && precision == kFP64) return launch_rows64_jerk(n, x, v, m, a, jk, G, eps, excl, s);
   if (cfg.sym_jerk64 && precision == kFP64) return launch_sym_jerk64(n, x, v, m, a, jk, G, eps, excl, cfg, s);
   const int split = cfg.split < 1 ? 1 : cfg.split;
   const bool one = cfg.ipl <= 1;
@@ -905,7 +905,7 @@ int launch_accel_jerk(int64_t n, const double* x, const double* v, const double*
 int launch_accel(int64_t n, const double* x, const double* m, double* a, double G, double eps,
                  int precision, bool excl, const PairConfig& cfg, hipStream_t s) {
   if (n == 0) return NBODY_OK;
-  if (cfg.rows && precision == kFP64) return launch_rows64_accel(n, x, m, a, G, eps, excl, s);
+  if (cfg.rows) return launch_rows_accel(RowCall{n, m, G, eps, precision, excl, cfg.rescue != 0, s}, x, a);
   if (cfg.sym) {
     if (precision == kFP64) return launch_sym_accel64(n, x, m, a, G, eps, excl, cfg, s);
     return launch_sym_accel(n, x, m, a, G, eps, precision, excl, cfg, s);
@@ -933,8 +933,8 @@ int launch_accel(int64_t n, const double* x, const double* m, double* a, double 
 int launch_vjp(int64_t n, const double* x, const double* m, const double* w, double* gx, double* gm,
                double G, double eps, int precision, bool excl, const PairConfig& cfg, hipStream_t s) {
   if (n == 0) return NBODY_OK;
+  if (cfg.rows_eval) return launch_rows_vjp(RowCall{n, m, G, eps, precision, excl, false, s}, x, w, gx, gm);
   if (cfg.sym_vjp && precision != kFP64) return launch_sym_vjp(n, x, m, w, gx, gm, G, eps, precision, excl, cfg, s);
-  if (cfg.rows && precision == kFP64) return launch_rows64_vjp(n, x, m, w, gx, gm, G, eps, excl, s);
   if (cfg.sym_vjp64 && precision == kFP64) return launch_sym_vjp64(n, x, m, w, gx, gm, G, eps, cfg, s);
   const int split = cfg.split < 1 ? 1 : cfg.split;
   // The VJP keeps twice the accumulators of the force, so it runs at most 2 i per lane.
@@ -955,7 +955,7 @@ int launch_vjp(int64_t n, const double* x, const double* m, const double* w, dou
 int launch_potential(int64_t n, const double* x, const double* m, double eps, double scale, double* phi,
                      const PairConfig& cfg, hipStream_t s) {
   if (n == 0) return NBODY_OK;
-  if (cfg.rows) return launch_rows64_potential(n, x, m, eps, scale, phi, s);
+  if (cfg.rows) return launch_rows_potential(RowCall{n, m, scale, eps, NBODY_FP64, true, false, s}, x, scale, phi);
   int split = cfg.split;
   if (cfg.sym) {
     const int st = launch_sym_pot64(n, x, m, phi, scale, eps, cfg, s);

@@ -1,6 +1,6 @@
-// Launchers of the FP64 row kernels (rows64.h): evaluations and whole steps of
-// systems of up to kRowsMaxN particles, one launch each.
+// The FP64 row kernels (rows64.h), one launch for each evaluation and update.
 #include "rows64.h"
+#include "rows_launch.h"
 
 namespace nb {
 namespace {
@@ -18,63 +18,44 @@ int launch_u(const RowArgs& A, bool excl, const Epi& epi, hipStream_t s) {
 }
 
 template <class E, class Epi>
-int launch(int64_t n, const double* x, const double* m, const double* w, const double* u, double eps, bool excl,
-           const Epi& epi, hipStream_t s) {
-  if (n == 0) return NBODY_OK;
-  if (n > kRowsMaxN) return set_error(NBODY_EINVAL, "row kernel: n too large");
-  const RowArgs A{(int)n, x, m, w, u, eps * eps};
-  if (n <= kAheadMaxN) return launch_u<E, (E::NW > 7 ? 2 : 4)>(A, excl, epi, s);
-  return launch_u<E, 1>(A, excl, epi, s);
+int launch(const RowCall& c, const double* x, const double* w, const double* u, const Epi& epi) {
+  if (c.n == 0) return NBODY_OK;
+  if (c.n > kRowsMaxN) return set_error(NBODY_EINVAL, "row kernel: n too large");
+  const RowArgs A{(int)c.n, x, c.m, w, u, c.eps * c.eps};
+  if (c.n <= kAheadMaxN) return launch_u<E, (E::NW > 7 ? 2 : 4)>(A, c.excl, epi, c.s);
+  return launch_u<E, 1>(A, c.excl, epi, c.s);
 }
 
 }  // namespace
 
-int launch_rows64_accel(int64_t n, const double* x, const double* m, double* a, double G, double eps, bool excl,
-                        hipStream_t s) {
-  return launch<RowAccel>(n, x, m, nullptr, nullptr, eps, excl, EpiStore{G, a, nullptr, nullptr}, s);
+template <class Epi>
+int rows64(RowEval e, const RowCall& c, const double* x, const double* w, const double* u, const Epi& epi) {
+  if constexpr (Epi::eval == RowEval::kAny) {
+    switch (e) {
+      case RowEval::kAccel: return launch<RowAccel>(c, x, w, u, epi);
+      case RowEval::kJerk: return launch<RowJerk>(c, x, w, u, epi);
+      case RowEval::kSnap: return launch<RowSnap>(c, x, w, u, epi);
+      case RowEval::kVjp: return launch<RowVjp>(c, x, w, u, epi);
+      case RowEval::kPot: return launch<RowPot>(c, x, w, u, epi);
+      default: return set_error(NBODY_EINVAL, "row kernel: unknown evaluation");
+    }
+  } else if constexpr (Epi::eval == RowEval::kAccel) {
+    return launch<RowAccel>(c, x, w, u, epi);
+  } else if constexpr (Epi::eval == RowEval::kJerk) {
+    return launch<RowJerk>(c, x, w, u, epi);
+  } else if constexpr (Epi::eval == RowEval::kSnap) {
+    return launch<RowSnap>(c, x, w, u, epi);
+  } else {
+    return launch<RowVjp>(c, x, w, u, epi);
+  }
 }
 
-int launch_rows64_jerk(int64_t n, const double* x, const double* v, const double* m, double* a, double* jk, double G,
-                       double eps, bool excl, hipStream_t s) {
-  return launch<RowJerk>(n, x, m, v, nullptr, eps, excl, EpiStore{G, a, jk, nullptr}, s);
-}
-
-int launch_rows64_snap(int64_t n, const double* x, const double* v, const double* acc, const double* m, double* a,
-                       double* jk, double* sn, double G, double eps, bool excl, hipStream_t s) {
-  return launch<RowSnap>(n, x, m, v, acc, eps, excl, EpiStore{G, a, jk, sn}, s);
-}
-
-int launch_rows64_vjp(int64_t n, const double* x, const double* m, const double* w, double* gx, double* gm, double G,
-                      double eps, bool excl, hipStream_t s) {
-  return launch<RowVjp>(n, x, m, w, nullptr, eps, excl, EpiStore{G, gx, gm, nullptr}, s);
-}
-
-int launch_rows64_potential(int64_t n, const double* x, const double* m, double eps, double scale, double* phi,
-                            hipStream_t s) {
-  return launch<RowPot>(n, x, m, nullptr, nullptr, eps, true, EpiStore{scale, phi, nullptr, nullptr}, s);
-}
-
-int launch_rows64_kdk(int64_t n, const double* x, double* xo, double* v, double* a, const double* m, double h, double dt,
-                      int nkicks, double G, double eps, bool excl, hipStream_t s) {
-  return launch<RowAccel>(n, x, m, nullptr, nullptr, eps, excl, EpiKdk{G, h, dt, nkicks, x, xo, v, a}, s);
-}
-
-int launch_rows64_hermite4(int64_t n, const double* xp, const double* vp, const double* m, double* x, double* v,
-                           double* a, double* jk, double* xo, double* vo, double dt, double G, double eps, bool excl,
-                           hipStream_t s) {
-  return launch<RowJerk>(n, xp, m, vp, nullptr, eps, excl, EpiHermite4{G, dt, x, v, a, jk, xo, vo}, s);
-}
-
-int launch_rows64_hermite6(int64_t n, double* const* p, const double* m, double* x, double* v, double* a, double* jk,
-                           double* sn, double* cr, double* const* o, double dt, double G, double eps, bool excl,
-                           hipStream_t s) {
-  const EpiHermite6 epi{G, dt, x, v, a, jk, sn, cr, o ? o[0] : nullptr, o ? o[1] : nullptr, o ? o[2] : nullptr};
-  return launch<RowSnap>(n, p[0], m, p[1], p[2], eps, excl, epi, s);
-}
-
-int launch_rows64_adjoint(int64_t n, const double* x, const double* m, const double* lv, double* lx, double* gm,
-                          double* lvo, double dt, double G, double eps, bool excl, hipStream_t s) {
-  return launch<RowVjp>(n, x, m, lv, nullptr, eps, excl, EpiAdjoint{G, dt, lx, gm, lv, lvo}, s);
-}
+#define NB_ROWS64(Epi) \
+  template int rows64<Epi>(RowEval, const RowCall&, const double*, const double*, const double*, const Epi&)
+NB_ROWS64(EpiStore);
+NB_ROWS64(EpiKdk);
+NB_ROWS64(EpiHermite4);
+NB_ROWS64(EpiHermite6);
+NB_ROWS64(EpiAdjoint);
 
 }  // namespace nb

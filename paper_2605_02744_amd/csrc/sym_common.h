@@ -9,6 +9,7 @@
 #include <mutex>
 
 #include "pair_math.h"
+#include "wave64.h"
 
 namespace nb {
 namespace {
@@ -50,16 +51,6 @@ __device__ __forceinline__ int xcd_local_index(int bid, int grid) {
   if (bid >= whole) return bid;
   const int x = bid % kXCDs, k = bid / kXCDs;
   return ((k / kXCDRun) * kXCDs + x) * kXCDRun + k % kXCDRun;
-}
-
-// Orders a wave's LDS accesses around a rewrite by other lanes (LDS
-// instructions of one wave execute in order; this keeps the compiler from
-// moving, merging or dropping reads and writes across the point, which it may
-// otherwise do because to it different lanes are different threads).
-__device__ __forceinline__ void wave_sync() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
 struct SymArgs {

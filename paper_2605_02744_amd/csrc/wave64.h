@@ -31,4 +31,55 @@ __device__ __forceinline__ double swap_add(double a, double b) {
   }
 }
 
+// Sums the M values of every lane over the wave and stores them at dst[0 .. M).
+// After the two exchanges slot q of a lane in row r (of 4) holds value
+// 4q + 2 (r & 1) + (r >> 1), summed over the four rows.
+template <int M>
+__device__ __forceinline__ void wave_sums(const double (&p)[M], double* dst) {
+  const int lane = threadIdx.x & 63, row = lane >> 4;
+#pragma unroll
+  for (int q = 0; q < M; q += 4) {
+    auto at = [&](int k) { return q + k < M ? p[q + k < M ? q + k : 0] : 0.0; };
+    double v = swap_add<16>(swap_add<32>(at(0), at(1)), swap_add<32>(at(2), at(3)));
+    v += row_ror64<8>(v);
+    v += row_ror64<4>(v);
+    v += row_ror64<2>(v);
+    v += row_ror64<1>(v);
+    const int k = q + 2 * (row & 1) + (row >> 1);
+    if ((lane & 15) == 0 && k < M) dst[k] = v;
+  }
+}
+
+// Sums the V values of the 64 / I groups of I lanes (I = 16 or 32) into dst,
+// value c of lane k of the groups at dst[c * I + k].
+template <int I, int V>
+__device__ __forceinline__ void group_sums(const double (&p)[V], double* dst) {
+  const int lane = threadIdx.x & 63, row = lane >> 4;
+  if constexpr (I == 16) {
+#pragma unroll
+    for (int q = 0; q < V; q += 4) {
+      auto at = [&](int k) { return q + k < V ? p[q + k < V ? q + k : 0] : 0.0; };
+      const double v = swap_add<16>(swap_add<32>(at(0), at(1)), swap_add<32>(at(2), at(3)));
+      const int k = q + 2 * (row & 1) + (row >> 1);
+      if (k < V) dst[k * I + (lane & 15)] = v;
+    }
+  } else {
+    static_assert(I == 32, "groups of 16 or 32 lanes");
+#pragma unroll
+    for (int q = 0; q < V; q += 2) {
+      const double v = swap_add<32>(p[q], q + 1 < V ? p[q + 1 < V ? q + 1 : 0] : 0.0);
+      const int k = q + (lane >> 5);
+      if (k < V) dst[k * I + (lane & 31)] = v;
+    }
+  }
+}
+
+// Orders a wave's LDS accesses around a rewrite by other lanes of the same wave
+// (they execute in order; the compiler may otherwise move or merge them).
+__device__ __forceinline__ void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 }  // namespace nb
