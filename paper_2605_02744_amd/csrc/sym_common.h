@@ -229,11 +229,20 @@ int run_sym_chunks(SideStream* side, hipStream_t s, int nchunks, int nbuf, Diag 
 // block-diagonal sums: tiles per workgroup (T: whole distances of kSTiles
 // tiles, or for small rings a part of one) and distances per launch (D), the
 // sum slots of a launch kept near 1 GiB and the whole layout within budget
-// bytes; launches > 0 asks for at least that many launches.  Returns the bytes
-// the layout needs, which exceed budget only if one distance per launch does
-// not fit.
+// bytes; launches > 0 asks for at least that many launches.  Rings of fewer than
+// `fine` tiles take one tile per workgroup (kFineTiles, kFineTiles64).  Returns
+// the bytes the layout needs, which exceed budget only if one distance per launch
+// does not fit.
+//
+// One tile per workgroup spreads a small ring more evenly over the CUs (12400
+// particles are 8.6 tiles a CU: 9 by ones, 10 by twos) and pays for it with a
+// prologue and an i-side sum per tile, which weighs more in FP64.  FP32C VJP 154 ->
+// 142 us at 12400, 213 -> 194 at 16384, 293 -> 284 at 20000, but 341 -> 330 for the
+// VJP against 528 -> 560 for the snap at 22500; FP64 VJP 122 -> 114 at 9973, 158 ->
+// 151 at 12000, 244 -> 246 at 16384.
+constexpr int64_t kFineTiles = 7168, kFineTiles64 = 3072;
 inline size_t sym_plan(int64_t n, int launches, int slot_bytes, int sum_bytes, int part_bytes, int fixed_bytes,
-                       size_t budget, int* nb_out, int* T_out, int* D_out) {
+                       size_t budget, int64_t fine, int* nb_out, int* T_out, int* D_out) {
   const int nb = (int)((n + kSI - 1) / kSI);
   const int dmax = nb / 2;
   const int64_t npad = (int64_t)nb * kSI;
@@ -261,7 +270,7 @@ inline size_t sym_plan(int64_t n, int launches, int slot_bytes, int sum_bytes, i
       T = kSTiles;
       D = d0;
     } else {
-      T = bp * kSTiles / 4096 >= 4 ? 4 : 2;
+      T = bp * kSTiles / 4096 >= 4 ? 4 : bp * kSTiles < fine ? 1 : 2;
       D = d0;
     }
     need = (size_t)npad * ((size_t)fixed_bytes + (size_t)D * slot_bytes + (size_t)(D * kSTiles / T) * part_bytes);

@@ -452,7 +452,7 @@ int launch_sym_jerk(int64_t n, const double* x, const double* v, const double* m
   // FP64 block-diagonal sums (in pds slices) and three staged float4 records
   const int pds = diag_slices((int)((n + kSI - 1) / kSI));
   sym_plan(n, cfg.launches, kJC * sizeof(float), kJC * sizeof(float), kJC * sizeof(double),
-           pds * kJC * (int)sizeof(double) + 3 * (int)sizeof(float4), cfg.scratch ? cfg.scratch_bytes : SIZE_MAX, &nb,
+           pds * kJC * (int)sizeof(double) + 3 * (int)sizeof(float4), cfg.scratch ? cfg.scratch_bytes : SIZE_MAX, kFineTiles, &nb,
            &T, &D);
   const int dmax = nb / 2;
   const int half = (nb % 2 == 0) ? 1 : 0;

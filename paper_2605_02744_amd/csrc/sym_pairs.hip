@@ -576,7 +576,7 @@ int launch_sym_accel(int64_t n, const double* x, const double* m, double* a, dou
   sym_plan(n, cfg.launches, 3 * sizeof(float) + est_slot, 3 * sizeof(float), 3 * sizeof(double) + est_part,
            pds * (3 * (int)sizeof(double) + (rescue ? (int)sizeof(float) : 0)) + 2 * sizeof(float4) + est_fixed -
                (rescue ? (int)sizeof(float) : 0),
-           cfg.scratch ? cfg.scratch_bytes - count_bytes : SIZE_MAX, &nb, &T, &D);
+           cfg.scratch ? cfg.scratch_bytes - count_bytes : SIZE_MAX, kFineTiles, &nb, &T, &D);
   const int dmax = nb / 2;
   const int half = (nb % 2 == 0) ? 1 : 0;
   const int64_t npad = (int64_t)nb * kSI;

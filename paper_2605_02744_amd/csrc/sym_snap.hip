@@ -459,7 +459,7 @@ int launch_sym_snap(int64_t n, const double* x, const double* v, const double* a
   // FP64 block-diagonal sums (in pds slices) and four staged float4 records
   const int pds = diag_slices((int)((n + kSI - 1) / kSI));
   sym_plan(n, cfg.launches, kSC * sizeof(float), kSC * sizeof(float), kSC * sizeof(double),
-           pds * kSC * (int)sizeof(double) + 4 * (int)sizeof(float4), cfg.scratch ? cfg.scratch_bytes : SIZE_MAX, &nb,
+           pds * kSC * (int)sizeof(double) + 4 * (int)sizeof(float4), cfg.scratch ? cfg.scratch_bytes : SIZE_MAX, kFineTiles, &nb,
            &T, &D);
   const int dmax = nb / 2;
   const int half = (nb % 2 == 0) ? 1 : 0;

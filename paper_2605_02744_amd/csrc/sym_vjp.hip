@@ -436,7 +436,7 @@ int launch_sym_vjp(int64_t n, const double* x, const double* m, const double* w,
   // FP64 block-diagonal sums (in pds slices) and three staged float4 records
   const int pds = diag_slices((int)((n + kSI - 1) / kSI));
   sym_plan(n, cfg.launches, kVC * sizeof(float), kVC * sizeof(float), kVC * sizeof(double),
-           pds * kVC * (int)sizeof(double) + 3 * (int)sizeof(float4), cfg.scratch ? cfg.scratch_bytes : SIZE_MAX, &nb,
+           pds * kVC * (int)sizeof(double) + 3 * (int)sizeof(float4), cfg.scratch ? cfg.scratch_bytes : SIZE_MAX, kFineTiles, &nb,
            &T, &D);
   const int dmax = nb / 2;
   const int half = (nb % 2 == 0) ? 1 : 0;
