@@ -140,16 +140,20 @@ __global__ void ssym_stage_kernel(SymArgs A, float4* __restrict__ rhi, float4* _
   rlo[j] = lo;
 }
 
-// Near-field correction of one lane's tile (FP32C): every pair of the lane's
-// two i with the tile's 64 j closer than the larger repair radius of its two
-// particles gets (float-float term - rounded term) added, times m_j to the
-// lane's i-side sums p and times -m_i to the wave's j-side sums of the tile
-// (part: components kSW * kST apart).  The j are visited in the rotated order
-// of the pair loop, so at each step the lanes of a row touch distinct j; the
-// four rows of the wave, which share the slots, take turns.
+// Near-field correction of one lane's tile (FP32C): every pair of the lane's two i
+// with the tile's 64 j closer than the larger repair radius of its two particles
+// gets (float-float term - rounded term) added, times m_j to the lane's i-side
+// sums p and times -m_i to the wave's j-side sums of the tile (part: components
+// kSW * kST apart).  The j are visited in the rotated order of the pair loop, so
+// at each step the lanes of a row touch distinct j; the four rows of the wave,
+// which share the slots, take turns.  near: the lane's flagged sub-blocks (bit q);
+// a wave passes over a sub-block that no lane flagged and a step that corrected
+// nothing, since the visit costs the wave 64 steps of four turns whichever lane
+// asked for it and a flagged lane has one such sub-block as a rule (acceleration,
+// jerk and snap 36.2 -> 34.8 ms at 204800 particles).
 __device__ __forceinline__ void ssym_repair(const SymArgs& A, int g, int t, int rl, float e2, const SSet& s,
                                             float (&p)[2][kSC], const float4* hi, const float4* vr, const float4* ar,
-                                            const float4* lo, float* part) {
+                                            const float4* lo, float* part, unsigned near) {
   const int n = A.n;
   const int wrow = (t & 63) / kSR;
   float rc[2];
@@ -160,6 +164,7 @@ __device__ __forceinline__ void ssym_repair(const SymArgs& A, int g, int t, int 
   }
   for (int jj = 0; jj < kST; ++jj) {
     const int q = jj / kSR;
+    if (!(near >> q & 1)) continue;
     const int jl = q * kSR + ((rl + jj) & (kSR - 1));
     const float4 rh = hi[q * 2 * kSR + (jl % kSR)];
     const float4 vj = vr[q * 2 * kSR + (jl % kSR)];
@@ -193,6 +198,7 @@ __device__ __forceinline__ void ssym_repair(const SymArgs& A, int g, int t, int 
         any = true;
       }
     }
+    if (!__any(any)) continue;
     for (int r = 0; r < 4; ++r) {
       if (wrow == r && any) {
 #pragma unroll
@@ -280,14 +286,16 @@ __global__ __launch_bounds__(kSL, 3) void ssym_kernel(SymArgs A) {
     for (int u = 0; u < 2; ++u)
 #pragma unroll
       for (int c = 0; c < kSC; ++c) p[u][c] = 0.f;
-    float r2min[2] = {3.0e38f, 3.0e38f};
+    unsigned near = 0u;  // the lane's sub-blocks that may hold a pair to repair
 #pragma unroll 1
     for (int q = 0; q < 4; ++q) {
+      float r2min[2] = {3.0e38f, 3.0e38f};
       float aj[kSC];
 #pragma unroll
       for (int c = 0; c < kSC; ++c) aj[c] = 0.f;
       ssym_sub<NEAR>(s, &s_hi[b][q][rl], &s_v[b][q][rl], &s_a[b][q][rl], e2, p, r2min, aj,
                      std::make_integer_sequence<int, kSR>{});
+      if (NEAR && (r2min[0] < thr[0] || r2min[1] < thr[1])) near |= 1u << q;
       // the four rows' sums of the same 16 j, as in the acceleration
 #pragma unroll
       for (int c = 0; c < kSC; ++c) {
@@ -297,9 +305,9 @@ __global__ __launch_bounds__(kSL, 3) void ssym_kernel(SymArgs A) {
       }
     }
     if constexpr (NEAR) {
-      if (r2min[0] < thr[0] || r2min[1] < thr[1])
+      if (near)
         ssym_repair(A, g, t, rl, e2, s, p, &s_hi[b][0][0], &s_v[b][0][0], &s_a[b][0][0], &s_lo[b][0],
-                    &s_part[0][wave][0]);
+                    &s_part[0][wave][0], near);
     }
 #pragma unroll
     for (int u = 0; u < 2; ++u)
