@@ -93,79 +93,98 @@ __device__ __forceinline__ float sym_rc2(double xa, double ya, double za, double
 
 using lds_ptr = __attribute__((address_space(3))) void*;
 
+// add(q[k stride]) for k in [k, end), kRedU loads in flight.
+constexpr int kRedU = 8;
+template <typename S, typename Add>
+__device__ __forceinline__ void add_run(const S* __restrict__ q, size_t stride, int k, int end, Add add) {
+  for (; k < end; k += kRedU) {
+    S v[kRedU];
+#pragma unroll
+    for (int u = 0; u < kRedU; ++u) v[u] = q[(size_t)min(k + u, end - 1) * stride];
+#pragma unroll
+    for (int u = 0; u < kRedU; ++u) add(k + u < end ? v[u] : S(0));
+  }
+}
+
 // Adds the chunk's slots into the outputs (component c < 3 at out[c n + p],
 // 3 <= c < 6 at outm[(c - 3) n + p], c >= 6 at outs[(c - 6) n + p]): the j-side tile sums of distances d_lo .. d_lo + D - 1
 // that were evaluated (slots of type S: float, or double for the FP64 kernel),
-// then the i-side sums of the chunk's workgroups; the first chunk starts from
-// the distance-0 sums pd, the last applies G.  One thread per (particle,
-// component), fixed order.  Only the largest distance can be missing for some
+// and the i-side sums of the chunk's workgroups; the first chunk starts from
+// the distance-0 sums pd, the last applies G.  A workgroup (p-block, c) holds 64
+// particles, one per lane; its kRedW waves each add a run of the slots and a run
+// of the i-side sums, wave 0 also what came before, and wave 0 adds the waves'
+// sums in wave order.  Only the largest distance can be missing for some
 // blocks (the opposite block of an even ring, visited from the lower half only).
-// With eo (FP32C force only; the thread of component 0 does it): the error
-// estimate of the rescue in eo[npad], the far side's shares pw of the chunk's
-// distances and the workgroups' i-side shares pe added to what earlier chunks
-// left, or to the block-diagonal shares ed in the first chunk.  The
+// With eo (FP32C force only; the workgroups of row c = C do it, a lane per
+// particle): the error estimate of the rescue in eo[npad], the far side's shares
+// pw of the chunk's distances and the workgroups' i-side shares pe added to what
+// earlier chunks left, or to the block-diagonal shares ed in the first chunk.  The
 // block-diagonal sums come in pds slices (pd[pds][C][npad], ed[pds][npad]),
 // added in slice order.
+//
+// Bound by the latency of the loads and, from a few tens of MB of slots, by the
+// last-level cache they lie in (6.4 TB/s for the 201 MB of the FP32C VJP at 65536).
+// One thread per (particle, component) with four loads in flight, and the estimate's
+// loads one after another behind component 0, took 12.2 us for the FP64 VJP at 9973
+// and 54 us for the FP32C force at 65536; runs of eight over four waves and the
+// estimate in workgroups of its own take 7.2 and 31.
+constexpr int kRedP = 64, kRedW = 4;
+inline dim3 sym_reduce_grid(int64_t n, int comps, bool est) {
+  return dim3((unsigned)((n + kRedP - 1) / kRedP), (unsigned)(comps + (est ? 1 : 0)));
+}
 template <int C, typename S>
-__global__ void sym_reduce_kernel(int n, int npad, int nb, int dmax, int half, int d_lo, int D, int nparts,
-                                  const S* __restrict__ pj, const double* __restrict__ pi,
-                                  const double* __restrict__ pd, double* __restrict__ out, double* __restrict__ outm,
-                                  double G, int first, int last, const float* __restrict__ pe = nullptr,
-                                  const float* __restrict__ pw = nullptr, const float* __restrict__ ed = nullptr,
-                                  float* __restrict__ eo = nullptr, int pds = 1, double* __restrict__ outs = nullptr) {
-  const int p = blockIdx.x * blockDim.x + threadIdx.x;
+__global__ __launch_bounds__(kRedP * kRedW) void sym_reduce_kernel(
+    int n, int npad, int nb, int dmax, int half, int d_lo, int D, int nparts, const S* __restrict__ pj,
+    const double* __restrict__ pi, const double* __restrict__ pd, double* __restrict__ out, double* __restrict__ outm,
+    double G, int first, int last, const float* __restrict__ pe = nullptr, const float* __restrict__ pw = nullptr,
+    const float* __restrict__ ed = nullptr, float* __restrict__ eo = nullptr, int pds = 1,
+    double* __restrict__ outs = nullptr) {
+  __shared__ double red[C == 1 ? 2 : 1][kRedW - 1][kRedP];
   const int c = blockIdx.y;
-  if (p >= n) return;
-  double* o = c < 3 ? out + (size_t)c * n + p : c < 6 ? outm + (size_t)(c - 3) * n + p : outs + (size_t)(c - 6) * n + p;
+  const int wave = threadIdx.x / kRedP;
+  const bool est = c == C;
+  const int p = est ? blockIdx.x * (kRedP * kRedW) + threadIdx.x : blockIdx.x * kRedP + threadIdx.x % kRedP;
+  if (est && p >= n) return;  // (p < npad in the others: a multiple of kRedP)
   const int J = p / kSI;
-  // the potential's terms all have one sign, so plain adds would not average
-  // their roundings out as they do for the others' random signs
-  double acc = first ? 0.0 : *o, lo = 0.0;
-  auto add = [&](double v) {
-    if constexpr (C == 1) fold(acc, lo, v);
-    else acc += v;
-  };
-  if (first)
-    for (int k = 0; k < pds; ++k) add(pd[((size_t)k * C + c) * npad + p]);
-  const bool est = eo && c == 0;
-  float ea = 0.f;
-  if (est) {
-    if (first)
-      for (int k = 0; k < pds; ++k) ea += ed[(size_t)k * npad + p];
-    else
-      ea = eo[p];
-  }
   const int send = min(D, dmax - d_lo + 1);  // slots of this chunk within the ring
   // the last slot of the ring is dropped where its block pair was not evaluated
   const bool drop_last = half && d_lo + send - 1 == dmax && ((J - dmax) % nb + nb) % nb >= nb / 2;
   const int sn = drop_last ? send - 1 : send;
-  const S* q = pj + (size_t)c * npad + p;
-  const size_t stride = (size_t)C * npad;
-  int s = 0;
-  for (; s + 4 <= sn; s += 4) {
-    const S v0 = q[s * stride], v1 = q[(s + 1) * stride], v2 = q[(s + 2) * stride], v3 = q[(s + 3) * stride];
-    add((double)v0);
-    add((double)v1);
-    add((double)v2);
-    add((double)v3);
-  }
-  for (; s < sn; ++s) add((double)q[s * stride]);
-  const double* qi = pi + (size_t)c * npad + p;
-  const size_t pstride = (size_t)C * npad;
-  int k = 0;
-  for (; k + 4 <= nparts; k += 4) {
-    const double v0 = qi[k * pstride], v1 = qi[(k + 1) * pstride], v2 = qi[(k + 2) * pstride],
-                 v3 = qi[(k + 3) * pstride];
-    add(v0);
-    add(v1);
-    add(v2);
-    add(v3);
-  }
-  for (; k < nparts; ++k) add(qi[k * pstride]);
   if (est) {
-    for (int d = 0; d < sn; ++d) ea += pw[(size_t)d * npad + p];
-    for (int k = 0; k < nparts; ++k) ea += pe[(size_t)k * npad + p];
+    float ea = 0.f;
+    auto adde = [&](float v) { ea += v; };
+    if (first) add_run(ed + p, npad, 0, pds, adde);
+    else ea = eo[p];
+    add_run(pw + p, npad, 0, sn, adde);
+    add_run(pe + p, npad, 0, nparts, adde);
     eo[p] = ea;
+    return;
+  }
+  // the potential's terms all have one sign, so plain adds would not average
+  // their roundings out as they do for the others' random signs
+  double acc = 0.0, lo = 0.0;
+  auto add = [&](double v) {
+    if constexpr (C == 1) fold(acc, lo, v);
+    else acc += v;
+  };
+  double* o = c < 3 ? out + (size_t)c * n + p : c < 6 ? outm + (size_t)(c - 3) * n + p : outs + (size_t)(c - 6) * n + p;
+  const size_t stride = (size_t)C * npad, at = (size_t)c * npad + p;
+  if (wave == 0) {
+    if (first) add_run(pd + at, stride, 0, pds, add);
+    else if (p < n) acc = *o;
+  }
+  add_run(pj + at, stride, sn * wave / kRedW, sn * (wave + 1) / kRedW, [&](S v) { add((double)v); });
+  add_run(pi + at, stride, nparts * wave / kRedW, nparts * (wave + 1) / kRedW, add);
+  if (wave > 0) {
+    red[0][wave - 1][threadIdx.x % kRedP] = acc;
+    if constexpr (C == 1) red[1][wave - 1][threadIdx.x % kRedP] = lo;
+  }
+  __syncthreads();
+  if (wave > 0 || p >= n) return;
+#pragma unroll
+  for (int w = 0; w < kRedW - 1; ++w) {
+    add(red[0][w][threadIdx.x]);
+    if constexpr (C == 1) lo += red[1][w][threadIdx.x];
   }
   if constexpr (C == 1) acc += lo;
   *o = last ? G * acc : acc;

@@ -420,11 +420,11 @@ int launch_sym64(int64_t n, const double* x, const double* m, const double* w, c
     NB_LAUNCH_CHECK("sym64_kernel");
     return NBODY_OK;
   };
-  const dim3 rg((unsigned)((n + 255) / 256), NC);
+  const dim3 rg = sym_reduce_grid(n, NC, false);
   auto sum = [&](int c, int b, hipStream_t rs) -> int {
     Sym64Args B = A;
     slots(b, B);
-    sym_reduce_kernel<NC, double><<<rg, 256, 0, rs>>>((int)n, (int)npad, nb, dmax, half, 1 + c * D, dmax > 0 ? D : 0,
+    sym_reduce_kernel<NC, double><<<rg, kRedP * kRedW, 0, rs>>>((int)n, (int)npad, nb, dmax, half, 1 + c * D, dmax > 0 ? D : 0,
                                                       dmax > 0 ? nparts : 0, B.pj, B.pi, A.pd, out, outm, G, c == 0,
                                                       c + 1 >= nchunks, nullptr, nullptr, nullptr, nullptr, pds, outs);
     NB_LAUNCH_CHECK("sym_reduce_kernel");

@@ -522,10 +522,10 @@ int launch_sym_snap(int64_t n, const double* x, const double* v, const double* a
     NB_LAUNCH_CHECK("ssym_diag_kernel");
     return NBODY_OK;
   };
-  const dim3 rg((unsigned)((n + 255) / 256), kSC);
+  const dim3 rg = sym_reduce_grid(n, kSC, false);
   if (dmax == 0) {
     if ((st = diag(s))) return st;
-    sym_reduce_kernel<kSC, float><<<rg, 256, 0, s>>>((int)n, (int)npad, nb, dmax, half, 1, 0, 0, A.pj, A.pi, pd, a, jk, G,
+    sym_reduce_kernel<kSC, float><<<rg, kRedP * kRedW, 0, s>>>((int)n, (int)npad, nb, dmax, half, 1, 0, 0, A.pj, A.pi, pd, a, jk, G,
                                               1, 1, nullptr, nullptr, nullptr, nullptr, pds, sn);
     NB_LAUNCH_CHECK("sym_reduce_kernel");
     return NBODY_OK;
@@ -543,7 +543,7 @@ int launch_sym_snap(int64_t n, const double* x, const double* v, const double* a
   auto sum = [&](int c, int b, hipStream_t rs) -> int {
     SymArgs B = A;
     slots(b, B);
-    sym_reduce_kernel<kSC, float><<<rg, 256, 0, rs>>>((int)n, (int)npad, nb, dmax, half, 1 + c * D, D, nparts, B.pj, B.pi,
+    sym_reduce_kernel<kSC, float><<<rg, kRedP * kRedW, 0, rs>>>((int)n, (int)npad, nb, dmax, half, 1 + c * D, D, nparts, B.pj, B.pi,
                                                pd, a, jk, G, c == 0, c == nchunks - 1, nullptr, nullptr, nullptr,
                                                nullptr, pds, sn);
     NB_LAUNCH_CHECK("sym_reduce_kernel");

@@ -500,10 +500,10 @@ int launch_sym_vjp(int64_t n, const double* x, const double* m, const double* w,
     NB_LAUNCH_CHECK("vsym_diag_kernel");
     return NBODY_OK;
   };
-  const dim3 rg((unsigned)((n + 255) / 256), kVC);
+  const dim3 rg = sym_reduce_grid(n, kVC, false);
   if (dmax == 0) {
     if ((st = diag(s))) return st;
-    sym_reduce_kernel<kVC, float><<<rg, 256, 0, s>>>((int)n, (int)npad, nb, dmax, half, 1, 0, 0, A.pj, A.pi, pd, gx, gm, G,
+    sym_reduce_kernel<kVC, float><<<rg, kRedP * kRedW, 0, s>>>((int)n, (int)npad, nb, dmax, half, 1, 0, 0, A.pj, A.pi, pd, gx, gm, G,
                                               1, 1, nullptr, nullptr, nullptr, nullptr, pds);
     NB_LAUNCH_CHECK("sym_reduce_kernel");
     return NBODY_OK;
@@ -521,7 +521,7 @@ int launch_sym_vjp(int64_t n, const double* x, const double* m, const double* w,
   auto sum = [&](int c, int b, hipStream_t rs) -> int {
     SymArgs B = A;
     slots(b, B);
-    sym_reduce_kernel<kVC, float><<<rg, 256, 0, rs>>>((int)n, (int)npad, nb, dmax, half, 1 + c * D, D, nparts, B.pj, B.pi,
+    sym_reduce_kernel<kVC, float><<<rg, kRedP * kRedW, 0, rs>>>((int)n, (int)npad, nb, dmax, half, 1 + c * D, D, nparts, B.pj, B.pi,
                                                pd, gx, gm, G, c == 0, c == nchunks - 1, nullptr, nullptr, nullptr,
                                                nullptr, pds);
     NB_LAUNCH_CHECK("sym_reduce_kernel");
