@@ -166,12 +166,22 @@ __device__ __forceinline__ void esym_step(const float4& ip, float mneg, const fl
   }
 }
 
-template <bool NEAR, int... K>
+// Steps K0 + K of a sub-block.
+template <bool NEAR, int K0, int... K>
 __device__ __forceinline__ void esym_sub(const float4& ip, float mneg, const float4* __restrict__ rowp, float e2,
                                          float& px, float& py, float& pz, float& r2m, float& ajx, float& ajy,
                                          float& ajz, std::integer_sequence<int, K...>) {
-  (esym_step<K, NEAR>(ip, mneg, rowp, e2, px, py, pz, r2m, ajx, ajy, ajz), ...);
+  (esym_step<K0 + K, NEAR>(ip, mneg, rowp, e2, px, py, pz, r2m, ajx, ajy, ajz), ...);
 }
+
+// Steps of a sub-block flagged together for the near-field repair.  The repair radius
+// of a system of a few hundred to a few thousand particles reaches some lane's pair in
+// nearly every block pair, and walking all 64 steps with four turns each for it cost
+// as much as the pairs themselves there; only the wave's flagged runs are walked, and
+// only steps with a close pair take turns (per step: 512 systems of 64 to 512 particles
+// 91 -> 66 us, 100 of 64 to 2000 125 -> 109, 512 of 64 to 4096 1003 -> 993, bitwise the
+// same).  Runs of 16 steps spill 56 registers.
+constexpr int kERun = 8;
 
 // EST (FP32C with the rescue): the i-side shares of the error estimate into
 // iest, each block pair's closest pair left in rounded positions into wslots.
@@ -303,12 +313,27 @@ __global__ __launch_bounds__(kEBlock, kEOcc) void esym_force_kernel(
       const int J = it.b + d < nb ? it.b + d : it.b + d - nb;
       put(nh, nq);
       if (d + 1 < it.d1) fetch(J + 1 < nb ? J + 1 : J + 1 - nb, nh, nq);
-      float px = 0.f, py = 0.f, pz = 0.f, r2m = 3.0e38f;
+      float px = 0.f, py = 0.f, pz = 0.f;
+      // the lane's closest pair of the runs of kERun steps that no lane has to
+      // repair, and a bit per run that some lane may have to
+      float r2m = 3.0e38f;
+      unsigned runs = 0u;
 #pragma unroll 1
       for (int q = 0; q < 4; ++q) {
         float ajx = 0.f, ajy = 0.f, ajz = 0.f;
-        esym_sub<NEAR>(ip, mneg, &s_hi[wv][q][rl], e2, px, py, pz, r2m, ajx, ajy, ajz,
-                       std::make_integer_sequence<int, kSR>{});
+        auto run = [&](auto k0) {
+          constexpr int K0 = decltype(k0)::value;
+          float r2r = 3.0e38f;
+          esym_sub<NEAR, K0>(ip, mneg, &s_hi[wv][q][rl], e2, px, py, pz, r2r, ajx, ajy, ajz,
+                             std::make_integer_sequence<int, kERun>{});
+          if constexpr (NEAR) {
+            const bool any = __any(r2r < thr);
+            runs |= any ? 1u << (q * (kSR / kERun) + K0 / kERun) : 0u;
+            r2m = fminf(r2m, any ? 3.0e38f : r2r);
+          }
+        };
+        run(std::integral_constant<int, 0>{});
+        if constexpr (kERun < kSR) run(std::integral_constant<int, kERun % kSR>{});
         // the four rows' sums of the same 16 j: rows (0 + 1) and (2 + 3) by a
         // swizzle, then the two halves by a permute; every row then holds the
         // totals and stores the same values
@@ -324,24 +349,27 @@ __global__ __launch_bounds__(kEBlock, kEOcc) void esym_force_kernel(
       }
       if constexpr (NEAR) {
         wave_sync();
-        float r2nr = r2m;  // a lane without a repair keeps all its pairs in rounded positions
-        if (r2m < thr) {
-          r2nr = 3.0e38f;
-          // rare: for every pair of the lane's i closer than the larger repair
-          // radius of its two particles, the rounded-position term is replaced
-          // by the float-float one on both sides.  The j are visited in the
-          // rotated order of the pair loop, so at each step the lanes of a row
-          // touch distinct j; the four rows, which share the j, take turns.
-          for (int jj = 0; jj < 64; ++jj) {
-            const int q = jj >> 4;
+        // for every pair closer than the larger repair radius of its two
+        // particles, the rounded-position term is replaced by the float-float one
+        // on both sides.  The j are visited in the rotated order of the pair
+        // loop, so at each step the lanes of a row touch distinct j; the four
+        // rows, which share the j, take turns.
+        while (runs) {
+          const int r0 = (__ffs((int)runs) - 1) * kERun;
+          runs &= runs - 1;
+#pragma unroll
+          for (int u = 0; u < kERun; ++u) {
+            const int q = r0 / kSR, jj = r0 % kSR + u;
             const int jl = q * kSR + ((rl + jj) & (kSR - 1));
-            const float4 r = s_hi[wv][q][jl & (kSR - 1)];
-            const float4 ql = s_lo[wv][jl];
+            const float4 r = s_hi[wv][q][rl + jj];
             const float dx = r.x - ip.x, dy = r.y - ip.y, dz = r.z - ip.z;
             const float r2 = fmaf(dz, dz, fmaf(dy, dy, fmaf(dx, dx, e2)));
+            const bool close = r2 < fmaxf(iq.w, s_lo[wv][jl].w);
+            if (!close) r2m = fminf(r2m, r2);
+            if (!__any(close)) continue;
             float cx = 0.f, cy = 0.f, cz = 0.f;
-            if (!(r2 < fmaxf(iq.w, ql.w))) r2nr = fminf(r2nr, r2);
-            if (r2 < fmaxf(iq.w, ql.w)) {
+            if (close) {
+              const float4 ql = s_lo[wv][jl];
               const float ex = dx + (ql.x - iq.x), ey = dy + (ql.y - iq.y), ez = dz + (ql.z - iq.z);
               const float ri = rsqrt32(r2);
               const float ri3 = (ri * ri) * ri;
@@ -370,10 +398,10 @@ __global__ __launch_bounds__(kEBlock, kEOcc) void esym_force_kernel(
           }
         }
         if constexpr (EST) {
-          eacc = est_add(eacc, px, py, pz, xinf(), r2nr);
+          eacc = est_add(eacc, px, py, pz, xinf(), r2m);
           // the wave's minimum: within each row of 16 by rotations, then rows
           // (0 + 1) and (2 + 3) by a swizzle, then the two halves by a permute
-          float tm = r2nr;
+          float tm = r2m;
           tm = fminf(tm, row_ror<8>(tm));
           tm = fminf(tm, row_ror<4>(tm));
           tm = fminf(tm, row_ror<2>(tm));
