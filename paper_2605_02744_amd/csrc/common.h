@@ -180,7 +180,7 @@ int run_hermite6(int64_t n, double* x, double* v, double* a, double* jk, double*
 // against |a_i| and recomputes them in FP64 in place in a.  list (n ints) and
 // count (one int) are scratch; count must be zero when the flag kernel starts
 // (the evaluation's first kernel clears it).
-int launch_rescue(int64_t n, const double* x, const double* m, double eps, double G, bool excl, const float* est,
+int launch_rescue(int64_t n, const double* x, const double* m, double eps, double G, bool excl, float* est,
                   int nslices, size_t stride, double* a, int* list, int* count, hipStream_t s);
 
 // FP64 rescue of batched FP32C rows: the rcnt[c] rows of system c listed in

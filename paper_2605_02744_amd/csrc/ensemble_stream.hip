@@ -43,6 +43,7 @@
 #include <vector>
 
 #include "pair_math.h"
+#include "wave64.h"
 
 namespace nb {
 namespace {
@@ -685,99 +686,116 @@ __global__ __launch_bounds__(kSBlock, wave_kernel_waves<MODE>()) void ens_wavefo
   }
 }
 
-// The FP64 rescue of the rows the force kernel flagged: kRSplit workgroups
-// per system (kRWaves waves each) share its listed rows, kRRow rows per wave
-// and pass, workgroup p taking the passes p, p + kRSplit, ...; each stages
-// the system's FP64 positions and masses in LDS (kRStage records at a time; a
-// system that fits is staged once) unless it has no rows, and lane l of a wave
-// takes j = l, l + 64, ... of each stage; the lane sums are added by a
-// butterfly, so the result does not depend on the list's order or the grid.
-constexpr int kRWaves = 8;
-constexpr int kRRow = 2;
-constexpr int kRStage = 2048;
-constexpr int kRSplit = 8;
+// The FP64 rescue of the rows the force kernel flagged.  A unit is up to kRRow listed
+// rows of one system; the workgroups of the grid stride over the units of all systems,
+// which each counts for itself from rcnt (thread t the systems of its share, then a
+// prefix sum).  The lanes of a workgroup split the unit's j (lane t takes t, t + 256,
+// ...), kRAhead records loaded ahead of the arithmetic and straight from L2; the lane
+// sums are added in registers, then the wave sums in wave order, so the result does
+// not depend on the list's order or the grid.
+//
+// Bound by FP64 issue (21 issue slots a pair) and the latency of a unit's start.  About
+// 2 % of the rows are listed, some tens in a system: eight workgroups a system, a wave
+// per two rows, left 1.6 waves a SIMD at work on average, long systems last.  512
+// systems of 64 to 4096, 21000 rows, 40 us of issue: 93 -> 69 us.
+constexpr int kRXcds = 8;  // workgroups go to the chip's 8 XCDs, each with its own L2, in turn
+constexpr int kRBlock = 256;
+constexpr int kRRow = 4;
+constexpr int kRAhead = 2;
 template <bool EXCL>
-__global__ __launch_bounds__(64 * kRWaves) void ens_rescue_kernel(const int64_t* __restrict__ off,
-                                                                  const double* __restrict__ epsv, int64_t total,
-                                                                  const double* __restrict__ x,
-                                                                  const double* __restrict__ m, double G,
-                                                                  const int* __restrict__ rcnt,
-                                                                  const int* __restrict__ rlist,
-                                                                  double* __restrict__ a) {
-  __shared__ double sj[4][kRStage];
-  const int c = blockIdx.x;
-  const int nf = rcnt[c];
-  constexpr int kPass = kRWaves * kRRow;
-  if ((int)blockIdx.y * kPass >= nf) return;
+__global__ __launch_bounds__(kRBlock) void ens_rescue_kernel(int ncl, const int64_t* __restrict__ off,
+                                                             const double* __restrict__ epsv, int64_t total,
+                                                             const double* __restrict__ x,
+                                                             const double* __restrict__ m, double G,
+                                                             const int* __restrict__ rcnt,
+                                                             const int* __restrict__ rlist, double* __restrict__ a) {
+  constexpr int W = kRBlock / 64;
+  __shared__ int64_t pre[kRBlock + 1];  // units of the systems before thread t's share
+  __shared__ int64_t wsum[W];
+  __shared__ double red[W][kRRow * 3];
   const int t = threadIdx.x, wave = t / 64, lane = t % 64;
-  const int64_t o = off[c];
-  const int nc = (int)(off[c + 1] - o);
-  const double e2 = epsv[c] * epsv[c];
-  auto stage = [&](int c0) {
-    const int cn = min(kRStage, nc - c0);
-    for (int j = t; j < cn; j += 64 * kRWaves) {
-      sj[0][j] = x[o + c0 + j];
-      sj[1][j] = x[total + o + c0 + j];
-      sj[2][j] = x[2 * total + o + c0 + j];
-      sj[3][j] = m[o + c0 + j];
+  const int share = (ncl + kRBlock - 1) / kRBlock;
+  auto units = [&](int c) { return (rcnt[c] + kRRow - 1) / kRRow; };
+  {
+    int64_t v = 0;
+    for (int c = t * share; c < min(ncl, (t + 1) * share); ++c) v += units(c);
+    for (int w = 1; w < 64; w <<= 1) {
+      const int64_t q = __shfl_up((long long)v, w, 64);
+      if (lane >= w) v += q;
     }
-  };
-  const bool once = nc <= kRStage;
-  if (once) {
-    stage(0);
+    if (lane == 63) wsum[wave] = v;
+    __syncthreads();
+    for (int w = 0; w < wave; ++w) v += wsum[w];
+    pre[t + 1] = v;
+    if (t == 0) pre[0] = 0;
     __syncthreads();
   }
-  for (int g0 = blockIdx.y * kPass; g0 < nf; g0 += kRSplit * kPass) {
+  // each XCD (workgroup id mod kRXcds) takes a run of the units: neighbouring units read
+  // the same system
+  const int64_t nu = pre[kRBlock];
+  const int xcd = blockIdx.x % kRXcds;
+  const int64_t uend = nu * (xcd + 1) / kRXcds;
+  for (int64_t unit = nu * xcd / kRXcds + blockIdx.x / kRXcds; unit < uend; unit += gridDim.x / kRXcds) {
+    // the share that holds the unit, then the system
+    int lo = 0;
+#pragma unroll
+    for (int w = kRBlock / 2; w > 0; w >>= 1)
+      if (pre[lo + w] <= unit) lo += w;
+    int c = lo * share, r0 = (int)(unit - pre[lo]);
+    for (int u; r0 >= (u = units(c)); ++c) r0 -= u;
+    const int nf = rcnt[c];
+    r0 *= kRRow;
+    const int64_t o = off[c];
+    const int nc = (int)(off[c + 1] - o);
+    const double e2 = epsv[c] * epsv[c];
+    const double *xs = x + o, *ys = x + total + o, *zs = x + 2 * total + o, *ms = m + o;
     int li[kRRow];
-    double xi[kRRow], yi[kRRow], zi[kRRow], sx[kRRow], sy[kRRow], sz[kRRow];
+    double xi[kRRow], yi[kRRow], zi[kRRow], sum[3 * kRRow];
 #pragma unroll
     for (int k = 0; k < kRRow; ++k) {
-      const int r = g0 + wave * kRRow + k;
-      li[k] = r < nf ? rlist[o + r] : -1;
-      const int64_t i = o + (li[k] < 0 ? 0 : li[k]);
-      xi[k] = x[i];
-      yi[k] = x[total + i];
-      zi[k] = x[2 * total + i];
-      sx[k] = sy[k] = sz[k] = 0.0;
+      li[k] = r0 + k < nf ? rlist[o + r0 + k] : -1;
+      const int i = li[k] < 0 ? 0 : li[k];
+      xi[k] = xs[i];
+      yi[k] = ys[i];
+      zi[k] = zs[i];
+      sum[3 * k] = sum[3 * k + 1] = sum[3 * k + 2] = 0.0;
     }
-    for (int c0 = 0; c0 < nc; c0 += kRStage) {
-      if (!once) {
-        __syncthreads();  // the previous stage has been read
-        stage(c0);
-        __syncthreads();
+    for (int j0 = t; j0 < nc; j0 += kRBlock * kRAhead) {
+      // past the system: far away and massless, adding exact zeros
+      double xj[kRAhead], yj[kRAhead], zj[kRAhead], mj[kRAhead];
+#pragma unroll
+      for (int u = 0; u < kRAhead; ++u) {
+        const int j = j0 + kRBlock * u;
+        const bool in = j < nc;
+        xj[u] = in ? xs[j] : kFarAway;
+        yj[u] = in ? ys[j] : kFarAway;
+        zj[u] = in ? zs[j] : kFarAway;
+        mj[u] = in ? ms[j] : 0.0;
       }
-      if (li[0] < 0) continue;
-      const int cn = min(kRStage, nc - c0);
-#pragma unroll 2
-      for (int j = lane; j < cn; j += 64) {
-        const double xj = sj[0][j], yj = sj[1][j], zj = sj[2][j], mj = sj[3][j];
+#pragma unroll
+      for (int u = 0; u < kRAhead; ++u) {
 #pragma unroll
         for (int k = 0; k < kRRow; ++k) {
-          const double dx = xj - xi[k], dy = yj - yi[k], dz = zj - zi[k];
+          const double dx = xj[u] - xi[k], dy = yj[u] - yi[k], dz = zj[u] - zi[k];
           const double r2 = fma(dz, dz, fma(dy, dy, fma(dx, dx, e2)));
           const double rr = rsqrt64(r2);
-          double sc = (mj * rr) * (rr * rr);
-          if (EXCL && c0 + j == li[k]) sc = 0.0;
-          sx[k] = fma(sc, dx, sx[k]);
-          sy[k] = fma(sc, dy, sy[k]);
-          sz[k] = fma(sc, dz, sz[k]);
+          double sc = (mj[u] * rr) * (rr * rr);
+          if (EXCL && j0 + kRBlock * u == li[k]) sc = 0.0;
+          sum[3 * k] = fma(sc, dx, sum[3 * k]);
+          sum[3 * k + 1] = fma(sc, dy, sum[3 * k + 1]);
+          sum[3 * k + 2] = fma(sc, dz, sum[3 * k + 2]);
         }
       }
     }
+    wave_sums(sum, red[wave]);
+    __syncthreads();
+    if (t < 3 * kRRow && r0 + t / 3 < nf) {  // lane t: row t / 3, component t % 3
+      double v = red[0][t];
 #pragma unroll
-    for (int k = 0; k < kRRow; ++k) {
-      for (int w = 32; w > 0; w >>= 1) {
-        sx[k] += __shfl_xor(sx[k], w, 64);
-        sy[k] += __shfl_xor(sy[k], w, 64);
-        sz[k] += __shfl_xor(sz[k], w, 64);
-      }
-      if (lane == 0 && li[k] >= 0) {
-        const int64_t i = o + li[k];
-        a[i] = G * sx[k];
-        a[total + i] = G * sy[k];
-        a[2 * total + i] = G * sz[k];
-      }
+      for (int w = 1; w < W; ++w) v += red[w][t];
+      a[(t % 3) * total + o + rlist[o + r0 + t / 3]] = G * v;
     }
+    __syncthreads();
   }
 }
 
@@ -1119,10 +1137,16 @@ int launch_ens_rescue(int32_t ncl, const int64_t* d_off, const double* d_eps, in
                       const double* m, double G, bool excl, const int* rcnt, const int* rlist, double* a,
                       hipStream_t s) {
   if (ncl <= 0) return NBODY_OK;
+  // some two rounds of resident workgroups, so that CUs which are done early take more
+  // of them (512 systems of 64 to 4096: 4, 7 and 16 a CU take 77, 71 and 69 us); with
+  // very many systems each workgroup's own prefix sum over them weighs more
+  const int64_t per_cu = ncl <= 8192 ? 16 : 4;
+  const unsigned grid = (unsigned)std::max<int64_t>(
+      kRXcds, std::min<int64_t>(total / kRRow + ncl, per_cu * cu_count(current_device())) / kRXcds * kRXcds);
   if (excl)
-    ens_rescue_kernel<true><<<dim3(ncl, kRSplit), 64 * kRWaves, 0, s>>>(d_off, d_eps, total, x, m, G, rcnt, rlist, a);
+    ens_rescue_kernel<true><<<grid, kRBlock, 0, s>>>(ncl, d_off, d_eps, total, x, m, G, rcnt, rlist, a);
   else
-    ens_rescue_kernel<false><<<dim3(ncl, kRSplit), 64 * kRWaves, 0, s>>>(d_off, d_eps, total, x, m, G, rcnt, rlist, a);
+    ens_rescue_kernel<false><<<grid, kRBlock, 0, s>>>(ncl, d_off, d_eps, total, x, m, G, rcnt, rlist, a);
   NB_LAUNCH_CHECK("ens_rescue_kernel");
   return NBODY_OK;
 }

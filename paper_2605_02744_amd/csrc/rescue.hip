@@ -40,30 +40,31 @@
 //
 // Here, for the force of one system: the flagged rows go to a list (an atomic
 // counter, one add per wave, orders them, which does not change any result:
-// every row is recomputed on its own, in a fixed order) and a grid-stride
-// kernel recomputes them in FP64.  The count of flagged rows is cleared by the
+// every row is recomputed on its own, in an order that depends only on how many
+// there are) and a grid-stride kernel recomputes them in FP64.  The count of flagged rows is cleared by the
 // first kernel of the evaluation (its block 0, thread 0), so that the flag
 // kernel starts from zero without a launch of its own.  The batched wave items
 // (ensemble_stream.hip) flag their rows in the force kernel, where each wave
 // holds whole rows, into per-system lists that their own rescue kernel reads.
 #include "pair_math.h"
+#include "wave64.h"
 
 namespace nb {
 namespace {
 
-constexpr int64_t kRSmall = 131072;  // systems up to this size take one row per workgroup pass
-
 // One thread per particle: sums the nslices slices of the estimate (stride
 // apart) and appends the row to the list if scale * sqrt(E_i) > |a_i|.  A
-// wave reserves the places of all its flagged rows with one atomic add.
-__global__ void flag_rows_kernel(int n, const float* __restrict__ est, int nslices, size_t stride,
-                                 const double* __restrict__ a, double scale, int* __restrict__ list,
-                                 int* __restrict__ count) {
+// wave reserves the places of all its flagged rows with one atomic add.  The first
+// nclear words of the estimate, once read, become the rescue's zeroed arrival counts
+// (word i is read by this thread alone).
+__global__ void flag_rows_kernel(int n, float* est, int nslices, size_t stride, const double* __restrict__ a,
+                                 double scale, int* __restrict__ list, int* __restrict__ count, int nclear) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   bool flag = false;
   if (i < n) {
     float e = 0.f;
     for (int k = 0; k < nslices; ++k) e += est[(size_t)k * stride + i];
+    if (i < nclear) est[i] = 0.f;
     const double ax = a[i], ay = a[n + i], az = a[2 * n + i];
     const double an = sqrt(ax * ax + ay * ay + az * az);
     flag = sqrt((double)e) * scale > an;
@@ -78,27 +79,42 @@ __global__ void flag_rows_kernel(int n, const float* __restrict__ est, int nslic
 }
 
 // Recomputes the listed rows of a = G sum_j m_j d / (|d|^2 + eps^2)^(3/2) in
-// FP64: each pass takes R rows of the list (8 for large systems, where each j
-// record then serves eight rows; 1 for small ones, where the few flagged rows
-// should run side by side), the B lanes split the j-range (lane t takes
-// j = t, t + B, ...), loading U records ahead of the arithmetic (the records
-// come from L2 or HBM, and few waves are resident when few rows are flagged),
-// and the lane sums are added in a fixed order: a butterfly inside each wave,
-// then the wave sums in wave order.
+// FP64.  A unit is a group of R listed rows (each j record serves them all) and one
+// of S equal runs of j: with few rows S is what fills the chip, up to runs of one
+// pass of a workgroup (B U records) and ucap units; with many it is 1.  Units of the
+// same run are neighbours, so the workgroups at work at one time read the same
+// records out of L2.  The B lanes split a unit's j (lane t takes t, t + B, ...),
+// loading U records ahead of the arithmetic, and the lane sums are added in a fixed
+// order: inside each wave in registers, then the wave sums in wave order.  With S > 1
+// the unit's sums go to part, and the workgroup whose arrival completes the group
+// (arrived counts them; no workgroup waits) adds the runs in a fixed order.
+//
+// Bound by FP64 issue where there are rows enough (21 issue slots a pair), by the
+// latency of the loads where there are few.  Against a group of rows per workgroup
+// over all j: 38 -> 15 us for the 21 rows of a Plummer sphere of 65536, 1.59 -> 1.27
+// ms for the 1367 of the two-component model of 2^20 (1.41 with groups of four).
 template <int R, int B, int U>
 __global__ __launch_bounds__(B) void rescue_rows_kernel(int n, const double* __restrict__ x,
                                                         const double* __restrict__ m, double eps, double G,
                                                         int excl, const int* __restrict__ list,
-                                                        const int* __restrict__ count, double* __restrict__ a) {
+                                                        const int* __restrict__ count, double* __restrict__ a,
+                                                        int* arrived, double* part, int ucap) {
   constexpr int W = B / 64;
-  __shared__ double red[3][R][W];
+  __shared__ double red[W][R * 3];
+  __shared__ int last;
   const int t = threadIdx.x;
   const int wave = t / 64, lane = t % 64;
   const int cnt = *count;
+  if (cnt == 0) return;
   const double e2 = eps * eps;
-  for (int r0 = blockIdx.x * R; r0 < cnt; r0 += gridDim.x * R) {
+  const int groups = (cnt + R - 1) / R;
+  const int S = max(1, min(ucap / groups, (n + B * U - 1) / (B * U)));
+  const int len = ((n + S - 1) / S + 63) / 64 * 64;
+  for (int unit = blockIdx.x; unit < groups * S; unit += gridDim.x) {
+    const int grp = unit % groups, r0 = grp * R;
+    const int jbeg = unit / groups * len, jend = min(n, jbeg + len);
     int row[R];
-    double xi[R], yi[R], zi[R], sx[R], sy[R], sz[R];
+    double xi[R], yi[R], zi[R], sum[3 * R];
 #pragma unroll
     for (int k = 0; k < R; ++k) {
       row[k] = r0 + k < cnt ? list[r0 + k] : -1;
@@ -106,16 +122,16 @@ __global__ __launch_bounds__(B) void rescue_rows_kernel(int n, const double* __r
       xi[k] = x[i];
       yi[k] = x[n + i];
       zi[k] = x[2 * n + i];
-      sx[k] = sy[k] = sz[k] = 0.0;
+      sum[3 * k] = sum[3 * k + 1] = sum[3 * k + 2] = 0.0;
     }
-    for (int j0 = t; j0 < n; j0 += U * B) {
-      // U records per lane, all loaded before any is used; past n: far away
+    for (int j0 = jbeg + t; j0 < jend; j0 += U * B) {
+      // U records per lane, all loaded before any is used; past the run: far away
       // and massless, so they add exact zeros
       double xj[U], yj[U], zj[U], mj[U];
 #pragma unroll
       for (int u = 0; u < U; ++u) {
         const int j = j0 + u * B;
-        const bool in = j < n;
+        const bool in = j < jend;
         xj[u] = in ? x[j] : 1.0e30;
         yj[u] = in ? x[n + j] : 1.0e30;
         zj[u] = in ? x[2 * n + j] : 1.0e30;
@@ -131,67 +147,73 @@ __global__ __launch_bounds__(B) void rescue_rows_kernel(int n, const double* __r
           const double ri = rsqrt64(r2);
           double s = (mj[u] * ri) * (ri * ri);
           if (excl && j == row[k]) s = 0.0;
-          sx[k] = fma(s, dx, sx[k]);
-          sy[k] = fma(s, dy, sy[k]);
-          sz[k] = fma(s, dz, sz[k]);
+          sum[3 * k] = fma(s, dx, sum[3 * k]);
+          sum[3 * k + 1] = fma(s, dy, sum[3 * k + 1]);
+          sum[3 * k + 2] = fma(s, dz, sum[3 * k + 2]);
         }
       }
     }
-#pragma unroll
-    for (int k = 0; k < R; ++k) {
-      for (int off = 32; off > 0; off >>= 1) {
-        sx[k] += __shfl_xor(sx[k], off, 64);
-        sy[k] += __shfl_xor(sy[k], off, 64);
-        sz[k] += __shfl_xor(sz[k], off, 64);
-      }
-      if (lane == 0) {
-        red[0][k][wave] = sx[k];
-        red[1][k][wave] = sy[k];
-        red[2][k][wave] = sz[k];
-      }
-    }
+    wave_sums(sum, red[wave]);
     __syncthreads();
-    if (t < R && row[t] >= 0) {
-      const int i = row[t];
-      double v[3];
+    // lane t < 3 R: row t / 3, component t % 3
+    double v = 0.0;
+    if (t < 3 * R) {
+      v = red[0][t];
 #pragma unroll
-      for (int c = 0; c < 3; ++c) {
-        v[c] = red[c][t][0];
-#pragma unroll
-        for (int w = 1; w < W; ++w) v[c] += red[c][t][w];
-      }
-      a[i] = G * v[0];
-      a[n + i] = G * v[1];
-      a[2 * n + i] = G * v[2];
+      for (int w = 1; w < W; ++w) v += red[w][t];
+      if (S > 1)
+        __hip_atomic_store(&part[(size_t)unit * 3 * R + t], v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
+    if (S > 1) {
+      __syncthreads();
+      if (t == 0)
+        last = __hip_atomic_fetch_add(&arrived[grp], 1, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) == S - 1;
+      __syncthreads();
+      if (last) {
+        // wave w adds the runs w, w + W, ..., then the waves' sums in wave order
+        if (lane < 3 * R) {
+          v = 0.0;
+          for (int q = wave; q < S; q += W) v += part[((size_t)q * groups + grp) * 3 * R + lane];
+          red[wave][lane] = v;
+        }
+        __syncthreads();
+        if (t < 3 * R) {
+          v = red[0][t];
+#pragma unroll
+          for (int w = 1; w < W; ++w) v += red[w][t];
+        }
+      }
+    }
+    if (t < 3 * R && r0 + t / 3 < cnt && (S == 1 || last)) a[(size_t)(t % 3) * n + list[r0 + t / 3]] = G * v;
     __syncthreads();
   }
 }
 
-// Launch shapes of the rescue, small systems (one row per pass) and large ones
-// (eight rows per pass): lanes per workgroup and records loaded ahead.
-constexpr int kRBSmall = 512, kRUSmall = 8;
-constexpr int kRBLarge = 1024, kRULarge = 4;
+// Rows of a group, lanes per workgroup and records loaded ahead.
+constexpr int kRRows = 8, kRLanes = 512, kRAhead = 2;
+// Units of a rescue with runs of j, at most; their counts and sums lie in the
+// estimate's own memory (n floats), which the flagging has read by then.
+constexpr int64_t kRUnits = 8192;
 
 }  // namespace
 
-int launch_rescue(int64_t n, const double* x, const double* m, double eps, double G, bool excl, const float* est,
+int launch_rescue(int64_t n, const double* x, const double* m, double eps, double G, bool excl, float* est,
                   int nslices, size_t stride, double* a, int* list, int* count, hipStream_t s) {
   if (n == 0) return NBODY_OK;
   const double scale = kRescueScale * std::fabs(G);
-  flag_rows_kernel<<<(unsigned)((n + 255) / 256), 256, 0, s>>>((int)n, est, nslices, stride, a, scale, list, count);
+  // a group has runs (S > 1) only if there are at most ucap / 2 groups
+  constexpr int64_t unit_bytes = 3 * kRRows * (int64_t)sizeof(double);
+  const int64_t ucap = n < 1024 ? 0 : std::min<int64_t>(kRUnits, n * (int64_t)sizeof(float) / (unit_bytes + 4));
+  const int64_t nclear = ucap / 2;
+  double* part = reinterpret_cast<double*>(est + (nclear + 1) / 2 * 2);
+  flag_rows_kernel<<<(unsigned)((n + 255) / 256), 256, 0, s>>>((int)n, est, nslices, stride, a, scale, list, count,
+                                                               (int)nclear);
   NB_LAUNCH_CHECK("flag_rows_kernel");
-  const int cus = cu_count(current_device());
-  // about as many workgroups as are resident at once; each strides over the list
-  if (n <= kRSmall) {
-    const unsigned grid = (unsigned)std::min<int64_t>(n, (2048 / kRBSmall) * (int64_t)cus);
-    rescue_rows_kernel<1, kRBSmall, kRUSmall><<<grid, kRBSmall, 0, s>>>((int)n, x, m, eps, G, excl ? 1 : 0, list,
-                                                                        count, a);
-  } else {
-    const unsigned grid = (unsigned)std::min<int64_t>((n + 7) / 8, (2048 / kRBLarge) * (int64_t)cus);
-    rescue_rows_kernel<8, kRBLarge, kRULarge><<<grid, kRBLarge, 0, s>>>((int)n, x, m, eps, G, excl ? 1 : 0, list,
-                                                                        count, a);
-  }
+  // about as many workgroups as are resident at once; each strides over the units
+  const unsigned grid = (unsigned)std::min<int64_t>((n + kRRows - 1) / kRRows + ucap, 2 * (int64_t)cu_count(current_device()));
+  rescue_rows_kernel<kRRows, kRLanes, kRAhead><<<grid, kRLanes, 0, s>>>((int)n, x, m, eps, G, excl ? 1 : 0, list, count,
+                                                                        a, reinterpret_cast<int*>(est), part,
+                                                                        (int)ucap);
   NB_LAUNCH_CHECK("rescue_rows_kernel");
   return NBODY_OK;
 }
