@@ -123,12 +123,8 @@ __device__ __forceinline__ void load_jset(const SymArgs& A, int g, int t, JSet& 
 // velocities rounded to FP32 (rw), and the lo parts with the repair radius^2
 // (-1 without the repair); padding past n far away, massless, at rest.
 template <bool NEAR>
-__global__ void jsym_stage_kernel(SymArgs A, float4* __restrict__ rhi, float4* __restrict__ rv,
-                                  float4* __restrict__ rlo) {
-  const int j = blockIdx.x * blockDim.x + threadIdx.x;
-  if (j >= A.npad) return;
+__device__ __forceinline__ void jsym_record(const SymArgs& A, int j, float4& hi, float4& vv, float4& lo) {
   const int n = A.n;
-  float4 hi, vv, lo;
   if (j < n) {
     const double xa = A.x[j], ya = A.x[n + j], za = A.x[2 * n + j];
     hi = make_float4((float)xa, (float)ya, (float)za, (float)A.m[j]);
@@ -140,9 +136,6 @@ __global__ void jsym_stage_kernel(SymArgs A, float4* __restrict__ rhi, float4* _
     vv = make_float4(0.f, 0.f, 0.f, 0.f);
     lo = make_float4(0.f, 0.f, 0.f, -1.f);
   }
-  rhi[j] = hi;
-  rv[j] = vv;
-  rlo[j] = lo;
 }
 
 // Near-field correction of one lane's tile (FP32C): every pair of the lane's two i
@@ -342,7 +335,8 @@ __global__ __launch_bounds__(kSL, 4) void jsym_kernel(SymArgs A) {
 // kDiagG groups of kSL lanes each a part of the slice; group 0 adds the
 // groups' hi + lo in group order into pd[slice][6][npad].
 template <bool NEAR>
-__global__ __launch_bounds__(kSL* kDiagG) void jsym_diag_kernel(SymArgs A, double* __restrict__ pd) {
+__global__ __launch_bounds__(kSL* kDiagG) void jsym_diag_kernel(
+    SymArgs A, float4* __restrict__ rhi, float4* __restrict__ rv, float4* __restrict__ rlo, double* __restrict__ pd) {
   __shared__ float4 s_hi[kSI];
   __shared__ float4 s_v[kSI];
   __shared__ float4 s_lo[kSI];
@@ -356,10 +350,17 @@ __global__ __launch_bounds__(kSL* kDiagG) void jsym_diag_kernel(SymArgs A, doubl
   float thr[2];
   load_jset<false>(A, g, t, s, thr);
   for (int k = threadIdx.x; k < kSI; k += kSL * kDiagG) {
-    const size_t j = (size_t)g * kSI + k;
-    s_hi[k] = A.rhi[j];
-    s_v[k] = A.rw[j];
-    s_lo[k] = A.rlo[j];
+    const int j = g * kSI + k;
+    float4 hi, vv, lo;
+    jsym_record<NEAR>(A, j, hi, vv, lo);
+    s_hi[k] = hi;
+    s_v[k] = vv;
+    s_lo[k] = lo;
+    if (blockIdx.y == 0) {
+      rhi[j] = hi;
+      rv[j] = vv;
+      rlo[j] = lo;
+    }
   }
   __syncthreads();
   float h[2][kJC], l[2][kJC];
@@ -469,7 +470,7 @@ int launch_sym_jerk(int64_t n, const double* x, const double* v, const double* m
   const int nparts = D * kSTiles / T;
   const int nchunks = dmax > 0 ? (dmax + D - 1) / D : 0;
   // with two half-ring chunks or more and the library's own workspace, the
-  // block-diagonal kernel and the slot sums run on the side stream, and the
+  // slot sums run on the side stream, and the
   // slots come twice (see sym_pairs.hip)
   std::unique_lock<std::mutex> side_lk;
   SideStream* side = nchunks >= 2 && !cfg.scratch ? acquire_side_stream(s, side_lk) : nullptr;
@@ -501,22 +502,14 @@ int launch_sym_jerk(int64_t n, const double* x, const double* v, const double* m
   A.rw = rv;
   A.rlo = rlo;
   const bool near = precision == kFP32C;
-  const unsigned sg = (unsigned)((npad + 255) / 256);
-  if (near) jsym_stage_kernel<true><<<sg, 256, 0, s>>>(A, rhi, rv, rlo);
-  else jsym_stage_kernel<false><<<sg, 256, 0, s>>>(A, rhi, rv, rlo);
-  NB_LAUNCH_CHECK("jsym_stage_kernel");
   // the own pair is always left out of the block-diagonal sums, so exclude_self needs no variant
   (void)excl;
   const dim3 dg((unsigned)nb, (unsigned)pds);
-  auto diag = [&](hipStream_t ds) -> int {
-    if (near) jsym_diag_kernel<true><<<dg, kSL * kDiagG, 0, ds>>>(A, pd);
-    else jsym_diag_kernel<false><<<dg, kSL * kDiagG, 0, ds>>>(A, pd);
-    NB_LAUNCH_CHECK("jsym_diag_kernel");
-    return NBODY_OK;
-  };
+  if (near) jsym_diag_kernel<true><<<dg, kSL * kDiagG, 0, s>>>(A, rhi, rv, rlo, pd);
+  else jsym_diag_kernel<false><<<dg, kSL * kDiagG, 0, s>>>(A, rhi, rv, rlo, pd);
+  NB_LAUNCH_CHECK("jsym_diag_kernel");
   const dim3 rg = sym_reduce_grid(n, kJC, false);
   if (dmax == 0) {
-    if ((st = diag(s))) return st;
     sym_reduce_kernel<kJC, float><<<rg, kRedP * kRedW, 0, s>>>((int)n, (int)npad, nb, dmax, half, 1, 0, 0, A.pj, A.pi, pd, a, jk, G,
                                               1, 1, nullptr, nullptr, nullptr, nullptr, pds);
     NB_LAUNCH_CHECK("sym_reduce_kernel");
@@ -541,7 +534,7 @@ int launch_sym_jerk(int64_t n, const double* x, const double* v, const double* m
     NB_LAUNCH_CHECK("sym_reduce_kernel");
     return NBODY_OK;
   };
-  return run_sym_chunks(side, s, nchunks, nbuf, diag, pair, sum);
+  return run_sym_chunks(side, s, nchunks, nbuf, pair, sum);
 }
 
 }  // namespace nb

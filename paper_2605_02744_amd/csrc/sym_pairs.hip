@@ -120,15 +120,11 @@ __device__ __forceinline__ void near_delta(float dx, float dy, float dz, float r
   fz = fmaf(qi3, ez, -(ri3 * dz));
 }
 
-// The j-records of all npad particles (padding past n: far away, massless,
-// never repaired), converted once per evaluation so that the force kernel's
-// tiles are plain 16-byte copies.
+// The j-record of a particle (padding past n: far away, massless, never repaired).
+// The block-diagonal kernel converts all npad of them once per evaluation, so that
+// the force kernel's tiles are plain 16-byte copies.
 template <bool NEAR>
-__global__ void sym_stage_kernel(SymArgs A, float4* __restrict__ rhi, float4* __restrict__ rlo, int* __restrict__ zc) {
-  const int j = blockIdx.x * blockDim.x + threadIdx.x;
-  if (zc && j == 0) *zc = 0;  // the rescue's count of flagged rows
-  if (j >= A.npad) return;
-  float4 hi, lo;
+__device__ __forceinline__ void sym_record(const SymArgs& A, int j, float4& hi, float4& lo) {
   const int n = A.n;
   if (j < n) {
     const double xa = A.x[j], ya = A.x[n + j], za = A.x[2 * n + j];
@@ -139,8 +135,6 @@ __global__ void sym_stage_kernel(SymArgs A, float4* __restrict__ rhi, float4* __
     hi = make_float4((float)kFarAway, (float)kFarAway, (float)kFarAway, 0.f);
     lo = make_float4(0.f, 0.f, 0.f, -1.f);
   }
-  rhi[j] = hi;
-  rlo[j] = lo;
 }
 
 struct P6 {
@@ -387,10 +381,13 @@ __global__ __launch_bounds__(kSL, 7) void sym_accel_kernel(SymArgs A) {
 // The gridDim.y workgroups of a block each take a slice of its j, and their
 // kDiagG groups of kSL lanes each a part of the slice (so that the launch has
 // several waves per SIMD); group 0 adds the groups' hi + lo in group order and
-// writes the slice's sums into pd[slice][3][npad] (ed[slice][npad]).
+// writes the slice's sums into pd[slice][3][npad] (ed[slice][npad]).  Every
+// workgroup converts its block's records for itself and slice 0's also writes them
+// for the pair kernels: a launch of its own for that took 5 us.
 template <bool NEAR, bool EXCL>
-__global__ __launch_bounds__(kSL* kDiagG) void sym_diag_kernel(SymArgs A, double* __restrict__ pd,
-                                                                float* __restrict__ ed) {
+__global__ __launch_bounds__(kSL* kDiagG) void sym_diag_kernel(SymArgs A, float4* __restrict__ rhi,
+                                                                float4* __restrict__ rlo, double* __restrict__ pd,
+                                                                float* __restrict__ ed, int* __restrict__ zc) {
   __shared__ float4 s_hi[kSI];
   __shared__ float4 s_lo[kSI];
   __shared__ double s_part[kDiagG - 1][3][kSI];
@@ -404,9 +401,17 @@ __global__ __launch_bounds__(kSL* kDiagG) void sym_diag_kernel(SymArgs A, double
   ISet s;
   float thr[2];
   load_iset<false>(A, g, t, s, thr);
+  if (zc && blockIdx.x + blockIdx.y == 0 && threadIdx.x == 0) *zc = 0;  // the rescue's count of flagged rows
   for (int k = threadIdx.x; k < kSI; k += kSL * kDiagG) {
-    s_hi[k] = A.rhi[(size_t)g * kSI + k];
-    s_lo[k] = A.rlo[(size_t)g * kSI + k];
+    const int j = g * kSI + k;
+    float4 hi, lo;
+    sym_record<NEAR>(A, j, hi, lo);
+    s_hi[k] = hi;
+    s_lo[k] = lo;
+    if (blockIdx.y == 0) {
+      rhi[j] = hi;
+      rlo[j] = lo;
+    }
   }
   __syncthreads();
   float hx[2] = {0.f, 0.f}, hy[2] = {0.f, 0.f}, hz[2] = {0.f, 0.f};
@@ -510,7 +515,7 @@ std::mutex g_side_mu;
 SideStream g_side[kSideDev];
 
 void destroy_side(SideStream& S) {
-  for (hipEvent_t* e : {&S.stage, &S.pair[0], &S.pair[1], &S.red[0], &S.red[1], &S.join})
+  for (hipEvent_t* e : {&S.pair[0], &S.pair[1], &S.red[0], &S.red[1], &S.join})
     if (*e) {
       (void)hipEventDestroy(*e);
       *e = nullptr;
@@ -530,7 +535,7 @@ SideStream* acquire_side_stream(hipStream_t s, std::unique_lock<std::mutex>& lk)
   hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
   bool ok = hipStreamIsCapturing(s, &cs) == hipSuccess && cs == hipStreamCaptureStatusNone &&
             hipStreamCreateWithFlags(&S.side, hipStreamNonBlocking) == hipSuccess;
-  for (hipEvent_t* e : {&S.stage, &S.pair[0], &S.pair[1], &S.red[0], &S.red[1], &S.join})
+  for (hipEvent_t* e : {&S.pair[0], &S.pair[1], &S.red[0], &S.red[1], &S.join})
     ok = ok && hipEventCreateWithFlags(e, hipEventDisableTiming) == hipSuccess;
   if (!ok) {
     (void)hipGetLastError();
@@ -583,7 +588,7 @@ int launch_sym_accel(int64_t n, const double* x, const double* m, double* a, dou
   const int nparts = D * kSTiles / T;
   const int nchunks = dmax > 0 ? (dmax + D - 1) / D : 0;
   // with two half-ring chunks or more and the library's own workspace, the
-  // block-diagonal kernel and the slot sums run on the side stream, and the
+  // slot sums run on the side stream, and the
   // slots come twice, so that a chunk's pair kernel need not wait for the
   // previous chunk's slot sum (with one chunk the cross-stream waits cost more
   // than the overlap gains: 15 us of a 0.15 ms evaluation at 16384)
@@ -626,25 +631,17 @@ int launch_sym_accel(int64_t n, const double* x, const double* m, double* a, dou
   float* eo = rescue ? reinterpret_cast<float*>(tail) : nullptr;
   float* ed = rescue ? eo + npad : nullptr;
   int* list = rescue ? reinterpret_cast<int*>(tail + eo_bytes) : nullptr;
-  const unsigned sg = (unsigned)((npad + 255) / 256);
-  if (near) sym_stage_kernel<true><<<sg, 256, 0, s>>>(A, rhi, rlo, list);
-  else sym_stage_kernel<false><<<sg, 256, 0, s>>>(A, rhi, rlo, list);
-  NB_LAUNCH_CHECK("sym_stage_kernel");
   const dim3 dg((unsigned)nb, (unsigned)pds);
-  auto diag = [&](hipStream_t ds) -> int {
-    if (near) {
-      if (excl) sym_diag_kernel<true, true><<<dg, kSL * kDiagG, 0, ds>>>(A, pd, ed);
-      else sym_diag_kernel<true, false><<<dg, kSL * kDiagG, 0, ds>>>(A, pd, ed);
-    } else {
-      if (excl) sym_diag_kernel<false, true><<<dg, kSL * kDiagG, 0, ds>>>(A, pd, ed);
-      else sym_diag_kernel<false, false><<<dg, kSL * kDiagG, 0, ds>>>(A, pd, ed);
-    }
-    NB_LAUNCH_CHECK("sym_diag_kernel");
-    return NBODY_OK;
-  };
+  if (near) {
+    if (excl) sym_diag_kernel<true, true><<<dg, kSL * kDiagG, 0, s>>>(A, rhi, rlo, pd, ed, list);
+    else sym_diag_kernel<true, false><<<dg, kSL * kDiagG, 0, s>>>(A, rhi, rlo, pd, ed, list);
+  } else {
+    if (excl) sym_diag_kernel<false, true><<<dg, kSL * kDiagG, 0, s>>>(A, rhi, rlo, pd, ed, list);
+    else sym_diag_kernel<false, false><<<dg, kSL * kDiagG, 0, s>>>(A, rhi, rlo, pd, ed, list);
+  }
+  NB_LAUNCH_CHECK("sym_diag_kernel");
   const dim3 rg = sym_reduce_grid(n, 3, rescue);
   if (dmax == 0) {
-    if ((st = diag(s))) return st;
     sym_reduce_kernel<3, float><<<rg, kRedP * kRedW, 0, s>>>((int)n, (int)npad, nb, dmax, half, 1, 0, 0, A.pj, A.pi, pd, a, nullptr, G,
                                             1, 1, A.pe, A.pw, ed, eo, pds);
     NB_LAUNCH_CHECK("sym_reduce_kernel");
@@ -668,7 +665,7 @@ int launch_sym_accel(int64_t n, const double* x, const double* m, double* a, dou
       NB_LAUNCH_CHECK("sym_reduce_kernel");
       return NBODY_OK;
     };
-    if ((st = run_sym_chunks(side, s, nchunks, nbuf, diag, pair, sum))) return st;
+    if ((st = run_sym_chunks(side, s, nchunks, nbuf, pair, sum))) return st;
   }
   if (rescue) return launch_rescue(n, x, m, eps, G, excl, eo, 1, (size_t)npad, a, list + 64, list, s);
   return NBODY_OK;

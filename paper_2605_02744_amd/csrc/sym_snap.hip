@@ -116,12 +116,8 @@ __device__ __forceinline__ void load_sset(const SymArgs& A, int g, int t, SSet& 
 // the repair radius^2 (-1 without the repair); padding past n far away,
 // massless, at rest.
 template <bool NEAR>
-__global__ void ssym_stage_kernel(SymArgs A, float4* __restrict__ rhi, float4* __restrict__ rv,
-                                  float4* __restrict__ ra, float4* __restrict__ rlo) {
-  const int j = blockIdx.x * blockDim.x + threadIdx.x;
-  if (j >= A.npad) return;
+__device__ __forceinline__ void ssym_record(const SymArgs& A, int j, float4& hi, float4& vv, float4& aa, float4& lo) {
   const int n = A.n;
-  float4 hi, vv, aa, lo;
   if (j < n) {
     const double xa = A.x[j], ya = A.x[n + j], za = A.x[2 * n + j];
     hi = make_float4((float)xa, (float)ya, (float)za, (float)A.m[j]);
@@ -134,10 +130,6 @@ __global__ void ssym_stage_kernel(SymArgs A, float4* __restrict__ rhi, float4* _
     vv = aa = make_float4(0.f, 0.f, 0.f, 0.f);
     lo = make_float4(0.f, 0.f, 0.f, -1.f);
   }
-  rhi[j] = hi;
-  rv[j] = vv;
-  ra[j] = aa;
-  rlo[j] = lo;
 }
 
 // Near-field correction of one lane's tile (FP32C): every pair of the lane's two i
@@ -348,7 +340,8 @@ __global__ __launch_bounds__(kSL, 3) void ssym_kernel(SymArgs A) {
 // kDiagG groups of kSL lanes each a part of the slice; group 0 adds the
 // groups' hi + lo in group order into pd[slice][9][npad].
 template <bool NEAR>
-__global__ __launch_bounds__(kSL* kDiagG) void ssym_diag_kernel(SymArgs A, double* __restrict__ pd) {
+__global__ __launch_bounds__(kSL* kDiagG) void ssym_diag_kernel(
+    SymArgs A, float4* __restrict__ rhi, float4* __restrict__ rv, float4* __restrict__ ra, float4* __restrict__ rlo, double* __restrict__ pd) {
   __shared__ float4 s_hi[kSI];
   __shared__ float4 s_v[kSI];
   __shared__ float4 s_a[kSI];
@@ -363,11 +356,19 @@ __global__ __launch_bounds__(kSL* kDiagG) void ssym_diag_kernel(SymArgs A, doubl
   float thr[2];
   load_sset<false>(A, g, t, s, thr);
   for (int k = threadIdx.x; k < kSI; k += kSL * kDiagG) {
-    const size_t j = (size_t)g * kSI + k;
-    s_hi[k] = A.rhi[j];
-    s_v[k] = A.rw[j];
-    s_a[k] = A.ru[j];
-    s_lo[k] = A.rlo[j];
+    const int j = g * kSI + k;
+    float4 hi, vv, aa, lo;
+    ssym_record<NEAR>(A, j, hi, vv, aa, lo);
+    s_hi[k] = hi;
+    s_v[k] = vv;
+    s_a[k] = aa;
+    s_lo[k] = lo;
+    if (blockIdx.y == 0) {
+      rhi[j] = hi;
+      rv[j] = vv;
+      ra[j] = aa;
+      rlo[j] = lo;
+    }
   }
   __syncthreads();
   float h[2][kSC], l[2][kSC];
@@ -475,7 +476,7 @@ int launch_sym_snap(int64_t n, const double* x, const double* v, const double* a
   const int nparts = D * kSTiles / T;
   const int nchunks = dmax > 0 ? (dmax + D - 1) / D : 0;
   // with two half-ring chunks or more and the library's own workspace, the
-  // block-diagonal kernel and the slot sums run on the side stream, and the
+  // slot sums run on the side stream, and the
   // slots come twice (see sym_pairs.hip)
   std::unique_lock<std::mutex> side_lk;
   SideStream* side = nchunks >= 2 && !cfg.scratch ? acquire_side_stream(s, side_lk) : nullptr;
@@ -509,22 +510,14 @@ int launch_sym_snap(int64_t n, const double* x, const double* v, const double* a
   A.ru = ra;
   A.rlo = rlo;
   const bool near = precision == kFP32C;
-  const unsigned sg = (unsigned)((npad + 255) / 256);
-  if (near) ssym_stage_kernel<true><<<sg, 256, 0, s>>>(A, rhi, rv, ra, rlo);
-  else ssym_stage_kernel<false><<<sg, 256, 0, s>>>(A, rhi, rv, ra, rlo);
-  NB_LAUNCH_CHECK("ssym_stage_kernel");
   // the own pair is always left out of the block-diagonal sums, so exclude_self needs no variant
   (void)excl;
   const dim3 dg((unsigned)nb, (unsigned)pds);
-  auto diag = [&](hipStream_t ds) -> int {
-    if (near) ssym_diag_kernel<true><<<dg, kSL * kDiagG, 0, ds>>>(A, pd);
-    else ssym_diag_kernel<false><<<dg, kSL * kDiagG, 0, ds>>>(A, pd);
-    NB_LAUNCH_CHECK("ssym_diag_kernel");
-    return NBODY_OK;
-  };
+  if (near) ssym_diag_kernel<true><<<dg, kSL * kDiagG, 0, s>>>(A, rhi, rv, ra, rlo, pd);
+  else ssym_diag_kernel<false><<<dg, kSL * kDiagG, 0, s>>>(A, rhi, rv, ra, rlo, pd);
+  NB_LAUNCH_CHECK("ssym_diag_kernel");
   const dim3 rg = sym_reduce_grid(n, kSC, false);
   if (dmax == 0) {
-    if ((st = diag(s))) return st;
     sym_reduce_kernel<kSC, float><<<rg, kRedP * kRedW, 0, s>>>((int)n, (int)npad, nb, dmax, half, 1, 0, 0, A.pj, A.pi, pd, a, jk, G,
                                               1, 1, nullptr, nullptr, nullptr, nullptr, pds, sn);
     NB_LAUNCH_CHECK("sym_reduce_kernel");
@@ -549,7 +542,7 @@ int launch_sym_snap(int64_t n, const double* x, const double* v, const double* a
     NB_LAUNCH_CHECK("sym_reduce_kernel");
     return NBODY_OK;
   };
-  return run_sym_chunks(side, s, nchunks, nbuf, diag, pair, sum);
+  return run_sym_chunks(side, s, nchunks, nbuf, pair, sum);
 }
 
 }  // namespace nb

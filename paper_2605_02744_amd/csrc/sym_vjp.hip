@@ -118,12 +118,8 @@ __device__ __forceinline__ void load_vset(const SymArgs& A, int g, int t, VSet& 
 }
 
 template <bool NEAR>
-__global__ void vsym_stage_kernel(SymArgs A, float4* __restrict__ rhi, float4* __restrict__ rw,
-                                  float4* __restrict__ rlo) {
-  const int j = blockIdx.x * blockDim.x + threadIdx.x;
-  if (j >= A.npad) return;
+__device__ __forceinline__ void vsym_record(const SymArgs& A, int j, float4& hi, float4& wv, float4& lo) {
   const int n = A.n;
-  float4 hi, wv, lo;
   if (j < n) {
     const double xa = A.x[j], ya = A.x[n + j], za = A.x[2 * n + j];
     hi = make_float4((float)xa, (float)ya, (float)za, (float)A.m[j]);
@@ -135,9 +131,6 @@ __global__ void vsym_stage_kernel(SymArgs A, float4* __restrict__ rhi, float4* _
     wv = make_float4(0.f, 0.f, 0.f, 0.f);
     lo = make_float4(0.f, 0.f, 0.f, -1.f);
   }
-  rhi[j] = hi;
-  rw[j] = wv;
-  rlo[j] = lo;
 }
 
 // Near-field correction of one lane's tile (FP32C): every pair of the lane's two k
@@ -331,7 +324,8 @@ __global__ __launch_bounds__(kSL, 6) void vsym_kernel(SymArgs A) {
 // of the slice; group 0 adds the groups' hi + lo in group order into
 // pd[slice][4][npad].
 template <bool NEAR>
-__global__ __launch_bounds__(kSL* kDiagG) void vsym_diag_kernel(SymArgs A, double* __restrict__ pd) {
+__global__ __launch_bounds__(kSL* kDiagG) void vsym_diag_kernel(
+    SymArgs A, float4* __restrict__ rhi, float4* __restrict__ rw, float4* __restrict__ rlo, double* __restrict__ pd) {
   __shared__ float4 s_hi[kSI];
   __shared__ float4 s_w[kSI];
   __shared__ float4 s_lo[kSI];
@@ -345,10 +339,17 @@ __global__ __launch_bounds__(kSL* kDiagG) void vsym_diag_kernel(SymArgs A, doubl
   float thr[2];
   load_vset<false>(A, g, t, s, thr);
   for (int k = threadIdx.x; k < kSI; k += kSL * kDiagG) {
-    const size_t j = (size_t)g * kSI + k;
-    s_hi[k] = A.rhi[j];
-    s_w[k] = A.rw[j];
-    s_lo[k] = A.rlo[j];
+    const int j = g * kSI + k;
+    float4 hi, wv, lo;
+    vsym_record<NEAR>(A, j, hi, wv, lo);
+    s_hi[k] = hi;
+    s_w[k] = wv;
+    s_lo[k] = lo;
+    if (blockIdx.y == 0) {
+      rhi[j] = hi;
+      rw[j] = wv;
+      rlo[j] = lo;
+    }
   }
   __syncthreads();
   float h[2][kVC], l[2][kVC];
@@ -453,7 +454,7 @@ int launch_sym_vjp(int64_t n, const double* x, const double* m, const double* w,
   const int nparts = D * kSTiles / T;
   const int nchunks = dmax > 0 ? (dmax + D - 1) / D : 0;
   // with two half-ring chunks or more and the library's own workspace, the
-  // block-diagonal kernel and the slot sums run on the side stream, and the
+  // slot sums run on the side stream, and the
   // slots come twice, so that a chunk's pair kernel need not wait for the
   // previous chunk's slot sum (with one chunk the cross-stream waits cost more
   // than the overlap gains: 15 us of a 0.15 ms evaluation at 16384)
@@ -487,22 +488,14 @@ int launch_sym_vjp(int64_t n, const double* x, const double* m, const double* w,
   A.rw = rw;
   A.rlo = rlo;
   const bool near = precision == kFP32C;
-  const unsigned sg = (unsigned)((npad + 255) / 256);
-  if (near) vsym_stage_kernel<true><<<sg, 256, 0, s>>>(A, rhi, rw, rlo);
-  else vsym_stage_kernel<false><<<sg, 256, 0, s>>>(A, rhi, rw, rlo);
-  NB_LAUNCH_CHECK("vsym_stage_kernel");
   // the own pair is always left out of the block-diagonal sums, so exclude_self needs no variant
   (void)excl;
   const dim3 dg((unsigned)nb, (unsigned)pds);
-  auto diag = [&](hipStream_t ds) -> int {
-    if (near) vsym_diag_kernel<true><<<dg, kSL * kDiagG, 0, ds>>>(A, pd);
-    else vsym_diag_kernel<false><<<dg, kSL * kDiagG, 0, ds>>>(A, pd);
-    NB_LAUNCH_CHECK("vsym_diag_kernel");
-    return NBODY_OK;
-  };
+  if (near) vsym_diag_kernel<true><<<dg, kSL * kDiagG, 0, s>>>(A, rhi, rw, rlo, pd);
+  else vsym_diag_kernel<false><<<dg, kSL * kDiagG, 0, s>>>(A, rhi, rw, rlo, pd);
+  NB_LAUNCH_CHECK("vsym_diag_kernel");
   const dim3 rg = sym_reduce_grid(n, kVC, false);
   if (dmax == 0) {
-    if ((st = diag(s))) return st;
     sym_reduce_kernel<kVC, float><<<rg, kRedP * kRedW, 0, s>>>((int)n, (int)npad, nb, dmax, half, 1, 0, 0, A.pj, A.pi, pd, gx, gm, G,
                                               1, 1, nullptr, nullptr, nullptr, nullptr, pds);
     NB_LAUNCH_CHECK("sym_reduce_kernel");
@@ -527,7 +520,7 @@ int launch_sym_vjp(int64_t n, const double* x, const double* m, const double* w,
     NB_LAUNCH_CHECK("sym_reduce_kernel");
     return NBODY_OK;
   };
-  return run_sym_chunks(side, s, nchunks, nbuf, diag, pair, sum);
+  return run_sym_chunks(side, s, nchunks, nbuf, pair, sum);
 }
 
 }  // namespace nb
