@@ -192,15 +192,15 @@ __global__ __launch_bounds__(kRedP * kRedW) void sym_reduce_kernel(
 
 }  // namespace
 
-// A second stream per device for the symmetric evaluations: their slot sums
-// run on it while the caller's stream runs the half ring's pair kernels (the
-// slot sums stream HBM, the pair kernels are bound by VALU issue), ordered by
-// events.  Created on first use
+// A second stream per device for the symmetric evaluations: their
+// block-diagonal kernel and their slot sums run on it while the caller's
+// stream runs the half ring's pair kernels (the slot sums stream HBM, the pair
+// kernels are bound by VALU issue), ordered by events.  Created on first use
 // outside stream capture (a captured call then records the fork and the join
 // into the graph) and kept until nbody_finalize.
 struct SideStream {
   hipStream_t side = nullptr;
-  hipEvent_t pair[2] = {nullptr, nullptr}, red[2] = {nullptr, nullptr}, join = nullptr;
+  hipEvent_t stage = nullptr, pair[2] = {nullptr, nullptr}, red[2] = {nullptr, nullptr}, join = nullptr;
 };
 
 // The current device's side stream, with lk (the side streams' mutex, which
@@ -208,17 +208,23 @@ struct SideStream {
 // unlocked, where there is none: the caller then runs on its own stream.
 SideStream* acquire_side_stream(hipStream_t s, std::unique_lock<std::mutex>& lk);
 
-// The launches of one symmetric evaluation after those that stage its records on s:
-// pair(c, b) launches the pair kernel of half-ring chunk c on s, writing slot set
-// b = c % nbuf, and sum(c, b, stream) that chunk's slot sum.  Without a side stream
-// everything runs on s in that order.  With one, the slot sums run on it, each after
-// its pair kernel; a pair kernel that reuses a slot set waits for the slot sum that
-// last read it, and s waits for the last slot sum before it goes on.
-template <class Pair, class Sum>
-int run_sym_chunks(SideStream* side, hipStream_t s, int nchunks, int nbuf, Pair pair, Sum sum) {
+// The launches of one symmetric evaluation (with a side stream, after its staging
+// kernel on s): diag(stream) launches the block-diagonal kernel, pair(c, b) the pair
+// kernel of half-ring chunk c on s, writing slot set b = c % nbuf, and sum(c, b,
+// stream) that chunk's slot sum.  Without a side stream everything runs on s in that
+// order.  With one, the diagonal kernel waits for the staging and the slot sums run
+// after it on the side stream, each after its pair kernel; a pair kernel that reuses a
+// slot set waits for the slot sum that last read it, and s waits for the last slot sum
+// before it goes on.
+template <class Diag, class Pair, class Sum>
+int run_sym_chunks(SideStream* side, hipStream_t s, int nchunks, int nbuf, Diag diag, Pair pair, Sum sum) {
   auto ok = [](hipError_t e, const char* what) { return e == hipSuccess ? NBODY_OK : hip_fail(e, what); };
   int st = NBODY_OK;
   const hipStream_t rs = side ? side->side : s;
+  if (side && ((st = ok(hipEventRecord(side->stage, s), "hipEventRecord")) ||
+               (st = ok(hipStreamWaitEvent(rs, side->stage, 0), "hipStreamWaitEvent"))))
+    return st;
+  if ((st = diag(rs))) return st;
   for (int c = 0; c < nchunks; ++c) {
     const int b = c % nbuf;
     if (side && c >= nbuf && (st = ok(hipStreamWaitEvent(s, side->red[b], 0), "hipStreamWaitEvent"))) return st;

@@ -431,7 +431,7 @@ int launch_sym64(int64_t n, const double* x, const double* m, const double* w, c
     return NBODY_OK;
   };
   if (dmax == 0) return (st = pair(0, 0)) ? st : sum(0, 0, s);
-  return run_sym_chunks(side, s, nchunks, nbuf, pair, sum);
+  return run_sym_chunks(side, s, nchunks, nbuf, [](hipStream_t) { return NBODY_OK; }, pair, sum);
 }
 
 }  // namespace

@@ -138,6 +138,19 @@ __device__ __forceinline__ void jsym_record(const SymArgs& A, int j, float4& hi,
   }
 }
 
+// All records by a launch of their own, where the block-diagonal kernel runs beside
+// the pair kernels (several half-ring chunks).
+template <bool NEAR>
+__global__ void jsym_stage_kernel(SymArgs A, float4* __restrict__ rhi, float4* __restrict__ rv, float4* __restrict__ rlo) {
+  const int j = blockIdx.x * blockDim.x + threadIdx.x;
+  if (j >= A.npad) return;
+  float4 hi, vv, lo;
+  jsym_record<NEAR>(A, j, hi, vv, lo);
+  rhi[j] = hi;
+  rv[j] = vv;
+  rlo[j] = lo;
+}
+
 // Near-field correction of one lane's tile (FP32C): every pair of the lane's two i
 // with the tile's 64 j closer than the larger repair radius of its two particles
 // gets (float-float term - rounded term) added, times m_j to the lane's i-side
@@ -356,7 +369,7 @@ __global__ __launch_bounds__(kSL* kDiagG) void jsym_diag_kernel(
     s_hi[k] = hi;
     s_v[k] = vv;
     s_lo[k] = lo;
-    if (blockIdx.y == 0) {
+    if (rhi && blockIdx.y == 0) {
       rhi[j] = hi;
       rv[j] = vv;
       rlo[j] = lo;
@@ -470,7 +483,7 @@ int launch_sym_jerk(int64_t n, const double* x, const double* v, const double* m
   const int nparts = D * kSTiles / T;
   const int nchunks = dmax > 0 ? (dmax + D - 1) / D : 0;
   // with two half-ring chunks or more and the library's own workspace, the
-  // slot sums run on the side stream, and the
+  // block-diagonal kernel and the slot sums run on the side stream, and the
   // slots come twice (see sym_pairs.hip)
   std::unique_lock<std::mutex> side_lk;
   SideStream* side = nchunks >= 2 && !cfg.scratch ? acquire_side_stream(s, side_lk) : nullptr;
@@ -504,12 +517,23 @@ int launch_sym_jerk(int64_t n, const double* x, const double* v, const double* m
   const bool near = precision == kFP32C;
   // the own pair is always left out of the block-diagonal sums, so exclude_self needs no variant
   (void)excl;
+  // beside the pair kernels the block-diagonal kernel cannot stage their records
+  if (side) {
+    const unsigned sg = (unsigned)((npad + 255) / 256);
+    if (near) jsym_stage_kernel<true><<<sg, 256, 0, s>>>(A, rhi, rv, rlo);
+    else jsym_stage_kernel<false><<<sg, 256, 0, s>>>(A, rhi, rv, rlo);
+    NB_LAUNCH_CHECK("jsym_stage_kernel");
+  }
   const dim3 dg((unsigned)nb, (unsigned)pds);
-  if (near) jsym_diag_kernel<true><<<dg, kSL * kDiagG, 0, s>>>(A, rhi, rv, rlo, pd);
-  else jsym_diag_kernel<false><<<dg, kSL * kDiagG, 0, s>>>(A, rhi, rv, rlo, pd);
-  NB_LAUNCH_CHECK("jsym_diag_kernel");
+  auto diag = [&](hipStream_t ds) -> int {
+    if (near) jsym_diag_kernel<true><<<dg, kSL * kDiagG, 0, ds>>>(A, side ? nullptr : rhi, rv, rlo, pd);
+    else jsym_diag_kernel<false><<<dg, kSL * kDiagG, 0, ds>>>(A, side ? nullptr : rhi, rv, rlo, pd);
+    NB_LAUNCH_CHECK("jsym_diag_kernel");
+    return NBODY_OK;
+  };
   const dim3 rg = sym_reduce_grid(n, kJC, false);
   if (dmax == 0) {
+    if ((st = diag(s))) return st;
     sym_reduce_kernel<kJC, float><<<rg, kRedP * kRedW, 0, s>>>((int)n, (int)npad, nb, dmax, half, 1, 0, 0, A.pj, A.pi, pd, a, jk, G,
                                               1, 1, nullptr, nullptr, nullptr, nullptr, pds);
     NB_LAUNCH_CHECK("sym_reduce_kernel");
@@ -534,7 +558,7 @@ int launch_sym_jerk(int64_t n, const double* x, const double* v, const double* m
     NB_LAUNCH_CHECK("sym_reduce_kernel");
     return NBODY_OK;
   };
-  return run_sym_chunks(side, s, nchunks, nbuf, pair, sum);
+  return run_sym_chunks(side, s, nchunks, nbuf, diag, pair, sum);
 }
 
 }  // namespace nb

@@ -137,6 +137,19 @@ __device__ __forceinline__ void sym_record(const SymArgs& A, int j, float4& hi, 
   }
 }
 
+// All records by a launch of their own, where the block-diagonal kernel runs beside
+// the pair kernels (several half-ring chunks).
+template <bool NEAR>
+__global__ void sym_stage_kernel(SymArgs A, float4* __restrict__ rhi, float4* __restrict__ rlo, int* __restrict__ zc) {
+  const int j = blockIdx.x * blockDim.x + threadIdx.x;
+  if (zc && j == 0) *zc = 0;  // the rescue's count of flagged rows
+  if (j >= A.npad) return;
+  float4 hi, lo;
+  sym_record<NEAR>(A, j, hi, lo);
+  rhi[j] = hi;
+  rlo[j] = lo;
+}
+
 struct P6 {
   float x0, x1, y0, y1, z0, z1;
 };
@@ -382,8 +395,8 @@ __global__ __launch_bounds__(kSL, 7) void sym_accel_kernel(SymArgs A) {
 // kDiagG groups of kSL lanes each a part of the slice (so that the launch has
 // several waves per SIMD); group 0 adds the groups' hi + lo in group order and
 // writes the slice's sums into pd[slice][3][npad] (ed[slice][npad]).  Every
-// workgroup converts its block's records for itself and slice 0's also writes them
-// for the pair kernels: a launch of its own for that took 5 us.
+// workgroup converts its block's records for itself and slice 0's, with rhi, also
+// writes them for the pair kernels: a launch of its own for that takes 5 us.
 template <bool NEAR, bool EXCL>
 __global__ __launch_bounds__(kSL* kDiagG) void sym_diag_kernel(SymArgs A, float4* __restrict__ rhi,
                                                                 float4* __restrict__ rlo, double* __restrict__ pd,
@@ -408,7 +421,7 @@ __global__ __launch_bounds__(kSL* kDiagG) void sym_diag_kernel(SymArgs A, float4
     sym_record<NEAR>(A, j, hi, lo);
     s_hi[k] = hi;
     s_lo[k] = lo;
-    if (blockIdx.y == 0) {
+    if (rhi && blockIdx.y == 0) {
       rhi[j] = hi;
       rlo[j] = lo;
     }
@@ -515,7 +528,7 @@ std::mutex g_side_mu;
 SideStream g_side[kSideDev];
 
 void destroy_side(SideStream& S) {
-  for (hipEvent_t* e : {&S.pair[0], &S.pair[1], &S.red[0], &S.red[1], &S.join})
+  for (hipEvent_t* e : {&S.stage, &S.pair[0], &S.pair[1], &S.red[0], &S.red[1], &S.join})
     if (*e) {
       (void)hipEventDestroy(*e);
       *e = nullptr;
@@ -535,7 +548,7 @@ SideStream* acquire_side_stream(hipStream_t s, std::unique_lock<std::mutex>& lk)
   hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
   bool ok = hipStreamIsCapturing(s, &cs) == hipSuccess && cs == hipStreamCaptureStatusNone &&
             hipStreamCreateWithFlags(&S.side, hipStreamNonBlocking) == hipSuccess;
-  for (hipEvent_t* e : {&S.pair[0], &S.pair[1], &S.red[0], &S.red[1], &S.join})
+  for (hipEvent_t* e : {&S.stage, &S.pair[0], &S.pair[1], &S.red[0], &S.red[1], &S.join})
     ok = ok && hipEventCreateWithFlags(e, hipEventDisableTiming) == hipSuccess;
   if (!ok) {
     (void)hipGetLastError();
@@ -588,7 +601,7 @@ int launch_sym_accel(int64_t n, const double* x, const double* m, double* a, dou
   const int nparts = D * kSTiles / T;
   const int nchunks = dmax > 0 ? (dmax + D - 1) / D : 0;
   // with two half-ring chunks or more and the library's own workspace, the
-  // slot sums run on the side stream, and the
+  // block-diagonal kernel and the slot sums run on the side stream, and the
   // slots come twice, so that a chunk's pair kernel need not wait for the
   // previous chunk's slot sum (with one chunk the cross-stream waits cost more
   // than the overlap gains: 15 us of a 0.15 ms evaluation at 16384)
@@ -631,17 +644,28 @@ int launch_sym_accel(int64_t n, const double* x, const double* m, double* a, dou
   float* eo = rescue ? reinterpret_cast<float*>(tail) : nullptr;
   float* ed = rescue ? eo + npad : nullptr;
   int* list = rescue ? reinterpret_cast<int*>(tail + eo_bytes) : nullptr;
-  const dim3 dg((unsigned)nb, (unsigned)pds);
-  if (near) {
-    if (excl) sym_diag_kernel<true, true><<<dg, kSL * kDiagG, 0, s>>>(A, rhi, rlo, pd, ed, list);
-    else sym_diag_kernel<true, false><<<dg, kSL * kDiagG, 0, s>>>(A, rhi, rlo, pd, ed, list);
-  } else {
-    if (excl) sym_diag_kernel<false, true><<<dg, kSL * kDiagG, 0, s>>>(A, rhi, rlo, pd, ed, list);
-    else sym_diag_kernel<false, false><<<dg, kSL * kDiagG, 0, s>>>(A, rhi, rlo, pd, ed, list);
+  // beside the pair kernels the block-diagonal kernel cannot stage their records
+  if (side) {
+    const unsigned sg = (unsigned)((npad + 255) / 256);
+    if (near) sym_stage_kernel<true><<<sg, 256, 0, s>>>(A, rhi, rlo, list);
+    else sym_stage_kernel<false><<<sg, 256, 0, s>>>(A, rhi, rlo, list);
+    NB_LAUNCH_CHECK("sym_stage_kernel");
   }
-  NB_LAUNCH_CHECK("sym_diag_kernel");
+  const dim3 dg((unsigned)nb, (unsigned)pds);
+  auto diag = [&](hipStream_t ds) -> int {
+    if (near) {
+      if (excl) sym_diag_kernel<true, true><<<dg, kSL * kDiagG, 0, ds>>>(A, side ? nullptr : rhi, rlo, pd, ed, side ? nullptr : list);
+      else sym_diag_kernel<true, false><<<dg, kSL * kDiagG, 0, ds>>>(A, side ? nullptr : rhi, rlo, pd, ed, side ? nullptr : list);
+    } else {
+      if (excl) sym_diag_kernel<false, true><<<dg, kSL * kDiagG, 0, ds>>>(A, side ? nullptr : rhi, rlo, pd, ed, side ? nullptr : list);
+      else sym_diag_kernel<false, false><<<dg, kSL * kDiagG, 0, ds>>>(A, side ? nullptr : rhi, rlo, pd, ed, side ? nullptr : list);
+    }
+    NB_LAUNCH_CHECK("sym_diag_kernel");
+    return NBODY_OK;
+  };
   const dim3 rg = sym_reduce_grid(n, 3, rescue);
   if (dmax == 0) {
+    if ((st = diag(s))) return st;
     sym_reduce_kernel<3, float><<<rg, kRedP * kRedW, 0, s>>>((int)n, (int)npad, nb, dmax, half, 1, 0, 0, A.pj, A.pi, pd, a, nullptr, G,
                                             1, 1, A.pe, A.pw, ed, eo, pds);
     NB_LAUNCH_CHECK("sym_reduce_kernel");
@@ -665,7 +689,7 @@ int launch_sym_accel(int64_t n, const double* x, const double* m, double* a, dou
       NB_LAUNCH_CHECK("sym_reduce_kernel");
       return NBODY_OK;
     };
-    if ((st = run_sym_chunks(side, s, nchunks, nbuf, pair, sum))) return st;
+    if ((st = run_sym_chunks(side, s, nchunks, nbuf, diag, pair, sum))) return st;
   }
   if (rescue) return launch_rescue(n, x, m, eps, G, excl, eo, 1, (size_t)npad, a, list + 64, list, s);
   return NBODY_OK;

@@ -132,6 +132,20 @@ __device__ __forceinline__ void ssym_record(const SymArgs& A, int j, float4& hi,
   }
 }
 
+// All records by a launch of their own, where the block-diagonal kernel runs beside
+// the pair kernels (several half-ring chunks).
+template <bool NEAR>
+__global__ void ssym_stage_kernel(SymArgs A, float4* __restrict__ rhi, float4* __restrict__ rv, float4* __restrict__ ra, float4* __restrict__ rlo) {
+  const int j = blockIdx.x * blockDim.x + threadIdx.x;
+  if (j >= A.npad) return;
+  float4 hi, vv, aa, lo;
+  ssym_record<NEAR>(A, j, hi, vv, aa, lo);
+  rhi[j] = hi;
+  rv[j] = vv;
+  ra[j] = aa;
+  rlo[j] = lo;
+}
+
 // Near-field correction of one lane's tile (FP32C): every pair of the lane's two i
 // with the tile's 64 j closer than the larger repair radius of its two particles
 // gets (float-float term - rounded term) added, times m_j to the lane's i-side
@@ -363,7 +377,7 @@ __global__ __launch_bounds__(kSL* kDiagG) void ssym_diag_kernel(
     s_v[k] = vv;
     s_a[k] = aa;
     s_lo[k] = lo;
-    if (blockIdx.y == 0) {
+    if (rhi && blockIdx.y == 0) {
       rhi[j] = hi;
       rv[j] = vv;
       ra[j] = aa;
@@ -476,7 +490,7 @@ int launch_sym_snap(int64_t n, const double* x, const double* v, const double* a
   const int nparts = D * kSTiles / T;
   const int nchunks = dmax > 0 ? (dmax + D - 1) / D : 0;
   // with two half-ring chunks or more and the library's own workspace, the
-  // slot sums run on the side stream, and the
+  // block-diagonal kernel and the slot sums run on the side stream, and the
   // slots come twice (see sym_pairs.hip)
   std::unique_lock<std::mutex> side_lk;
   SideStream* side = nchunks >= 2 && !cfg.scratch ? acquire_side_stream(s, side_lk) : nullptr;
@@ -512,12 +526,23 @@ int launch_sym_snap(int64_t n, const double* x, const double* v, const double* a
   const bool near = precision == kFP32C;
   // the own pair is always left out of the block-diagonal sums, so exclude_self needs no variant
   (void)excl;
+  // beside the pair kernels the block-diagonal kernel cannot stage their records
+  if (side) {
+    const unsigned sg = (unsigned)((npad + 255) / 256);
+    if (near) ssym_stage_kernel<true><<<sg, 256, 0, s>>>(A, rhi, rv, ra, rlo);
+    else ssym_stage_kernel<false><<<sg, 256, 0, s>>>(A, rhi, rv, ra, rlo);
+    NB_LAUNCH_CHECK("ssym_stage_kernel");
+  }
   const dim3 dg((unsigned)nb, (unsigned)pds);
-  if (near) ssym_diag_kernel<true><<<dg, kSL * kDiagG, 0, s>>>(A, rhi, rv, ra, rlo, pd);
-  else ssym_diag_kernel<false><<<dg, kSL * kDiagG, 0, s>>>(A, rhi, rv, ra, rlo, pd);
-  NB_LAUNCH_CHECK("ssym_diag_kernel");
+  auto diag = [&](hipStream_t ds) -> int {
+    if (near) ssym_diag_kernel<true><<<dg, kSL * kDiagG, 0, ds>>>(A, side ? nullptr : rhi, rv, ra, rlo, pd);
+    else ssym_diag_kernel<false><<<dg, kSL * kDiagG, 0, ds>>>(A, side ? nullptr : rhi, rv, ra, rlo, pd);
+    NB_LAUNCH_CHECK("ssym_diag_kernel");
+    return NBODY_OK;
+  };
   const dim3 rg = sym_reduce_grid(n, kSC, false);
   if (dmax == 0) {
+    if ((st = diag(s))) return st;
     sym_reduce_kernel<kSC, float><<<rg, kRedP * kRedW, 0, s>>>((int)n, (int)npad, nb, dmax, half, 1, 0, 0, A.pj, A.pi, pd, a, jk, G,
                                               1, 1, nullptr, nullptr, nullptr, nullptr, pds, sn);
     NB_LAUNCH_CHECK("sym_reduce_kernel");
@@ -542,7 +567,7 @@ int launch_sym_snap(int64_t n, const double* x, const double* v, const double* a
     NB_LAUNCH_CHECK("sym_reduce_kernel");
     return NBODY_OK;
   };
-  return run_sym_chunks(side, s, nchunks, nbuf, pair, sum);
+  return run_sym_chunks(side, s, nchunks, nbuf, diag, pair, sum);
 }
 
 }  // namespace nb

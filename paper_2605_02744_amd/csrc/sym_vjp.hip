@@ -133,6 +133,19 @@ __device__ __forceinline__ void vsym_record(const SymArgs& A, int j, float4& hi,
   }
 }
 
+// All records by a launch of their own, where the block-diagonal kernel runs beside
+// the pair kernels (several half-ring chunks).
+template <bool NEAR>
+__global__ void vsym_stage_kernel(SymArgs A, float4* __restrict__ rhi, float4* __restrict__ rw, float4* __restrict__ rlo) {
+  const int j = blockIdx.x * blockDim.x + threadIdx.x;
+  if (j >= A.npad) return;
+  float4 hi, wv, lo;
+  vsym_record<NEAR>(A, j, hi, wv, lo);
+  rhi[j] = hi;
+  rw[j] = wv;
+  rlo[j] = lo;
+}
+
 // Near-field correction of one lane's tile (FP32C): every pair of the lane's two k
 // with the tile's 64 j closer than the larger repair radius of its two particles
 // gets (float-float term - rounded term) added, to the lane's k-side sums p and to
@@ -345,7 +358,7 @@ __global__ __launch_bounds__(kSL* kDiagG) void vsym_diag_kernel(
     s_hi[k] = hi;
     s_w[k] = wv;
     s_lo[k] = lo;
-    if (blockIdx.y == 0) {
+    if (rhi && blockIdx.y == 0) {
       rhi[j] = hi;
       rw[j] = wv;
       rlo[j] = lo;
@@ -454,7 +467,7 @@ int launch_sym_vjp(int64_t n, const double* x, const double* m, const double* w,
   const int nparts = D * kSTiles / T;
   const int nchunks = dmax > 0 ? (dmax + D - 1) / D : 0;
   // with two half-ring chunks or more and the library's own workspace, the
-  // slot sums run on the side stream, and the
+  // block-diagonal kernel and the slot sums run on the side stream, and the
   // slots come twice, so that a chunk's pair kernel need not wait for the
   // previous chunk's slot sum (with one chunk the cross-stream waits cost more
   // than the overlap gains: 15 us of a 0.15 ms evaluation at 16384)
@@ -490,12 +503,23 @@ int launch_sym_vjp(int64_t n, const double* x, const double* m, const double* w,
   const bool near = precision == kFP32C;
   // the own pair is always left out of the block-diagonal sums, so exclude_self needs no variant
   (void)excl;
+  // beside the pair kernels the block-diagonal kernel cannot stage their records
+  if (side) {
+    const unsigned sg = (unsigned)((npad + 255) / 256);
+    if (near) vsym_stage_kernel<true><<<sg, 256, 0, s>>>(A, rhi, rw, rlo);
+    else vsym_stage_kernel<false><<<sg, 256, 0, s>>>(A, rhi, rw, rlo);
+    NB_LAUNCH_CHECK("vsym_stage_kernel");
+  }
   const dim3 dg((unsigned)nb, (unsigned)pds);
-  if (near) vsym_diag_kernel<true><<<dg, kSL * kDiagG, 0, s>>>(A, rhi, rw, rlo, pd);
-  else vsym_diag_kernel<false><<<dg, kSL * kDiagG, 0, s>>>(A, rhi, rw, rlo, pd);
-  NB_LAUNCH_CHECK("vsym_diag_kernel");
+  auto diag = [&](hipStream_t ds) -> int {
+    if (near) vsym_diag_kernel<true><<<dg, kSL * kDiagG, 0, ds>>>(A, side ? nullptr : rhi, rw, rlo, pd);
+    else vsym_diag_kernel<false><<<dg, kSL * kDiagG, 0, ds>>>(A, side ? nullptr : rhi, rw, rlo, pd);
+    NB_LAUNCH_CHECK("vsym_diag_kernel");
+    return NBODY_OK;
+  };
   const dim3 rg = sym_reduce_grid(n, kVC, false);
   if (dmax == 0) {
+    if ((st = diag(s))) return st;
     sym_reduce_kernel<kVC, float><<<rg, kRedP * kRedW, 0, s>>>((int)n, (int)npad, nb, dmax, half, 1, 0, 0, A.pj, A.pi, pd, gx, gm, G,
                                               1, 1, nullptr, nullptr, nullptr, nullptr, pds);
     NB_LAUNCH_CHECK("sym_reduce_kernel");
@@ -520,7 +544,7 @@ int launch_sym_vjp(int64_t n, const double* x, const double* m, const double* w,
     NB_LAUNCH_CHECK("sym_reduce_kernel");
     return NBODY_OK;
   };
-  return run_sym_chunks(side, s, nchunks, nbuf, pair, sum);
+  return run_sym_chunks(side, s, nchunks, nbuf, diag, pair, sum);
 }
 
 }  // namespace nb
