@@ -91,6 +91,13 @@ __device__ __forceinline__ float sym_rc2(double xa, double ya, double za, double
   return dc * dc + (float)(eps * eps);
 }
 
+// The same from the position rounded to FP32 (the largest coordinate rounds to the
+// largest rounded one, so the results agree), without a load of the FP64 one.
+__device__ __forceinline__ float sym_rc2f(float xh, float yh, float zh, double eps, float f) {
+  const float dc = fmaxf(f * fmaxf(fabsf(xh), fmaxf(fabsf(yh), fabsf(zh))), kNearEps * (float)eps);
+  return dc * dc + (float)(eps * eps);
+}
+
 using lds_ptr = __attribute__((address_space(3))) void*;
 
 // add(q[k stride]) for k in [k, end), kRedU loads in flight.

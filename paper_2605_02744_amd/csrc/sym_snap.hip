@@ -166,7 +166,7 @@ __device__ __forceinline__ void ssym_repair(const SymArgs& A, int g, int t, int 
 #pragma unroll
   for (int u = 0; u < 2; ++u) {
     const int i = g * kSI + u * kSL + t;
-    rc[u] = i < n ? sym_rc2(A.x[i], A.x[n + i], A.x[2 * n + i], A.eps, A.fx) : -1.f;
+    rc[u] = i < n ? sym_rc2f(s.x[u], s.y[u], s.z[u], A.eps, A.fx) : -1.f;
   }
   for (int jj = 0; jj < kST; ++jj) {
     const int q = jj / kSR;
