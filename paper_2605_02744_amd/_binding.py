@@ -111,9 +111,9 @@ def _ptr(t, name, shape=None, dtype=torch.float64):
         raise TypeError("%s must be %s, got %s" % (name, dtype, t.dtype))
     if not t.is_contiguous():
         raise ValueError("%s must be contiguous" % name)
-    if shape is not None and tuple(t.shape) != tuple(shape):
+    if shape is not None and t.shape != shape:
         raise ValueError("%s must have shape %s, got %s" % (name, tuple(shape), tuple(t.shape)))
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
 def _params(G, eps, precision, flags):
@@ -127,8 +127,19 @@ def _flags(exclude_self=False, check_finite=False, acc_valid=False):
             | (NBODY_ACC_VALID if acc_valid else 0))
 
 
-def _stream(dev):
-    return ctypes.c_void_p(torch.cuda.current_stream(dev).cuda_stream)
+def _run(f, dev, *args):
+    """f(*args, dev's current stream) with dev current; raises on a non-zero status.
+    The device is switched only where another one is current, and the stream is asked
+    for as the raw handle: a Stream object and a device context cost 3 of the 10 us of
+    a small evaluation, which takes the GPU less than that."""
+    i = dev.index
+    if i is None or i != torch.cuda.current_device():
+        with torch.cuda.device(dev):
+            status = f(*args, torch._C._cuda_getCurrentRawStream(torch.cuda.current_device()))
+    else:
+        status = f(*args, torch._C._cuda_getCurrentRawStream(i))
+    if status != NBODY_OK:
+        _check(status)
 
 
 def nbody_accel(x, m, *, G=1.0, eps, precision="fp32c", exclude_self=False, check_finite=False, out=None):
@@ -138,9 +149,8 @@ def nbody_accel(x, m, *, G=1.0, eps, precision="fp32c", exclude_self=False, chec
     if out is None:
         out = torch.empty((3, n), dtype=torch.float64, device=x.device)
     p = _params(G, eps, precision, _flags(exclude_self, check_finite))
-    with torch.cuda.device(x.device):
-        _check(lib.nbody_accel(n, _ptr(x, "x", (3, n)), _ptr(m, "m", (n,)), _ptr(out, "a", (3, n)),
-                               ctypes.byref(p), _stream(x.device)))
+    _run(lib.nbody_accel, x.device, n, _ptr(x, "x", (3, n)), _ptr(m, "m", (n,)), _ptr(out, "a", (3, n)),
+         ctypes.byref(p))
     return out
 
 
@@ -153,9 +163,8 @@ def nbody_accel_noalloc(x, m, *, G=1.0, eps, precision="fp32c", exclude_self=Fal
     if out is None:
         out = torch.empty((3, n), dtype=torch.float64, device=x.device)
     p = _params(G, eps, precision, _flags(exclude_self))
-    with torch.cuda.device(x.device):
-        _check(lib.nbody_accel_noalloc(n, _ptr(x, "x", (3, n)), _ptr(m, "m", (n,)), _ptr(out, "a", (3, n)),
-                                       ctypes.byref(p), _stream(x.device)))
+    _run(lib.nbody_accel_noalloc, x.device, n, _ptr(x, "x", (3, n)), _ptr(m, "m", (n,)), _ptr(out, "a", (3, n)),
+         ctypes.byref(p))
     return out
 
 
@@ -165,9 +174,8 @@ def nbody_step(x, v, a, m, dt, nsteps, *, G=1.0, eps, precision="fp32c", acc_val
     lib = load()
     n = m.shape[0]
     p = _params(G, eps, precision, _flags(exclude_self, check_finite, acc_valid))
-    with torch.cuda.device(x.device):
-        _check(lib.nbody_step(n, _ptr(x, "x", (3, n)), _ptr(v, "v", (3, n)), _ptr(a, "a", (3, n)),
-                              _ptr(m, "m", (n,)), float(dt), int(nsteps), ctypes.byref(p), _stream(x.device)))
+    _run(lib.nbody_step, x.device, n, _ptr(x, "x", (3, n)), _ptr(v, "v", (3, n)), _ptr(a, "a", (3, n)),
+         _ptr(m, "m", (n,)), float(dt), int(nsteps), ctypes.byref(p))
     return x, v, a
 
 
@@ -181,9 +189,8 @@ def nbody_energy(x, v, m, *, G=1.0, eps, check_finite=False, out=None):
     if out is None:
         out = torch.empty(9, dtype=torch.float64, device=x.device)
     p = _params(G, eps, NBODY_FP64, _flags(False, check_finite))
-    with torch.cuda.device(x.device):
-        _check(lib.nbody_energy(n, _ptr(x, "x", (3, n)), _ptr(v, "v", (3, n)), _ptr(m, "m", (n,)),
-                                ctypes.byref(p), _ptr(out, "out9", (9,)), _stream(x.device)))
+    _run(lib.nbody_energy, x.device, n, _ptr(x, "x", (3, n)), _ptr(v, "v", (3, n)), _ptr(m, "m", (n,)),
+         ctypes.byref(p), _ptr(out, "out9", (9,)))
     return out
 
 
@@ -194,10 +201,8 @@ def nbody_accel_vjp(x, m, w, *, G=1.0, eps, precision="fp32c", exclude_self=Fals
     gx = torch.empty((3, n), dtype=torch.float64, device=x.device)
     gm = torch.empty(n, dtype=torch.float64, device=x.device)
     p = _params(G, eps, precision, _flags(exclude_self, check_finite))
-    with torch.cuda.device(x.device):
-        _check(lib.nbody_accel_vjp(n, _ptr(x, "x", (3, n)), _ptr(m, "m", (n,)), _ptr(w, "w", (3, n)),
-                                   _ptr(gx, "gx", (3, n)), _ptr(gm, "gm", (n,)), ctypes.byref(p),
-                                   _stream(x.device)))
+    _run(lib.nbody_accel_vjp, x.device, n, _ptr(x, "x", (3, n)), _ptr(m, "m", (n,)), _ptr(w, "w", (3, n)),
+         _ptr(gx, "gx", (3, n)), _ptr(gm, "gm", (n,)), ctypes.byref(p))
     return gx, gm
 
 
@@ -212,12 +217,9 @@ def nbody_traj_grad(ckpt_x, ckpt_v, every, nsteps, m, dt, gxT, gvT, *, G=1.0, ep
     gv0 = torch.empty((3, n), dtype=torch.float64, device=m.device)
     gm = torch.empty(n, dtype=torch.float64, device=m.device)
     p = _params(G, eps, precision, _flags(exclude_self, check_finite))
-    with torch.cuda.device(m.device):
-        _check(lib.nbody_traj_grad(n, _ptr(ckpt_x, "ckpt_x", (nck, 3, n)), _ptr(ckpt_v, "ckpt_v", (nck, 3, n)),
-                                   int(every), int(nsteps), _ptr(m, "m", (n,)), float(dt),
-                                   _ptr(gxT, "gxT", (3, n)), _ptr(gvT, "gvT", (3, n)), _ptr(gx0, "gx0", (3, n)),
-                                   _ptr(gv0, "gv0", (3, n)), _ptr(gm, "gm", (n,)), ctypes.byref(p),
-                                   _stream(m.device)))
+    _run(lib.nbody_traj_grad, m.device, n, _ptr(ckpt_x, "ckpt_x", (nck, 3, n)), _ptr(ckpt_v, "ckpt_v", (nck, 3, n)),
+         int(every), int(nsteps), _ptr(m, "m", (n,)), float(dt), _ptr(gxT, "gxT", (3, n)), _ptr(gvT, "gvT", (3, n)),
+         _ptr(gx0, "gx0", (3, n)), _ptr(gv0, "gv0", (3, n)), _ptr(gm, "gm", (n,)), ctypes.byref(p))
     return gx0, gv0, gm
 
 
@@ -234,12 +236,9 @@ def nbody_step_batched(off, eps, x, v, a, m, dt, nsteps, *, G=1.0, precision="fp
         raise ValueError("off must have ncl + 1 entries")
     total = int(off_h[-1])
     p = _params(G, 0.0, precision, _flags(exclude_self, check_finite, acc_valid))
-    with torch.cuda.device(x.device):
-        _check(lib.nbody_step_batched(ncl, off_h.ctypes.data_as(ctypes.POINTER(ctypes.c_int64)),
-                                      eps_h.ctypes.data_as(ctypes.POINTER(ctypes.c_double)),
-                                      _ptr(x, "x", (3, total)), _ptr(v, "v", (3, total)), _ptr(a, "a", (3, total)),
-                                      _ptr(m, "m", (total,)), float(dt), int(nsteps), ctypes.byref(p),
-                                      _stream(x.device)))
+    _run(lib.nbody_step_batched, x.device, ncl, off_h.ctypes.data_as(ctypes.POINTER(ctypes.c_int64)),
+         eps_h.ctypes.data_as(ctypes.POINTER(ctypes.c_double)), _ptr(x, "x", (3, total)), _ptr(v, "v", (3, total)),
+         _ptr(a, "a", (3, total)), _ptr(m, "m", (total,)), float(dt), int(nsteps), ctypes.byref(p))
     return x, v, a
 
 
@@ -279,9 +278,8 @@ def nbody_accel_jerk(x, v, m, *, G=1.0, eps, precision="fp32c", exclude_self=Fal
     a = torch.empty((3, n), dtype=torch.float64, device=x.device)
     jk = torch.empty((3, n), dtype=torch.float64, device=x.device)
     p = _params(G, eps, precision, _flags(exclude_self, check_finite))
-    with torch.cuda.device(x.device):
-        _check(lib.nbody_accel_jerk(n, _ptr(x, "x", (3, n)), _ptr(v, "v", (3, n)), _ptr(m, "m", (n,)),
-                                    _ptr(a, "a", (3, n)), _ptr(jk, "jk", (3, n)), ctypes.byref(p), _stream(x.device)))
+    _run(lib.nbody_accel_jerk, x.device, n, _ptr(x, "x", (3, n)), _ptr(v, "v", (3, n)), _ptr(m, "m", (n,)),
+         _ptr(a, "a", (3, n)), _ptr(jk, "jk", (3, n)), ctypes.byref(p))
     return a, jk
 
 
@@ -291,10 +289,8 @@ def nbody_step_hermite(x, v, a, jk, m, dt, nsteps, *, G=1.0, eps, precision="fp3
     lib = load()
     n = m.shape[0]
     p = _params(G, eps, precision, _flags(exclude_self, check_finite, acc_valid))
-    with torch.cuda.device(x.device):
-        _check(lib.nbody_step_hermite(n, _ptr(x, "x", (3, n)), _ptr(v, "v", (3, n)), _ptr(a, "a", (3, n)),
-                                      _ptr(jk, "jk", (3, n)), _ptr(m, "m", (n,)), float(dt), int(nsteps),
-                                      ctypes.byref(p), _stream(x.device)))
+    _run(lib.nbody_step_hermite, x.device, n, _ptr(x, "x", (3, n)), _ptr(v, "v", (3, n)), _ptr(a, "a", (3, n)),
+         _ptr(jk, "jk", (3, n)), _ptr(m, "m", (n,)), float(dt), int(nsteps), ctypes.byref(p))
     return x, v, a, jk
 
 
@@ -305,9 +301,8 @@ def nbody_potential(x, m, *, G=1.0, eps, check_finite=False, out=None):
     if out is None:
         out = torch.empty(n, dtype=torch.float64, device=x.device)
     p = _params(G, eps, NBODY_FP64, _flags(False, check_finite))
-    with torch.cuda.device(x.device):
-        _check(lib.nbody_potential(n, _ptr(x, "x", (3, n)), _ptr(m, "m", (n,)), _ptr(out, "phi", (n,)),
-                                   ctypes.byref(p), _stream(x.device)))
+    _run(lib.nbody_potential, x.device, n, _ptr(x, "x", (3, n)), _ptr(m, "m", (n,)), _ptr(out, "phi", (n,)),
+         ctypes.byref(p))
     return out
 
 
@@ -317,10 +312,8 @@ def nbody_accel_jerk_snap(x, v, acc, m, *, G=1.0, eps, precision="fp32c", exclud
     n = m.shape[0]
     a, jk, sn = (torch.empty((3, n), dtype=torch.float64, device=x.device) for _ in range(3))
     p = _params(G, eps, precision, _flags(exclude_self, check_finite))
-    with torch.cuda.device(x.device):
-        _check(lib.nbody_accel_jerk_snap(n, _ptr(x, "x", (3, n)), _ptr(v, "v", (3, n)), _ptr(acc, "acc", (3, n)),
-                                         _ptr(m, "m", (n,)), _ptr(a, "a", (3, n)), _ptr(jk, "jk", (3, n)),
-                                         _ptr(sn, "sn", (3, n)), ctypes.byref(p), _stream(x.device)))
+    _run(lib.nbody_accel_jerk_snap, x.device, n, _ptr(x, "x", (3, n)), _ptr(v, "v", (3, n)), _ptr(acc, "acc", (3, n)),
+         _ptr(m, "m", (n,)), _ptr(a, "a", (3, n)), _ptr(jk, "jk", (3, n)), _ptr(sn, "sn", (3, n)), ctypes.byref(p))
     return a, jk, sn
 
 
@@ -330,11 +323,9 @@ def nbody_step_hermite6(x, v, a, jk, sn, cr, m, dt, nsteps, *, G=1.0, eps, preci
     lib = load()
     n = m.shape[0]
     p = _params(G, eps, precision, _flags(exclude_self, check_finite, acc_valid))
-    with torch.cuda.device(x.device):
-        _check(lib.nbody_step_hermite6(n, _ptr(x, "x", (3, n)), _ptr(v, "v", (3, n)), _ptr(a, "a", (3, n)),
-                                       _ptr(jk, "jk", (3, n)), _ptr(sn, "sn", (3, n)), _ptr(cr, "cr", (3, n)),
-                                       _ptr(m, "m", (n,)), float(dt), int(nsteps), ctypes.byref(p),
-                                       _stream(x.device)))
+    _run(lib.nbody_step_hermite6, x.device, n, _ptr(x, "x", (3, n)), _ptr(v, "v", (3, n)), _ptr(a, "a", (3, n)),
+         _ptr(jk, "jk", (3, n)), _ptr(sn, "sn", (3, n)), _ptr(cr, "cr", (3, n)), _ptr(m, "m", (n,)), float(dt),
+         int(nsteps), ctypes.byref(p))
 
 
 def nbody_set_config(ipl=0, split=0, bsplit=0, bpass=0, bitem=0, pairs=0, rescue=0, sweep=0):
