@@ -118,9 +118,24 @@ int launch_accel(int64_t n, const double* x, const double* m, double* a, double 
 int launch_sym_accel(int64_t n, const double* x, const double* m, double* a, double G, double eps, int precision,
                      bool exclude_self, const PairConfig& cfg, hipStream_t s);
 
-// The same accelerations in FP64 from the symmetric FP64 kernel.
+// The same accelerations in FP64 from the symmetric FP64 kernel (with step, as part of
+// a KDK step).
+// The rest of a KDK step, done by the kernel that adds the evaluation's slots: nk kicks
+// v = fma(h, a, v), then with drift x = fma(dt, v, x), in place, and into xt if given.
+// The drift also writes the new positions' records where the next evaluation of the same
+// run looks for them: staged, set by the evaluation, is the number of slot sets that
+// their place follows from (0: no records yet).
+struct Sym64Kdk {
+  double* x;
+  double* v;
+  double h, dt;
+  int nk;
+  bool drift;
+  double* xt;
+  int staged;
+};
 int launch_sym_accel64(int64_t n, const double* x, const double* m, double* a, double G, double eps,
-                       bool exclude_self, const PairConfig& cfg, hipStream_t s);
+                       bool exclude_self, const PairConfig& cfg, hipStream_t s, Sym64Kdk* step = nullptr);
 
 // Acceleration and jerk (Algorithm 3) from the symmetric kernel: each
 // unordered pair once, both particles' terms (FP32C or FP32; launches as above).

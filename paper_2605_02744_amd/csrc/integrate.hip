@@ -268,10 +268,35 @@ static int run_kdk_rows(int64_t n, double* x, double* v, double* a, const double
   return NBODY_OK;
 }
 
+// The KDK loop on the symmetric FP64 force: the evaluation's last kernel kicks, drifts
+// and writes the next evaluation's records, so a step is two launches.
+static int run_kdk_sym64(int64_t n, double* x, double* v, double* a, const double* m, double dt, int64_t nsteps, double G,
+                         double eps, bool excl, bool acc_valid, const PairConfig& cfg, hipStream_t s, double* traj) {
+  const int64_t n3 = 3 * n;
+  auto slot = [&](int64_t k) -> double* { return traj ? traj + (size_t)k * n3 : nullptr; };
+  Sym64Kdk t{x, v, 0.5 * dt, dt, 1, true, slot(1), 0};
+  int st;
+  if (!acc_valid) {
+    if ((st = launch_sym_accel64(n, x, m, a, G, eps, excl, cfg, s, &t))) return st;
+  } else {
+    if ((st = launch_kick_drift(n3, x, x, v, a, t.h, dt, 1, s))) return st;
+    if (traj && (st = launch_copy(n3, x, slot(1), s))) return st;
+  }
+  for (int64_t k = 1; k <= nsteps; ++k) {
+    t.drift = k < nsteps;
+    t.nk = t.drift ? 2 : 1;
+    t.xt = t.drift ? slot(k + 1) : nullptr;
+    if ((st = launch_sym_accel64(n, x, m, a, G, eps, excl, cfg, s, &t))) return st;
+  }
+  return NBODY_OK;
+}
+
 int run_kdk(int64_t n, double* x, double* v, double* a, const double* m, double dt, int64_t nsteps,
             double G, double eps, int precision, bool excl, bool acc_valid, const PairConfig& cfg,
             hipStream_t s, double* traj) {
   if (cfg.rows) return run_kdk_rows(n, x, v, a, m, dt, nsteps, G, eps, precision, excl, acc_valid, cfg, s, traj);
+  if (cfg.sym && precision == NBODY_FP64 && nsteps > 0)
+    return run_kdk_sym64(n, x, v, a, m, dt, nsteps, G, eps, excl, acc_valid, cfg, s, traj);
   const int64_t n3 = 3 * n;
   const double h = 0.5 * dt;
   int st;

@@ -369,7 +369,8 @@ __global__ __launch_bounds__(kSL, E::kWaves) void sym64_kernel(Sym64Args A) {
 // sum (component c of the sums to out, outm, outs as in sym_reduce_kernel).
 template <class E>
 int launch_sym64(int64_t n, const double* x, const double* m, const double* w, const double* u, double* out, double* outm,
-                 double* outs, double G, double eps, bool excl, const PairConfig& cfg, hipStream_t s) {
+                 double* outs, double G, double eps, bool excl, const PairConfig& cfg, hipStream_t s,
+                 Sym64Kdk* step = nullptr) {
   constexpr int NC = E::NC;
   if (n == 0) return NBODY_OK;
   int nb, T, D;
@@ -408,8 +409,15 @@ int launch_sym64(int64_t n, const double* x, const double* m, const double* w, c
     Q.pj = reinterpret_cast<double*>(ws + (size_t)b * buf_bytes);
     Q.pi = reinterpret_cast<double*>(ws + (size_t)b * buf_bytes + comp * D);
   };
-  sym64_stage_kernel<E><<<(unsigned)((npad + 255) / 256), 256, 0, s>>>((int)n, (int)npad, x, m, w, u, rec);
-  NB_LAUNCH_CHECK("sym64_stage_kernel");
+  if (!step || step->staged != nbuf) {
+    sym64_stage_kernel<E><<<(unsigned)((npad + 255) / 256), 256, 0, s>>>((int)n, (int)npad, x, m, w, u, rec);
+    NB_LAUNCH_CHECK("sym64_stage_kernel");
+  }
+  KdkTail tail;
+  if (step)
+    tail = KdkTail{step->x,  step->v,  step->xt, reinterpret_cast<double*>(rec),
+                   step->h, step->dt, step->nk, step->drift ? 1 : 0};
+  if (step) step->staged = step->drift ? nbuf : 0;
   auto pair = [&](int c, int b) -> int {
     Sym64Args B = A;
     slots(b, B);
@@ -424,9 +432,17 @@ int launch_sym64(int64_t n, const double* x, const double* m, const double* w, c
   auto sum = [&](int c, int b, hipStream_t rs) -> int {
     Sym64Args B = A;
     slots(b, B);
-    sym_reduce_kernel<NC, double><<<rg, kRedP * kRedW, 0, rs>>>((int)n, (int)npad, nb, dmax, half, 1 + c * D, dmax > 0 ? D : 0,
-                                                      dmax > 0 ? nparts : 0, B.pj, B.pi, A.pd, out, outm, G, c == 0,
-                                                      c + 1 >= nchunks, nullptr, nullptr, nullptr, nullptr, pds, outs);
+    auto red = [&](auto kdk) {
+      sym_reduce_kernel<NC, double, decltype(kdk)::value><<<rg, kRedP * kRedW, 0, rs>>>(
+          (int)n, (int)npad, nb, dmax, half, 1 + c * D, dmax > 0 ? D : 0, dmax > 0 ? nparts : 0, B.pj, B.pi, A.pd, out,
+          outm, G, c == 0, c + 1 >= nchunks, nullptr, nullptr, nullptr, nullptr, pds, outs, tail);
+    };
+    if constexpr (NC == 3) {
+      if (step) red(std::true_type{});
+      else red(std::false_type{});
+    } else {
+      red(std::false_type{});
+    }
     NB_LAUNCH_CHECK("sym_reduce_kernel");
     return NBODY_OK;
   };
@@ -437,8 +453,8 @@ int launch_sym64(int64_t n, const double* x, const double* m, const double* w, c
 }  // namespace
 
 int launch_sym_accel64(int64_t n, const double* x, const double* m, double* a, double G, double eps, bool excl,
-                       const PairConfig& cfg, hipStream_t s) {
-  return launch_sym64<Sym64Accel>(n, x, m, nullptr, nullptr, a, nullptr, nullptr, G, eps, excl, cfg, s);
+                       const PairConfig& cfg, hipStream_t s, Sym64Kdk* step) {
+  return launch_sym64<Sym64Accel>(n, x, m, nullptr, nullptr, a, nullptr, nullptr, G, eps, excl, cfg, s, step);
 }
 
 int launch_sym_pot64(int64_t n, const double* x, const double* m, double* phi, double scale, double eps,
