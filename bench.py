@@ -664,10 +664,10 @@ def bench_grad(args, torch, nb):
     vk = "vsym_kernel<%s> (symmetric from 12288 particles: staging, block diagonal, half ring, slot sums; " \
          "48 flops per interaction)" if n >= 12288 and args.precision != "fp64" else "vjp_kernel<%s> (48 flops per interaction)"
     roof = roofline(vk % args.precision.upper(), pairs * FLOPS_VJP, msv,
-                    force=roofline("accel_kernel<%s> (with its slice sum and the FP64 rescue)" % args.precision.upper(),
+                    force=roofline("%s force (every launch of the automatic choice at this size)" % args.precision.upper(),
                                    pairs * FLOPS_PER_PAIR, msa),
                     force_fp64=roofline("sym64_kernel (FP64, symmetric from 8192 particles: staging, block "
-                                        "diagonal, half ring, slot sum)" if n >= 8192 else "accel_kernel<FP64>",
+                                        "diagonal, half ring, slot sum)" if n >= 8192 else "rows64_kernel<RowAccel>",
                                         pairs * FLOPS_PER_PAIR, msa64, peak=FP64_PEAK_TFLOPS))
     cpu = None
     if not args.no_cpu:
@@ -756,7 +756,7 @@ def bench_kdk1k(args, torch, nb):
     pairs = float(n) * (n - 1) * (steps + 1)
     fa = torch.empty_like(tx)
     msf, _, _ = timed(lambda: nb.nbody_accel(tx, tm, eps=eps, precision="fp64", out=fa), 200, 50, torch)
-    roof = roofline("accel_kernel<FP64> (launch-latency bound at this size)", float(n) * (n - 1) * FLOPS_PER_PAIR,
+    roof = roofline("rows64_kernel<RowAccel> (launch-latency bound at this size)", float(n) * (n - 1) * FLOPS_PER_PAIR,
                     msf, peak=FP64_PEAK_TFLOPS)
     return {"metric": METRIC, "value": round(pairs / (ms * 1e-3) / 1e9, 3), "unit": UNIT, "n_gpus": 1,
             "steps": args.steps, "warmup": args.warmup, "ms_per_step": round(ms, 4), "higher_is_better": True,

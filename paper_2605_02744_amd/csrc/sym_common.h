@@ -1,6 +1,7 @@
 // Definitions shared by the symmetric all-pairs kernels (sym_pairs.hip: the
-// FP32C/FP32 acceleration; sym_fp64.hip: the FP64 acceleration; sym_vjp.hip:
-// the vector-Jacobian product): block and tile
+// FP32C/FP32 acceleration; sym_vjp.hip, sym_jerk.hip, sym_snap.hip: the
+// vector-Jacobian product, the jerk and the snap; sym_fp64.hip: all of them and
+// the potential in FP64): block and tile
 // sizes, the in-row rotation, the kernel arguments, the half ring of block
 // pairs and the slot sums.  Each unordered pair {i, j} is evaluated once and
 // its term applied to both particles; the layout is described in sym_pairs.hip.
