@@ -74,7 +74,7 @@ struct SymArgs {
   const double* u;  // [3][n] accelerations the particles move with (acceleration + jerk + snap)
   const float4* ru; // [npad] staged accelerations
   float* pj;        // [D][C][npad] j-side tile sums of the chunk's distances (C = 3; 4 for the VJP, 6 for a + jerk, 9 with snap)
-  double* pi;       // [nparts][C][npad] i-side sums of the chunk's workgroups
+  double* pi;       // [nparts][C][npad] i-side sums of the chunk's workgroups (VJP, jerk, snap: floats where T = 1)
   float* pe;        // [nparts][npad] i-side error estimates of the chunk's workgroups (FP32C force), or null
   float* pw;        // [D][npad] j-side error estimates of the chunk's distances (FP32C force), or null
 };
@@ -137,6 +137,10 @@ __device__ __forceinline__ void add_run(const S* __restrict__ q, size_t stride, 
 // and 54 us for the FP32C force at 65536; runs of eight over four waves and the
 // estimate in workgroups of its own take 7.2 and 31.
 //
+// PI: the i-side sums' type.  A workgroup of one tile folds one FP32 sum, which a float
+// holds exactly: half the bytes of the largest part of a small ring's slots (FP32C VJP
+// at 16384: 67 MB of i-side sums beside 4 of slots).
+//
 // With KDK (FP64 force), the thread that finishes a component also kicks it, drifts it
 // and writes it into the next step's record: two launches a step instead of four (51.5
 // -> 48.4 us a step at 8192 particles, 132.4 -> 129.9 at 16384, 407 -> 403 at 30011).
@@ -152,10 +156,10 @@ struct KdkTail {
 inline dim3 sym_reduce_grid(int64_t n, int comps, bool est) {
   return dim3((unsigned)((n + kRedP - 1) / kRedP), (unsigned)(comps + (est ? 1 : 0)));
 }
-template <int C, typename S, bool KDK = false>
+template <int C, typename S, bool KDK = false, typename PI = double>
 __global__ __launch_bounds__(kRedP * kRedW) void sym_reduce_kernel(
     int n, int npad, int nb, int dmax, int half, int d_lo, int D, int nparts, const S* __restrict__ pj,
-    const double* __restrict__ pi, const double* __restrict__ pd, double* __restrict__ out, double* __restrict__ outm,
+    const PI* __restrict__ pi, const double* __restrict__ pd, double* __restrict__ out, double* __restrict__ outm,
     double G, int first, int last, const float* __restrict__ pe = nullptr, const float* __restrict__ pw = nullptr,
     const float* __restrict__ ed = nullptr, float* __restrict__ eo = nullptr, int pds = 1,
     double* __restrict__ outs = nullptr, KdkTail kdk = KdkTail()) {
@@ -194,7 +198,7 @@ __global__ __launch_bounds__(kRedP * kRedW) void sym_reduce_kernel(
     else if (p < n) acc = *o;
   }
   add_run(pj + at, stride, sn * wave / kRedW, sn * (wave + 1) / kRedW, [&](S v) { add((double)v); });
-  add_run(pi + at, stride, nparts * wave / kRedW, nparts * (wave + 1) / kRedW, add);
+  add_run(pi + at, stride, nparts * wave / kRedW, nparts * (wave + 1) / kRedW, [&](PI v) { add((double)v); });
   if (wave > 0) {
     red[0][wave - 1][threadIdx.x % kRedP] = acc;
     if constexpr (C == 1) red[1][wave - 1][threadIdx.x % kRedP] = lo;
@@ -283,7 +287,7 @@ int run_sym_chunks(SideStream* side, hipStream_t s, int nchunks, int nbuf, Diag 
 // tiles, or for small rings a part of one) and distances per launch (D), the
 // sum slots of a launch kept near 1 GiB and the whole layout within budget
 // bytes; launches > 0 asks for at least that many launches.  Rings of fewer than
-// `fine` tiles take one tile per workgroup (kFineTiles, kFineTiles64).  Returns
+// `fine` tiles take one tile per workgroup (the kFineTiles constants).  Returns
 // the bytes the layout needs, which exceed budget only if one distance per launch
 // does not fit.
 //
@@ -293,7 +297,11 @@ int run_sym_chunks(SideStream* side, hipStream_t s, int nchunks, int nbuf, Diag 
 // 142 us at 12400, 213 -> 194 at 16384, 293 -> 284 at 20000, but 341 -> 330 for the
 // VJP against 528 -> 560 for the snap at 22500; FP64 VJP 122 -> 114 at 9973, 158 ->
 // 151 at 12000, 244 -> 246 at 16384.
-constexpr int64_t kFineTiles = 7168, kFineTiles64 = 3072;
+// Where the i-side sums of one tile are kept as floats (kFineTilesFl: the FP32C/FP32 VJP,
+// jerk and snap) it weighs less: VJP / jerk / snap 306 / 286 / 501 -> 300 / 279 / 485 us
+// at 22500, 332 / 309 / 541 -> 330 / 305 / 536 at 24000, but 378 / 355 / 623 -> 383 / 356 /
+// 620 at 26000.
+constexpr int64_t kFineTiles = 7168, kFineTilesFl = 9000, kFineTiles64 = 3072;
 inline size_t sym_plan(int64_t n, int launches, int slot_bytes, int sum_bytes, int part_bytes, int fixed_bytes,
                        size_t budget, int64_t fine, int* nb_out, int* T_out, int* D_out) {
   const int nb = (int)((n + kSI - 1) / kSI);

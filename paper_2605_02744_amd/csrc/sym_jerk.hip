@@ -331,6 +331,15 @@ __global__ __launch_bounds__(kSL, 4) void jsym_kernel(SymArgs A) {
   }
 
   // the i-side sums of this workgroup
+  if (A.T == 1) {  // one fold: a float holds the sum (as in the slot sums' PI)
+    float* o = reinterpret_cast<float*>(A.pi) + (size_t)part * kJC * A.npad;
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+#pragma unroll
+      for (int c = 0; c < kJC; ++c)
+        o[(size_t)c * A.npad + (size_t)g * kSI + u * kSL + t] = h[u][c] + s_acc_lo[u * kJC + c][t];
+    return;
+  }
   double* o = A.pi + (size_t)part * kJC * A.npad;
 #pragma unroll
   for (int u = 0; u < 2; ++u) {
@@ -475,7 +484,7 @@ int launch_sym_jerk(int64_t n, const double* x, const double* v, const double* m
   // FP64 block-diagonal sums (in pds slices) and three staged float4 records
   const int pds = diag_slices((int)((n + kSI - 1) / kSI));
   sym_plan(n, cfg.launches, kJC * sizeof(float), kJC * sizeof(float), kJC * sizeof(double),
-           pds * kJC * (int)sizeof(double) + 3 * (int)sizeof(float4), cfg.scratch ? cfg.scratch_bytes : SIZE_MAX, kFineTiles, &nb,
+           pds * kJC * (int)sizeof(double) + 3 * (int)sizeof(float4), cfg.scratch ? cfg.scratch_bytes : SIZE_MAX, kFineTilesFl, &nb,
            &T, &D);
   const int dmax = nb / 2;
   const int half = (nb % 2 == 0) ? 1 : 0;
@@ -490,7 +499,7 @@ int launch_sym_jerk(int64_t n, const double* x, const double* v, const double* m
   const int nbuf = side ? 2 : 1;
   int st = NBODY_OK;
   const size_t pj_bytes = sizeof(float) * kJC * (size_t)npad * D;
-  const size_t pi_bytes = sizeof(double) * kJC * (size_t)npad * nparts;
+  const size_t pi_bytes = (T == 1 ? sizeof(float) : sizeof(double)) * kJC * (size_t)npad * nparts;
   const size_t pd_bytes = sizeof(double) * kJC * (size_t)npad * pds;
   const size_t rec_bytes = sizeof(float4) * (size_t)npad;
   const size_t buf_bytes = pj_bytes + pi_bytes;  // one slot set
@@ -552,9 +561,13 @@ int launch_sym_jerk(int64_t n, const double* x, const double* v, const double* m
   auto sum = [&](int c, int b, hipStream_t rs) -> int {
     SymArgs B = A;
     slots(b, B);
-    sym_reduce_kernel<kJC, float><<<rg, kRedP * kRedW, 0, rs>>>((int)n, (int)npad, nb, dmax, half, 1 + c * D, D, nparts, B.pj, B.pi,
-                                               pd, a, jk, G, c == 0, c == nchunks - 1, nullptr, nullptr, nullptr,
-                                               nullptr, pds);
+    auto red = [&](auto* pi) {
+      sym_reduce_kernel<kJC, float, false, std::remove_pointer_t<decltype(pi)>><<<rg, kRedP * kRedW, 0, rs>>>(
+          (int)n, (int)npad, nb, dmax, half, 1 + c * D, D, nparts, B.pj, pi, pd, a, jk, G, c == 0, c == nchunks - 1,
+          nullptr, nullptr, nullptr, nullptr, pds);
+    };
+    if (T == 1) red(reinterpret_cast<float*>(B.pi));
+    else red(B.pi);
     NB_LAUNCH_CHECK("sym_reduce_kernel");
     return NBODY_OK;
   };

@@ -337,6 +337,15 @@ __global__ __launch_bounds__(kSL, 3) void ssym_kernel(SymArgs A) {
   }
 
   // the i-side sums of this workgroup
+  if (A.T == 1) {  // one fold: a float holds the sum (as in the slot sums' PI)
+    float* o = reinterpret_cast<float*>(A.pi) + (size_t)part * kSC * A.npad;
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+#pragma unroll
+      for (int c = 0; c < kSC; ++c)
+        o[(size_t)c * A.npad + (size_t)g * kSI + u * kSL + t] = h[u][c] + s_acc_lo[u * kSC + c][t];
+    return;
+  }
   double* o = A.pi + (size_t)part * kSC * A.npad;
 #pragma unroll
   for (int u = 0; u < 2; ++u) {
@@ -482,7 +491,7 @@ int launch_sym_snap(int64_t n, const double* x, const double* v, const double* a
   // FP64 block-diagonal sums (in pds slices) and four staged float4 records
   const int pds = diag_slices((int)((n + kSI - 1) / kSI));
   sym_plan(n, cfg.launches, kSC * sizeof(float), kSC * sizeof(float), kSC * sizeof(double),
-           pds * kSC * (int)sizeof(double) + 4 * (int)sizeof(float4), cfg.scratch ? cfg.scratch_bytes : SIZE_MAX, kFineTiles, &nb,
+           pds * kSC * (int)sizeof(double) + 4 * (int)sizeof(float4), cfg.scratch ? cfg.scratch_bytes : SIZE_MAX, kFineTilesFl, &nb,
            &T, &D);
   const int dmax = nb / 2;
   const int half = (nb % 2 == 0) ? 1 : 0;
@@ -497,7 +506,7 @@ int launch_sym_snap(int64_t n, const double* x, const double* v, const double* a
   const int nbuf = side ? 2 : 1;
   int st = NBODY_OK;
   const size_t pj_bytes = sizeof(float) * kSC * (size_t)npad * D;
-  const size_t pi_bytes = sizeof(double) * kSC * (size_t)npad * nparts;
+  const size_t pi_bytes = (T == 1 ? sizeof(float) : sizeof(double)) * kSC * (size_t)npad * nparts;
   const size_t pd_bytes = sizeof(double) * kSC * (size_t)npad * pds;
   const size_t rec_bytes = sizeof(float4) * (size_t)npad;
   const size_t buf_bytes = pj_bytes + pi_bytes;  // one slot set
@@ -561,9 +570,13 @@ int launch_sym_snap(int64_t n, const double* x, const double* v, const double* a
   auto sum = [&](int c, int b, hipStream_t rs) -> int {
     SymArgs B = A;
     slots(b, B);
-    sym_reduce_kernel<kSC, float><<<rg, kRedP * kRedW, 0, rs>>>((int)n, (int)npad, nb, dmax, half, 1 + c * D, D, nparts, B.pj, B.pi,
-                                               pd, a, jk, G, c == 0, c == nchunks - 1, nullptr, nullptr, nullptr,
-                                               nullptr, pds, sn);
+    auto red = [&](auto* pi) {
+      sym_reduce_kernel<kSC, float, false, std::remove_pointer_t<decltype(pi)>><<<rg, kRedP * kRedW, 0, rs>>>(
+          (int)n, (int)npad, nb, dmax, half, 1 + c * D, D, nparts, B.pj, pi, pd, a, jk, G, c == 0, c == nchunks - 1,
+          nullptr, nullptr, nullptr, nullptr, pds, sn);
+    };
+    if (T == 1) red(reinterpret_cast<float*>(B.pi));
+    else red(B.pi);
     NB_LAUNCH_CHECK("sym_reduce_kernel");
     return NBODY_OK;
   };

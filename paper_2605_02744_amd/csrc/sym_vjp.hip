@@ -320,6 +320,15 @@ __global__ __launch_bounds__(kSL, 6) void vsym_kernel(SymArgs A) {
   }
 
   // the k-side sums of this workgroup
+  if (A.T == 1) {  // one fold: a float holds the sum (as in the slot sums' PI)
+    float* o = reinterpret_cast<float*>(A.pi) + (size_t)part * kVC * A.npad;
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+#pragma unroll
+      for (int c = 0; c < kVC; ++c)
+        o[(size_t)c * A.npad + (size_t)g * kSI + u * kSL + t] = h[u][c] + s_acc_lo[u * kVC + c][t];
+    return;
+  }
   double* o = A.pi + (size_t)part * kVC * A.npad;
 #pragma unroll
   for (int u = 0; u < 2; ++u) {
@@ -459,7 +468,7 @@ int launch_sym_vjp(int64_t n, const double* x, const double* m, const double* w,
   // FP64 block-diagonal sums (in pds slices) and three staged float4 records
   const int pds = diag_slices((int)((n + kSI - 1) / kSI));
   sym_plan(n, cfg.launches, kVC * sizeof(float), kVC * sizeof(float), kVC * sizeof(double),
-           pds * kVC * (int)sizeof(double) + 3 * (int)sizeof(float4), cfg.scratch ? cfg.scratch_bytes : SIZE_MAX, kFineTiles, &nb,
+           pds * kVC * (int)sizeof(double) + 3 * (int)sizeof(float4), cfg.scratch ? cfg.scratch_bytes : SIZE_MAX, kFineTilesFl, &nb,
            &T, &D);
   const int dmax = nb / 2;
   const int half = (nb % 2 == 0) ? 1 : 0;
@@ -476,7 +485,7 @@ int launch_sym_vjp(int64_t n, const double* x, const double* m, const double* w,
   const int nbuf = side ? 2 : 1;
   int st = NBODY_OK;
   const size_t pj_bytes = sizeof(float) * kVC * (size_t)npad * D;
-  const size_t pi_bytes = sizeof(double) * kVC * (size_t)npad * nparts;
+  const size_t pi_bytes = (T == 1 ? sizeof(float) : sizeof(double)) * kVC * (size_t)npad * nparts;
   const size_t pd_bytes = sizeof(double) * kVC * (size_t)npad * pds;
   const size_t rec_bytes = sizeof(float4) * (size_t)npad;
   const size_t buf_bytes = pj_bytes + pi_bytes;  // one slot set
@@ -538,9 +547,13 @@ int launch_sym_vjp(int64_t n, const double* x, const double* m, const double* w,
   auto sum = [&](int c, int b, hipStream_t rs) -> int {
     SymArgs B = A;
     slots(b, B);
-    sym_reduce_kernel<kVC, float><<<rg, kRedP * kRedW, 0, rs>>>((int)n, (int)npad, nb, dmax, half, 1 + c * D, D, nparts, B.pj, B.pi,
-                                               pd, gx, gm, G, c == 0, c == nchunks - 1, nullptr, nullptr, nullptr,
-                                               nullptr, pds);
+    auto red = [&](auto* pi) {
+      sym_reduce_kernel<kVC, float, false, std::remove_pointer_t<decltype(pi)>><<<rg, kRedP * kRedW, 0, rs>>>(
+          (int)n, (int)npad, nb, dmax, half, 1 + c * D, D, nparts, B.pj, pi, pd, gx, gm, G, c == 0, c == nchunks - 1,
+          nullptr, nullptr, nullptr, nullptr, pds);
+    };
+    if (T == 1) red(reinterpret_cast<float*>(B.pi));
+    else red(B.pi);
     NB_LAUNCH_CHECK("sym_reduce_kernel");
     return NBODY_OK;
   };
