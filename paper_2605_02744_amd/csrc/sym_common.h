@@ -84,6 +84,10 @@ __device__ __forceinline__ int ring_end(const SymArgs& A, int g) {
   return (A.half && g >= A.nb / 2) ? A.dmax : A.dmax + 1;
 }
 
+// Steps of a sub-block that the VJP, jerk and snap kernels flag together (a bit per run,
+// the same for the whole wave) for the near-field repair, which walks the flagged runs.
+constexpr int kNearRun = 8;
+
 // Squared repair radius (the near-field rule of the ordered kernel, with its
 // n-dependent factor f given): a pair closer than max(f |x|_inf, kNearEps eps)
 // to the particle at (xa, ya, za) gets float-float displacements.

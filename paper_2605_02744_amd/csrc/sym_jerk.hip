@@ -88,11 +88,11 @@ __device__ __forceinline__ void jsym_step(const JSet& s, const float4* __restric
   }
 }
 
-template <bool NEAR, int... K>
+template <bool NEAR, int K0, int... K>
 __device__ __forceinline__ void jsym_sub(const JSet& s, const float4* __restrict__ rowp,
                                          const float4* __restrict__ rowv, float e2, float (&p)[2][kJC],
                                          float (&r2min)[2], float (&aj)[kJC], std::integer_sequence<int, K...>) {
-  (jsym_step<K, NEAR>(s, rowp, rowv, e2, p, r2min, aj), ...);
+  (jsym_step<K0 + K, NEAR>(s, rowp, rowv, e2, p, r2min, aj), ...);
 }
 
 // Loads the two i of lane t of I-block g (padding: far away, massless, at
@@ -151,20 +151,20 @@ __global__ void jsym_stage_kernel(SymArgs A, float4* __restrict__ rhi, float4* _
   rlo[j] = lo;
 }
 
-// Near-field correction of one lane's tile (FP32C): every pair of the lane's two i
+// Near-field correction of a wave's tile (FP32C): every pair of a lane's two i
 // with the tile's 64 j closer than the larger repair radius of its two particles
 // gets (float-float term - rounded term) added, times m_j to the lane's i-side
 // sums p and times -m_i to the wave's j-side sums of the tile (part: components
 // kSW * kST apart).  The j are visited in the rotated order of the pair loop, so
 // at each step the lanes of a row touch distinct j; the four rows of the wave,
-// which share the slots, take turns.  near: the lane's flagged sub-blocks (bit q);
-// a wave passes over a sub-block that no lane flagged and a step that corrected
-// nothing, since the visit costs the wave 64 steps of four turns whichever lane
-// asked for it and a flagged lane has one such sub-block as a rule (acceleration +
-// jerk 18.6 -> 17.8 ms at 204800 particles).
+// which share the slots, take turns.  runs: the wave's flagged runs of kNearRun
+// steps. Only those are walked, a step without a close pair does nothing, and only
+// rows that corrected take turns (against all 64 steps of four turns: acceleration
+// + jerk 18.6 -> 17.8 ms at 204800 particles; against flags per lane and sub-block
+// of 16: 156 -> 149 us at 16384).
 __device__ __forceinline__ void jsym_repair(const SymArgs& A, int g, int t, int rl, float e2, const JSet& s,
                                             float (&p)[2][kJC], const float4* hi, const float4* vr, const float4* lo,
-                                            float* part, unsigned near) {
+                                            float* part, unsigned runs) {
   const int n = A.n;
   const int wrow = (t & 63) / kSR;
   float rc[2];
@@ -173,46 +173,57 @@ __device__ __forceinline__ void jsym_repair(const SymArgs& A, int g, int t, int 
     const int i = g * kSI + u * kSL + t;
     rc[u] = i < n ? sym_rc2f(s.x[u], s.y[u], s.z[u], A.eps, A.fx) : -1.f;
   }
-  for (int jj = 0; jj < kST; ++jj) {
-    const int q = jj / kSR;
-    if (!(near >> q & 1)) continue;
-    const int jl = q * kSR + ((rl + jj) & (kSR - 1));
-    const float4 rh = hi[q * 2 * kSR + (jl % kSR)];
-    const float4 vj = vr[q * 2 * kSR + (jl % kSR)];
-    const float4 rlj = lo[jl];
-    float c[kJC] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+  while (runs) {
+    const int k0 = (__ffs((int)runs) - 1) * kNearRun;
+    runs &= runs - 1;
+    for (int jj = k0; jj < k0 + kNearRun; ++jj) {
+      const int q = jj / kSR;
+      const int jl = q * kSR + ((rl + jj) & (kSR - 1));
+      const float4 rh = hi[q * 2 * kSR + (jl % kSR)];
+      const float rcj = lo[jl].w;
+      bool close[2];
 #pragma unroll
-    for (int u = 0; u < 2; ++u) {
-      const float dx = rh.x - s.x[u], dy = rh.y - s.y[u], dz = rh.z - s.z[u];
-      const float r2 = fmaf(dz, dz, fmaf(dy, dy, fmaf(dx, dx, e2)));
-      if (rc[u] >= 0.f && r2 < fmaxf(rc[u], rlj.w)) {
-        const int i = g * kSI + u * kSL + t;
-        const double xa = A.x[i], ya = A.x[n + i], za = A.x[2 * n + i];
-        const float ex = dx + (rlj.x - (float)(xa - (double)s.x[u]));
-        const float ey = dy + (rlj.y - (float)(ya - (double)s.y[u]));
-        const float ez = dz + (rlj.z - (float)(za - (double)s.z[u]));
-        const float wx = vj.x - s.vx[u], wy = vj.y - s.vy[u], wz = vj.z - s.vz[u];
-        float ra[3], rj[3], fa[3], fj[3];
-        jerk_terms(dx, dy, dz, wx, wy, wz, e2, ra, rj);
-        jerk_terms(ex, ey, ez, wx, wy, wz, e2, fa, fj);
+      for (int u = 0; u < 2; ++u) {
+        const float dx = rh.x - s.x[u], dy = rh.y - s.y[u], dz = rh.z - s.z[u];
+        close[u] = rc[u] >= 0.f && fmaf(dz, dz, fmaf(dy, dy, fmaf(dx, dx, e2))) < fmaxf(rc[u], rcj);
+      }
+      if (!__any(close[0] || close[1])) continue;
+      const float4 rlj = lo[jl];
+      const float4 vj = vr[q * 2 * kSR + (jl % kSR)];
+      float c[kJC] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int k = 0; k < 3; ++k) {
-          const float da = fa[k] - ra[k], dj = fj[k] - rj[k];
-          p[u][k] = fmaf(rh.w, da, p[u][k]);
-          p[u][3 + k] = fmaf(rh.w, dj, p[u][3 + k]);
-          c[k] = fmaf(s.mneg[u], da, c[k]);
-          c[3 + k] = fmaf(s.mneg[u], dj, c[3 + k]);
+      for (int u = 0; u < 2; ++u) {
+        const float dx = rh.x - s.x[u], dy = rh.y - s.y[u], dz = rh.z - s.z[u];
+        if (close[u]) {
+          const int i = g * kSI + u * kSL + t;
+          const double xa = A.x[i], ya = A.x[n + i], za = A.x[2 * n + i];
+          const float ex = dx + (rlj.x - (float)(xa - (double)s.x[u]));
+          const float ey = dy + (rlj.y - (float)(ya - (double)s.y[u]));
+          const float ez = dz + (rlj.z - (float)(za - (double)s.z[u]));
+          const float wx = vj.x - s.vx[u], wy = vj.y - s.vy[u], wz = vj.z - s.vz[u];
+          float ra[3], rj[3], fa[3], fj[3];
+          jerk_terms(dx, dy, dz, wx, wy, wz, e2, ra, rj);
+          jerk_terms(ex, ey, ez, wx, wy, wz, e2, fa, fj);
+#pragma unroll
+          for (int k = 0; k < 3; ++k) {
+            const float da = fa[k] - ra[k], dj = fj[k] - rj[k];
+            p[u][k] = fmaf(rh.w, da, p[u][k]);
+            p[u][3 + k] = fmaf(rh.w, dj, p[u][3 + k]);
+            c[k] = fmaf(s.mneg[u], da, c[k]);
+            c[3 + k] = fmaf(s.mneg[u], dj, c[3 + k]);
+          }
         }
       }
-    }
-    const bool corrected = c[0] != 0.f || c[1] != 0.f || c[2] != 0.f || c[3] != 0.f || c[4] != 0.f || c[5] != 0.f;
-    if (!__any(corrected)) continue;
-    for (int r = 0; r < 4; ++r) {
-      if (wrow == r && corrected) {
+      const bool corrected = c[0] != 0.f || c[1] != 0.f || c[2] != 0.f || c[3] != 0.f || c[4] != 0.f || c[5] != 0.f;
+      const unsigned long long turns = __ballot(corrected);
+      for (int r = 0; r < 4; ++r) {
+        if (!(turns >> (r * kSR) & 0xFFFFu)) continue;
+        if (wrow == r && corrected) {
 #pragma unroll
-        for (int k = 0; k < kJC; ++k) part[k * kSW * kST + jl] += c[k];
+          for (int k = 0; k < kJC; ++k) part[k * kSW * kST + jl] += c[k];
+        }
+        wave_sync();  // one row's turn ends before the next row reads the sums
       }
-      wave_sync();  // one row's turn ends before the next row reads the sums
     }
   }
 }
@@ -290,13 +301,20 @@ __global__ __launch_bounds__(kSL, 4) void jsym_kernel(SymArgs A) {
     for (int u = 0; u < 2; ++u)
 #pragma unroll
       for (int c = 0; c < kJC; ++c) p[u][c] = 0.f;
-    unsigned near = 0u;  // the lane's sub-blocks that may hold a pair to repair
+    unsigned runs = 0u;  // the runs of steps that may hold a pair to repair, for any lane
 #pragma unroll 1
     for (int q = 0; q < 4; ++q) {
-      float r2min[2] = {3.0e38f, 3.0e38f};
       float aj[kJC] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-      jsym_sub<NEAR>(s, &s_hi[b][q][rl], &s_v[b][q][rl], e2, p, r2min, aj, std::make_integer_sequence<int, kSR>{});
-      if (NEAR && (r2min[0] < thr[0] || r2min[1] < thr[1])) near |= 1u << q;
+      auto run = [&](auto k0) {
+        float r2min[2] = {3.0e38f, 3.0e38f};
+        jsym_sub<NEAR, decltype(k0)::value>(s, &s_hi[b][q][rl], &s_v[b][q][rl], e2, p, r2min, aj, std::make_integer_sequence<int, kNearRun>{});
+        if constexpr (NEAR)
+          // (no branch here: the compiler would move the pair loop's sums past it and spill)
+          runs |= (unsigned)(__ballot((r2min[0] < thr[0]) | (r2min[1] < thr[1])) != 0ull)
+                  << ((q * kSR + decltype(k0)::value) / kNearRun);
+      };
+      run(std::integral_constant<int, 0>{});
+      run(std::integral_constant<int, kNearRun>{});
       // the four rows' sums of the same 16 j, as in the acceleration
 #pragma unroll
       for (int c = 0; c < kJC; ++c) {
@@ -306,8 +324,8 @@ __global__ __launch_bounds__(kSL, 4) void jsym_kernel(SymArgs A) {
       }
     }
     if constexpr (NEAR) {
-      if (near)
-        jsym_repair(A, g, t, rl, e2, s, p, &s_hi[b][0][0], &s_v[b][0][0], &s_lo[b][0], &s_part[0][wave][0], near);
+      if (runs)
+        jsym_repair(A, g, t, rl, e2, s, p, &s_hi[b][0][0], &s_v[b][0][0], &s_lo[b][0], &s_part[0][wave][0], runs);
     }
 #pragma unroll
     for (int u = 0; u < 2; ++u)
