@@ -163,11 +163,11 @@ struct P6 {
 // distinct j; the four rows of the wave, which share the slots, take turns.
 // r2nr receives, per i, the smallest squared distance of the tile's pairs that
 // keep their rounded-position terms (for the error estimate of the rescue).
-// A step that corrected nothing takes no turns, and nothing is loaded for a tile
-// without a pair to correct (four steps at 65536 particles 4364 -> 4318 us, the
-// force at 204800 10.32 -> 10.21 ms).  Flags per sub-block, as the other symmetric
-// kernels keep them, gained 1 % at 65536 here and lost 1.5 % at 2^20: eight more
-// instructions per sub-block, in every tile.
+// A step goes on only if some lane has a close pair there, nothing but the positions is
+// loaded before, and only rows that corrected take turns (four steps at 65536 particles
+// 4364 -> 4318 -> 4256 us with that, the force at 2^20 246.0 -> 244.8 ms).  Flags per
+// sub-block or run, as the other symmetric kernels keep them, gained 0.4 to 1 % at 65536
+// here and lost 1.5 % at 2^20: more instructions in every tile.
 __device__ __forceinline__ P6 sym_repair(const double* __restrict__ x, int n, double eps, float fx, int g, int t, int rl,
                                          float e2, ISet s, P6 p, const float4* hi, const float4* lo, float* part,
                                          float (&r2nr)[2]) {
@@ -184,14 +184,24 @@ __device__ __forceinline__ P6 sym_repair(const double* __restrict__ x, int n, do
     const int q = jj / kSR;
     const int jl = q * kSR + ((rl + jj) & (kSR - 1));
     const float4 rh = hi[q * 2 * kSR + (jl % kSR)];
-    const float4 rl4 = lo[jl];
-    float cx = 0.f, cy = 0.f, cz = 0.f;
+    const float rcj = lo[jl].w;
+    bool close[2];
 #pragma unroll
     for (int u = 0; u < 2; ++u) {
       const float dx = rh.x - s.x[u], dy = rh.y - s.y[u], dz = rh.z - s.z[u];
       const float r2 = fmaf(dz, dz, fmaf(dy, dy, fmaf(dx, dx, e2)));
-      if (!(r2 < fmaxf(rc[u], rl4.w))) r2nr[u] = fminf(r2nr[u], r2);
-      if (rc[u] >= 0.f && r2 < fmaxf(rc[u], rl4.w)) {
+      const bool in = r2 < fmaxf(rc[u], rcj);
+      r2nr[u] = fminf(r2nr[u], in ? 3.0e38f : r2);
+      close[u] = in & (rc[u] >= 0.f);
+    }
+    if (!__any(close[0] | close[1])) continue;
+    const float4 rl4 = lo[jl];
+    float cx = 0.f, cy = 0.f, cz = 0.f;
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      if (close[u]) {
+        const float dx = rh.x - s.x[u], dy = rh.y - s.y[u], dz = rh.z - s.z[u];
+        const float r2 = fmaf(dz, dz, fmaf(dy, dy, fmaf(dx, dx, e2)));
         const int i = g * kSI + u * kSL + t;
         const double xa = x[i], ya = x[n + i], za = x[2 * n + i];
         const float ex = dx + (rl4.x - (float)(xa - (double)s.x[u]));
@@ -208,8 +218,9 @@ __device__ __forceinline__ P6 sym_repair(const double* __restrict__ x, int n, do
       }
     }
     const bool corrected = cx != 0.f || cy != 0.f || cz != 0.f;
-    if (!__any(corrected)) continue;
+    const unsigned long long turns = __ballot(corrected);
     for (int r = 0; r < 4; ++r) {
+      if (!(turns >> (r * kSR) & 0xFFFFu)) continue;
       if (wrow == r && corrected) {
         part[jl] += cx;
         part[kSW * kST + jl] += cy;
