@@ -318,7 +318,7 @@ __global__ __launch_bounds__(kSL, 3) void ssym_kernel(SymArgs A) {
                   << ((q * kSR + decltype(k0)::value) / kNearRun);
       };
       run(std::integral_constant<int, 0>{});
-      run(std::integral_constant<int, kNearRun>{});
+      if constexpr (kNearRun < kSR) run(std::integral_constant<int, kNearRun % kSR>{});
       // the four rows' sums of the same 16 j, as in the acceleration
 #pragma unroll
       for (int c = 0; c < kSC; ++c) {

@@ -86,11 +86,11 @@ __device__ __forceinline__ void vsym_step(const VSet& s, const float4* __restric
   }
 }
 
-template <bool NEAR, int K0, int... K>
+template <bool NEAR, int... K>
 __device__ __forceinline__ void vsym_sub(const VSet& s, const float4* __restrict__ rowp,
                                          const float4* __restrict__ roww, float e2, float (&p)[2][kVC],
                                          float (&r2min)[2], float (&aj)[kVC], std::integer_sequence<int, K...>) {
-  (vsym_step<K0 + K, NEAR>(s, rowp, roww, e2, p, r2min, aj), ...);
+  (vsym_step<K, NEAR>(s, rowp, roww, e2, p, r2min, aj), ...);
 }
 
 // Loads the two k of lane t of I-block g (padding: far away, massless, zero
@@ -146,19 +146,20 @@ __global__ void vsym_stage_kernel(SymArgs A, float4* __restrict__ rhi, float4* _
   rlo[j] = lo;
 }
 
-// Near-field correction of a wave's tile (FP32C): every pair of a lane's two k
+// Near-field correction of one lane's tile (FP32C): every pair of the lane's two k
 // with the tile's 64 j closer than the larger repair radius of its two particles
 // gets (float-float term - rounded term) added, to the lane's k-side sums p and to
 // the wave's j-side sums of the tile (part: components kSW * kST apart).  The j
 // are visited in the rotated order of the pair loop, so at each step the lanes of
 // a row touch distinct j; the four rows of the wave, which share the slots, take
-// turns.  runs: the wave's flagged runs of kNearRun steps. Only those are walked,
-// a step without a close pair does nothing, and only rows that corrected take
-// turns (against all 64 steps of four turns: VJP 2161 -> 2080 us at 65536
-// particles; against flags per lane and sub-block of 16: 163 -> 158 us at 16384).
+// turns.  near: the lane's flagged sub-blocks (bit q); a wave passes over a
+// sub-block that no lane flagged and a step that corrected nothing, since the
+// visit costs the wave 64 steps of four turns whichever lane asked for it and a
+// flagged lane has one such sub-block as a rule (VJP 2161 -> 2074 us at 65536
+// particles, 194 -> 176 at 16384).
 __device__ __forceinline__ void vsym_repair(const SymArgs& A, int g, int t, int rl, float e2, const VSet& s,
                                             float (&p)[2][kVC], const float4* hi, const float4* wr, const float4* lo,
-                                            float* part, unsigned runs) {
+                                            float* part, unsigned near) {
   const int n = A.n;
   const int wrow = (t & 63) / kSR;
   float rc[2];
@@ -167,55 +168,44 @@ __device__ __forceinline__ void vsym_repair(const SymArgs& A, int g, int t, int 
     const int i = g * kSI + u * kSL + t;
     rc[u] = i < n ? sym_rc2f(s.x[u], s.y[u], s.z[u], A.eps, A.fx) : -1.f;
   }
-  while (runs) {
-    const int k0 = (__ffs((int)runs) - 1) * kNearRun;
-    runs &= runs - 1;
-    for (int jj = k0; jj < k0 + kNearRun; ++jj) {
-      const int q = jj / kSR;
-      const int jl = q * kSR + ((rl + jj) & (kSR - 1));
-      const float4 rh = hi[q * 2 * kSR + (jl % kSR)];
-      const float rcj = lo[jl].w;
-      bool close[2];
+  for (int jj = 0; jj < kST; ++jj) {
+    const int q = jj / kSR;
+    if (!(near >> q & 1)) continue;
+    const int jl = q * kSR + ((rl + jj) & (kSR - 1));
+    const float4 rh = hi[q * 2 * kSR + (jl % kSR)];
+    const float4 wj = wr[q * 2 * kSR + (jl % kSR)];
+    const float4 rlj = lo[jl];
+    float c[kVC] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-      for (int u = 0; u < 2; ++u) {
-        const float dx = rh.x - s.x[u], dy = rh.y - s.y[u], dz = rh.z - s.z[u];
-        close[u] = rc[u] >= 0.f && fmaf(dz, dz, fmaf(dy, dy, fmaf(dx, dx, e2))) < fmaxf(rc[u], rcj);
-      }
-      if (!__any(close[0] || close[1])) continue;
-      const float4 rlj = lo[jl];
-      const float4 wj = wr[q * 2 * kSR + (jl % kSR)];
-      float c[kVC] = {0.f, 0.f, 0.f, 0.f};
+    for (int u = 0; u < 2; ++u) {
+      const float dx = rh.x - s.x[u], dy = rh.y - s.y[u], dz = rh.z - s.z[u];
+      const float r2 = fmaf(dz, dz, fmaf(dy, dy, fmaf(dx, dx, e2)));
+      if (rc[u] >= 0.f && r2 < fmaxf(rc[u], rlj.w)) {
+        const int i = g * kSI + u * kSL + t;
+        const double xa = A.x[i], ya = A.x[n + i], za = A.x[2 * n + i];
+        const float ex = dx + (rlj.x - (float)(xa - (double)s.x[u]));
+        const float ey = dy + (rlj.y - (float)(ya - (double)s.y[u]));
+        const float ez = dz + (rlj.z - (float)(za - (double)s.z[u]));
+        float tr[3], tf[3], qkr, qjr, qkf, qjf;
+        vjp_terms(dx, dy, dz, e2, s.m[u], s.wx[u], s.wy[u], s.wz[u], rh.w, wj.x, wj.y, wj.z, tr, qkr, qjr);
+        vjp_terms(ex, ey, ez, e2, s.m[u], s.wx[u], s.wy[u], s.wz[u], rh.w, wj.x, wj.y, wj.z, tf, qkf, qjf);
 #pragma unroll
-      for (int u = 0; u < 2; ++u) {
-        const float dx = rh.x - s.x[u], dy = rh.y - s.y[u], dz = rh.z - s.z[u];
-        if (close[u]) {
-          const int i = g * kSI + u * kSL + t;
-          const double xa = A.x[i], ya = A.x[n + i], za = A.x[2 * n + i];
-          const float ex = dx + (rlj.x - (float)(xa - (double)s.x[u]));
-          const float ey = dy + (rlj.y - (float)(ya - (double)s.y[u]));
-          const float ez = dz + (rlj.z - (float)(za - (double)s.z[u]));
-          float tr[3], tf[3], qkr, qjr, qkf, qjf;
-          vjp_terms(dx, dy, dz, e2, s.m[u], s.wx[u], s.wy[u], s.wz[u], rh.w, wj.x, wj.y, wj.z, tr, qkr, qjr);
-          vjp_terms(ex, ey, ez, e2, s.m[u], s.wx[u], s.wy[u], s.wz[u], rh.w, wj.x, wj.y, wj.z, tf, qkf, qjf);
-#pragma unroll
-          for (int k = 0; k < 3; ++k) {
-            p[u][k] += tf[k] - tr[k];
-            c[k] -= tf[k] - tr[k];
-          }
-          p[u][3] += qkf - qkr;
-          c[3] += qjf - qjr;
+        for (int k = 0; k < 3; ++k) {
+          p[u][k] += tf[k] - tr[k];
+          c[k] -= tf[k] - tr[k];
         }
+        p[u][3] += qkf - qkr;
+        c[3] += qjf - qjr;
       }
-      const bool corrected = c[0] != 0.f || c[1] != 0.f || c[2] != 0.f || c[3] != 0.f;
-      const unsigned long long turns = __ballot(corrected);
-      for (int r = 0; r < 4; ++r) {
-        if (!(turns >> (r * kSR) & 0xFFFFu)) continue;
-        if (wrow == r && corrected) {
+    }
+    const bool corrected = c[0] != 0.f || c[1] != 0.f || c[2] != 0.f || c[3] != 0.f;
+    if (!__any(corrected)) continue;
+    for (int r = 0; r < 4; ++r) {
+      if (wrow == r && corrected) {
 #pragma unroll
-          for (int k = 0; k < kVC; ++k) part[k * kSW * kST + jl] += c[k];
-        }
-        wave_sync();  // one row's turn ends before the next row reads the sums
+        for (int k = 0; k < kVC; ++k) part[k * kSW * kST + jl] += c[k];
       }
+      wave_sync();  // one row's turn ends before the next row reads the sums
     }
   }
 }
@@ -292,20 +282,13 @@ __global__ __launch_bounds__(kSL, 6) void vsym_kernel(SymArgs A) {
     for (int u = 0; u < 2; ++u)
 #pragma unroll
       for (int c = 0; c < kVC; ++c) p[u][c] = 0.f;
-    unsigned runs = 0u;  // the runs of steps that may hold a pair to repair, for any lane
+    unsigned near = 0u;  // the lane's sub-blocks that may hold a pair to repair
 #pragma unroll 1
     for (int q = 0; q < 4; ++q) {
+      float r2min[2] = {3.0e38f, 3.0e38f};
       float aj[kVC] = {0.f, 0.f, 0.f, 0.f};
-      auto run = [&](auto k0) {
-        float r2min[2] = {3.0e38f, 3.0e38f};
-        vsym_sub<NEAR, decltype(k0)::value>(s, &s_hi[b][q][rl], &s_w[b][q][rl], e2, p, r2min, aj, std::make_integer_sequence<int, kNearRun>{});
-        if constexpr (NEAR)
-          // (no branch here: the compiler would move the pair loop's sums past it and spill)
-          runs |= (unsigned)(__ballot((r2min[0] < thr[0]) | (r2min[1] < thr[1])) != 0ull)
-                  << ((q * kSR + decltype(k0)::value) / kNearRun);
-      };
-      run(std::integral_constant<int, 0>{});
-      run(std::integral_constant<int, kNearRun>{});
+      vsym_sub<NEAR>(s, &s_hi[b][q][rl], &s_w[b][q][rl], e2, p, r2min, aj, std::make_integer_sequence<int, kSR>{});
+      if (NEAR && (r2min[0] < thr[0] || r2min[1] < thr[1])) near |= 1u << q;
       // the four rows' sums of the same 16 j, as in the acceleration
 #pragma unroll
       for (int c = 0; c < kVC; ++c) {
@@ -315,8 +298,8 @@ __global__ __launch_bounds__(kSL, 6) void vsym_kernel(SymArgs A) {
       }
     }
     if constexpr (NEAR) {
-      if (runs)
-        vsym_repair(A, g, t, rl, e2, s, p, &s_hi[b][0][0], &s_w[b][0][0], &s_lo[b][0], &s_part[0][wave][0], runs);
+      if (near)
+        vsym_repair(A, g, t, rl, e2, s, p, &s_hi[b][0][0], &s_w[b][0][0], &s_lo[b][0], &s_part[0][wave][0], near);
     }
 #pragma unroll
     for (int u = 0; u < 2; ++u)
