@@ -168,7 +168,10 @@ int nbody_potential(int64_t n, const double* x, const double* m, double* phi, co
  * particles in FP32C/FP32 and from 8192 in FP64 (or as nbody_config.pairs
  * says) each unordered pair is evaluated once and serves both particles (the
  * pair term changes sign when k and j swap), with sums in a fixed order; the
- * own pair is then always left out (its term is zero for eps > 0).
+ * own pair is then always left out (its term is zero for eps > 0).  Below 8192
+ * particles gx and gm may lie over x, w or m (not over each other), for example
+ * gx == w: the outputs are then stored after all reads, by kernels that take a
+ * little longer.
  * Errors: as nbody_accel. */
 int nbody_accel_vjp(int64_t n, const double* x, const double* m, const double* w,
                     double* gx, double* gm, const nbody_params* p, void* stream);

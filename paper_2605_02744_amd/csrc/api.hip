@@ -247,6 +247,12 @@ int check_dev_range(const void* p, size_t bytes, const char* name) {
   return NBODY_OK;
 }
 
+// Whether the arrays of na and nb doubles at p and q share memory.
+bool overlaps(const double* p, int64_t na, const double* q, int64_t nb) {
+  const uintptr_t a = reinterpret_cast<uintptr_t>(p), b = reinterpret_cast<uintptr_t>(q);
+  return a < b + sizeof(double) * (size_t)nb && b < a + sizeof(double) * (size_t)na;
+}
+
 constexpr int64_t kMaxN = int64_t(1) << 29;
 
 int check_common(int64_t n, const nbody_params* p, bool need_eps_rule) {
@@ -481,6 +487,10 @@ int nbody_accel_vjp(int64_t n, const double* x, const double* m, const double* w
   NB_TRY(check_dev_range(gm, b1, "gm"));
   hipStream_t s = static_cast<hipStream_t>(stream);
   PairConfig cfg = choose_config(n, p->precision, current_device());
+  // outputs over the inputs: a row kernel's workgroup stores its rows while others
+  // still read, the other kernels store after the last read
+  for (const auto& in : {std::make_pair(x, 3 * n), std::make_pair(w, 3 * n), std::make_pair(m, n)})
+    if (overlaps(gx, 3 * n, in.first, in.second) || overlaps(gm, n, in.first, in.second)) cfg.rows_eval = 0;
   int st = launch_vjp(n, x, m, w, gx, gm, p->G, p->eps, p->precision, (p->flags & NBODY_EXCLUDE_SELF) != 0, cfg, s);
   return finish(st, s, p, {{gx, 3 * n}, {gm, n}});
 }
