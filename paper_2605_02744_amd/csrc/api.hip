@@ -118,6 +118,15 @@ void* pair_scratch(const PairConfig& cfg, size_t bytes, int* status) {
   return cfg.scratch;
 }
 
+void* pair_scratch_ready(const PairConfig& cfg, size_t bytes) {
+  if (cfg.scratch) return bytes <= cfg.scratch_bytes ? cfg.scratch : nullptr;
+  const int dev = current_device();
+  if (dev < 0 || dev >= kMaxDev) return nullptr;
+  std::lock_guard<std::mutex> lk(g_ws_mu);
+  const Buf& b = g_ws[dev][cfg.ws_slot];
+  return b.bytes >= bytes ? b.p : nullptr;
+}
+
 void release_workspaces() {
   std::lock_guard<std::mutex> lk(g_ws_mu);
   for (int d = 0; d < kMaxDev; ++d)

@@ -99,6 +99,8 @@ struct PairConfig {
 // `bytes` of scratch for one all-pairs launch: cfg.scratch when the caller lent
 // memory (NBODY_EINVAL if it is smaller), else workspace slot cfg.ws_slot.
 void* pair_scratch(const PairConfig& cfg, size_t bytes, int* status);
+// The same if it is there already, else nullptr (no allocation).
+void* pair_scratch_ready(const PairConfig& cfg, size_t bytes);
 
 PairConfig choose_config(int64_t n, int precision, int device);
 void set_thread_config(const nbody_config& c);

@@ -240,10 +240,20 @@ int check_finite(const double* p, int64_t cnt, hipStream_t s, bool* all_finite) 
   return NBODY_OK;
 }
 
+// Whether s is being captured, where memory cannot be allocated.
+static bool capturing(hipStream_t s) {
+  hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(s, &cs) != hipSuccess) (void)hipGetLastError();
+  return cs != hipStreamCaptureStatusNone;
+}
+
 // The KDK loop on the row kernels: one launch a step, which evaluates the
 // positions x_k, kicks, and drifts into x_{k+1} in another buffer (other
 // workgroups still read x_k): traj's next slot, or x and a temporary in turn so
-// that x_nsteps lands in x.
+// that x_nsteps lands in x.  Where no temporary can be had (a capture before any
+// call has sized the workspace: nbody_accel and nsteps <= 1 need none on these
+// kernels; or no memory) the drift is a launch of its own, in place, bitwise the
+// same.
 static int run_kdk_rows(int64_t n, double* x, double* v, double* a, const double* m, double dt, int64_t nsteps, double G,
                         double eps, int precision, bool excl, bool acc_valid, const PairConfig& cfg, hipStream_t s,
                         double* traj) {
@@ -252,8 +262,14 @@ static int run_kdk_rows(int64_t n, double* x, double* v, double* a, const double
   const RowCall c{n, m, G, eps, precision, excl, cfg.rescue != 0, s};
   int st = NBODY_OK;
   double* tmp = nullptr;
-  if (!traj && nsteps > 1 && !(tmp = static_cast<double*>(pair_scratch(cfg, sizeof(double) * (size_t)n3, &st)))) return st;
-  auto at = [&](int64_t k) -> double* { return traj ? traj + (size_t)k * n3 : (nsteps - k) % 2 == 0 || k == 0 ? x : tmp; };
+  if (!traj && nsteps > 1) {
+    const size_t bytes = sizeof(double) * (size_t)n3;
+    tmp = static_cast<double*>(pair_scratch_ready(cfg, bytes));
+    if (!tmp && !capturing(s) && !(tmp = static_cast<double*>(pair_scratch(cfg, bytes, &st))) && st != NBODY_ENOMEM) return st;
+  }
+  auto at = [&](int64_t k) -> double* {
+    return traj ? traj + (size_t)k * n3 : !tmp || (nsteps - k) % 2 == 0 || k == 0 ? x : tmp;
+  };
   if (!acc_valid) {
     // a(x_0), with the first kick and drift where x_1 has a buffer of its own
     const bool fuse = nsteps > 0 && at(1) != at(0);
@@ -262,8 +278,9 @@ static int run_kdk_rows(int64_t n, double* x, double* v, double* a, const double
   }
   if (nsteps > 0 && acc_valid && (st = launch_kick_drift(n3, at(0), at(1), v, a, h, dt, 1, s))) return st;
   for (int64_t k = 1; k <= nsteps; ++k) {
-    const bool last = k == nsteps;
-    if ((st = launch_rows_kdk(c, at(k), last ? nullptr : at(k + 1), v, a, h, dt, last ? 1 : 2))) return st;
+    const bool last = k == nsteps, fuse = !last && at(k + 1) != at(k);
+    if ((st = launch_rows_kdk(c, at(k), fuse ? at(k + 1) : nullptr, v, a, h, dt, last ? 1 : 2))) return st;
+    if (!last && !fuse && (st = launch_kick_drift(n3, at(k), at(k + 1), v, a, h, dt, 0, s))) return st;
   }
   return NBODY_OK;
 }
