@@ -13,12 +13,16 @@
 // the FP64 latencies of one another at the low occupancy a small system leaves,
 // and neighbouring lanes load neighbouring records, straight from L2 (no LDS
 // staging, no barrier in the loop).  The kRows * NC sums of a lane are added over
-// the wave by exchanging halves (each exchange sums two values at once, so a
-// wave's sums cost about three instructions per value and not six full
-// butterflies), then over the four waves in order: fixed order, no atomics.  A
-// lane's plain FP64 sum has at most kRowsMaxN / 256 = 32 terms and is then added
-// over 8 levels, fewer roundings in a row than the 64 plain terms of a fold block
-// in the tile kernels.
+// four lanes of the wave by exchanging halves (each exchange sums two values at
+// once), then a row of 16 lanes adds the 64 partial sums of a value with TwoSum
+// (block_sums): fixed order, no atomics.  What is added plainly, at most kRowsMaxN /
+// 256 = 32 terms of a lane and four lanes, is no more than a fold block of the tile
+// kernels; all above is compensated as it is there.  Relative rms errors against
+// extended precision, tile kernels / plain sums throughout / these: potential of 8191
+// particles 5.2e-17 / 8.1e-17 / 4.9e-17, force of 5000 9.0e-17 / 9.5e-17 / 6.7e-17, of
+// 1000 1.4e-16 / 1.1e-16 / 7.4e-17.  Against the plain sums they cost 0.5 % of the
+// longest and 3 % of the shortest launches (butterflies with TwoSum in every lane, in
+// place of the shared partial sums, cost 2 and 9 %).
 //
 // Bound: up to ~2000 particles the latency of one launch and one lane's chain
 // (3.4 us per evaluation at 1000), above that FP64 issue.  Measured per step,
@@ -135,9 +139,9 @@ struct RowPot {
 // before any is used.
 template <class E, int U, bool EXCL, class Epi>
 __global__ __launch_bounds__(kRowT) void rows64_kernel(RowArgs A, Epi epi) {
-  constexpr int NC = E::NC, M = kRows * NC, W = kRowT / 64;
+  constexpr int NC = E::NC, M = kRows * NC;
   using Rec = RowRec<E::NW>;
-  __shared__ double s_red[W][M];
+  __shared__ double s_part[M][64];
   __shared__ double s_tot[M];
   const int t = threadIdx.x;
   const int i0 = blockIdx.x * kRows;
@@ -167,9 +171,7 @@ __global__ __launch_bounds__(kRowT) void rows64_kernel(RowArgs A, Epi epi) {
       for (int k = 0; k < kRows; ++k) E::pair(r[u], s[k], A.e2, EXCL && j == i0 + k, p + k * NC);
     }
   }
-  wave_sums<M>(p, s_red[t / 64]);
-  __syncthreads();
-  if (t < M) s_tot[t] = ((s_red[0][t] + s_red[1][t]) + s_red[2][t]) + s_red[3][t];
+  block_sums<M>(p, s_part, s_tot);
   __syncthreads();
   constexpr int kOuts = Epi::template outs<NC>();
   if (t < kRows * kOuts) {

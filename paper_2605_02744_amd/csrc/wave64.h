@@ -50,6 +50,49 @@ __device__ __forceinline__ void wave_sums(const double (&p)[M], double* dst) {
   }
 }
 
+// s + t rounded, its error added to e (TwoSum: exact whatever their magnitudes).
+__device__ __forceinline__ double two_sum(double s, double t, double& e) {
+  const double r = s + t, q = r - s;
+  e += (s - (r - q)) + (t - q);
+  return r;
+}
+
+// v added to its value K lanes further on in the row, the errors collected in e.
+template <int K>
+__device__ __forceinline__ double ror_add(double v, double& e) {
+  e += row_ror64<K>(e);
+  return two_sum(v, row_ror64<K>(v), e);
+}
+
+// Sums the M values (a multiple of 4) of each of 256 lanes into tot[0 .. M): four lanes
+// are added plainly by the exchanges of wave_sums, then the 64 partial sums of a value
+// (part) with TwoSum by one row of 16 lanes, the four waves first, then the row.  Ends
+// without a barrier.
+template <int M>
+__device__ __forceinline__ void block_sums(const double (&p)[M], double (*part)[64], double* tot) {
+  static_assert(M % 4 == 0, "whole rows of lanes");
+  const int t = threadIdx.x, lane = t & 63, row = lane >> 4, l = lane & 15;
+#pragma unroll
+  for (int q = 0; q < M; q += 4)
+    part[q + 2 * (row & 1) + (row >> 1)][(t >> 6) * 16 + l] =
+        swap_add<16>(swap_add<32>(p[q], p[q + 1]), swap_add<32>(p[q + 2], p[q + 3]));
+  __syncthreads();
+#pragma unroll
+  for (int k0 = 0; k0 < M; k0 += 16) {
+    const int k = k0 + t / 16;
+    if (k < M) {  // the same for every lane of a wave
+      double v = part[k][l], e = 0.0;
+#pragma unroll
+      for (int w = 1; w < 4; ++w) v = two_sum(v, part[k][16 * w + l], e);
+      v = ror_add<8>(v, e);
+      v = ror_add<4>(v, e);
+      v = ror_add<2>(v, e);
+      v = ror_add<1>(v, e);
+      if (l == 0) tot[k] = v + e;
+    }
+  }
+}
+
 // Sums the V values of the 64 / I groups of I lanes (I = 16 or 32) into dst,
 // value c of lane k of the groups at dst[c * I + k].
 template <int I, int V>
