@@ -138,7 +138,9 @@ int nbody_step(int64_t n, double* x, double* v, double* a, const double* m, doub
  *   (the self pair is always excluded), E = K + W, P = sum m v, L = sum m x x v.
  * These are the energies compared in Sec. 4.1 (Fig. 4) and the conserved
  * quantities of the integrator.  p->precision is ignored.  eps == 0 is
- * allowed (the self pair is excluded by index). */
+ * allowed (the self pair is excluded by index).  From 8192 particles on each
+ * unordered pair is evaluated once, as in nbody_potential; nbody_config has no
+ * effect on the form. */
 int nbody_energy(int64_t n, const double* x, const double* v, const double* m,
                  const nbody_params* p, double* out9, void* stream);
 
@@ -148,10 +150,9 @@ int nbody_energy(int64_t n, const double* x, const double* v, const double* m,
  * specific energy of particle i is |v_i|^2/2 + phi_i: the per-particle energy
  * distribution that Sec. 4.1 (Fig. 4) compares between the accelerated run
  * and the double-precision reference; sum_i m_i phi_i = 2 W of nbody_energy.
- * From 8192 particles on (or as nbody_config.pairs says; the same holds for
- * nbody_energy) each unordered pair is evaluated once and applied to both
- * particles, summed in a fixed order, with a workspace of per-distance sums as
- * nbody_accel's.
+ * From 8192 particles on (or as nbody_config.pairs says) each unordered pair is
+ * evaluated once and applied to both particles, summed in a fixed order, with a
+ * workspace of per-distance sums as nbody_accel's.
  * x: [3][n], m: [n], phi: [n] FP64 device memory, caller-owned; phi must not
  * alias x or m.  Errors: as nbody_accel (NBODY_ENONFINITE with
  * NBODY_CHECK_FINITE). */
@@ -349,7 +350,7 @@ typedef struct nbody_config {
   int32_t pairs;   /* form of the force kernel of nbody_accel and of the KDK
                       steps, of nbody_accel_vjp and the adjoint sweep, of
                       nbody_accel_jerk, nbody_accel_jerk_snap and the Hermite
-                      steps, of nbody_potential and nbody_energy:
+                      steps, of nbody_potential:
                       0 = automatic (the tuned choice for (n, precision),
                       else symmetric from 49152 particles on in FP32C/FP32
                       and from 8192 in FP64 for the force, from 12288 in

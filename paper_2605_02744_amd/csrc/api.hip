@@ -215,15 +215,15 @@ PairConfig choose_config(int64_t n, int precision, int device) {
   return c;
 }
 
-PairConfig potential_config(int64_t n, int device) {
-  const nbody_config& t = t_cfg;
+PairConfig potential_config(int64_t n, int device, bool set_form) {
+  const int pairs = set_form ? t_cfg.pairs : 0, split = set_form ? t_cfg.split : 0;
   PairConfig c;
   // a set split without a set form is the ordered kernel's, as are ipl and split for the force
-  const bool ordered = t.pairs == 1 || (t.split && t.pairs != 2);
-  c.sym = t.pairs == 2 || (!ordered && n >= kSymMinNPot) ? 1 : 0;
-  c.rows = !c.sym && !t.split && n <= kRowsMaxN ? 1 : 0;
-  c.launches = t.split;
-  c.split = t.split ? t.split : auto_split(n, 1, device);
+  const bool ordered = pairs == 1 || (split && pairs != 2);
+  c.sym = pairs == 2 || (!ordered && n >= kSymMinNPot) ? 1 : 0;
+  c.rows = !c.sym && !split && n <= kRowsMaxN ? 1 : 0;
+  c.launches = split;
+  c.split = split ? split : auto_split(n, 1, device);
   return c;
 }
 
@@ -684,7 +684,7 @@ int nbody_potential(int64_t n, const double* x, const double* m, double* phi, co
   NB_TRY(check_dev_range(phi, b1, "phi"));
   if ((const double*)phi == x || (const double*)phi == m) return set_error(NBODY_EINVAL, "phi must not alias x or m");
   hipStream_t s = static_cast<hipStream_t>(stream);
-  int st = launch_potential(n, x, m, p->eps, -p->G, phi, potential_config(n, current_device()), s);
+  int st = launch_potential(n, x, m, p->eps, -p->G, phi, potential_config(n, current_device(), true), s);
   return finish(st, s, p, {{phi, n}});
 }
 

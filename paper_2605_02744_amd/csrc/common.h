@@ -258,8 +258,11 @@ int launch_potential(int64_t n, const double* x, const double* m, double eps, do
 int launch_sym_pot64(int64_t n, const double* x, const double* m, double* phi, double scale, double eps,
                      const PairConfig& cfg, hipStream_t s);
 
-// The form of the potential of n particles on this thread (cfg of launch_potential).
-PairConfig potential_config(int64_t n, int device);
+// The form of the potential of n particles: with set_form as this thread's
+// configuration says, else the automatic one, which the diagnostics take (a form set
+// for the force would cost them: at 65536 particles a split of 1 4.2 ms instead of
+// 1.2, at 7000 the symmetric form in 3 launches 116 us instead of 48).
+PairConfig potential_config(int64_t n, int device, bool set_form);
 
 // Configuration of the batched (ensemble) kernels: mode 0 resident systems,
 // 1 resident with split systems, 2 streamed items, 3 per-step wave items, 4

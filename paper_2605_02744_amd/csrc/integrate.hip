@@ -214,7 +214,7 @@ int launch_energy(int64_t n, const double* x, const double* v, const double* m, 
   DD* part = reinterpret_cast<DD*>(ws);
   double* phi = reinterpret_cast<double*>(ws + part_bytes);
   if (n > 0) {
-    if ((st = launch_potential(n, x, m, eps, 1.0, phi, potential_config(n, current_device()), s))) return st;
+    if ((st = launch_potential(n, x, m, eps, 1.0, phi, potential_config(n, current_device(), false), s))) return st;
   }
   energy_partial_kernel<<<kRedBlocks, kRedBlock, 0, s>>>(n, x, v, m, phi, G, part);
   NB_LAUNCH_CHECK("energy_partial_kernel");
