@@ -358,8 +358,8 @@ typedef struct nbody_config {
                       acceleration + jerk, from 8192 in every precision for
                       acceleration + jerk + snap, from 8192 for the potential),
                       1 = ordered: every ordered pair evaluated for its i
-                      (below 8192 particles, and up to 24576 for the force in
-                      FP32C and FP32, by one launch per evaluation or step,
+                      (below 8192 particles, and up to 16384 for the force in
+                      FP32C, 16383 in FP32, by one launch per evaluation or step,
                       unless ipl or split is set);
                       2 = symmetric: every unordered pair evaluated once and
                       applied to both particles (a_j gets the opposite of i's
@@ -406,7 +406,7 @@ int nbody_set_config(const nbody_config* cfg);
  * in the library's per-device table, which automatic selection then uses for
  * that (n, precision).  The choice is per (n, precision) because the fastest
  * tiling depends on both, hence those arguments.  (For small systems,
- * below 8192 particles in FP64 and up to 24576 in FP32C and FP32, the automatic
+ * below 8192 particles in FP64, up to 16384 in FP32C and 16383 in FP32, the automatic
  * choice needs no tile configuration: one launch per evaluation, each workgroup
  * summing a few particles over every j; it stays the automatic choice if it beats
  * every tile configuration, and best then still names the fastest of those.)  If cache_path is non-NULL

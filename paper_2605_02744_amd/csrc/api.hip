@@ -172,7 +172,9 @@ static int auto_split(int64_t n, int ipl, int device) {
 }
 
 // Largest system whose force the row kernels serve.
-static int64_t rows_max_n(int precision) { return precision == NBODY_FP64 ? kRowsMaxN : kRowsMaxNForce32; }
+static int64_t rows_max_n(int precision) {
+  return precision == NBODY_FP64 ? kRowsMaxN : precision == NBODY_FP32C ? kRowsMaxNForce32C : kRowsMaxNForce32;
+}
 
 PairConfig choose_config(int64_t n, int precision, int device) {
   PairConfig c;

@@ -64,13 +64,13 @@ constexpr int64_t kSymMinNPot = 8192;
 // Largest systems of the row kernels.  In FP64 they serve every evaluation below
 // the symmetric kernels' sizes (their lanes' plain sums are also only as long as a
 // fold block up to there).  In FP32C and FP32 (us, rows against tile kernels with
-// their slice sums, flags and rescue): force 64 / 99 at 10000, 103 / 116 at 16384 (512
-// workgroups of 32 rows, all resident), 169 / 171 at 20000, 204 / 224 at 24000 and
-// 304 / 285 at 28000, which starts the second round of workgroups; jerk 66 / 77 and
-// VJP 75 / 84 at 8191, 155 / 102 and 175 / 113 at 10000; snap 108 / 130 at 8191,
-// where the symmetric kernel takes over.
+// their slice sums, flags and rescue): force in FP32C 64 / 99 at 10000, 103 / 116 at
+// 16384 (512 workgroups of 32 rows, two a CU, all at work at once; with a third on some
+// CUs 144 / 140 at 17201), in FP32 84 / 111 at 15563 and 91 / 88 at 16384, from where
+// the tile kernels take longer slices; jerk 66 / 77 and VJP 75 / 84 at 8191, 155 / 102
+// and 175 / 113 at 10000; snap 108 / 130 at 8191, where the symmetric kernel takes over.
 constexpr int64_t kRowsMaxN = 8191;
-constexpr int64_t kRowsMaxNForce32 = 24576;
+constexpr int64_t kRowsMaxNForce32C = 16384, kRowsMaxNForce32 = 16383;
 
 // Per-call configuration of the all-pairs kernels.
 struct PairConfig {

@@ -51,7 +51,7 @@ int launch_n(const Row32Args& A, const Epi& epi, hipStream_t s) {
 template <class E, class Epi>
 int launch(const RowCall& c, const double* x, const double* w, const double* u, const Epi& epi) {
   if (c.n == 0) return NBODY_OK;
-  if (c.n > kRowsMaxNForce32) return set_error(NBODY_EINVAL, "row kernel: n too large");
+  if (c.n > kRowsMaxNForce32C) return set_error(NBODY_EINVAL, "row kernel: n too large");
   const Row32Args A{(int)c.n, x, c.m, w, u, c.eps, c.G};
   constexpr bool kForce = E::NR == 1;
   if (c.precision == kFP32)
