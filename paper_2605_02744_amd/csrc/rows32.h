@@ -115,10 +115,13 @@ struct Row32Vjp {
 // goes (three operations on 13: 8.8 against 10.3 us at 1000, but 15.3 against 14.7
 // at 4096), else in a second pass over a block that holds one, and then corrects
 // them one by one: as many turns as the lane with most of them needs, not one for
-// every j that is close to some lane.
+// every j that is close to some lane.  Where a block took more than kDense turns (far
+// from the origin most pairs are close, the radius grows with |x|) the wave's next
+// block is corrected in step, in one pass without marks (dense).
+constexpr int kDense = 24;
 template <class E, bool NEAR, bool SMALL, bool EXCL, bool OWN>
 __device__ __forceinline__ void row32_block(const float4* rec, int own, const Row32& s, float e2, float (&p)[E::NC],
-                                            float& r2min) {
+                                            float& r2min, bool& dense) {
   const float4* lo = rec + E::NR * kJBlock;
   unsigned close[2] = {0u, 0u};  // pair jj of each half at bit 31 - jj
   auto sq = [&](const float* d) { return fma(d[2], d[2], fma(d[1], d[1], fma(d[0], d[0], e2))); };
@@ -168,6 +171,36 @@ __device__ __forceinline__ void row32_block(const float4* rec, int own, const Ro
     else if constexpr (NEAR) r2min = fminf(r2min, OWN && jj == own ? 3.0e38f : r2);
   }
   if constexpr (NEAR) {
+    // p with the rounded term of displacement d replaced by that of the full one
+    auto correct = [&](int jj, const float4* r, const float* d, bool near) {
+      float e[3];
+      full(jj, d, e);
+      const float ri = rsq(sq(d)), qi = rsq(sq(e));
+      const float f = (r[0].w * ri) * (ri * ri), g = (r[0].w * qi) * (qi * qi);
+#pragma unroll
+      for (int c = 0; c < 3; ++c) {
+        const float q = fma(g, e[c], fma(-f, d[c], p[c]));
+        p[c] = near ? q : p[c];
+      }
+    };
+    if (dense) {
+      if (!(r2min < s.rc2)) return;
+      r2min = 3.0e38f;
+      int many = 0;
+#pragma unroll 4
+      for (int jj = 0; jj < kJBlock; ++jj) {
+        float4 r[E::NR];
+        float d[3];
+        load(jj, r, d);
+        const float r2 = sq(d);
+        const bool near = r2 < s.rc2;
+        r2min = fminf(r2min, near ? 3.0e38f : r2);
+        many += near ? 1 : 0;
+        correct(jj, r, d, near && !(OWN && jj == own));
+      }
+      dense = __any(many > kDense);
+      return;
+    }
     if (!SMALL && r2min < s.rc2) {
       r2min = 3.0e38f;
 #pragma unroll 16
@@ -178,47 +211,65 @@ __device__ __forceinline__ void row32_block(const float4* rec, int own, const Ro
         mark(jj, sq(d));
       }
     }
+    dense = !SMALL && __any(__popc(close[0]) + __popc(close[1]) > kDense);
 #pragma unroll
     for (int half = 0; half < 2; ++half)
       while (close[half]) {
         const int bit = __clz((int)close[half]), jj = half * 32 + bit;
         close[half] &= ~(0x80000000u >> bit);
         float4 r[E::NR];
-        float d[3], e[3];
+        float d[3];
         load(jj, r, d);
-        full(jj, d, e);
-        const float ri = rsq(sq(d)), qi = rsq(sq(e));
-        const float f = (r[0].w * ri) * (ri * ri), g = (r[0].w * qi) * (qi * qi);
-#pragma unroll
-        for (int c = 0; c < 3; ++c) p[c] = fma(g, e[c], fma(-f, d[c], p[c]));
+        correct(jj, r, d, true);
       }
   }
 }
 
-// The FP64 sums of row i over all j by the whole workgroup (the rescue), into
-// out[0 .. 2]; red holds 3 doubles per wave.  The workgroup's lanes take j in
-// turn, lane sums are added over the wave and the waves in order.
-__device__ __forceinline__ void row32_rescue(const Row32Args& A, int i, bool excl, double* red, double* out) {
+// The FP64 sums over all j of the first R of the rows i0 + k, bit k of mask, by the whole
+// workgroup (the rescue), into out[k V .. k V + 2]; red holds 3 R doubles per wave.  The
+// workgroup's lanes take j in turn, lane sums are added over the wave and the waves in
+// order.  Returns the mask without these rows.
+template <int R, int V>
+__device__ __forceinline__ unsigned row32_rescue(const Row32Args& A, int i0, unsigned mask, bool excl, double* red,
+                                                 double* out) {
   const int t = threadIdx.x, T = blockDim.x;
   const double e2 = A.eps * A.eps;
-  const double xi = A.x[i], yi = A.x[A.n + i], zi = A.x[2 * A.n + i];
-  double v[3] = {0.0, 0.0, 0.0};
+  int row[R];
+  double xi[R][3], v[3 * R];
+#pragma unroll
+  for (int k = 0; k < R; ++k) {
+    row[k] = mask ? __ffs((int)mask) - 1 : row[k > 0 ? k - 1 : 0];
+    mask &= mask - 1;
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+      xi[k][c] = A.x[(size_t)c * A.n + i0 + row[k]];
+      v[3 * k + c] = 0.0;
+    }
+  }
   for (int j = t; j < A.n; j += T) {
-    const double dx = A.x[j] - xi, dy = A.x[A.n + j] - yi, dz = A.x[2 * A.n + j] - zi;
-    double f = A.m[j] * rsqrt64_cubed(fma(dz, dz, fma(dy, dy, fma(dx, dx, e2))));
-    if (excl && j == i) f = 0.0;
-    v[0] = fma(f, dx, v[0]);
-    v[1] = fma(f, dy, v[1]);
-    v[2] = fma(f, dz, v[2]);
+    const double xj = A.x[j], yj = A.x[A.n + j], zj = A.x[2 * (size_t)A.n + j], mj = A.m[j];
+#pragma unroll
+    for (int k = 0; k < R; ++k) {
+      const double dx = xj - xi[k][0], dy = yj - xi[k][1], dz = zj - xi[k][2];
+      double f = mj * rsqrt64_cubed(fma(dz, dz, fma(dy, dy, fma(dx, dx, e2))));
+      if (excl && j == i0 + row[k]) f = 0.0;
+      v[3 * k] = fma(f, dx, v[3 * k]);
+      v[3 * k + 1] = fma(f, dy, v[3 * k + 1]);
+      v[3 * k + 2] = fma(f, dz, v[3 * k + 2]);
+    }
   }
-  wave_sums<3>(v, red + 3 * (t / 64));
+  wave_sums<3 * R>(v, red + 3 * R * (t / 64));
   __syncthreads();
-  if (t < 3) {
+  if (t < 3 * R) {
     double s = red[t];
-    for (int w = 1; w < T / 64; ++w) s += red[3 * w + t];
-    out[t] = s;
+    for (int w = 1; w < T / 64; ++w) s += red[3 * R * w + t];
+    int k = row[0];
+#pragma unroll
+    for (int q = 1; q < R; ++q) k = t / 3 == q ? row[q] : k;
+    out[k * V + t % 3] = s;
   }
   __syncthreads();
+  return mask;
 }
 
 // float4s of a group of I lanes in LDS, and bytes of dynamic LDS of W waves.
@@ -269,6 +320,7 @@ __global__ __launch_bounds__(1024, E::NR == 1 ? 8 : E::NR == 2 ? 7 : 5) void row
   for (int c = 0; c < NC; ++c) hi[c] = lo[c] = 0.f;
 
   const int nblk = (n + kJBlock - 1) / kJBlock, ownb = i0 / kJBlock;
+  bool dense = false;
   for (int b0 = wave * GW; b0 < nblk; b0 += W * GW) {
     // the wave's GW blocks of records, padding past n far away and massless
     wave_sync();
@@ -296,8 +348,8 @@ __global__ __launch_bounds__(1024, E::NR == 1 ? 8 : E::NR == 2 ? 7 : 5) void row
 #pragma unroll
     for (int c = 0; c < NC; ++c) p[c] = 0.f;
     // the workgroup's rows lie in one block of j: its wave leaves the own pairs out
-    if (ownb >= b0 && ownb < b0 + GW) row32_block<E, NEAR, SMALL, EXCL, true>(rec + grp * kGroup, i - (b0 + grp) * kJBlock, s, e2, p, r2min);
-    else row32_block<E, NEAR, SMALL, EXCL, false>(rec + grp * kGroup, -1, s, e2, p, r2min);
+    if (ownb >= b0 && ownb < b0 + GW) row32_block<E, NEAR, SMALL, EXCL, true>(rec + grp * kGroup, i - (b0 + grp) * kJBlock, s, e2, p, r2min, dense);
+    else row32_block<E, NEAR, SMALL, EXCL, false>(rec + grp * kGroup, -1, s, e2, p, r2min, dense);
     if constexpr (EST) eacc = est_add(eacc, p[0], p[1], p[2], s.xinf, r2min);
 #pragma unroll
     for (int c = 0; c < NC; ++c) fold(hi[c], lo[c], p[c]);
@@ -332,10 +384,11 @@ __global__ __launch_bounds__(1024, E::NR == 1 ? 8 : E::NR == 2 ? 7 : 5) void row
       if (t == 0) s_mask = (unsigned)mask;
     }
     __syncthreads();
-    for (unsigned mask = s_mask; mask; mask &= mask - 1) {
-      const int k = __ffs((int)mask) - 1;
-      row32_rescue(A, i0 + k, EXCL, red, s_tot + k * V);
-    }
+    // two rows on each record read (four at a time spill scalar registers, which costs the
+    // smallest systems up to 8 %)
+    for (unsigned mask = (unsigned)__builtin_amdgcn_readfirstlane((int)s_mask); mask;)
+      mask = mask & (mask - 1) ? row32_rescue<2, V>(A, i0, mask, EXCL, red, s_tot)
+                               : row32_rescue<1, V>(A, i0, mask, EXCL, red, s_tot);
   }
   constexpr int kOuts = Epi::template outs<NC>();
   for (int q = t; q < I * kOuts; q += blockDim.x) {

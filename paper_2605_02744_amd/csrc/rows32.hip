@@ -13,18 +13,24 @@ namespace {
 // records staged for half as many rows cost more (force 14.7 / 21.6 us at 4096, 42.8
 // / 36.9 at 8191; jerk 24.5 / 33.8, 84.8 / 66.0).
 constexpr int64_t kRows16MaxN = 4096;
+// The force takes 16 in workgroups of half the waves from 8193 to 12288 particles, where
+// three half workgroups a CU take less than two whole ones (four from there on): force
+// of a Plummer sphere 53.8 / 54.1 us at 9011, 67.1 / 67.9 at 11468; of one around 100,
+// all of whose rows are corrected and rescued, 147 / 179 and 201 / 229 (tile kernels 151
+// and 211).
+constexpr int64_t kHalfMinN = 8193, kHalfMaxN = 12288;
 // The force marks its close pairs in the pair loop up to here (see row32_block).
 constexpr int64_t kMarkMaxN = 2048;
 // LDS a workgroup may take: records of 140 KB, so that the sums fit beside them.
 constexpr size_t kRow32MaxLds = size_t(140) << 10;
 
-// One wave per 64 / I blocks of j, at most 16 and as many as their records fit.
+// One wave per 64 / I blocks of j, at most `waves` and as many as their records fit.
 template <class E, int I, bool NEAR, bool SMALL, bool EXCL, bool EST, class Epi>
-int launch_i(const Row32Args& A, const Epi& epi, hipStream_t s) {
+int launch_i(const Row32Args& A, const Epi& epi, hipStream_t s, int waves = 16) {
   constexpr int GW = 64 / I;
   constexpr int kMost = (int)(kRow32MaxLds / row32_lds<E, I, NEAR>(1));
   const int nblk = (A.n + kJBlock - 1) / kJBlock;
-  const int W = std::min(std::min(16, kMost), (nblk + GW - 1) / GW);
+  const int W = std::min(std::min(waves, kMost), (nblk + GW - 1) / GW);
   const size_t lds = row32_lds<E, I, NEAR>(W);
   auto* kernel = rows32_kernel<E, I, NEAR, SMALL, EXCL, EST, Epi>;
   // more LDS than a kernel may take unasked: allowed once per kernel and device
@@ -45,6 +51,8 @@ int launch_n(const Row32Args& A, const Epi& epi, hipStream_t s) {
   if constexpr (NEAR && !E::kChoose)
     if (A.n <= kMarkMaxN) return launch_i<E, 16, NEAR, true, EXCL, EST>(A, epi, s);
   if (A.n <= kRows16MaxN) return launch_i<E, 16, NEAR, false, EXCL, EST>(A, epi, s);
+  if constexpr (E::NR == 1)
+    if (A.n >= kHalfMinN && A.n <= kHalfMaxN) return launch_i<E, 16, NEAR, false, EXCL, EST>(A, epi, s, 8);
   return launch_i<E, 32, NEAR, false, EXCL, EST>(A, epi, s);
 }
 
