@@ -206,7 +206,7 @@ int launch_rescue(int64_t n, const double* x, const double* m, double eps, doubl
 // place (x, a: [3][total], m: [total]; d_off: ncl + 1 system offsets, d_eps:
 // ncl softenings, all on the device).  Results do not depend on the lists'
 // order.
-int launch_ens_rescue(int32_t ncl, const int64_t* d_off, const double* d_eps, int64_t total, const double* x,
+int launch_ens_rescue(int32_t ncl, int64_t nmax, const int64_t* d_off, const double* d_eps, int64_t total, const double* x,
                       const double* m, double G, bool excl, const int* rcnt, const int* rlist, double* a,
                       hipStream_t s);
 

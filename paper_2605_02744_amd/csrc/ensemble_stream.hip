@@ -799,6 +799,68 @@ __global__ __launch_bounds__(kRBlock) void ens_rescue_kernel(int ncl, const int6
   }
 }
 
+// The same for layouts of small systems: blockIdx.x is the system, its listed rows are
+// dealt to the waves of its gridDim.y workgroups, kSRow at a time, and a workgroup of a
+// system without any leaves after one load.  The prefix sum of the kernel above costs
+// each of its workgroups a few microseconds however little is listed.  Whole step of the
+// ordered items with one workgroup per system and eighth of its rows, the system in LDS /
+// with the kernel above / with this one, in us: 8 systems of 64 particles 17.7 / 18.5 /
+// 17.7, 512 of 64 26.3 / 28.2 / 25.3, 4096 of 64 45 / 60 / 31; symmetric items of 512 of
+// 129 to 192 57 / 45 / 43, 4096 of 64 to 256 144 / 133 / 102, of 512 of 64 to 512 89 /
+// 63.5 / 62.8.
+constexpr int kSmBlock = 256;
+constexpr int kSRow = 2;  // rows of a wave at a time
+constexpr int64_t kSmMaxN = 256;  // largest system of such a layout
+template <bool EXCL>
+__global__ __launch_bounds__(kSmBlock) void ens_rescue_small_kernel(const int64_t* __restrict__ off,
+                                                                    const double* __restrict__ epsv, int64_t total,
+                                                                    const double* __restrict__ x,
+                                                                    const double* __restrict__ m, double G,
+                                                                    const int* __restrict__ rcnt,
+                                                                    const int* __restrict__ rlist,
+                                                                    double* __restrict__ a) {
+  constexpr int W = kSmBlock / 64;
+  __shared__ double red[W][kSRow * 3];
+  const int c = blockIdx.x, nf = rcnt[c];
+  const int t = threadIdx.x, wave = t / 64, lane = t % 64;
+  int r0 = ((int)blockIdx.y * W + wave) * kSRow;
+  if (r0 >= nf) return;
+  const int64_t o = off[c];
+  const int nc = (int)(off[c + 1] - o);
+  const double e2 = epsv[c] * epsv[c];
+  const double *xs = x + o, *ys = x + total + o, *zs = x + 2 * total + o, *ms = m + o;
+  for (; r0 < nf; r0 += (int)gridDim.y * W * kSRow) {
+    int li[kSRow];
+    double xi[kSRow], yi[kSRow], zi[kSRow], sum[3 * kSRow];
+#pragma unroll
+    for (int k = 0; k < kSRow; ++k) {
+      li[k] = rlist[o + min(r0 + k, nf - 1)];
+      xi[k] = xs[li[k]];
+      yi[k] = ys[li[k]];
+      zi[k] = zs[li[k]];
+      sum[3 * k] = sum[3 * k + 1] = sum[3 * k + 2] = 0.0;
+    }
+    for (int j = lane; j < nc; j += 64) {
+      const double xj = xs[j], yj = ys[j], zj = zs[j], mj = ms[j];
+#pragma unroll
+      for (int k = 0; k < kSRow; ++k) {
+        const double dx = xj - xi[k], dy = yj - yi[k], dz = zj - zi[k];
+        const double rr = rsqrt64(fma(dz, dz, fma(dy, dy, fma(dx, dx, e2))));
+        double sc = (mj * rr) * (rr * rr);
+        if (EXCL && j == li[k]) sc = 0.0;
+        sum[3 * k] = fma(sc, dx, sum[3 * k]);
+        sum[3 * k + 1] = fma(sc, dy, sum[3 * k + 1]);
+        sum[3 * k + 2] = fma(sc, dz, sum[3 * k + 2]);
+      }
+    }
+    wave_sums(sum, red[wave]);
+    wave_sync();
+    if (lane < 3 * kSRow && r0 + lane / 3 < nf)  // lane: row lane / 3, component lane % 3
+      a[(lane % 3) * total + o + (lane < 3 ? li[0] : li[1])] = G * red[wave][lane];
+    wave_sync();
+  }
+}
+
 __global__ void zero_counters_kernel(int* c, int n) {
   for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) c[i] = 0;
 }
@@ -808,7 +870,7 @@ struct SPlan {
   std::vector<int64_t> off;
   std::vector<double> eps;
   int precision = 0, device = 0, nwg = 0, ncl = 0, bitem = 0;
-  int64_t total = 0;
+  int64_t total = 0, nmax = 0;  // particles of all systems and (wave items) of the largest
   uint64_t wait_ticks = 0;  // bound of one counter wait, 100 MHz ticks
   int64_t* d_off = nullptr;
   double* d_eps = nullptr;
@@ -981,6 +1043,7 @@ int build_wplan(int32_t ncl, const int64_t* off, const double* eps, int precisio
       delete p;
       return set_error(NBODY_EUNSUPPORTED, "batched: a system of more than 2^24 particles");
     }
+    p->nmax = std::max(p->nmax, nc);
     for (int64_t i0 = 0; i0 < nc; i0 += 64) {
       items.push_back(SItem{c, (int)i0, (int)std::min<int64_t>(64, nc - i0), 1});
       cost.push_back((double)((nc + 63) / 64 * 64) + 48.0);
@@ -1110,7 +1173,7 @@ int launch_wsteps(const SPlan* p, double* x, double* v, double* a, const double*
       ens_waveforce_kernel<MODE, false><<<p->nwg, kSBlock, 0, s>>>(p->d_off, p->d_eps, p->d_items, p->d_wg_off,
                                                                    p->d_wg_list, rec, a, p->total, G, rcnt, rlist);
     NB_LAUNCH_CHECK("ens_waveforce_kernel");
-    if (rcnt) return launch_ens_rescue(p->ncl, p->d_off, p->d_eps, p->total, x, m, G, excl, rcnt, rlist, a, s);
+    if (rcnt) return launch_ens_rescue(p->ncl, p->nmax, p->d_off, p->d_eps, p->total, x, m, G, excl, rcnt, rlist, a, s);
     return NBODY_OK;
   };
   int st;
@@ -1133,10 +1196,21 @@ int launch_wsteps(const SPlan* p, double* x, double* v, double* a, const double*
 
 }  // namespace
 
-int launch_ens_rescue(int32_t ncl, const int64_t* d_off, const double* d_eps, int64_t total, const double* x,
+int launch_ens_rescue(int32_t ncl, int64_t nmax, const int64_t* d_off, const double* d_eps, int64_t total, const double* x,
                       const double* m, double G, bool excl, const int* rcnt, const int* rlist, double* a,
                       hipStream_t s) {
   if (ncl <= 0) return NBODY_OK;
+  if (nmax <= kSmMaxN) {
+    // every row of a system at once where there are few systems, one workgroup each where many
+    const int64_t rows = (kSmBlock / 64) * kSRow;
+    const dim3 g((unsigned)ncl, (unsigned)std::max<int64_t>(1, std::min<int64_t>((nmax + rows - 1) / rows, 4096 / ncl)));
+    if (excl)
+      ens_rescue_small_kernel<true><<<g, kSmBlock, 0, s>>>(d_off, d_eps, total, x, m, G, rcnt, rlist, a);
+    else
+      ens_rescue_small_kernel<false><<<g, kSmBlock, 0, s>>>(d_off, d_eps, total, x, m, G, rcnt, rlist, a);
+    NB_LAUNCH_CHECK("ens_rescue_small_kernel");
+    return NBODY_OK;
+  }
   // some two rounds of resident workgroups, so that CUs which are done early take more
   // of them (512 systems of 64 to 4096: 4, 7 and 16 a CU take 77, 71 and 69 us); with
   // very many systems each workgroup's own prefix sum over them weighs more

@@ -766,7 +766,7 @@ struct EPlan {
   std::vector<int64_t> off;
   std::vector<double> eps;
   int precision = 0, device = 0, ncl = 0, nwg = 0, nblocks = 0;
-  int64_t total = 0;
+  int64_t total = 0, nmax = 0;  // particles of all systems and of the largest
   ESys* d_sys = nullptr;
   EItem* d_blocks = nullptr;  // one per block of 64 (publish, reduce)
   EItem* d_items = nullptr;   // the parts (force)
@@ -869,6 +869,7 @@ int build_eplan(int32_t ncl, const int64_t* off, const double* eps, int precisio
   for (int c = 0; c < ncl; ++c) {
     const int64_t nc = off[c + 1] - off[c];
     ESys& S = sys[c];
+    p->nmax = std::max(p->nmax, nc);
     S.o = off[c];
     S.sbase = sbase;
     S.ibase = ibase;
@@ -981,7 +982,7 @@ int launch_esteps(const EPlan* p, double* x, double* v, double* a, const double*
                                                 p->d_iest, p->d_wslots, p->d_rhi, p->d_rlo, a, G, p->d_rcnt,
                                                 p->d_rlist);
       NB_LAUNCH_CHECK("esym_reduce_est_kernel");
-      return launch_ens_rescue(p->ncl, p->d_off, p->d_eps, p->total, x, m, G, excl, p->d_rcnt, p->d_rlist, a, s);
+      return launch_ens_rescue(p->ncl, p->nmax, p->d_off, p->d_eps, p->total, x, m, G, excl, p->d_rcnt, p->d_rlist, a, s);
     }
     esym_reduce_kernel<<<dim3(ew, 3), 256, 0, s>>>(p->nblocks, p->d_blocks, p->d_sys, p->total, p->d_islot,
                                                    p->d_slots, a, G);

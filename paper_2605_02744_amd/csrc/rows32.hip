@@ -16,8 +16,7 @@ constexpr int64_t kRows16MaxN = 4096;
 // The force takes 16 in workgroups of half the waves from 8193 to 12288 particles, where
 // three half workgroups a CU take less than two whole ones (four from there on): force
 // of a Plummer sphere 53.8 / 54.1 us at 9011, 67.1 / 67.9 at 11468; of one around 100,
-// all of whose rows are corrected and rescued, 147 / 179 and 201 / 229 (tile kernels 151
-// and 211).
+// most of whose pairs are corrected, 147 / 179 and 201 / 229 (tile kernels 151 and 211).
 constexpr int64_t kHalfMinN = 8193, kHalfMaxN = 12288;
 // The force marks its close pairs in the pair loop up to here (see row32_block).
 constexpr int64_t kMarkMaxN = 2048;

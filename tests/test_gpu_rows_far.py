@@ -1,5 +1,6 @@
-"""The FP32C row force where most pairs are corrected and rows rescued: a cluster far from
-the origin (the repair radius and the error estimate grow with |x|), one of two such parts
+"""The FP32C row force where most pairs are corrected and several rows of a workgroup
+rescued: a cluster far from the origin (the repair radius and the error estimate grow with
+|x|; at 100, 3 to 7 % of the rows are rescued), one of two such parts
 (blocks of many corrections next to blocks of few, in one wave), at the edges of the launch
 shapes (16 rows with marks in the pair loop, 16, 32, 16 in half workgroups, 32).
 
