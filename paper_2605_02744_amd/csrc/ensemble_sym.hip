@@ -787,10 +787,17 @@ struct EPlan {
   double* d_eps = nullptr;
   int* d_rcnt = nullptr;   // ncl
   int* d_rlist = nullptr;  // total
+  size_t bytes = 0;        // device memory, but for the item lists
+  uint64_t used = 0;       // g_eplan_clock at its last call
+  bool captured = false;   // a captured call's graph holds its pointers
 };
 
 std::mutex g_eplan_mu;
 std::vector<EPlan*> g_eplans;
+uint64_t g_eplan_clock = 0;
+// Plans kept on a device, by their memory: beyond this the one whose last call lies
+// furthest back goes (a captured one never does).  At least eight of the largest.
+constexpr size_t kEPlanCap = size_t(9) << 30;
 
 void free_eplan(EPlan* p) {
   for (void* q : {(void*)p->d_sys, (void*)p->d_blocks, (void*)p->d_items, (void*)p->d_islot, (void*)p->d_wg_off,
@@ -919,6 +926,8 @@ int build_eplan(int32_t ncl, const int64_t* off, const double* eps, int precisio
   p->nwg = nwg;
   p->nblocks = (int)blocks.size();
   const size_t nrec = (size_t)std::max<int64_t>(1, p->total);
+  p->bytes = (size_t)sbase * (f64 ? sizeof(double) : sizeof(float)) + (size_t)ibase * sizeof(double) + nrec * sizeof(double4) +
+             (precision == NBODY_FP32C ? ((size_t)iebase + (size_t)wbase + nrec) * sizeof(float) : 0);
   bool ok = eupload(&p->d_sys, sys) && eupload(&p->d_blocks, blocks) && eupload(&p->d_items, items) &&
             hipMalloc(&p->d_islot, sizeof(double) * (size_t)std::max<int64_t>(1, ibase)) == hipSuccess && eupload(&p->d_wg_off, wg_off) &&
             eupload(&p->d_wg_list, wg_list);
@@ -951,6 +960,24 @@ EPlan* find_eplan(int32_t ncl, const int64_t* off, const double* eps, int precis
     if (std::equal(p->off.begin(), p->off.end(), off) && std::equal(p->eps.begin(), p->eps.end(), eps)) return p;
   }
   return nullptr;
+}
+
+// Frees the device's plans, those not used for longest first, until the others and
+// `need` bytes are within cap; what is enqueued may still read them.
+void evict_eplans(int device, size_t need, size_t cap) {
+  for (bool waited = false;; waited = true) {
+    size_t held = need;
+    auto victim = g_eplans.end();
+    for (auto it = g_eplans.begin(); it != g_eplans.end(); ++it) {
+      if ((*it)->device != device) continue;
+      held += (*it)->bytes;
+      if (!(*it)->captured && (victim == g_eplans.end() || (*it)->used < (*victim)->used)) victim = it;
+    }
+    if (held <= cap || victim == g_eplans.end()) return;
+    if (!waited) (void)hipDeviceSynchronize();
+    free_eplan(*victim);
+    g_eplans.erase(victim);
+  }
 }
 
 // EST (FP32C with the rescue): each step's force also keeps the error
@@ -1048,17 +1075,26 @@ int run_batched_sym(int32_t ncl, const int64_t* off, const double* eps, double* 
   const int device = current_device();
   std::lock_guard<std::mutex> lk(g_eplan_mu);
   EPlan* p = find_eplan(ncl, off, eps, precision, device);
+  hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(s, &cs) != hipSuccess) (void)hipGetLastError();
+  const bool capture = cs != hipStreamCaptureStatusNone;
   if (!p) {
-    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(s, &cs) == hipSuccess && cs != hipStreamCaptureStatusNone)
+    if (capture)
       return set_error(NBODY_EINVAL, "batched: the plan for this layout must be built by one call outside stream capture");
+    evict_eplans(device, esym_slot_bytes(ncl, off, precision), kEPlanCap);
     int st = build_eplan(ncl, off, eps, precision, device, &p);
+    if (st == NBODY_ENOMEM) {
+      evict_eplans(device, 1, 0);
+      st = build_eplan(ncl, off, eps, precision, device, &p);
+    }
     if (st == NBODY_ENOMEM && bc.mode == 5)  // an automatic choice: without room for its slots, the ordered items
       return run_batched_stream(ncl, off, eps, x, v, a, m, dt, nsteps, G, precision, excl, acc_valid, 64, true, rescue,
                                 s);
     if (st) return st;
     g_eplans.push_back(p);
   }
+  p->used = ++g_eplan_clock;
+  p->captured = p->captured || capture;
   if (precision == NBODY_FP64) return launch_esteps64(p, x, v, a, m, dt, nsteps, G, acc_valid, excl, s);
   if (precision == NBODY_FP32C && rescue)
     return launch_esteps<true, true>(p, x, v, a, m, dt, nsteps, G, acc_valid, excl, s);
