@@ -790,6 +790,7 @@ struct EPlan {
   size_t bytes = 0;        // device memory, but for the item lists
   uint64_t used = 0;       // g_eplan_clock at its last call
   bool captured = false;   // a captured call's graph holds its pointers
+  bool none = false;       // no room when it was to be built: the ordered items serve the layout
 };
 
 std::mutex g_eplan_mu;
@@ -969,7 +970,7 @@ void evict_eplans(int device, size_t need, size_t cap) {
     size_t held = need;
     auto victim = g_eplans.end();
     for (auto it = g_eplans.begin(); it != g_eplans.end(); ++it) {
-      if ((*it)->device != device) continue;
+      if ((*it)->device != device || (*it)->none) continue;
       held += (*it)->bytes;
       if (!(*it)->captured && (victim == g_eplans.end() || (*it)->used < (*victim)->used)) victim = it;
     }
@@ -1087,12 +1088,23 @@ int run_batched_sym(int32_t ncl, const int64_t* off, const double* eps, double* 
       evict_eplans(device, 1, 0);
       st = build_eplan(ncl, off, eps, precision, device, &p);
     }
-    if (st == NBODY_ENOMEM && bc.mode == 5)  // an automatic choice: without room for its slots, the ordered items
-      return run_batched_stream(ncl, off, eps, x, v, a, m, dt, nsteps, G, precision, excl, acc_valid, 64, true, rescue,
-                                s);
-    if (st) return st;
+    if (st == NBODY_ENOMEM && bc.mode == 5) {
+      // an automatic choice: without room for its slots, the ordered items, from now on
+      // (later calls do not try again, and a captured one finds their plan)
+      p = new EPlan();
+      p->off.assign(off, off + ncl + 1);
+      p->eps.assign(eps, eps + ncl);
+      p->precision = precision;
+      p->device = device;
+      p->ncl = ncl;
+      p->none = true;
+    } else if (st) {
+      return st;
+    }
     g_eplans.push_back(p);
   }
+  if (p->none)
+    return run_batched_stream(ncl, off, eps, x, v, a, m, dt, nsteps, G, precision, excl, acc_valid, 64, true, rescue, s);
   p->used = ++g_eplan_clock;
   p->captured = p->captured || capture;
   if (precision == NBODY_FP64) return launch_esteps64(p, x, v, a, m, dt, nsteps, G, acc_valid, excl, s);

@@ -1,6 +1,7 @@
 """The plans that the symmetric ensemble items keep per layout (their slots take up to 1
 GiB each): a bound on what they hold together, plans given back and built again with
-the same results, and a captured plan that stays."""
+the same results, a captured plan that stays; and FP64 layouts whose slots find no room,
+which take the ordered items from then on, also under capture."""
 import numpy as np
 import pytest
 
@@ -65,3 +66,49 @@ def test_plans_are_bounded_and_captured_ones_stay(nb):
     torch.cuda.synchronize()
     assert torch.equal(sa, ref)
     assert torch.equal(accel(1, ta), first)
+
+
+def test_no_room_for_the_slots(nb):
+    """With 256 to 512 MiB of the card's memory left, a layout whose slots take 980 MiB."""
+    n = 74000
+    x, v, m = ics.plummer(n, seed=5)
+    tx, tv, tm = dev(x), dev(v), dev(m)
+    off, eps = [0, n], [0.01]
+    ta = torch.empty_like(tx)
+    nb.nbody_set_config(bsplit=3)
+    try:
+        nb.nbody_step_batched(off, eps, tx, tv, ta, tm, 1.0 / 512, 0, precision="fp64")
+    finally:
+        nb.nbody_set_config()
+    ordered = ta.clone()
+    torch.cuda.synchronize()
+    nb.nbody_finalize()
+    torch.cuda.empty_cache()
+    fill, chunk = [], 256 << 20
+    try:
+        while len(fill) < 2048:
+            try:
+                fill.append(torch.empty(chunk, dtype=torch.uint8, device="cuda:0"))
+            except torch.OutOfMemoryError:
+                break
+        assert len(fill) < 2048
+        print("%d chunks of 256 MiB fit" % len(fill), flush=True)
+        del fill[-1:]
+        torch.cuda.empty_cache()
+        nb.nbody_step_batched(off, eps, tx, tv, ta, tm, 1.0 / 512, 0, precision="fp64")
+        assert torch.equal(ta, ordered)
+        g = torch.cuda.CUDAGraph()
+        torch.cuda.synchronize()
+        with torch.cuda.graph(g):
+            nb.nbody_step_batched(off, eps, tx, tv, ta, tm, 1.0 / 512, 0, precision="fp64")
+        for _ in range(3):
+            ta.zero_()
+            g.replay()
+            torch.cuda.synchronize()
+            assert torch.equal(ta, ordered)
+        del g
+    finally:
+        fill.clear()
+        torch.cuda.empty_cache()
+        torch.cuda.synchronize()
+        nb.nbody_finalize()
