@@ -409,7 +409,8 @@ int nbody_set_config(const nbody_config* cfg);
  * below 8192 particles in FP64, up to 16384 in FP32C and 16383 in FP32, the automatic
  * choice needs no tile configuration: one launch per evaluation, each workgroup
  * summing a few particles over every j; it stays the automatic choice if it beats
- * every tile configuration, and best then still names the fastest of those.)  If cache_path is non-NULL
+ * every tile configuration, and best then still names the fastest of those; set as
+ * reported, ipl, split and pairs stand for the automatic choice at that (n, precision).)  If cache_path is non-NULL
  * the table is also appended there as one JSON object per line.  best (host,
  * may be NULL) receives the chosen configuration. */
 int nbody_tune(int64_t n, int32_t precision, const char* cache_path, nbody_config* best);
@@ -423,7 +424,8 @@ int nbody_tune(int64_t n, int32_t precision, const char* cache_path, nbody_confi
  * fastest whose state stays finite.  Candidates: the resident kernel with 1, 2
  * or 4 i-particles per lane per pass, the per-step items of 64 (mode 3) and,
  * their symmetric form (mode 4, or its FP64 form, which cannot be set: where it
- * is the fastest, later calls use it and best names the fastest of the others);
+ * is the fastest, later calls use it and best names the fastest of the others,
+ * which, set as reported, stands for it on that layout);
  * with allow_cooperative != 0 also the
  * split mode and the streamed kernel with items of 64, 256, 512 or 1024 particles
  * (the modes that need every workgroup of a launch resident at once). allow_cooperative = 2 keeps

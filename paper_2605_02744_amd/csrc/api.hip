@@ -182,7 +182,7 @@ PairConfig choose_config(int64_t n, int precision, int device) {
   // four for FP64 (whose rsqrt refinement leaves more latency to hide); fewer
   // for smaller FP64 systems so that they still spread over many workgroups
   c.ipl = precision != NBODY_FP64 ? 1 : (n >= (int64_t(1) << 18) ? 4 : (n >= (int64_t(1) << 14) ? 2 : 1));
-  const nbody_config& t = t_cfg;
+  nbody_config t = t_cfg;
   bool tuned = false;
   {
     std::lock_guard<std::mutex> lk(g_tune_mu);
@@ -193,6 +193,8 @@ PairConfig choose_config(int64_t n, int precision, int device) {
       c.sym = n >= (precision == NBODY_FP64 ? kSymMinN64 : kSymMinN) ? 1 : 0;
     }
   }
+  // what nbody_tune reported beside the row kernels, set as reported, stands for its choice
+  if (c.rows && t.ipl == c.ipl && t.split == c.split && t.pairs == (c.sym ? 2 : 1)) t.ipl = t.split = t.pairs = 0;
   c.sym_vjp = n >= kSymMinNVjp ? 1 : 0;
   c.sym_vjp64 = n >= kSymMinNVjp64 ? 1 : 0;
   c.sym_jerk = n >= kSymMinNJerk ? 1 : 0;
@@ -337,7 +339,7 @@ struct TunedBatch {
   int device, precision;
   std::vector<int64_t> off;
   std::vector<double> eps;
-  BatchConfig bc;
+  BatchConfig bc, set;  // the choice, and the one reported where the choice (mode 5) cannot be set
 };
 std::mutex g_tb_mu;
 std::vector<TunedBatch> g_tuned_batch;
@@ -350,18 +352,22 @@ BatchConfig batch_config_for(int32_t ncl, const int64_t* off, const double* eps,
   const nbody_config& t = t_cfg;
   BatchConfig bc;
   bc.rescue = t.rescue == 2 ? 0 : 1;
-  if (t.bsplit || t.bpass || t.bitem) {
-    bc.mode = t.bsplit;
-    bc.pass = t.bpass;
-    bc.item = t.bitem;
-    return bc;
+  const bool forced = t.bsplit || t.bpass || t.bitem;
+  bc.mode = t.bsplit;
+  bc.pass = t.bpass;
+  bc.item = t.bitem;
+  {
+    std::lock_guard<std::mutex> lk(g_tb_mu);
+    for (const TunedBatch& e : g_tuned_batch)
+      if (e.device == device && e.precision == precision && (int)e.eps.size() == ncl &&
+          std::equal(e.off.begin(), e.off.end(), off) && std::equal(e.eps.begin(), e.eps.end(), eps) &&
+          e.bc.rescue == bc.rescue) {
+        // (what the tuner reported in place of mode 5, set as reported, stands for that)
+        const BatchConfig& r = e.set;
+        if (!forced || (e.bc.mode == 5 && r.mode == bc.mode && r.pass == bc.pass && r.item == bc.item)) return e.bc;
+      }
   }
-  std::lock_guard<std::mutex> lk(g_tb_mu);
-  for (const TunedBatch& e : g_tuned_batch)
-    if (e.device == device && e.precision == precision && (int)e.eps.size() == ncl &&
-        std::equal(e.off.begin(), e.off.end(), off) && std::equal(e.eps.begin(), e.eps.end(), eps) &&
-        e.bc.rescue == bc.rescue)
-      return e.bc;
+  if (forced) return bc;
   // the symmetric per-step items where they pay (layouts whose systems mostly
   // span several blocks of 64), else the ordered ones; both carry the FP32C rescue
   const int sym = precision == NBODY_FP64 ? 5 : 4;
@@ -637,7 +643,7 @@ int nbody_tune_batched(int32_t ncl, const int64_t* off, const double* eps, const
   }
   cleanup();
   if (best_k < 0) return set_error(NBODY_ENONFINITE, "tune_batched: every configuration produced non-finite state");
-  const BatchConfig bc = cand[best_k];
+  const BatchConfig bc = cand[best_k], rc = set_k < 0 ? BatchConfig{} : cand[set_k];
   {
     std::lock_guard<std::mutex> lk(g_tb_mu);
     bool found = false;
@@ -646,13 +652,13 @@ int nbody_tune_batched(int32_t ncl, const int64_t* off, const double* eps, const
           std::equal(e.off.begin(), e.off.end(), off) && std::equal(e.eps.begin(), e.eps.end(), eps) &&
           e.bc.rescue == bc.rescue) {
         e.bc = bc;
+        e.set = rc;
         found = true;
       }
     if (!found)
       g_tuned_batch.push_back(TunedBatch{dev, p->precision, std::vector<int64_t>(off, off + ncl + 1),
-                                         std::vector<double>(eps, eps + ncl), bc});
+                                         std::vector<double>(eps, eps + ncl), bc, rc});
   }
-  const BatchConfig rc = set_k < 0 ? BatchConfig{} : cand[set_k];
   if (best) *best = nbody_config{0, 0, rc.mode, rc.pass, rc.item, 0, 0};
   return NBODY_OK;
 }
@@ -883,8 +889,8 @@ int nbody_tune(int64_t n, int32_t precision, const char* cache_path, nbody_confi
     if (f) {
       hipDeviceProp_t prop;
       (void)hipGetDeviceProperties(&prop, dev);
-      std::fprintf(f, "{\"arch\": \"%s\", \"n\": %lld, \"precision\": %d, \"ipl\": %d, \"split\": %d, \"pairs\": %d, \"ms\": %.6f, \"trials\": [",
-                   prop.gcnArchName, (long long)n, precision, bc.ipl, bc.split, bc.sym ? 2 : 1, best_ms);
+      std::fprintf(f, "{\"arch\": \"%s\", \"n\": %lld, \"precision\": %d, \"ipl\": %d, \"split\": %d, \"pairs\": %d, \"ms\": %.6f, \"rows\": %d, \"trials\": [",
+                   prop.gcnArchName, (long long)n, precision, bc.ipl, bc.split, bc.sym ? 2 : 1, best_ms, bc.rows);
       for (size_t k = 0; k < log.size(); ++k)
         std::fprintf(f, "%s[%d, %d, %d, %.6f]", k ? ", " : "", log[k].first.ipl, log[k].first.split,
                      log[k].first.sym ? 2 : 1, log[k].second);
