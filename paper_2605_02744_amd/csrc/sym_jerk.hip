@@ -158,10 +158,12 @@ __global__ void jsym_stage_kernel(SymArgs A, float4* __restrict__ rhi, float4* _
 // kSW * kST apart).  The j are visited in the rotated order of the pair loop, so
 // at each step the lanes of a row touch distinct j; the four rows of the wave,
 // which share the slots, take turns.  runs: the wave's flagged runs of kNearRun
-// steps. Only those are walked, a step without a close pair does nothing, and only
-// rows that corrected take turns (against all 64 steps of four turns: acceleration
-// + jerk 18.6 -> 17.8 ms at 204800 particles; against flags per lane and sub-block
-// of 16: 156 -> 149 us at 16384).
+// steps.  Only those are walked and a step without a close pair does nothing.  Against
+// the kernel that walked all 64 steps with four turns each (and its slot sums), in us,
+// 65536 particles with eps = 0.01 / 131072 with 1e-7: 2039 -> 1884 / 7217 -> 7217; around
+// 100, where nearly all pairs are close, 6221 -> 6265 / 24.7 -> 24.9 ms.  Records are
+// loaded before the look and all rows take their turn: loading after it and passing
+// over rows without a correction took 6576 / 26.1 ms there, and 1884 / 7167 on the others.
 __device__ __forceinline__ void jsym_repair(const SymArgs& A, int g, int t, int rl, float e2, const JSet& s,
                                             float (&p)[2][kJC], const float4* hi, const float4* vr, const float4* lo,
                                             float* part, unsigned runs) {
@@ -180,20 +182,22 @@ __device__ __forceinline__ void jsym_repair(const SymArgs& A, int g, int t, int 
       const int q = jj / kSR;
       const int jl = q * kSR + ((rl + jj) & (kSR - 1));
       const float4 rh = hi[q * 2 * kSR + (jl % kSR)];
-      const float rcj = lo[jl].w;
+      const float4 rlj = lo[jl];
+      float d[2][3];
       bool close[2];
 #pragma unroll
       for (int u = 0; u < 2; ++u) {
-        const float dx = rh.x - s.x[u], dy = rh.y - s.y[u], dz = rh.z - s.z[u];
-        close[u] = rc[u] >= 0.f && fmaf(dz, dz, fmaf(dy, dy, fmaf(dx, dx, e2))) < fmaxf(rc[u], rcj);
+        d[u][0] = rh.x - s.x[u];
+        d[u][1] = rh.y - s.y[u];
+        d[u][2] = rh.z - s.z[u];
+        close[u] = rc[u] >= 0.f && fmaf(d[u][2], d[u][2], fmaf(d[u][1], d[u][1], fmaf(d[u][0], d[u][0], e2))) < fmaxf(rc[u], rlj.w);
       }
       if (!__any(close[0] || close[1])) continue;
-      const float4 rlj = lo[jl];
       const float4 vj = vr[q * 2 * kSR + (jl % kSR)];
       float c[kJC] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
 #pragma unroll
       for (int u = 0; u < 2; ++u) {
-        const float dx = rh.x - s.x[u], dy = rh.y - s.y[u], dz = rh.z - s.z[u];
+        const float dx = d[u][0], dy = d[u][1], dz = d[u][2];
         if (close[u]) {
           const int i = g * kSI + u * kSL + t;
           const double xa = A.x[i], ya = A.x[n + i], za = A.x[2 * n + i];
@@ -215,9 +219,7 @@ __device__ __forceinline__ void jsym_repair(const SymArgs& A, int g, int t, int 
         }
       }
       const bool corrected = c[0] != 0.f || c[1] != 0.f || c[2] != 0.f || c[3] != 0.f || c[4] != 0.f || c[5] != 0.f;
-      const unsigned long long turns = __ballot(corrected);
       for (int r = 0; r < 4; ++r) {
-        if (!(turns >> (r * kSR) & 0xFFFFu)) continue;
         if (wrow == r && corrected) {
 #pragma unroll
           for (int k = 0; k < kJC; ++k) part[k * kSW * kST + jl] += c[k];

@@ -153,10 +153,12 @@ __global__ void ssym_stage_kernel(SymArgs A, float4* __restrict__ rhi, float4* _
 // kSW * kST apart).  The j are visited in the rotated order of the pair loop, so
 // at each step the lanes of a row touch distinct j; the four rows of the wave,
 // which share the slots, take turns.  runs: the wave's flagged runs of kNearRun
-// steps. Only those are walked, a step without a close pair does nothing, and only
-// rows that corrected take turns (against all 64 steps of four turns:
-// acceleration, jerk and snap 36.2 -> 34.8 ms at 204800 particles; against flags
-// per lane and sub-block of 16: 264 -> 258 us at 16384).
+// steps.  Only those are walked and a step without a close pair does nothing.  Against
+// the kernel that walked all 64 steps with four turns each (and its slot sums), in us,
+// 65536 particles with eps = 0.01 / 131072 with 1e-7: 3667 -> 3466 / 13443 -> 13363; around
+// 100, where nearly all pairs are close, 10.58 -> 10.54 / 41.66 -> 41.66 ms.  Records are
+// loaded before the look and all rows take their turn: loading after it and passing
+// over rows without a correction took 11.18 / 43.9 ms there, and 3483 / 13336 on the others.
 __device__ __forceinline__ void ssym_repair(const SymArgs& A, int g, int t, int rl, float e2, const SSet& s,
                                             float (&p)[2][kSC], const float4* hi, const float4* vr, const float4* ar,
                                             const float4* lo, float* part, unsigned runs) {
@@ -175,15 +177,17 @@ __device__ __forceinline__ void ssym_repair(const SymArgs& A, int g, int t, int 
       const int q = jj / kSR;
       const int jl = q * kSR + ((rl + jj) & (kSR - 1));
       const float4 rh = hi[q * 2 * kSR + (jl % kSR)];
-      const float rcj = lo[jl].w;
+      const float4 rlj = lo[jl];
+      float d[2][3];
       bool close[2];
 #pragma unroll
       for (int u = 0; u < 2; ++u) {
-        const float dx = rh.x - s.x[u], dy = rh.y - s.y[u], dz = rh.z - s.z[u];
-        close[u] = rc[u] >= 0.f && fmaf(dz, dz, fmaf(dy, dy, fmaf(dx, dx, e2))) < fmaxf(rc[u], rcj);
+        d[u][0] = rh.x - s.x[u];
+        d[u][1] = rh.y - s.y[u];
+        d[u][2] = rh.z - s.z[u];
+        close[u] = rc[u] >= 0.f && fmaf(d[u][2], d[u][2], fmaf(d[u][1], d[u][1], fmaf(d[u][0], d[u][0], e2))) < fmaxf(rc[u], rlj.w);
       }
       if (!__any(close[0] || close[1])) continue;
-      const float4 rlj = lo[jl];
       const float4 vj = vr[q * 2 * kSR + (jl % kSR)];
       const float4 acj = ar[q * 2 * kSR + (jl % kSR)];
       float c[kSC];
@@ -192,7 +196,7 @@ __device__ __forceinline__ void ssym_repair(const SymArgs& A, int g, int t, int 
       bool any = false;
 #pragma unroll
       for (int u = 0; u < 2; ++u) {
-        const float dx = rh.x - s.x[u], dy = rh.y - s.y[u], dz = rh.z - s.z[u];
+        const float dx = d[u][0], dy = d[u][1], dz = d[u][2];
         if (close[u]) {
           const int i = g * kSI + u * kSL + t;
           const double xa = A.x[i], ya = A.x[n + i], za = A.x[2 * n + i];
@@ -213,9 +217,7 @@ __device__ __forceinline__ void ssym_repair(const SymArgs& A, int g, int t, int 
           any = true;
         }
       }
-      const unsigned long long turns = __ballot(any);
       for (int r = 0; r < 4; ++r) {
-        if (!(turns >> (r * kSR) & 0xFFFFu)) continue;
         if (wrow == r && any) {
 #pragma unroll
           for (int k = 0; k < kSC; ++k) part[k * kSW * kST + jl] += c[k];
