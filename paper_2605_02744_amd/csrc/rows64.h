@@ -14,15 +14,15 @@
 // and neighbouring lanes load neighbouring records, straight from L2 (no LDS
 // staging, no barrier in the loop).  The kRows * NC sums of a lane are added over
 // four lanes of the wave by exchanging halves (each exchange sums two values at
-// once), then a row of 16 lanes adds the 64 partial sums of a value with TwoSum
+// once), then 4 to 16 lanes add the 64 partial sums of a value with TwoSum
 // (block_sums): fixed order, no atomics.  What is added plainly, at most kRowsMaxN /
 // 256 = 32 terms of a lane and four lanes, is no more than a fold block of the tile
 // kernels; all above is compensated as it is there.  Relative rms errors against
 // extended precision, tile kernels / plain sums throughout / these: potential of 8191
 // particles 5.2e-17 / 8.1e-17 / 4.9e-17, force of 5000 9.0e-17 / 9.5e-17 / 6.7e-17, of
-// 1000 1.4e-16 / 1.1e-16 / 7.4e-17.  Against the plain sums they cost 0.5 % of the
-// longest and 3 % of the shortest launches (butterflies with TwoSum in every lane, in
-// place of the shared partial sums, cost 2 and 9 %).
+// 1000 1.4e-16 / 1.1e-16 / 7.4e-17.  They cost up to 1 % of the longer
+// launches and up to 4 % of the shorter ones (KDK step at 1024 4.69 -> 4.73 us, at 2048
+// 6.8 -> 7.0, force at 5000 20.2 -> 20.5, fourth-order step there 36.6 -> 36.9).
 //
 // Bound: up to ~2000 particles the latency of one launch and one lane's chain
 // (3.4 us per evaluation at 1000), above that FP64 issue.  Measured per step,

@@ -57,39 +57,44 @@ __device__ __forceinline__ double two_sum(double s, double t, double& e) {
   return r;
 }
 
-// v added to its value K lanes further on in the row, the errors collected in e.
-template <int K>
-__device__ __forceinline__ double ror_add(double v, double& e) {
-  e += row_ror64<K>(e);
-  return two_sum(v, row_ror64<K>(v), e);
+// v added to the value of another lane (a DPP control that pairs lanes off), the errors
+// collected in e; both lanes end up with the same.
+template <int CTRL>
+__device__ __forceinline__ double dpp_add(double v, double& e) {
+  auto other = [](double w) {
+    const int l = __builtin_amdgcn_mov_dpp(__double2loint(w), CTRL, 0xF, 0xF, true);
+    const int h = __builtin_amdgcn_mov_dpp(__double2hiint(w), CTRL, 0xF, 0xF, true);
+    return __hiloint2double(h, l);
+  };
+  e += other(e);
+  return two_sum(v, other(v), e);
 }
 
 // Sums the M values (a multiple of 4) of each of 256 lanes into tot[0 .. M): four lanes
 // are added plainly by the exchanges of wave_sums, then the 64 partial sums of a value
-// (part) with TwoSum by one row of 16 lanes, the four waves first, then the row.  Ends
-// without a barrier.
+// (part) with TwoSum by P lanes, each its share in order, then between them: quads
+// (lane pairs, then the pairs of a quad), halves of a row of 16, rows.  P is what lets
+// 256 lanes take all values at once.  Ends without a barrier.
 template <int M>
 __device__ __forceinline__ void block_sums(const double (&p)[M], double (*part)[64], double* tot) {
-  static_assert(M % 4 == 0, "whole rows of lanes");
-  const int t = threadIdx.x, lane = t & 63, row = lane >> 4, l = lane & 15;
+  static_assert(M % 4 == 0 && M <= 64, "whole rows of lanes, and four lanes a value");
+  constexpr int P = M <= 16 ? 16 : M <= 32 ? 8 : 4;
+  const int t = threadIdx.x, lane = t & 63, row = lane >> 4;
 #pragma unroll
   for (int q = 0; q < M; q += 4)
-    part[q + 2 * (row & 1) + (row >> 1)][(t >> 6) * 16 + l] =
+    part[q + 2 * (row & 1) + (row >> 1)][(t >> 6) * 16 + (lane & 15)] =
         swap_add<16>(swap_add<32>(p[q], p[q + 1]), swap_add<32>(p[q + 2], p[q + 3]));
   __syncthreads();
+  const int k = t / P, l = t % P;
+  if (k < M) {  // the same for a value's lanes
+    double v = part[k][l], e = 0.0;
 #pragma unroll
-  for (int k0 = 0; k0 < M; k0 += 16) {
-    const int k = k0 + t / 16;
-    if (k < M) {  // the same for every lane of a wave
-      double v = part[k][l], e = 0.0;
-#pragma unroll
-      for (int w = 1; w < 4; ++w) v = two_sum(v, part[k][16 * w + l], e);
-      v = ror_add<8>(v, e);
-      v = ror_add<4>(v, e);
-      v = ror_add<2>(v, e);
-      v = ror_add<1>(v, e);
-      if (l == 0) tot[k] = v + e;
-    }
+    for (int w = 1; w < 64 / P; ++w) v = two_sum(v, part[k][P * w + l], e);
+    v = dpp_add<0xB1>(v, e);                          // quad_perm [1, 0, 3, 2]
+    v = dpp_add<0x4E>(v, e);                          // quad_perm [2, 3, 0, 1]
+    if constexpr (P >= 8) v = dpp_add<0x141>(v, e);   // row_half_mirror
+    if constexpr (P >= 16) v = dpp_add<0x140>(v, e);  // row_mirror
+    if (l == 0) tot[k] = v + e;
   }
 }
 
