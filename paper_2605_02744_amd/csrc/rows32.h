@@ -22,7 +22,9 @@
 //
 // Bound: up to ~2000 particles the latency of one launch and one lane's chain of 64
 // terms (about 5.5 cycles an instruction with one wave per SIMD), above that VALU
-// issue with 16 waves per workgroup and two workgroups per CU.  FP32C in us, tile
+// issue, with 16 waves per workgroup and two workgroups per CU where two fit into its
+// 160 KB of LDS: the force (66 KB) and the FP32 jerk and VJP; FP32C jerk and VJP (97 KB)
+// and the snap (97 and 129 KB) have one.  FP32C in us, tile
 // kernels with their slice sums, flags and rescue -> rows: force 27.9 -> 9.9 at
 // 1000, 37 -> 16 at 4096, 80 -> 35 at 8191, 195 -> 87 at 14336; jerk 28 -> 11.4 at
 // 1000, 34 -> 24 at 4096, 78 -> 67 at 8191; VJP 30 -> 12.7, 36 -> 26, 85 -> 75; snap

@@ -84,12 +84,6 @@ __device__ __forceinline__ int ring_end(const SymArgs& A, int g) {
   return (A.half && g >= A.nb / 2) ? A.dmax : A.dmax + 1;
 }
 
-// Steps of a sub-block that the jerk and snap kernels flag together (a bit per run, the
-// same for the whole wave) for the near-field repair, which walks the flagged runs.  Runs
-// of 8 are as fast to 24000 particles and 1 % slower from 65536 on (jerk 7255 against 7171
-// us, snap 13396 against 13256 at 131072, eps = 1e-7).
-constexpr int kNearRun = kSR;
-
 // Squared repair radius (the near-field rule of the ordered kernel, with its
 // n-dependent factor f given): a pair closer than max(f |x|_inf, kNearEps eps)
 // to the particle at (xa, ya, za) gets float-float displacements.

@@ -76,12 +76,12 @@ __device__ __forceinline__ void ssym_step(const SSet& s, const float4* __restric
   }
 }
 
-template <bool NEAR, int K0, int... K>
+template <bool NEAR, int... K>
 __device__ __forceinline__ void ssym_sub(const SSet& s, const float4* __restrict__ rowp,
                                          const float4* __restrict__ rowv, const float4* __restrict__ rowa, float e2,
                                          float (&p)[2][kSC], float (&r2min)[2], float (&aj)[kSC],
                                          std::integer_sequence<int, K...>) {
-  (ssym_step<K0 + K, NEAR>(s, rowp, rowv, rowa, e2, p, r2min, aj), ...);
+  (ssym_step<K, NEAR>(s, rowp, rowv, rowa, e2, p, r2min, aj), ...);
 }
 
 // Loads the two i of lane t of I-block g (padding: far away, massless, at
@@ -152,8 +152,8 @@ __global__ void ssym_stage_kernel(SymArgs A, float4* __restrict__ rhi, float4* _
 // sums p and times -m_i to the wave's j-side sums of the tile (part: components
 // kSW * kST apart).  The j are visited in the rotated order of the pair loop, so
 // at each step the lanes of a row touch distinct j; the four rows of the wave,
-// which share the slots, take turns.  runs: the wave's flagged runs of kNearRun
-// steps.  Only those are walked and a step without a close pair does nothing.  Against
+// which share the slots, take turns.  near: the wave's flagged sub-blocks, bit q.
+// Only those are walked and a step without a close pair does nothing.  Against
 // the kernel that walked all 64 steps with four turns each (and its slot sums), in us,
 // 65536 particles with eps = 0.01 / 131072 with 1e-7: 3667 -> 3466 / 13443 -> 13363; around
 // 100, where nearly all pairs are close, 10.58 -> 10.54 / 41.66 -> 41.66 ms.  Records are
@@ -161,7 +161,7 @@ __global__ void ssym_stage_kernel(SymArgs A, float4* __restrict__ rhi, float4* _
 // over rows without a correction took 11.18 / 43.9 ms there, and 3483 / 13336 on the others.
 __device__ __forceinline__ void ssym_repair(const SymArgs& A, int g, int t, int rl, float e2, const SSet& s,
                                             float (&p)[2][kSC], const float4* hi, const float4* vr, const float4* ar,
-                                            const float4* lo, float* part, unsigned runs) {
+                                            const float4* lo, float* part, unsigned near) {
   const int n = A.n;
   const int wrow = (t & 63) / kSR;
   float rc[2];
@@ -170,11 +170,10 @@ __device__ __forceinline__ void ssym_repair(const SymArgs& A, int g, int t, int 
     const int i = g * kSI + u * kSL + t;
     rc[u] = i < n ? sym_rc2f(s.x[u], s.y[u], s.z[u], A.eps, A.fx) : -1.f;
   }
-  while (runs) {
-    const int k0 = (__ffs((int)runs) - 1) * kNearRun;
-    runs &= runs - 1;
-    for (int jj = k0; jj < k0 + kNearRun; ++jj) {
-      const int q = jj / kSR;
+  while (near) {
+    const int q = __ffs((int)near) - 1;
+    near &= near - 1;
+    for (int jj = 0; jj < kSR; ++jj) {
       const int jl = q * kSR + ((rl + jj) & (kSR - 1));
       const float4 rh = hi[q * 2 * kSR + (jl % kSR)];
       const float4 rlj = lo[jl];
@@ -305,22 +304,17 @@ __global__ __launch_bounds__(kSL, 3) void ssym_kernel(SymArgs A) {
     for (int u = 0; u < 2; ++u)
 #pragma unroll
       for (int c = 0; c < kSC; ++c) p[u][c] = 0.f;
-    unsigned runs = 0u;  // the runs of steps that may hold a pair to repair, for any lane
+    unsigned near = 0u;  // the sub-blocks that may hold a pair to repair, for any lane
 #pragma unroll 1
     for (int q = 0; q < 4; ++q) {
       float aj[kSC];
 #pragma unroll
       for (int c = 0; c < kSC; ++c) aj[c] = 0.f;
-      auto run = [&](auto k0) {
-        float r2min[2] = {3.0e38f, 3.0e38f};
-        ssym_sub<NEAR, decltype(k0)::value>(s, &s_hi[b][q][rl], &s_v[b][q][rl], &s_a[b][q][rl], e2, p, r2min, aj, std::make_integer_sequence<int, kNearRun>{});
-        if constexpr (NEAR)
-          // (no branch here: the compiler would move the pair loop's sums past it and spill)
-          runs |= (unsigned)(__ballot((r2min[0] < thr[0]) | (r2min[1] < thr[1])) != 0ull)
-                  << ((q * kSR + decltype(k0)::value) / kNearRun);
-      };
-      run(std::integral_constant<int, 0>{});
-      if constexpr (kNearRun < kSR) run(std::integral_constant<int, kNearRun % kSR>{});
+      float r2min[2] = {3.0e38f, 3.0e38f};
+      ssym_sub<NEAR>(s, &s_hi[b][q][rl], &s_v[b][q][rl], &s_a[b][q][rl], e2, p, r2min, aj, std::make_integer_sequence<int, kSR>{});
+      if constexpr (NEAR)
+        // (no branch here: the compiler would move the pair loop's sums past it and spill)
+        near |= (unsigned)(__ballot((r2min[0] < thr[0]) | (r2min[1] < thr[1])) != 0ull) << q;
       // the four rows' sums of the same 16 j, as in the acceleration
 #pragma unroll
       for (int c = 0; c < kSC; ++c) {
@@ -330,9 +324,9 @@ __global__ __launch_bounds__(kSL, 3) void ssym_kernel(SymArgs A) {
       }
     }
     if constexpr (NEAR) {
-      if (runs)
+      if (near)
         ssym_repair(A, g, t, rl, e2, s, p, &s_hi[b][0][0], &s_v[b][0][0], &s_a[b][0][0], &s_lo[b][0],
-                    &s_part[0][wave][0], runs);
+                    &s_part[0][wave][0], near);
     }
 #pragma unroll
     for (int u = 0; u < 2; ++u)
