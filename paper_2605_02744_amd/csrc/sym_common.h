@@ -118,10 +118,10 @@ __device__ __forceinline__ void add_run(const S* __restrict__ q, size_t stride, 
 // 3 <= c < 6 at outm[(c - 3) n + p], c >= 6 at outs[(c - 6) n + p]): the j-side tile sums of distances d_lo .. d_lo + D - 1
 // that were evaluated (slots of type S: float, or double for the FP64 kernel),
 // and the i-side sums of the chunk's workgroups; the first chunk starts from
-// the distance-0 sums pd, the last applies G.  A workgroup (p-block, c) holds 64
-// particles, one per lane; its kRedW waves each add a run of the slots and a run
-// of the i-side sums, wave 0 also what came before, and wave 0 adds the waves'
-// sums in wave order.  Only the largest distance can be missing for some
+// the distance-0 sums pd, the last applies G.  A workgroup (p-block, c) holds P
+// particles in each of W shares of its lanes; a share adds a run of the slots and a
+// run of the i-side sums, the first also what came before, and it adds the shares'
+// sums in order.  Only the largest distance can be missing for some
 // blocks (the opposite block of an even ring, visited from the lower half only).
 // With eo (FP32C force only; the workgroups of row c = C do it, a lane per
 // particle): the error estimate of the rescue in eo[npad], the far side's shares
@@ -135,7 +135,10 @@ __device__ __forceinline__ void add_run(const S* __restrict__ q, size_t stride, 
 // One thread per (particle, component) with four loads in flight, and the estimate's
 // loads one after another behind component 0, took 12.2 us for the FP64 VJP at 9973
 // and 54 us for the FP32C force at 65536; runs of eight over four waves and the
-// estimate in workgroups of its own take 7.2 and 31.
+// estimate in workgroups of its own take 7.2 and 31.  A ring in several launches has its
+// slot sums beside the pair kernels, where memory is free and fewer waves are the better:
+// one share (FP32C acceleration + jerk at 2^20 471 -> 468 ms, VJP at 409600 81.8 -> 81.1,
+// FP64 acceleration + jerk at 204800 34.0 -> 33.6; at 131072 the two lie within 0.5 %).
 //
 // PI: the i-side sums' type.  A workgroup of one tile folds one FP32 sum, which a float
 // holds exactly: half the bytes of the largest part of a small ring's slots (FP32C VJP
@@ -144,7 +147,7 @@ __device__ __forceinline__ void add_run(const S* __restrict__ q, size_t stride, 
 // With KDK (FP64 force), the thread that finishes a component also kicks it, drifts it
 // and writes it into the next step's record: two launches a step instead of four (51.5
 // -> 48.4 us a step at 8192 particles, 132.4 -> 129.9 at 16384, 407 -> 403 at 30011).
-constexpr int kRedP = 64, kRedW = 4;
+constexpr int kRedLanes = 256;
 struct KdkTail {
   double* x = nullptr;
   double* v = nullptr;
@@ -153,22 +156,20 @@ struct KdkTail {
   double h = 0.0, dt = 0.0;
   int nk = 0, drift = 0;
 };
-inline dim3 sym_reduce_grid(int64_t n, int comps, bool est) {
-  return dim3((unsigned)((n + kRedP - 1) / kRedP), (unsigned)(comps + (est ? 1 : 0)));
-}
-template <int C, typename S, bool KDK = false, typename PI = double>
-__global__ __launch_bounds__(kRedP * kRedW) void sym_reduce_kernel(
+template <int W, int C, typename S, bool KDK, typename PI>
+__global__ __launch_bounds__(kRedLanes) void sym_reduce_kernel(
     int n, int npad, int nb, int dmax, int half, int d_lo, int D, int nparts, const S* __restrict__ pj,
     const PI* __restrict__ pi, const double* __restrict__ pd, double* __restrict__ out, double* __restrict__ outm,
     double G, int first, int last, const float* __restrict__ pe = nullptr, const float* __restrict__ pw = nullptr,
     const float* __restrict__ ed = nullptr, float* __restrict__ eo = nullptr, int pds = 1,
     double* __restrict__ outs = nullptr, KdkTail kdk = KdkTail()) {
-  __shared__ double red[C == 1 ? 2 : 1][kRedW - 1][kRedP];
+  constexpr int P = kRedLanes / W;
+  __shared__ double red[C == 1 ? 2 : 1][W > 1 ? W - 1 : 1][P];
   const int c = blockIdx.y;
-  const int wave = threadIdx.x / kRedP;
+  const int wave = threadIdx.x / P;
   const bool est = c == C;
-  const int p = est ? blockIdx.x * (kRedP * kRedW) + threadIdx.x : blockIdx.x * kRedP + threadIdx.x % kRedP;
-  if (est && p >= n) return;  // (p < npad in the others: a multiple of kRedP)
+  const int p = est ? blockIdx.x * kRedLanes + threadIdx.x : blockIdx.x * P + threadIdx.x % P;
+  if (est && p >= n) return;  // (p < npad in the others: a multiple of P)
   const int J = p / kSI;
   const int send = min(D, dmax - d_lo + 1);  // slots of this chunk within the ring
   // the last slot of the ring is dropped where its block pair was not evaluated
@@ -197,16 +198,16 @@ __global__ __launch_bounds__(kRedP * kRedW) void sym_reduce_kernel(
     if (first) add_run(pd + at, stride, 0, pds, add);
     else if (p < n) acc = *o;
   }
-  add_run(pj + at, stride, sn * wave / kRedW, sn * (wave + 1) / kRedW, [&](S v) { add((double)v); });
-  add_run(pi + at, stride, nparts * wave / kRedW, nparts * (wave + 1) / kRedW, [&](PI v) { add((double)v); });
+  add_run(pj + at, stride, sn * wave / W, sn * (wave + 1) / W, [&](S v) { add((double)v); });
+  add_run(pi + at, stride, nparts * wave / W, nparts * (wave + 1) / W, [&](PI v) { add((double)v); });
   if (wave > 0) {
-    red[0][wave - 1][threadIdx.x % kRedP] = acc;
-    if constexpr (C == 1) red[1][wave - 1][threadIdx.x % kRedP] = lo;
+    red[0][wave - 1][threadIdx.x % P] = acc;
+    if constexpr (C == 1) red[1][wave - 1][threadIdx.x % P] = lo;
   }
   __syncthreads();
   if (wave > 0 || p >= n) return;
 #pragma unroll
-  for (int w = 0; w < kRedW - 1; ++w) {
+  for (int w = 0; w < W - 1; ++w) {
     add(red[0][w][threadIdx.x]);
     if constexpr (C == 1) lo += red[1][w][threadIdx.x];
   }
@@ -226,6 +227,16 @@ __global__ __launch_bounds__(kRedP * kRedW) void sym_reduce_kernel(
       kdk.rec[2 * ((size_t)(c / 2) * npad + p) + (c & 1)] = xe;
     }
   }
+}
+
+// Its launch on s: est with the estimate's workgroups, beside for a ring in several launches.
+template <int C, typename S, bool KDK = false, typename PI = double, class... Args>
+int launch_sym_reduce(int64_t n, bool est, bool beside, hipStream_t s, Args... args) {
+  auto grid = [&](int p) { return dim3((unsigned)((n + p - 1) / p), (unsigned)(C + (est ? 1 : 0))); };
+  if (beside) sym_reduce_kernel<1, C, S, KDK, PI><<<grid(kRedLanes), kRedLanes, 0, s>>>(args...);
+  else sym_reduce_kernel<4, C, S, KDK, PI><<<grid(kRedLanes / 4), kRedLanes, 0, s>>>(args...);
+  NB_LAUNCH_CHECK("sym_reduce_kernel");
+  return NBODY_OK;
 }
 
 }  // namespace

@@ -428,23 +428,18 @@ int launch_sym64(int64_t n, const double* x, const double* m, const double* w, c
     NB_LAUNCH_CHECK("sym64_kernel");
     return NBODY_OK;
   };
-  const dim3 rg = sym_reduce_grid(n, NC, false);
   auto sum = [&](int c, int b, hipStream_t rs) -> int {
     Sym64Args B = A;
     slots(b, B);
     auto red = [&](auto kdk) {
-      sym_reduce_kernel<NC, double, decltype(kdk)::value><<<rg, kRedP * kRedW, 0, rs>>>(
-          (int)n, (int)npad, nb, dmax, half, 1 + c * D, dmax > 0 ? D : 0, dmax > 0 ? nparts : 0, B.pj, B.pi, A.pd, out,
-          outm, G, c == 0, c + 1 >= nchunks, nullptr, nullptr, nullptr, nullptr, pds, outs, tail);
+      return launch_sym_reduce<NC, double, decltype(kdk)::value>(
+          n, false, nchunks >= 2, rs, (int)n, (int)npad, nb, dmax, half, 1 + c * D,
+          dmax > 0 ? D : 0, dmax > 0 ? nparts : 0, B.pj, B.pi, A.pd, out, outm, G, c == 0,
+          c + 1 >= nchunks, nullptr, nullptr, nullptr, nullptr, pds, outs, tail);
     };
-    if constexpr (NC == 3) {
-      if (step) red(std::true_type{});
-      else red(std::false_type{});
-    } else {
-      red(std::false_type{});
-    }
-    NB_LAUNCH_CHECK("sym_reduce_kernel");
-    return NBODY_OK;
+    if constexpr (NC == 3)
+      if (step) return red(std::true_type{});
+    return red(std::false_type{});
   };
   if (dmax == 0) return (st = pair(0, 0)) ? st : sum(0, 0, s);
   return run_sym_chunks(side, s, nchunks, nbuf, [](hipStream_t) { return NBODY_OK; }, pair, sum);

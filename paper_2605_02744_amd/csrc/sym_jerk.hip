@@ -555,13 +555,10 @@ int launch_sym_jerk(int64_t n, const double* x, const double* v, const double* m
     NB_LAUNCH_CHECK("jsym_diag_kernel");
     return NBODY_OK;
   };
-  const dim3 rg = sym_reduce_grid(n, kJC, false);
   if (dmax == 0) {
     if ((st = diag(s))) return st;
-    sym_reduce_kernel<kJC, float><<<rg, kRedP * kRedW, 0, s>>>((int)n, (int)npad, nb, dmax, half, 1, 0, 0, A.pj, A.pi, pd, a, jk, G,
-                                              1, 1, nullptr, nullptr, nullptr, nullptr, pds);
-    NB_LAUNCH_CHECK("sym_reduce_kernel");
-    return NBODY_OK;
+    return launch_sym_reduce<kJC, float>(n, false, false, s, (int)n, (int)npad, nb, dmax, half, 1,
+        0, 0, A.pj, A.pi, pd, a, jk, G, 1, 1, nullptr, nullptr, nullptr, nullptr, pds);
   }
   auto pair = [&](int c, int b) -> int {
     SymArgs B = A;
@@ -577,14 +574,11 @@ int launch_sym_jerk(int64_t n, const double* x, const double* v, const double* m
     SymArgs B = A;
     slots(b, B);
     auto red = [&](auto* pi) {
-      sym_reduce_kernel<kJC, float, false, std::remove_pointer_t<decltype(pi)>><<<rg, kRedP * kRedW, 0, rs>>>(
-          (int)n, (int)npad, nb, dmax, half, 1 + c * D, D, nparts, B.pj, pi, pd, a, jk, G, c == 0, c == nchunks - 1,
-          nullptr, nullptr, nullptr, nullptr, pds);
+      return launch_sym_reduce<kJC, float, false, std::remove_pointer_t<decltype(pi)>>(
+          n, false, nchunks >= 2, rs, (int)n, (int)npad, nb, dmax, half, 1 + c * D, D, nparts, B.pj,
+          pi, pd, a, jk, G, c == 0, c == nchunks - 1, nullptr, nullptr, nullptr, nullptr, pds);
     };
-    if (T == 1) red(reinterpret_cast<float*>(B.pi));
-    else red(B.pi);
-    NB_LAUNCH_CHECK("sym_reduce_kernel");
-    return NBODY_OK;
+    return T == 1 ? red(reinterpret_cast<float*>(B.pi)) : red(B.pi);
   };
   return run_sym_chunks(side, s, nchunks, nbuf, diag, pair, sum);
 }

@@ -687,12 +687,11 @@ int launch_sym_accel(int64_t n, const double* x, const double* m, double* a, dou
     NB_LAUNCH_CHECK("sym_diag_kernel");
     return NBODY_OK;
   };
-  const dim3 rg = sym_reduce_grid(n, 3, rescue);
   if (dmax == 0) {
     if ((st = diag(s))) return st;
-    sym_reduce_kernel<3, float><<<rg, kRedP * kRedW, 0, s>>>((int)n, (int)npad, nb, dmax, half, 1, 0, 0, A.pj, A.pi, pd, a, nullptr, G,
-                                            1, 1, A.pe, A.pw, ed, eo, pds);
-    NB_LAUNCH_CHECK("sym_reduce_kernel");
+    if ((st = launch_sym_reduce<3, float>(n, rescue, false, s, (int)n, (int)npad, nb, dmax, half, 1,
+        0, 0, A.pj, A.pi, pd, a, nullptr, G, 1, 1, A.pe, A.pw, ed, eo, pds)))
+      return st;
   } else {
     auto pair = [&](int c, int b) -> int {
       SymArgs B = A;
@@ -708,10 +707,9 @@ int launch_sym_accel(int64_t n, const double* x, const double* m, double* a, dou
     auto sum = [&](int c, int b, hipStream_t rs) -> int {
       SymArgs B = A;
       slots(b, B);
-      sym_reduce_kernel<3, float><<<rg, kRedP * kRedW, 0, rs>>>((int)n, (int)npad, nb, dmax, half, 1 + c * D, D, nparts, B.pj, B.pi,
-                                               pd, a, nullptr, G, c == 0, c == nchunks - 1, B.pe, B.pw, ed, eo, pds);
-      NB_LAUNCH_CHECK("sym_reduce_kernel");
-      return NBODY_OK;
+      return launch_sym_reduce<3, float>(n, rescue, nchunks >= 2, rs, (int)n, (int)npad, nb, dmax,
+          half, 1 + c * D, D, nparts, B.pj, B.pi, pd, a, nullptr, G, c == 0, c == nchunks - 1, B.pe,
+          B.pw, ed, eo, pds);
     };
     if ((st = run_sym_chunks(side, s, nchunks, nbuf, diag, pair, sum))) return st;
   }

@@ -526,13 +526,10 @@ int launch_sym_vjp(int64_t n, const double* x, const double* m, const double* w,
     NB_LAUNCH_CHECK("vsym_diag_kernel");
     return NBODY_OK;
   };
-  const dim3 rg = sym_reduce_grid(n, kVC, false);
   if (dmax == 0) {
     if ((st = diag(s))) return st;
-    sym_reduce_kernel<kVC, float><<<rg, kRedP * kRedW, 0, s>>>((int)n, (int)npad, nb, dmax, half, 1, 0, 0, A.pj, A.pi, pd, gx, gm, G,
-                                              1, 1, nullptr, nullptr, nullptr, nullptr, pds);
-    NB_LAUNCH_CHECK("sym_reduce_kernel");
-    return NBODY_OK;
+    return launch_sym_reduce<kVC, float>(n, false, false, s, (int)n, (int)npad, nb, dmax, half, 1,
+        0, 0, A.pj, A.pi, pd, gx, gm, G, 1, 1, nullptr, nullptr, nullptr, nullptr, pds);
   }
   auto pair = [&](int c, int b) -> int {
     SymArgs B = A;
@@ -548,14 +545,11 @@ int launch_sym_vjp(int64_t n, const double* x, const double* m, const double* w,
     SymArgs B = A;
     slots(b, B);
     auto red = [&](auto* pi) {
-      sym_reduce_kernel<kVC, float, false, std::remove_pointer_t<decltype(pi)>><<<rg, kRedP * kRedW, 0, rs>>>(
-          (int)n, (int)npad, nb, dmax, half, 1 + c * D, D, nparts, B.pj, pi, pd, gx, gm, G, c == 0, c == nchunks - 1,
-          nullptr, nullptr, nullptr, nullptr, pds);
+      return launch_sym_reduce<kVC, float, false, std::remove_pointer_t<decltype(pi)>>(
+          n, false, nchunks >= 2, rs, (int)n, (int)npad, nb, dmax, half, 1 + c * D, D, nparts, B.pj,
+          pi, pd, gx, gm, G, c == 0, c == nchunks - 1, nullptr, nullptr, nullptr, nullptr, pds);
     };
-    if (T == 1) red(reinterpret_cast<float*>(B.pi));
-    else red(B.pi);
-    NB_LAUNCH_CHECK("sym_reduce_kernel");
-    return NBODY_OK;
+    return T == 1 ? red(reinterpret_cast<float*>(B.pi)) : red(B.pi);
   };
   return run_sym_chunks(side, s, nchunks, nbuf, diag, pair, sum);
 }
