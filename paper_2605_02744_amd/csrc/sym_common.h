@@ -118,10 +118,9 @@ __device__ __forceinline__ void add_run(const S* __restrict__ q, size_t stride, 
 // 3 <= c < 6 at outm[(c - 3) n + p], c >= 6 at outs[(c - 6) n + p]): the j-side tile sums of distances d_lo .. d_lo + D - 1
 // that were evaluated (slots of type S: float, or double for the FP64 kernel),
 // and the i-side sums of the chunk's workgroups; the first chunk starts from
-// the distance-0 sums pd, the last applies G.  A workgroup (p-block, c) holds P
-// particles in each of W shares of its lanes; a share adds a run of the slots and a
-// run of the i-side sums, the first also what came before, and it adds the shares'
-// sums in order.  Only the largest distance can be missing for some
+// the distance-0 sums pd, the last applies G.  A particle's sums are taken in
+// kRedShares shares, by W lanes: a share is a run of the slots and a run of the i-side
+// sums, the first also what came before, and the shares' sums are added in order.  Only the largest distance can be missing for some
 // blocks (the opposite block of an even ring, visited from the lower half only).
 // With eo (FP32C force only; the workgroups of row c = C do it, a lane per
 // particle): the error estimate of the rescue in eo[npad], the far side's shares
@@ -135,10 +134,14 @@ __device__ __forceinline__ void add_run(const S* __restrict__ q, size_t stride, 
 // One thread per (particle, component) with four loads in flight, and the estimate's
 // loads one after another behind component 0, took 12.2 us for the FP64 VJP at 9973
 // and 54 us for the FP32C force at 65536; runs of eight over four waves and the
-// estimate in workgroups of its own take 7.2 and 31.  A ring in several launches has its
-// slot sums beside the pair kernels, where memory is free and fewer waves are the better:
-// one share (FP32C acceleration + jerk at 2^20 471 -> 468 ms, VJP at 409600 81.8 -> 81.1,
-// FP64 acceleration + jerk at 204800 34.0 -> 33.6; at 131072 the two lie within 0.5 %).
+// estimate in workgroups of its own take 7.2 and 31.  An FP32 ring in several launches
+// has its slot sums beside the pair kernels, where memory is free and fewer waves are the
+// better: one lane takes the shares in turn (FP32C acceleration + jerk at 2^20 463.2 ->
+// 458.6 ms, 483.8 -> 481.7 on a slower card, VJP at 409600 79.5 -> 79.0, the others from
+// 131072 on up to 0.4 %; in FP64 it was 0.3 % slower).
+// The shares themselves stay: four short sums, added, err half as much as one long one
+// (relative rms of the FP64 force of 2^20 particles 4.8e-16 against 8.9e-16, of the
+// acceleration beside the jerk at 204800 1.8e-16 against 3.4e-16).
 //
 // PI: the i-side sums' type.  A workgroup of one tile folds one FP32 sum, which a float
 // holds exactly: half the bytes of the largest part of a small ring's slots (FP32C VJP
@@ -147,7 +150,7 @@ __device__ __forceinline__ void add_run(const S* __restrict__ q, size_t stride, 
 // With KDK (FP64 force), the thread that finishes a component also kicks it, drifts it
 // and writes it into the next step's record: two launches a step instead of four (51.5
 // -> 48.4 us a step at 8192 particles, 132.4 -> 129.9 at 16384, 407 -> 403 at 30011).
-constexpr int kRedLanes = 256;
+constexpr int kRedLanes = 256, kRedShares = 4;
 struct KdkTail {
   double* x = nullptr;
   double* v = nullptr;
@@ -163,6 +166,7 @@ __global__ __launch_bounds__(kRedLanes) void sym_reduce_kernel(
     double G, int first, int last, const float* __restrict__ pe = nullptr, const float* __restrict__ pw = nullptr,
     const float* __restrict__ ed = nullptr, float* __restrict__ eo = nullptr, int pds = 1,
     double* __restrict__ outs = nullptr, KdkTail kdk = KdkTail()) {
+  static_assert(W == 1 || W == kRedShares, "a lane takes all shares or one");
   constexpr int P = kRedLanes / W;
   __shared__ double red[C == 1 ? 2 : 1][W > 1 ? W - 1 : 1][P];
   const int c = blockIdx.y;
@@ -188,28 +192,43 @@ __global__ __launch_bounds__(kRedLanes) void sym_reduce_kernel(
   // the potential's terms all have one sign, so plain adds would not average
   // their roundings out as they do for the others' random signs
   double acc = 0.0, lo = 0.0;
-  auto add = [&](double v) {
-    if constexpr (C == 1) fold(acc, lo, v);
-    else acc += v;
+  auto add = [](double& a, double& l, double v) {
+    if constexpr (C == 1) fold(a, l, v);
+    else a += v;
   };
   double* o = c < 3 ? out + (size_t)c * n + p : c < 6 ? outm + (size_t)(c - 3) * n + p : outs + (size_t)(c - 6) * n + p;
   const size_t stride = (size_t)C * npad, at = (size_t)c * npad + p;
+  auto runs = [&](int q, double& a, double& l) {
+    add_run(pj + at, stride, sn * q / kRedShares, sn * (q + 1) / kRedShares, [&](S v) { add(a, l, (double)v); });
+    add_run(pi + at, stride, nparts * q / kRedShares, nparts * (q + 1) / kRedShares, [&](PI v) { add(a, l, (double)v); });
+  };
   if (wave == 0) {
-    if (first) add_run(pd + at, stride, 0, pds, add);
+    if (first) add_run(pd + at, stride, 0, pds, [&](double v) { add(acc, lo, v); });
     else if (p < n) acc = *o;
   }
-  add_run(pj + at, stride, sn * wave / W, sn * (wave + 1) / W, [&](S v) { add((double)v); });
-  add_run(pi + at, stride, nparts * wave / W, nparts * (wave + 1) / W, [&](PI v) { add((double)v); });
-  if (wave > 0) {
-    red[0][wave - 1][threadIdx.x % P] = acc;
-    if constexpr (C == 1) red[1][wave - 1][threadIdx.x % P] = lo;
+  runs(wave, acc, lo);
+  if constexpr (W > 1) {
+    if (wave > 0) {
+      red[0][wave - 1][threadIdx.x % P] = acc;
+      if constexpr (C == 1) red[1][wave - 1][threadIdx.x % P] = lo;
+    }
+    __syncthreads();
   }
-  __syncthreads();
   if (wave > 0 || p >= n) return;
+  auto join = [&](double a, double l) {
+    add(acc, lo, a);
+    if constexpr (C == 1) lo += l;
+  };
+  if constexpr (W > 1) {
 #pragma unroll
-  for (int w = 0; w < W - 1; ++w) {
-    add(red[0][w][threadIdx.x]);
-    if constexpr (C == 1) lo += red[1][w][threadIdx.x];
+    for (int q = 0; q < kRedShares - 1; ++q) join(red[0][q][threadIdx.x], red[C == 1 ? 1 : 0][q][threadIdx.x]);
+  } else {
+#pragma unroll 1
+    for (int q = 1; q < kRedShares; ++q) {
+      double a = 0.0, l = 0.0;
+      runs(q, a, l);
+      join(a, l);
+    }
   }
   if constexpr (C == 1) acc += lo;
   const double r = last ? G * acc : acc;
@@ -229,12 +248,19 @@ __global__ __launch_bounds__(kRedLanes) void sym_reduce_kernel(
   }
 }
 
-// Its launch on s: est with the estimate's workgroups, beside for a ring in several launches.
+// Its launch on s: est with the estimate's workgroups, beside for a lane that takes all
+// shares (an FP32 ring in several launches).
 template <int C, typename S, bool KDK = false, typename PI = double, class... Args>
 int launch_sym_reduce(int64_t n, bool est, bool beside, hipStream_t s, Args... args) {
   auto grid = [&](int p) { return dim3((unsigned)((n + p - 1) / p), (unsigned)(C + (est ? 1 : 0))); };
-  if (beside) sym_reduce_kernel<1, C, S, KDK, PI><<<grid(kRedLanes), kRedLanes, 0, s>>>(args...);
-  else sym_reduce_kernel<4, C, S, KDK, PI><<<grid(kRedLanes / 4), kRedLanes, 0, s>>>(args...);
+  if constexpr (std::is_same_v<S, float>) {
+    if (beside) {
+      sym_reduce_kernel<1, C, S, KDK, PI><<<grid(kRedLanes), kRedLanes, 0, s>>>(args...);
+      NB_LAUNCH_CHECK("sym_reduce_kernel");
+      return NBODY_OK;
+    }
+  }
+  sym_reduce_kernel<kRedShares, C, S, KDK, PI><<<grid(kRedLanes / kRedShares), kRedLanes, 0, s>>>(args...);
   NB_LAUNCH_CHECK("sym_reduce_kernel");
   return NBODY_OK;
 }
