@@ -134,11 +134,12 @@ __device__ __forceinline__ void add_run(const S* __restrict__ q, size_t stride, 
 // One thread per (particle, component) with four loads in flight, and the estimate's
 // loads one after another behind component 0, took 12.2 us for the FP64 VJP at 9973
 // and 54 us for the FP32C force at 65536; runs of eight over four waves and the
-// estimate in workgroups of its own take 7.2 and 31.  An FP32 ring in several launches
+// estimate in workgroups of its own take 7.2 and 31.  A ring in several launches
 // has its slot sums beside the pair kernels, where memory is free and fewer waves are the
 // better: one lane takes the shares in turn (FP32C acceleration + jerk at 2^20 463.2 ->
-// 458.6 ms, 483.8 -> 481.7 on a slower card, VJP at 409600 79.5 -> 79.0, the others from
-// 131072 on up to 0.4 %; in FP64 it was 0.3 % slower).
+// 458.6 ms, 483.8 -> 481.7 on a slower card, VJP at 409600 79.5 -> 79.0; FP64 acceleration
+// + jerk and VJP at 2^20 892 -> 876 and 968 -> 965 ms, at 262144 53.8 -> 53.4 and 60.9 ->
+// 60.2, means of four runs there that spread by 2 %; the others from 131072 on alike).
 // The shares themselves stay: four short sums, added, err half as much as one long one
 // (relative rms of the FP64 force of 2^20 particles 4.8e-16 against 8.9e-16, of the
 // acceleration beside the jerk at 204800 1.8e-16 against 3.4e-16).
@@ -248,19 +249,13 @@ __global__ __launch_bounds__(kRedLanes) void sym_reduce_kernel(
   }
 }
 
-// Its launch on s: est with the estimate's workgroups, beside for a lane that takes all
-// shares (an FP32 ring in several launches).
+// Its launch on s: est with the estimate's workgroups, beside for a ring in several launches.
 template <int C, typename S, bool KDK = false, typename PI = double, class... Args>
 int launch_sym_reduce(int64_t n, bool est, bool beside, hipStream_t s, Args... args) {
   auto grid = [&](int p) { return dim3((unsigned)((n + p - 1) / p), (unsigned)(C + (est ? 1 : 0))); };
-  if constexpr (std::is_same_v<S, float>) {
-    if (beside) {
-      sym_reduce_kernel<1, C, S, KDK, PI><<<grid(kRedLanes), kRedLanes, 0, s>>>(args...);
-      NB_LAUNCH_CHECK("sym_reduce_kernel");
-      return NBODY_OK;
-    }
-  }
-  sym_reduce_kernel<kRedShares, C, S, KDK, PI><<<grid(kRedLanes / kRedShares), kRedLanes, 0, s>>>(args...);
+  constexpr int L = kRedLanes, W = kRedShares;
+  if (beside) sym_reduce_kernel<1, C, S, KDK, PI><<<grid(L), L, 0, s>>>(args...);
+  else sym_reduce_kernel<W, C, S, KDK, PI><<<grid(L / W), L, 0, s>>>(args...);
   NB_LAUNCH_CHECK("sym_reduce_kernel");
   return NBODY_OK;
 }

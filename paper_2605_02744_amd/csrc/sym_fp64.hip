@@ -433,7 +433,7 @@ int launch_sym64(int64_t n, const double* x, const double* m, const double* w, c
     slots(b, B);
     auto red = [&](auto kdk) {
       return launch_sym_reduce<NC, double, decltype(kdk)::value>(
-          n, false, false, rs, (int)n, (int)npad, nb, dmax, half, 1 + c * D,
+          n, false, nchunks >= 2, rs, (int)n, (int)npad, nb, dmax, half, 1 + c * D,
           dmax > 0 ? D : 0, dmax > 0 ? nparts : 0, B.pj, B.pi, A.pd, out, outm, G, c == 0,
           c + 1 >= nchunks, nullptr, nullptr, nullptr, nullptr, pds, outs, tail);
     };
